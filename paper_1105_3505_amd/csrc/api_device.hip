@@ -1388,17 +1388,20 @@ void enqueue_passes(lfmm_plan* pl, const ExecPtrs* tab, const double* f1, double
     mark(3);
     if (pl->m2l.n > 0) {
         const BoxTile* mt = pl->m2l_tiles ? pl->m2l_tiles : pl->tiles + pl->m2l.t0;
+        const int32_t n_h1 = pl->Hmax >= 1 ? pl->hbase[2] - pl->hbase[1] : 0;
+        const double children = n_h1 > 0 ? double(pl->nleaf) / double(n_h1) : 0.0;
         if (mixed_bf16) {
             launch_split_q_bf16(pl->Q, pl->nbox + 1, pl->Qb, pl->qsum, st);
-            launch_m2l_bf16(mt, pl->d_m2l_ntiles, pl->m2l.n, pl->cls_box, pl->il27, pl->d_ops, pl->Qb, pl->qsum,
-                            pl->nbox, pl->U, st);
+            launch_m2l_bf16(mt, pl->d_m2l_ntiles, pl->m2l.n, children, pl->cls_box, pl->il27, pl->d_ops, pl->Qb,
+                            pl->qsum, pl->nbox, pl->U, st);
         } else if (mixed) {
             launch_split_q(pl->Q, pl->nbox + 1, pl->Qh, pl->Ql, pl->qsum, st);
-            launch_m2l_mixed(mt, pl->d_m2l_ntiles, pl->m2l.n, pl->cls_box, pl->il27, pl->d_ops, pl->Qh, pl->Ql,
-                             pl->qsum, pl->nbox, pl->U, st);
+            launch_m2l_mixed(mt, pl->d_m2l_ntiles, pl->m2l.n, children, pl->cls_box, pl->il27, pl->d_ops, pl->Qh,
+                             pl->Ql, pl->qsum, pl->nbox, pl->U, st);
         }
         else
-            launch_m2l(mt, pl->d_m2l_ntiles, pl->m2l.n, pl->cls_box, pl->il27, pl->d_ops, pl->Q, pl->nbox, pl->U, st);
+            launch_m2l(mt, pl->d_m2l_ntiles, pl->m2l.n, children, pl->cls_box, pl->il27, pl->d_ops, pl->Q, pl->nbox,
+                       pl->U, st);
     }
     mark(4);
     AdaptiveLists lists{};

@@ -27,6 +27,12 @@ constexpr int kWaves = kBlock / 64;
 // spread one tile over twelve blocks (measured: M2M gains up to 64 tiles, L2L up to 256).
 constexpr int32_t kFineM2mTiles = 64;
 constexpr int32_t kFineL2lTiles = 256;
+// M2L by tiles of 128 boxes, weighted by how full their interaction lists are (m2l_weighted): the
+// 16-box kernels up to the first three counts, then, in FP64, blocks of 64 boxes, then of 128.
+// Measured on uniform points (16-box / 64-box / 128-box kernel, us): 101 tiles 49 / 53 / 81, 190
+// tiles 86 / 80 / 85, 355 tiles - / 115 / 137, 680 tiles - / 209 / 195; FP32 mixed 355 tiles 307 / - /
+// 336; bf16 101 tiles 58 / - / 75, 190 tiles 86 / - / 78.
+constexpr int32_t kFineM2lTiles = 128, kFineM2lMixedTiles = 384, kFineM2lBf16Tiles = 128, kHalfM2lTiles = 512;
 constexpr double kPi = 3.14159265358979323846;
 constexpr double kEulerGamma = 0.57721566490153286061;
 
@@ -285,6 +291,15 @@ __device__ inline gptr<T> global(const T* p) {
     return (gptr<T>)(p);   // generic to global address space
 }
 
+// read-only data that every lane of a wave reads at the same address: constant address
+// space, so that uniform reads become scalar loads
+template <class T>
+using cptr = const __attribute__((address_space(4))) T*;
+template <class T>
+__device__ inline cptr<T> as_const(const T* p) {
+    return (cptr<T>)(p);   // generic to constant address space
+}
+
 template <int MODE>
 __device__ inline void boxmat_tiles(const BoxTile* tiles, int32_t ntiles, const int32_t* box_list,
                                     const int32_t* src_tab, const OpsPtrs* ops, const double* in, int32_t zrow,
@@ -435,33 +450,37 @@ __device__ inline void boxmat_tiles(const BoxTile* tiles, int32_t ntiles, const 
 // (empty list slots, boxes past the tile) read the zero row.
 // 16x16x4 FP64 instruction: step kk of row block m takes column g * 12 + kk in lane group
 // g = lane / 16; element i of lane (g, n) is row 16 m + g + 4 i, column n.
+// NC = 1: a block takes half a tile, one column block per wave, for plans of fewer tiles than the
+// device has room for (a block then lasts half as long: 128,000 uniform points 81 -> 53 us).
+template <int NC>
 __global__ __launch_bounds__(kBlock, 3) void k_m2l(const BoxTile* tiles, const int32_t* ntiles_dev,
                                                     const int32_t* box_list, const int32_t* il27, const OpsPtrs* ops,
                                                     const double* Q, int32_t zrow, double* U) {
-    const int32_t ntiles = uniform(*ntiles_dev);
+    constexpr int NB = 64 * NC, NH = kM2LTile / NB;   // boxes a block takes of a tile, and such parts
+    const int32_t ntiles = uniform(*ntiles_dev) * NH;
     constexpr int P = kRankPad, KQ = P / 4, NJ = KQ / 2, NS = kNumInteractions;
     constexpr int A2 = P * P / 2;                      // double2_t per operator: 4.5 per thread
     static_assert(A2 == 4 * kBlock + kBlock / 2, "staging below assumes P = 48");
-    static_assert(kM2LTile == 128, "two column blocks per wave");
     __shared__ double2_t sA[2][A2];
-    __shared__ int32_t s_src[kM2LTile * NS];     // source box of (tile column, slot), zrow if none
-    __shared__ int32_t s_box[kM2LTile];
+    __shared__ int32_t s_src[NB * NS];     // source box of (tile column, slot), zrow if none
+    __shared__ int32_t s_box[NB];
     __shared__ int s_dsl[NS];
     const int tid = int(threadIdx.x), wave = tid >> 6, lane = tid & 63;
     const int n = lane & 15, g = lane >> 4;
     const int32_t G = int32_t(gridDim.x);
     const double2_t z2 = {0.0, 0.0};
     for (int32_t step = 0;; ++step) {
-        const int32_t t = uniform(xcd_tile(int32_t(blockIdx.x), G, step, ntiles));
-        if (t < 0) break;                                  // uniform over the block
-        const int32_t count = uniform(tiles[t].count);
-        if (count == 0) continue;
-        const int32_t start = uniform(tiles[t].start), height = uniform(tiles[t].height);
+        const int32_t part = uniform(xcd_tile(int32_t(blockIdx.x), G, step, ntiles));
+        if (part < 0) break;                               // uniform over the block
+        const int32_t t = part / NH, first = (part % NH) * NB;
+        const int32_t count = uniform(tiles[t].count) - first;
+        if (count <= 0) continue;
+        const int32_t start = uniform(tiles[t].start) + first, height = uniform(tiles[t].height);
         const int32_t cls = uniform(tiles[t].cls), opi = uniform(tiles[t].ops);
         if (tid < NS) s_dsl[tid] = height * kNumIfoSlots + c_dslot.s[cls][tid];
-        if (tid < kM2LTile) s_box[tid] = (tid < count) ? box_list[start + tid] : -1;
+        if (tid < NB) s_box[tid] = (tid < count) ? box_list[start + tid] : -1;
         __syncthreads();
-        for (int i = tid; i < kM2LTile * NS; i += kBlock) {
+        for (int i = tid; i < NB * NS; i += kBlock) {
             const int b = i / NS;
             const int32_t box = s_box[b];
             const int32_t src = box >= 0 ? il27[size_t(box) * NS + (i - b * NS)] : -1;
@@ -469,12 +488,12 @@ __global__ __launch_bounds__(kBlock, 3) void k_m2l(const BoxTile* tiles, const i
         }
         const gptr<double2_t> Ah = global(reinterpret_cast<const double2_t*>(ops[opi].ifo));
         const gptr<double> Xg = global(Q) + g * KQ;
-        const int col0 = 32 * wave + n;
-        const int32_t box0 = s_box[col0], box1 = s_box[col0 + 16];
+        const int col0 = 16 * NC * wave + n;
+        const int32_t box0 = s_box[col0], box1 = NC == 2 ? s_box[col0 + 16] : -1;
         __syncthreads();
         const int* dsl = s_dsl;
         const int32_t* src0 = s_src + col0 * NS;          // this lane's two columns' lists
-        const int32_t* src1 = src0 + 16 * NS;
+        const int32_t* src1 = NC == 2 ? src0 + 16 * NS : src0 + 1;
         auto load_q = [&](int32_t src, double2_t (&r)[NJ]) {
             const gptr<double2_t> q = reinterpret_cast<gptr<double2_t>>(Xg + size_t(src) * P);
             #pragma unroll
@@ -487,9 +506,9 @@ __global__ __launch_bounds__(kBlock, 3) void k_m2l(const BoxTile* tiles, const i
         int32_t dsl_next = dsl[1];
         double2_t ra0 = A0[tid], ra1 = A0[tid + kBlock], ra2 = A0[tid + 2 * kBlock], ra3 = A0[tid + 3 * kBlock];
         double2_t ra4 = (tid < kBlock / 2) ? A0[tid + 4 * kBlock] : z2;
-        double4_t acc[2][3];
+        double4_t acc[NC][3];
         #pragma unroll
-        for (int c = 0; c < 2; ++c)
+        for (int c = 0; c < NC; ++c)
             #pragma unroll
             for (int m = 0; m < 3; ++m) acc[c][m] = double4_t{0.0, 0.0, 0.0, 0.0};
         for (int k = 0; k < NS; ++k) {
@@ -514,14 +533,17 @@ __global__ __launch_bounds__(kBlock, 3) void k_m2l(const BoxTile* tiles, const i
             // faster here; the same in the bf16 kernel measured 19 % slower)
             __builtin_amdgcn_s_setprio(1);
             #pragma unroll
-            for (int c = 0; c < 2; ++c) {
+            for (int c = 0; c < NC; ++c) {
                 // each pass reads its operator fragments from LDS anew: holding the first pass's
                 // fragments in registers for the second would cost 72 VGPRs (a third of them)
                 asm volatile("" ::: "memory");
                 #pragma unroll
                 for (int j = 0; j < NJ; ++j) bq[j] = nq[j];
                 // the next pair: (k, block 1) after block 0, (k + 1, block 0) after block 1
-                if (c == 0 || k + 1 < NS) {
+                if (NC == 1) {
+                    if (k + 1 < NS) load_q(idx_next, nq);
+                    idx_next = k + 2 < NS ? src0[k + 2] : zrow;
+                } else if (c == 0 || k + 1 < NS) {
                     load_q(idx_next, nq);
                     idx_next = (c == 0) ? (k + 1 < NS ? src0[k + 1] : zrow) : src1[k + 1];
                 }
@@ -541,7 +563,7 @@ __global__ __launch_bounds__(kBlock, 3) void k_m2l(const BoxTile* tiles, const i
             __builtin_amdgcn_s_setprio(0);
         }
         #pragma unroll
-        for (int c = 0; c < 2; ++c) {
+        for (int c = 0; c < NC; ++c) {
             const int32_t box = c ? box1 : box0;
             if (box >= 0) {
                 double* ob = U + size_t(box) * P;
@@ -1049,6 +1071,304 @@ __global__ __launch_bounds__(kBf16Block, 4) void k_m2l_bf16(const BoxTile* tiles
     }
 }
 
+// M2L for plans of few tiles (all precisions).  On the 128-box tiles above a block runs 27 slots
+// of 72 products per wave, so a plan of a handful of tiles lasts a whole tile's time (70-80 us) on a
+// handful of compute units.  Here a block takes one 16-box column block of a tile, one row block per
+// wave: the same products in the same order per result (bit-equal to the kernels above, which an
+// instance alone and in a forest relies on), spread over 24 waves per tile.  Operator fragments go
+// straight from the fragment-ordered tables to registers, the next slots' loads in flight; the
+// source expansions are loaded once per block (consecutive lanes on consecutive bytes of a row: a
+// fragment load spreads its lanes over 16 rows, and three waves of them saturated the texture
+// addresser), written to LDS, one barrier per slot, and read from there as fragments.  Slots that no
+// box of the column block has a source for are skipped: they would add zeros, and on curve-like
+// point sets (the boundary of a box) they are most of the list.  What is left is the chain of 27 x 12
+// dependent products (9.7 us) and about 10 us of dependent loads before it.  Phase times before / now:
+// 1,000 uniform points 70 / 23 us (FP32 mixed 110 / 42, bf16 52 / 27), 64,000 points 80 / 35 us,
+// 128,000 points on the boundary of a box 78 / 24 us.
+constexpr int kFineCols = 16;
+constexpr int kFineThreads = 64 * (kRankPad / 16);
+constexpr int kFineDepth = 3;   // register sets of the slot pipeline (4: a wave less per SIMD, no faster)
+
+// LDS of a fine block: interaction lists of its columns (absent sources as zrow), the slots any of
+// them uses, and the staged expansions (NV 16-byte vectors a row, one more of padding).
+template <int NV>
+struct FineLds {
+    int32_t src[kFineCols * kNumInteractions];
+    uint32_t slots;
+    u32x4_t rows[2][kFineCols * (NV + 1)];
+};
+
+// What a wave of the fine kernels needs of its tile; on false: nothing to do (uniform over the block).
+struct FineTile {
+    int32_t height, opi, box;   // box of this lane's column, -1 past the tile's end
+    int dsl;                    // lane k < 27: operator index of slot k
+    uint32_t slots;
+    bool on;
+};
+
+template <int NV>
+__device__ inline FineTile fine_tile(const BoxTile* tiles, const int32_t* ntiles_dev, const int32_t* box_list,
+                                     const int32_t* il27, int32_t zrow, FineLds<NV>& s) {
+    constexpr int NS = kNumInteractions, NB = kFineCols;
+    FineTile f{};
+    const int32_t b = int32_t(blockIdx.x), t = b / (kM2LTile / NB), q = b % (kM2LTile / NB);
+    // the tile (inside its table whatever their number) and the number of tiles in one round trip
+    const cptr<int4_t> tile = as_const(reinterpret_cast<const int4_t*>(tiles + t));
+    const int4_t t0 = tile[0], t1 = tile[1];   // ops, height, cls, start; count
+    const int32_t ntiles = as_const(ntiles_dev)[0];
+    const int32_t cols = min(NB, t1.x - NB * q), start = t0.w + NB * q;
+    if (t >= ntiles || cols <= 0) return f;
+    const int tid = int(threadIdx.x), lane = tid & 63, n = lane & 15;
+    if (tid == 0) s.slots = 0u;
+    // every thread's list entries loaded together (a column past the tile reads the last one's)
+    constexpr int NR = (NB * NS + kFineThreads - 1) / kFineThreads;
+    int32_t src[NR];
+    #pragma unroll
+    for (int r = 0; r < NR; ++r) src[r] = box_list[start + min(min(tid + r * kFineThreads, NB * NS - 1) / NS, cols - 1)];
+    f.box = box_list[start + min(n, cols - 1)];
+    #pragma unroll
+    for (int r = 0; r < NR; ++r) {
+        const int i = min(tid + r * kFineThreads, NB * NS - 1);
+        src[r] = il27[size_t(src[r]) * NS + (i - i / NS * NS)];
+    }
+    f.on = true;
+    f.height = t0.y;
+    f.opi = t0.x;
+    if (n >= cols) f.box = -1;
+    f.dsl = f.height * kNumIfoSlots + (lane < NS ? c_dslot.s[t0.z][lane] : 0);
+    __syncthreads();
+    uint32_t mine = 0u;
+    #pragma unroll
+    for (int r = 0; r < NR; ++r) {
+        const int i = tid + r * kFineThreads, c = i / NS;
+        if (c >= cols || src[r] < 0) src[r] = zrow;
+        else mine |= 1u << (i - c * NS);
+        if (i < NB * NS) s.src[i] = src[r];
+    }
+    if (mine) atomicOr(&s.slots, mine);
+    __syncthreads();
+    f.slots = uint32_t(uniform(int32_t(s.slots)));
+    return f;
+}
+
+// The slots in order: frag(a, k) loads the operator fragments of slot k, row(src, v) names vector v of
+// a source's expansion, use(a, b) runs the products with the staged row b of this lane's column.
+// kFineDepth register sets in turn, reloaded right after their use (past the last slot with the last
+// one again).  The buffer a slot writes was last read two slots earlier, before the previous barrier.
+template <int NV, class Frag, class LoadFrag, class Row, class Use>
+__device__ inline void fine_slots(uint32_t slots, FineLds<NV>& s, LoadFrag frag, Row row, Use use) {
+    constexpr int NR = (kFineCols * NV + kFineThreads - 1) / kFineThreads;
+    struct Set {
+        Frag a;
+        u32x4_t b[NR];
+    };
+    const int tid = int(threadIdx.x), n = tid & 15;
+    int left = __popc(slots), k = 0, par = 0;
+    if (left == 0) return;
+    int rsrc[NR], rvec[NR], rlds[NR];   // list position, vector and place in LDS of this thread's loads
+    #pragma unroll
+    for (int r = 0; r < NR; ++r) {
+        const int i = min(tid + r * kFineThreads, kFineCols * NV - 1), c = i / NV;
+        rsrc[r] = c * kNumInteractions;
+        rvec[r] = i - c * NV;
+        rlds[r] = c * (NV + 1) + rvec[r];
+    }
+    Set set[kFineDepth];
+    auto fetch = [&](Set& t) {
+        if (slots) {
+            k = __ffs(int(slots)) - 1;
+            slots &= slots - 1u;
+        }
+        #pragma unroll
+        for (int r = 0; r < NR; ++r) t.b[r] = *row(size_t(s.src[rsrc[r] + k]), rvec[r]);
+        frag(t.a, k);
+        asm volatile("" ::: "memory");   // keeps the loads here, not sunk to their uses
+    };
+    #pragma unroll
+    for (int d = 0; d < kFineDepth; ++d) fetch(set[d]);
+    for (;;) {
+        #pragma unroll
+        for (int d = 0; d < kFineDepth; ++d) {
+            u32x4_t* buf = s.rows[par];
+            par ^= 1;
+            #pragma unroll
+            for (int r = 0; r < NR; ++r) buf[rlds[r]] = set[d].b[r];
+            __syncthreads();
+            use(set[d].a, buf + n * (NV + 1));
+            if (--left == 0) return;
+            fetch(set[d]);
+        }
+    }
+}
+
+__global__ __launch_bounds__(kFineThreads) void k_m2l_fine(const BoxTile* tiles, const int32_t* ntiles_dev,
+                                                           const int32_t* box_list, const int32_t* il27,
+                                                           const OpsPtrs* ops, const double* Q, int32_t zrow,
+                                                           double* U) {
+    constexpr int P = kRankPad, NJ = P / 8, A2 = P * P / 2, NV = P / 2;
+    __shared__ FineLds<NV> lds;
+    const FineTile f = fine_tile(tiles, ntiles_dev, box_list, il27, zrow, lds);
+    if (!f.on) return;
+    const int m = int(threadIdx.x) >> 6, lane = int(threadIdx.x) & 63, g = lane >> 4;
+    const gptr<double2_t> A = global(reinterpret_cast<const double2_t*>(ops[f.opi].ifo)) + size_t(m * NJ) * 64 + lane;
+    const gptr<u32x4_t> X = global(reinterpret_cast<const u32x4_t*>(Q));
+    struct Frag {
+        double2_t a[NJ];
+    };
+    double4_t acc = {0.0, 0.0, 0.0, 0.0};
+    fine_slots<NV, Frag>(
+        f.slots, lds,
+        [&](Frag& s, int k) {
+            const gptr<double2_t> Ak = A + size_t(__builtin_amdgcn_readlane(f.dsl, k)) * A2;
+            #pragma unroll
+            for (int j = 0; j < NJ; ++j) s.a[j] = Ak[j * 64];
+        },
+        [&](size_t src, int v) { return X + src * NV + v; },
+        [&](const Frag& s, const u32x4_t* b) {
+            #pragma unroll
+            for (int j = 0; j < NJ; ++j) {
+                const double2_t q = __builtin_bit_cast(double2_t, b[g * NJ + j]);
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(s.a[j].x, q.x, acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(s.a[j].y, q.y, acc, 0, 0, 0);
+            }
+        });
+    if (f.box >= 0) {
+        double* ob = U + size_t(f.box) * P + 16 * m + g;
+        #pragma unroll
+        for (int i = 0; i < 4; ++i) ob[4 * i] = acc[i];
+    }
+}
+
+__global__ __launch_bounds__(kFineThreads) void k_m2l_mixed_fine(const BoxTile* tiles, const int32_t* ntiles_dev,
+                                                                 const int32_t* box_list, const int32_t* il27,
+                                                                 const OpsPtrs* ops, const float* Qh, const float* Ql,
+                                                                 const double* qs, int32_t zrow, double* U) {
+    constexpr int P = kRankPad, NJ4 = P / 16, A4 = P * P / 4, NH = P / 4, NV = 2 * NH;
+    __shared__ FineLds<NV> lds;
+    const FineTile f = fine_tile(tiles, ntiles_dev, box_list, il27, zrow, lds);
+    if (!f.on) return;
+    const int m = int(threadIdx.x) >> 6, lane = int(threadIdx.x) & 63, n = lane & 15, g = lane >> 4;
+    const gptr<float4_t> H = global(reinterpret_cast<const float4_t*>(ops[f.opi].ifo_hi)) + size_t(m * NJ4) * 64 + lane;
+    const gptr<float4_t> L = global(reinterpret_cast<const float4_t*>(ops[f.opi].ifo_lo)) + size_t(m * NJ4) * 64 + lane;
+    const gptr<u32x4_t> XH = global(reinterpret_cast<const u32x4_t*>(Qh)), XL = global(reinterpret_cast<const u32x4_t*>(Ql));
+    const gptr<double> mono = global(ops[f.opi].mono), QS = global(qs);
+    const int rk = uniform(ops[f.opi].rank[f.height]);
+    const float4_t zero = {0.f, 0.f, 0.f, 0.f};
+    struct Frag {
+        float4_t ah[NJ4], al[NJ4];
+        double c, q;
+    };
+    double4_t acc = {0.0, 0.0, 0.0, 0.0};
+    fine_slots<NV, Frag>(
+        f.slots, lds,
+        [&](Frag& s, int k) {
+            const size_t d = size_t(__builtin_amdgcn_readlane(f.dsl, k));
+            #pragma unroll
+            for (int j = 0; j < NJ4; ++j) {
+                s.ah[j] = H[d * A4 + j * 64];
+                s.al[j] = L[d * A4 + j * 64];
+            }
+            s.c = mono[d];
+            s.q = QS[size_t(lds.src[n * kNumInteractions + k])];
+        },
+        [&](size_t src, int v) { return v < NH ? XH + src * NH + v : XL + src * NH + (v - NH); },
+        [&](const Frag& s, const u32x4_t* b) {
+            const double mq = s.c * s.q;   // constant part of T^d times the charge sum
+            #pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (16 * m + 4 * g + i < rk) acc[i] += mq;
+            float4_t c1 = zero, c2 = zero;
+            #pragma unroll
+            for (int j = 0; j < NJ4; ++j) {
+                const float4_t bh = __builtin_bit_cast(float4_t, b[g * NJ4 + j]);
+                const float4_t bl = __builtin_bit_cast(float4_t, b[NH + g * NJ4 + j]);
+                #pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float4_t p = __builtin_amdgcn_mfma_f32_16x16x4f32(s.ah[j][e], bh[e], zero, 0, 0, 0);
+                    c1 = __builtin_amdgcn_mfma_f32_16x16x4f32(s.ah[j][e], bl[e], c1, 0, 0, 0);
+                    c2 = __builtin_amdgcn_mfma_f32_16x16x4f32(s.al[j][e], bh[e], c2, 0, 0, 0);
+                    #pragma unroll
+                    for (int i = 0; i < 4; ++i) acc[i] += double(p[i]);
+                }
+            }
+            #pragma unroll
+            for (int i = 0; i < 4; ++i) acc[i] += double(c1[i]) + double(c2[i]);
+        });
+    if (f.box >= 0) {
+        double* ob = U + size_t(f.box) * P + 16 * m + 4 * g;
+        #pragma unroll
+        for (int i = 0; i < 4; ++i) ob[i] = acc[i];
+    }
+}
+
+__global__ __launch_bounds__(kFineThreads) void k_m2l_bf16_fine(const BoxTile* tiles, const int32_t* ntiles_dev,
+                                                                const int32_t* box_list, const int32_t* il27,
+                                                                const OpsPtrs* ops, const uint16_t* Qb,
+                                                                const double* qs, int32_t zrow, double* U) {
+    constexpr int P = kRankPad, NF = kBf16OpVecs, NV = kBf16QVecs;
+    __shared__ FineLds<NV> lds;
+    const FineTile f = fine_tile(tiles, ntiles_dev, box_list, il27, zrow, lds);
+    if (!f.on) return;
+    const int m = int(threadIdx.x) >> 6, lane = int(threadIdx.x) & 63, n = lane & 15, g = lane >> 4;
+    const bool q0_lanes = g < 2;                 // the contraction layout of k_m2l_bf16
+    const int c0 = 3 * (g & 1);
+    const gptr<u32x4_t> A = global(reinterpret_cast<const u32x4_t*>(ops[f.opi].ifo_b)) + c0 * 16 + n + 96 * m;
+    const gptr<u32x4_t> X = global(reinterpret_cast<const u32x4_t*>(Qb));
+    const int a2 = q0_lanes ? 2 * 288 : 0, b1 = c0 + (q0_lanes ? 0 : 6), b2 = c0 + (q0_lanes ? 0 : 12);
+    const gptr<double> mono = global(ops[f.opi].mono), QS = global(qs);
+    const int rk = uniform(ops[f.opi].rank[f.height]);
+    const float4_t zero = {0.f, 0.f, 0.f, 0.f};
+    struct Frag {
+        u32x4_t a[9];
+        double c, q;
+    };
+    double4_t acc = {0.0, 0.0, 0.0, 0.0};
+    double mono_acc = 0.0;
+    fine_slots<NV, Frag>(
+        f.slots, lds,
+        [&](Frag& s, int k) {
+            const size_t d = size_t(__builtin_amdgcn_readlane(f.dsl, k));
+            const gptr<u32x4_t> Ak = A + d * NF;
+            #pragma unroll
+            for (int t = 0; t < 3; ++t) {
+                s.a[3 * t] = Ak[16 * t];
+                s.a[3 * t + 1] = Ak[288 + 16 * t];
+                s.a[3 * t + 2] = Ak[a2 + 16 * t];
+            }
+            s.c = mono[d];
+            s.q = QS[size_t(lds.src[n * kNumInteractions + k])];
+        },
+        [&](size_t src, int v) { return X + src * NV + v; },
+        [&](const Frag& s, const u32x4_t* b) {
+            mono_acc += s.c * s.q;
+            float4_t small = zero;
+            #pragma unroll
+            for (int t = 0; t < 3; ++t)
+                #pragma unroll
+                for (int r = 0; r < 3; ++r) {
+                    const bf16x8_t av = __builtin_bit_cast(bf16x8_t, s.a[3 * t + r]);
+                    const bf16x8_t bv = __builtin_bit_cast(bf16x8_t, b[(r == 2 ? b2 : b1) + t]);
+                    if (r == 0) {
+                        const float4_t p = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv, zero, 0, 0, 0);
+                        #pragma unroll
+                        for (int i = 0; i < 4; ++i) acc[i] += double(p[i]);
+                    } else {
+                        small = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv, small, 0, 0, 0);
+                    }
+                }
+            #pragma unroll
+            for (int i = 0; i < 4; ++i) acc[i] += double(small[i]);
+        });
+    if (f.box >= 0) {
+        double* ob = U + size_t(f.box) * P;
+        #pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int row = 16 * m + 4 * g + i;
+            ob[row] = acc[i] + (row < rk ? mono_acc : 0.0);   // padded rows stay zero
+        }
+    }
+}
+
 // Leaf pass: far field T_tfi u-hat with T_tfi = T_ofs^T (Section 7, symmetric kernel and
 // targets = sources) plus the direct sum over the points of the leaf and its neighbours
 // (Section 8.2 step 5), written back in the caller's point order.
@@ -1073,15 +1393,6 @@ constexpr int kNearTabMax = 64 * 64;   // doubles: W^2 for the window (side 16) 
 // waves and run persistently (each builds its table once); with the global table, 256-thread
 // blocks take one group per wave and the hardware balances uneven groups.
 constexpr int near_threads(int mode) { return mode == kGlobal ? 256 : 512; }
-
-// read-only data that every lane of a wave reads at the same address: constant address
-// space, so that uniform reads become scalar loads
-template <class T>
-using cptr = const __attribute__((address_space(4))) T*;
-template <class T>
-__device__ inline cptr<T> as_const(const T* p) {
-    return (cptr<T>)(p);   // generic to constant address space
-}
 
 // One group of leaves (see k_near).
 //   SLICED = false (groups of more than 32 targets): one target per lane over the whole group,
@@ -1881,13 +2192,28 @@ void launch_l2l(const BoxTile* tiles, int32_t ntiles, const int32_t* box_list, c
                        box_parent, ops, U, zrow, role);
 }
 
-void launch_m2l(const BoxTile* tiles, const int32_t* ntiles_dev, int32_t max_tiles, const int32_t* box_list,
-                const int32_t* il27, const OpsPtrs* ops, const double* Q, int32_t zrow, double* U, hipStream_t st) {
+// Tiles weighted by the expected share of their interaction lists that exists: boxes with `children`
+// children on average have about (children / 4)^2 of the 27 (a curve's 2 children: a quarter), and the
+// 16-box kernels skip the rest.
+static int32_t m2l_weighted(int32_t max_tiles, double children) {
+    const double w = std::min(1.0, std::max(0.0, children) / 4.0);
+    return int32_t(double(max_tiles) * w * w);
+}
+
+void launch_m2l(const BoxTile* tiles, const int32_t* ntiles_dev, int32_t max_tiles, double children,
+                const int32_t* box_list, const int32_t* il27, const OpsPtrs* ops, const double* Q, int32_t zrow,
+                double* U, hipStream_t st) {
     if (max_tiles <= 0) return;
-    int64_t g = std::min<int64_t>(max_tiles, 8192);
+    if (m2l_weighted(max_tiles, children) <= kFineM2lTiles) {
+        hipLaunchKernelGGL(k_m2l_fine, dim3(unsigned(max_tiles) * (kM2LTile / kFineCols)), dim3(kFineThreads), 0, st,
+                           tiles, ntiles_dev, box_list, il27, ops, Q, zrow, U);
+        return;
+    }
+    const bool half = max_tiles <= kHalfM2lTiles;
+    int64_t g = std::min<int64_t>(int64_t(max_tiles) * (half ? 2 : 1), 8192);
     g = std::max<int64_t>(8, (g + 7) / 8 * 8);
-    hipLaunchKernelGGL(k_m2l, dim3(static_cast<unsigned>(g)), dim3(kBlock), 0, st, tiles, ntiles_dev, box_list, il27,
-                       ops, Q, zrow, U);
+    hipLaunchKernelGGL(half ? k_m2l<1> : k_m2l<2>, dim3(static_cast<unsigned>(g)), dim3(kBlock), 0, st, tiles,
+                       ntiles_dev, box_list, il27, ops, Q, zrow, U);
 }
 
 void launch_split_q(const double* Q, int32_t nrows, float* Qh, float* Ql, double* qs, hipStream_t st) {
@@ -1895,10 +2221,15 @@ void launch_split_q(const double* Q, int32_t nrows, float* Qh, float* Ql, double
     hipLaunchKernelGGL(k_split_q, dim3(grid_for(int64_t(nrows) * 64)), dim3(kBlock), 0, st, Q, nrows, Qh, Ql, qs);
 }
 
-void launch_m2l_mixed(const BoxTile* tiles, const int32_t* ntiles_dev, int32_t max_tiles, const int32_t* box_list,
-                      const int32_t* il27, const OpsPtrs* ops, const float* Qh, const float* Ql, const double* qs,
+void launch_m2l_mixed(const BoxTile* tiles, const int32_t* ntiles_dev, int32_t max_tiles, double children,
+                      const int32_t* box_list, const int32_t* il27, const OpsPtrs* ops, const float* Qh, const float* Ql, const double* qs,
                       int32_t zrow, double* U, hipStream_t st) {
     if (max_tiles <= 0) return;
+    if (m2l_weighted(max_tiles, children) <= kFineM2lMixedTiles) {
+        hipLaunchKernelGGL(k_m2l_mixed_fine, dim3(unsigned(max_tiles) * (kM2LTile / kFineCols)), dim3(kFineThreads), 0, st, tiles,
+                           ntiles_dev, box_list, il27, ops, Qh, Ql, qs, zrow, U);
+        return;
+    }
     int64_t g = std::min<int64_t>(max_tiles, 8192);
     g = std::max<int64_t>(8, (g + 7) / 8 * 8);
     hipLaunchKernelGGL(k_m2l_mixed, dim3(static_cast<unsigned>(g)), dim3(kBlock), 0, st, tiles, ntiles_dev, box_list,
@@ -1910,10 +2241,15 @@ void launch_split_q_bf16(const double* Q, int32_t nrows, uint16_t* Qb, double* q
     hipLaunchKernelGGL(k_split_q_bf16, dim3(grid_for(int64_t(nrows) * 8)), dim3(kBlock), 0, st, Q, nrows, Qb, qs);
 }
 
-void launch_m2l_bf16(const BoxTile* tiles, const int32_t* ntiles_dev, int32_t max_tiles, const int32_t* box_list,
-                     const int32_t* il27, const OpsPtrs* ops, const uint16_t* Qb, const double* qs, int32_t zrow,
+void launch_m2l_bf16(const BoxTile* tiles, const int32_t* ntiles_dev, int32_t max_tiles, double children,
+                     const int32_t* box_list, const int32_t* il27, const OpsPtrs* ops, const uint16_t* Qb, const double* qs, int32_t zrow,
                      double* U, hipStream_t st) {
     if (max_tiles <= 0) return;
+    if (m2l_weighted(max_tiles, children) <= kFineM2lBf16Tiles) {
+        hipLaunchKernelGGL(k_m2l_bf16_fine, dim3(unsigned(max_tiles) * (kM2LTile / kFineCols)), dim3(kFineThreads), 0, st, tiles,
+                           ntiles_dev, box_list, il27, ops, Qb, qs, zrow, U);
+        return;
+    }
     int64_t g = std::min<int64_t>(max_tiles, 8192);
     g = std::max<int64_t>(8, (g + 7) / 8 * 8);
     hipLaunchKernelGGL(k_m2l_bf16, dim3(static_cast<unsigned>(g)), dim3(kBf16Block), 0, st, tiles, ntiles_dev,

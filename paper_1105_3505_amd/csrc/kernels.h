@@ -292,16 +292,18 @@ void launch_m2m(const BoxTile* tiles, int32_t ntiles, const int32_t* box_child, 
 void launch_l2l(const BoxTile* tiles, int32_t ntiles, const int32_t* box_list, const int32_t* box_parent,
                 const OpsPtrs* ops, double* U, int32_t zrow, const int8_t* role, hipStream_t st);
 // M2L over the class-sorted tiles, *ntiles_dev of them (max_tiles at most); Q row zrow is all
-// zeros (read for absent sources)
-void launch_m2l(const BoxTile* tiles, const int32_t* ntiles_dev, int32_t max_tiles, const int32_t* box_list,
-                const int32_t* il27, const OpsPtrs* ops, const double* Q, int32_t zrow, double* U, hipStream_t st);
+// zeros (read for absent sources); children, the mean number of children of a box above the
+// leaves, and max_tiles pick the kernel (same results bit for bit)
+void launch_m2l(const BoxTile* tiles, const int32_t* ntiles_dev, int32_t max_tiles, double children,
+                const int32_t* box_list, const int32_t* il27, const OpsPtrs* ops, const double* Q, int32_t zrow,
+                double* U, hipStream_t st);
 // mixed-precision operands of Q rows [0, nrows): FP32 hi and lo parts and FP64 charge sums
 void launch_split_q(const double* Q, int32_t nrows, float* Qh, float* Ql, double* qs, hipStream_t st);
 void launch_split_q_bf16(const double* Q, int32_t nrows, uint16_t* Qb, double* qs, hipStream_t st);
-void launch_m2l_bf16(const BoxTile* tiles, const int32_t* ntiles_dev, int32_t max_tiles, const int32_t* box_list,
-                     const int32_t* il27, const OpsPtrs* ops, const uint16_t* Qb, const double* qs, int32_t zrow,
+void launch_m2l_bf16(const BoxTile* tiles, const int32_t* ntiles_dev, int32_t max_tiles, double children,
+                     const int32_t* box_list, const int32_t* il27, const OpsPtrs* ops, const uint16_t* Qb, const double* qs, int32_t zrow,
                      double* U, hipStream_t st);
-void launch_m2l_mixed(const BoxTile* tiles, const int32_t* ntiles_dev, int32_t max_tiles,
+void launch_m2l_mixed(const BoxTile* tiles, const int32_t* ntiles_dev, int32_t max_tiles, double children,
                       const int32_t* box_list, const int32_t* il27, const OpsPtrs* ops,
                       const float* Qh, const float* Ql, const double* qs, int32_t zrow, double* U,
                       hipStream_t st);
