@@ -1387,7 +1387,7 @@ __global__ __launch_bounds__(kFineThreads) void k_m2l_bf16_fine(const BoxTile* t
 //   GLOBAL (side >= 64): the device octant table (radius kPhiDeviceRadius) in global memory,
 //     eq. (3.1) beyond.
 enum LeafMode { kWindow = 0, kQuad = 1, kGlobal = 2 };
-constexpr int kNearXcdChunk = 512;     // groups per chunk of the near field's XCD-aware walk
+constexpr int kNearXcdChunk = 512;     // most groups per chunk of the near field's XCD-aware walk
 constexpr int kNearTabMax = 64 * 64;   // doubles: W^2 for the window (side 16) and quad (side 32) tables
 // Block size per mode.  With an LDS phi table, 512-thread blocks share one table among eight
 // waves and run persistently (each builds its table once); with the global table, 256-thread
@@ -1603,10 +1603,13 @@ __global__ __launch_bounds__(near_threads(MODE), MODE == kWindow ? 6 : 1) void k
     const char* tb = reinterpret_cast<const char*>(tab);
     const uint32_t kofs = 8u * uint32_t(cw * W + cw);
     // XCD-aware walk of the group list: block b runs on XCD b % 8, and XCD x takes the chunks x,
-    // x + 8, x + 16, ... of kNearXcdChunk consecutive (Morton-ordered) groups, so that most sources
-    // that neighbouring groups share are read through one L2 (on 1e6 uniform points 5 % faster than
-    // the plain walk; one contiguous eighth per XCD was 8 % faster there but leaves an XCD with all
-    // of a dense region's work, which the same split made 1.1-1.8x slower in the clustered kernels).
+    // x + 8, x + 16, ... of C consecutive (Morton-ordered) groups, so that most sources that
+    // neighbouring groups share are read through one L2 (on 1e6 uniform points 5 % faster than the
+    // plain walk; one contiguous eighth per XCD was 8 % faster there but leaves an XCD with all of a
+    // dense region's work, which the same split made 1.1-1.8x slower in the clustered kernels).
+    // The list is cut into a multiple of 8 chunks of at most kNearXcdChunk groups, so that every XCD
+    // has the same share: with chunks of 512 groups whatever the list, a plan of 1,024 groups ran on
+    // two XCDs (16,000 uniform points 161 -> 28 us, 16,000 in 1/40 of the cells 301 -> 78 us).
     // With fewer than 8 blocks, the plain walk.
     const int32_t G = int32_t(gridDim.x);
     int32_t x = 0, first = int32_t(blockIdx.x), nb = G, C = q1 - q0 + 1;
@@ -1614,7 +1617,8 @@ __global__ __launch_bounds__(near_threads(MODE), MODE == kWindow ? 6 : 1) void k
         x = first & 7;
         first >>= 3;
         nb = (G + 7 - x) >> 3;   // blocks on XCD x
-        C = kNearXcdChunk;
+        const int32_t n = q1 - q0, chunks = (n + 8 * kNearXcdChunk - 1) / (8 * kNearXcdChunk) * 8;
+        C = (n + chunks - 1) / chunks;
     }
     for (int32_t l = first * kNearWaves + wave;; l += nb * kNearWaves) {
         const int32_t q = q0 + (8 * (l / C) + x) * C + l % C;   // increases with l
