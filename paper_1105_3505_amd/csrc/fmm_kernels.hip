@@ -1383,16 +1383,82 @@ __global__ __launch_bounds__(kFineThreads) void k_m2l_bf16_fine(const BoxTile* t
 //   WINDOW (side <= 16): phi sits in a window table over all offsets in [-(2s-1), 2s-1]^2 and
 //     each point carries the key K = 8 (y W + x) mod 2^32 (W = 4s - 1), so the byte offset of
 //     phi(x_i - x_j) is K_i - K_j plus a constant: one subtraction per pair.
-//   QUAD (side 32): a table over |dx|, |dy| < 64.
+//   QUAD (side 32): a table over |dx|, |dy| < 64; a pair's address is two sums of absolute differences.
 //   GLOBAL (side >= 64): the device octant table (radius kPhiDeviceRadius) in global memory,
 //     eq. (3.1) beyond.
 enum LeafMode { kWindow = 0, kQuad = 1, kGlobal = 2 };
 constexpr int kNearXcdChunk = 512;     // most groups per chunk of the near field's XCD-aware walk
-constexpr int kNearTabMax = 64 * 64;   // doubles: W^2 for the window (side 16) and quad (side 32) tables
+constexpr int kQuadRow = 65;           // doubles a row of the quad table (odd: rows start on different banks)
+constexpr int kNearTabMax = 64 * kQuadRow;   // doubles: the quad table (side 32); W^2 = 63^2 of the window (side 16)
 // Block size per mode.  With an LDS phi table, 512-thread blocks share one table among eight
 // waves and run persistently (each builds its table once); with the global table, 256-thread
 // blocks take one group per wave and the hardware balances uneven groups.
 constexpr int near_threads(int mode) { return mode == kGlobal ? 256 : 512; }
+
+// |a - b| + c in one instruction (spelled out, the compiler rearranges it into five); b uniform
+__device__ inline uint32_t sad(uint32_t a, uint32_t b, uint32_t c) {
+    uint32_t r;
+    asm("v_sad_u32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "s"(b), "v"(c));
+    return r;
+}
+
+// L2P of up to 64 targets i0 .. i0 + 63 (lane t holds the cell `loc` of target i0 + t): the far field
+// of this lane's target.  Leaf by leaf, eight targets at a time with eight lanes each, so that a load
+// reads whole 128-byte lines of eight operator rows and one of the leaf's expansion.  With one target
+// per lane the 24 loads of a row's pairs each touched about 27 lines (and 64 rows of the cell-major
+// table), and the texture addresser's time on them, 46 us of the pass on 1e6 points, was its largest
+// part (21 us now).  A target's sum: six terms per lane in order, then the eight lanes' by a tree.
+// sfar: 64 doubles of LDS of this wave.
+template <int P>
+__device__ inline double far_rows(int32_t leaf0, int32_t nleaf, const int32_t (&bnd)[5], int32_t i0, int32_t loc,
+                                  const double* leafT, const double* U, double* sfar) {
+    static_assert(P == 48, "three 128-byte lines a row");
+    const int lane = int(threadIdx.x) & 63, g8 = lane >> 3, l = lane & 7;
+    const gptr<double2_t> T = global(reinterpret_cast<const double2_t*>(leafT)) + l;
+    auto dpp_add = [](double v, auto ctrl) -> double {
+        const int2_t w = __builtin_bit_cast(int2_t, v);
+        return v + __builtin_bit_cast(double, int2_t{__builtin_amdgcn_update_dpp(0, w.x, ctrl(), 0xf, 0xf, true),
+                                                     __builtin_amdgcn_update_dpp(0, w.y, ctrl(), 0xf, 0xf, true)});
+    };
+    for (int c = 0; c < nleaf; ++c) {
+        const int32_t b0 = c == 0 ? bnd[0] : c == 1 ? bnd[1] : c == 2 ? bnd[2] : bnd[3];
+        const int32_t b1 = c == 0 ? bnd[1] : c == 1 ? bnd[2] : c == 2 ? bnd[3] : bnd[4];
+        const int32_t t0 = max(b0 - i0, 0), t1 = min(b1 - i0, 64);   // its targets among the 64 (uniform)
+        if (t0 >= t1) continue;
+        const gptr<double2_t> u = global(reinterpret_cast<const double2_t*>(U)) + size_t(leaf0 + c) * (P / 2) + l;
+        const double2_t u0 = u[0], u1 = u[8], u2 = u[16];
+        for (int32_t t = t0; t < t1; t += 16) {
+            const int32_t ta = t + g8, tb = t + 8 + g8;
+            const size_t ra = size_t(__shfl(loc, min(ta, 63), 64)) * (P / 2), rb = size_t(__shfl(loc, min(tb, 63), 64)) * (P / 2);
+            const double2_t x0 = T[ra], x1 = T[ra + 8], x2 = T[ra + 16], y0 = T[rb], y1 = T[rb + 8], y2 = T[rb + 16];
+            double a = x0.x * u0.x, b = y0.x * u0.x;
+            a += x0.y * u0.y;
+            b += y0.y * u0.y;
+            a += x1.x * u1.x;
+            b += y1.x * u1.x;
+            a += x1.y * u1.y;
+            b += y1.y * u1.y;
+            a += x2.x * u2.x;
+            b += y2.x * u2.x;
+            a += x2.y * u2.y;
+            b += y2.y * u2.y;
+            a = dpp_add(a, [] { return 0xB1; });    // the other of the pair, the other pair of the
+            b = dpp_add(b, [] { return 0xB1; });    // four, the other four (mirrored)
+            a = dpp_add(a, [] { return 0x4E; });
+            b = dpp_add(b, [] { return 0x4E; });
+            a = dpp_add(a, [] { return 0x141; });
+            b = dpp_add(b, [] { return 0x141; });
+            if (l == 0 && ta < t1) sfar[ta] = a;
+            if (l == 1 && tb < t1) sfar[tb] = b;
+        }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    const double v = sfar[lane];   // lanes past the targets: unused
+    __builtin_amdgcn_wave_barrier();
+    return v;
+}
 
 // One group of leaves (see k_near).
 //   SLICED = false (groups of more than 32 targets): one target per lane over the whole group,
@@ -1401,33 +1467,27 @@ constexpr int near_threads(int mode) { return mode == kGlobal ? 256 : 512; }
 //   SLICED = true (groups of at most 32 targets): leaf by leaf; the n targets of a leaf take T lanes each
 //     (T = the power of two at or above n, at most 64) of S = 64 / T slices, slice s summing
 //     every S-th source of each neighbouring range, and the slices are added by xor shuffles.
+// The group's record and entries come in registers (word l of the record in lane l, entry e in lane
+// e), loaded while the wave worked on the group before: read from memory when needed, they put three
+// dependent round trips in front of every group and one in front of every range, half the pass's time.
 template <int P, int MODE, bool SLICED>
-__device__ inline void near_group(int32_t qq, const NearGroup* groups, const int4* ents, const int32_t* box_pt0,
-                                  const int32_t* box_pt1, const uint64_t* box_key, const int32_t* box_inst,
-                                  int64_t side, int W, const double* tab, const char* tb, uint32_t kofs,
-                                  const int2* pts,
+__device__ inline void near_group(int32_t rec, int4 ent, int64_t side, int W, const double* tab, const char* tb,
+                                  uint32_t kofs, const int2* pts,
                                   const uint32_t* pkey, const double* fs, const int32_t* perm_local,
                                   const ExecPtrs* tab_ptrs, ExecPtrs single, const double* U,
-                                  const double* leafT, const double* leafTt, const uint8_t* far_inst,
-                                  const double* phi_oct_tab, const PhiFar* phi_far) {
+                                  const double* leafT, double* sfar, const double* phi_oct_tab,
+                                  const PhiFar* phi_far) {
     const int lane = threadIdx.x & 63;
-    const cptr<int4_t> E = as_const(reinterpret_cast<const int4_t*>(ents));
     const cptr<uint32_t> SK = as_const(pkey);
     const cptr<double> SF = as_const(fs);
     const cptr<int2_t> SP = as_const(reinterpret_cast<const int2_t*>(pts));
-    const int32_t leaf0 = uniform(groups[qq].leaf0), nleaf = uniform(groups[qq].nleaf);
-    const int32_t ne = uniform(groups[qq].ne);
-    // first point of each leaf of the group (uniform) and the end of the last
-    int32_t bnd[5];
-    bnd[0] = uniform(box_pt0[leaf0]);
-    bnd[1] = nleaf > 1 ? uniform(box_pt0[leaf0 + 1]) : bnd[0];
-    bnd[2] = nleaf > 2 ? uniform(box_pt0[leaf0 + 2]) : bnd[0];
-    bnd[3] = nleaf > 3 ? uniform(box_pt0[leaf0 + 3]) : bnd[0];
-    const int32_t t_end = uniform(box_pt1[leaf0 + nleaf - 1]);
-    bnd[nleaf] = t_end;
-    const int32_t k_inst = uniform(box_inst[leaf0]);
-    const bool far = far_inst[k_inst] != 0;
-    const ExecPtrs eio = tab_ptrs ? tab_ptrs[k_inst] : single;
+    auto word = [&](int k) -> int32_t { return __builtin_amdgcn_readlane(rec, k); };   // of the NearGroup
+    const int32_t leaf0 = word(0), nleaf = word(1), ne = word(2);
+    const int32_t bnd[5] = {word(4), word(5), word(6), word(7), word(8)};
+    const int32_t lx0 = word(9), ly0 = word(10), cposs = word(11);
+    const int32_t t_end = bnd[4];
+    const bool far = word(12) != 0;
+    const ExecPtrs eio = tab_ptrs ? tab_ptrs[word(3)] : single;
     double* u = eio.u;
     const bool sorted_out = eio.sorted != 0;   // u indexed by sorted point
     const int32_t tgt0 = eio.tgt0;   // first target index
@@ -1445,21 +1505,27 @@ __device__ inline void near_group(int32_t qq, const NearGroup* groups, const int
             const int32_t i = i0 + tl;
             const bool valid = i < p1;
             const int32_t ii = valid ? i : p0;
-            const int c = SLICED ? c0 : (nleaf > 1 && ii >= bnd[1]) + (nleaf > 2 && ii >= bnd[2]) +
-                                            (nleaf > 3 && ii >= bnd[3]);
+            // leaves past the last start at t_end, after every point
+            const int c = SLICED ? c0 : (ii >= bnd[1]) + (ii >= bnd[2]) + (ii >= bnd[3]);
             const int32_t leaf = leaf0 + c;
-            const uint64_t key = box_key[leaf];
-            const int32_t tx = int32_t(compact_bits(key)), ty = int32_t(compact_bits(key >> 1));
+            const int cpos = (cposs >> (2 * c)) & 3;
+            const int32_t tx = lx0 + (cpos & 1), ty = ly0 + (cpos >> 1);
             const int2 pi = pts[ii];
             // the window centre's byte offset is folded into the target's key once, so that a
             // pair costs one subtraction for its table address
             const uint32_t ki = (MODE == kWindow) ? pkey[ii] + kofs : 0u;
             const int32_t pout = perm_local[ii];
+            // QUAD: byte offsets of the table relative to the lower-left corner of the 4 x 4 leaves
+            const int32_t gx = (lx0 - 1) * int32_t(side), gy = (ly0 - 1) * int32_t(side);
+            const uint32_t qx = uint32_t(pi.x - gx) * 8u, qy = uint32_t(pi.y - gy) * (8u * kQuadRow);
             double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
             auto phi_at = [&](uint32_t kj, int2_t pj) -> double {
                 if (MODE == kWindow) return *reinterpret_cast<const double*>(tb + int32_t(ki - kj));
+                if (MODE == kQuad && !SLICED)   // the source is uniform: its offset is scaled by scalar instructions
+                    return *reinterpret_cast<const double*>(
+                        tb + sad(qy, uint32_t(pj.y - gy) * (8u * kQuadRow), sad(qx, uint32_t(pj.x - gx) * 8u, 0u)));
                 const int dx = abs(pi.x - pj.x), dy = abs(pi.y - pj.y);
-                if (MODE == kQuad) return tab[dy * W + dx];
+                if (MODE == kQuad) return tab[dy * kQuadRow + dx];
                 return phi_oct(dx, dy, phi_oct_tab, phi_far);
             };
             auto src_key = [&](int32_t j) -> uint32_t {
@@ -1476,13 +1542,12 @@ __device__ inline void near_group(int32_t qq, const NearGroup* groups, const int
             };
             auto src_f = [&](int32_t j) -> double { return SLICED ? fs[j] : SF[j]; };
             for (int e = 0; e < ne; ++e) {
-                const int4_t en = E[size_t(qq) * kNearEntries + e];   // (first point, end, leaf x, leaf y)
-                const bool near = (en.z == kNearAll || abs(en.z - tx) <= 1) &&
-                                  (en.w == kNearAll || abs(en.w - ty) <= 1);   // uniform when sliced
-                if (near) {
-                    int32_t j = en.x + sl;
+                const int32_t e0 = __builtin_amdgcn_readlane(ent.x, e), e1 = __builtin_amdgcn_readlane(ent.y, e);
+                const int32_t em = __builtin_amdgcn_readlane(ent.z, e);   // child positions near to the range
+                if ((em >> cpos) & 1) {   // uniform when sliced
+                    int32_t j = e0 + sl;
                     if (!SLICED)   // sixteen sources per step: few waits for their scalar loads
-                        for (; j + 15 < en.y; j += 16) {
+                        for (; j + 15 < e1; j += 16) {
                             #pragma unroll
                             for (int r = 0; r < 16; r += 4) {
                                 a0 += phi_at(src_key(j + r), src_pt(j + r)) * src_f(j + r);
@@ -1492,7 +1557,7 @@ __device__ inline void near_group(int32_t qq, const NearGroup* groups, const int
                             }
                         }
                     if (!SLICED)
-                        for (; j + 7 < en.y; j += 8) {
+                        for (; j + 7 < e1; j += 8) {
                             a0 += phi_at(src_key(j), src_pt(j)) * src_f(j);
                             a1 += phi_at(src_key(j + 1), src_pt(j + 1)) * src_f(j + 1);
                             a2 += phi_at(src_key(j + 2), src_pt(j + 2)) * src_f(j + 2);
@@ -1502,7 +1567,7 @@ __device__ inline void near_group(int32_t qq, const NearGroup* groups, const int
                             a2 += phi_at(src_key(j + 6), src_pt(j + 6)) * src_f(j + 6);
                             a3 += phi_at(src_key(j + 7), src_pt(j + 7)) * src_f(j + 7);
                         }
-                    for (; j + 3 * S < en.y; j += 4 * S) {
+                    for (; j + 3 * S < e1; j += 4 * S) {
                         a0 += phi_at(src_key(j), src_pt(j)) * src_f(j);
                         a1 += phi_at(src_key(j + S), src_pt(j + S)) * src_f(j + S);
                         a2 += phi_at(src_key(j + 2 * S), src_pt(j + 2 * S)) * src_f(j + 2 * S);
@@ -1510,7 +1575,7 @@ __device__ inline void near_group(int32_t qq, const NearGroup* groups, const int
                     }
                     if (!SLICED) {
                         // the last one to three sources with their loads issued together (one wait)
-                        const int32_t rem = en.y - j;
+                        const int32_t rem = e1 - j;
                         if (rem == 3) {
                             a0 += phi_at(src_key(j), src_pt(j)) * src_f(j);
                             a1 += phi_at(src_key(j + 1), src_pt(j + 1)) * src_f(j + 1);
@@ -1522,31 +1587,18 @@ __device__ inline void near_group(int32_t qq, const NearGroup* groups, const int
                             a0 += phi_at(src_key(j), src_pt(j)) * src_f(j);
                         }
                     } else {
-                        for (; j < en.y; j += S) a0 += phi_at(src_key(j), src_pt(j)) * src_f(j);
+                        for (; j < e1; j += S) a0 += phi_at(src_key(j), src_pt(j)) * src_f(j);
                     }
                 }
             }
             if (far) {
-                const int64_t loc = int64_t(pi.x - tx * side) + side * int64_t(pi.y - ty * side);
-                const double* tlp = leafT + loc * P;
-                const double* uh = U + size_t(leaf) * P;
+                const int32_t loc = pi.x - tx * int32_t(side) + int32_t(side) * (pi.y - ty * int32_t(side));
                 if (SLICED) {
+                    const double* tlp = leafT + size_t(loc) * P;
+                    const double* uh = U + size_t(leaf) * P;
                     for (int p = sl; p < P; p += S) a1 += tlp[p] * uh[p];
                 } else {
-                    // coefficient pairs from the coefficient-major table: the wave's lanes read
-                    // pair p of their cells from one span of 16 side^2 bytes (about half as many
-                    // cache lines per load as whole rows of the cell-major table)
-                    const int64_t nc = side * side;
-                    const double2_t* tl2 = reinterpret_cast<const double2_t*>(leafTt) + loc;
-                    const double2_t* uh2 = reinterpret_cast<const double2_t*>(uh);
-                    #pragma unroll
-                    for (int p = 0; p < P / 2; p += 2) {
-                        const double2_t x0 = tl2[p * nc], y0 = uh2[p], x1 = tl2[(p + 1) * nc], y1 = uh2[p + 1];
-                        a0 += x0.x * y0.x;
-                        a1 += x0.y * y0.y;
-                        a2 += x1.x * y1.x;
-                        a3 += x1.y * y1.y;
-                    }
+                    a1 += far_rows<P>(leaf0, nleaf, bnd, i0, loc, leafT, U, sfar);
                 }
             }
             double acc = (a0 + a1) + (a2 + a3);
@@ -1557,45 +1609,35 @@ __device__ inline void near_group(int32_t qq, const NearGroup* groups, const int
     }
 }
 
-// Window mode is held to six waves per SIMD (80 VGPRs): left free, the compiler keeps all 24
-// coefficient-pair loads of the far field in flight (103 VGPRs, four waves per SIMD), which
-// measured slower.
+// Four waves per SIMD: six spill scalar registers (16-source steps hold 48 of them) and measured
+// 115 against 93 us.
 template <int P, int MODE>
-__global__ __launch_bounds__(near_threads(MODE), MODE == kWindow ? 6 : 1) void k_near(int32_t q0, int32_t q1, const NearGroup* groups,
-                                                      const int4* ents, const int32_t* box_pt0,
-                                                      const int32_t* box_pt1, const uint64_t* box_key,
-                                                      const int32_t* box_inst, int64_t side, int W, const int2* pts,
-                                                      const uint32_t* pkey, const double* fs,
-                                                      const int32_t* perm_local, const ExecPtrs* tab_ptrs,
-                                                      ExecPtrs single, const double* U,
-                                                      const double* leafT, const double* leafTt,
-                                                      const uint8_t* far_inst, const double* phi_oct_tab,
-                                                      const PhiFar* phi_far) {
+__global__ __launch_bounds__(near_threads(MODE), 4) void k_near(
+    int32_t q0, int32_t q1, const NearGroup* groups, const int4* ents, int64_t side, int W, const int2* pts,
+    const uint32_t* pkey, const double* fs, const int32_t* perm_local, const ExecPtrs* tab_ptrs, ExecPtrs single,
+    const double* U, const double* leafT, const double* phi_oct_tab, const PhiFar* phi_far) {
     constexpr int kNearBlock = near_threads(MODE), kNearWaves = kNearBlock / 64;
     // fixed-size table (largest window: side 32), so that its base is a compile-time constant
     // and folds into the address of every read
     __shared__ double tab[MODE == kGlobal ? 1 : kNearTabMax];
+    __shared__ double sfar[kNearWaves][64];   // far fields of each wave's targets
     const int tid = threadIdx.x, wave = tid >> 6;
     if (MODE != kGlobal) {
-        const int c = (MODE == kWindow) ? int(2 * side - 1) : 0;
-        constexpr int kU = 8;   // loads in flight per thread
-        for (int i0 = tid; i0 < W * W; i0 += kNearBlock * kU) {
+        const int c = (MODE == kWindow) ? int(2 * side - 1) : 0, n = (MODE == kWindow) ? W * W : W * kQuadRow;
+        const int row = (MODE == kWindow) ? W : kQuadRow;
+        constexpr int kU = 9;   // loads in flight per thread: the whole table in one round
+        for (int i0 = tid; i0 < n; i0 += kNearBlock * kU) {
             double v[kU];
             #pragma unroll
             for (int u = 0; u < kU; ++u) {
-                const int i = i0 + u * kNearBlock;
-                v[u] = 0.0;
-                if (i < W * W) {
-                    int dy = i / W - c, dx = i - (i / W) * W - c;
-                    dx = dx < 0 ? -dx : dx;
-                    dy = dy < 0 ? -dy : dy;
-                    const int hi = max(dx, dy), lo = min(dx, dy);
-                    v[u] = phi_oct_tab[hi * (hi + 1) / 2 + lo];
-                }
+                const int i = min(i0 + u * kNearBlock, n - 1);
+                const int dy = abs(i / row - c), dx = abs(i - (i / row) * row - c);
+                const int hi = max(dx, dy), lo = min(dx, dy);
+                v[u] = phi_oct_tab[hi * (hi + 1) / 2 + lo];
             }
             #pragma unroll
             for (int u = 0; u < kU; ++u)
-                if (i0 + u * kNearBlock < W * W) tab[i0 + u * kNearBlock] = v[u];
+                if (i0 + u * kNearBlock < n) tab[i0 + u * kNearBlock] = v[u];
         }
         __syncthreads();
     }
@@ -1620,22 +1662,36 @@ __global__ __launch_bounds__(near_threads(MODE), MODE == kWindow ? 6 : 1) void k
         const int32_t n = q1 - q0, chunks = (n + 8 * kNearXcdChunk - 1) / (8 * kNearXcdChunk) * 8;
         C = (n + chunks - 1) / chunks;
     }
-    for (int32_t l = first * kNearWaves + wave;; l += nb * kNearWaves) {
-        const int32_t q = q0 + (8 * (l / C) + x) * C + l % C;   // increases with l
-        if (q >= q1) break;
-        const int32_t qq = uniform(q);
-        const int32_t leaf0 = uniform(groups[qq].leaf0), nleaf = uniform(groups[qq].nleaf);
-        const int32_t nt = uniform(box_pt1[leaf0 + nleaf - 1]) - uniform(box_pt0[leaf0]);
+    // word l of group q's record in lane l, its entry l in lane l (and again in the other rows of 16)
+    static_assert(sizeof(NearGroup) == 64, "16 words");
+    const int rl = tid & 15;
+    int32_t l = first * kNearWaves + wave, rec = 0;
+    int4 ent = make_int4(0, 0, 0, 0);
+    auto group_at = [&](int32_t ll) -> int32_t { return q0 + (8 * (ll / C) + x) * C + ll % C; };   // increases with ll
+    auto fetch = [&](int32_t q) {
+        if (q < q1) {
+            rec = reinterpret_cast<const int32_t*>(groups)[size_t(q) * 16 + rl];
+            ent = ents[size_t(q) * kNearEntries + rl];   // entries past the group's last are not used
+        }
+    };
+    int32_t q = group_at(l);
+    fetch(q);
+    while (q < q1) {
+        const int32_t r = rec;
+        const int4 en = ent;
+        l += nb * kNearWaves;
+        q = group_at(l);
+        fetch(q);
+        asm volatile("" ::: "memory");   // the next group's loads go out here
+        const int32_t nt = __builtin_amdgcn_readlane(r, 8) - __builtin_amdgcn_readlane(r, 4);
         // group mode when half a wave or more is busy and phi comes from an LDS table; leaf by
         // leaf otherwise (the octant table in global memory is read faster a leaf at a time)
         if (MODE != kGlobal && nt > 32)
-            near_group<P, MODE, false>(qq, groups, ents, box_pt0, box_pt1, box_key, box_inst, side, W, tab, tb, kofs, pts,
-                                       pkey, fs, perm_local, tab_ptrs, single, U, leafT, leafTt, far_inst,
-                                       phi_oct_tab, phi_far);
+            near_group<P, MODE, false>(r, en, side, W, tab, tb, kofs, pts, pkey, fs, perm_local, tab_ptrs, single, U,
+                                       leafT, sfar[wave], phi_oct_tab, phi_far);
         else
-            near_group<P, MODE, true>(qq, groups, ents, box_pt0, box_pt1, box_key, box_inst, side, W, tab, tb, kofs, pts,
-                                      pkey, fs, perm_local, tab_ptrs, single, U, leafT, leafTt, far_inst,
-                                      phi_oct_tab, phi_far);
+            near_group<P, MODE, true>(r, en, side, W, tab, tb, kofs, pts, pkey, fs, perm_local, tab_ptrs, single, U,
+                                      leafT, sfar[wave], phi_oct_tab, phi_far);
     }
 }
 
@@ -1707,10 +1763,9 @@ constexpr int kStageRound = 8;   // staged elements per lane with their loads in
 
 template <int P>
 __global__ __launch_bounds__(64 * kStagedWaves) void k_near_staged(
-    int32_t q0, int32_t q1, const NearGroup* groups, const int4* ents, const int32_t* box_pt0, const int32_t* box_pt1,
-    const uint64_t* box_key, const int32_t* box_inst, int64_t side, const int2* pts, const double* fs,
-    const int32_t* perm_local, const ExecPtrs* tab_ptrs, ExecPtrs single, const double* U,
-    const double* leafT, const uint8_t* far_inst, const double* phi_oct_tab) {
+    int32_t q0, int32_t q1, const NearGroup* groups, const int4* ents, int64_t side, const int2* pts, const double* fs,
+    const int32_t* perm_local, const ExecPtrs* tab_ptrs, ExecPtrs single, const double* U, const double* leafT,
+    const double* phi_oct_tab) {
     __shared__ int2 s_xy[kStagedWaves][kStageCap];
     __shared__ double s_f[kStagedWaves][kStageCap];
     const int lane = int(threadIdx.x) & 63, wave = int(threadIdx.x) >> 6;
@@ -1720,22 +1775,17 @@ __global__ __launch_bounds__(64 * kStagedWaves) void k_near_staged(
     int2* sxy = s_xy[wave];
     double* sf = s_f[wave];
     const cptr<int4_t> E = as_const(reinterpret_cast<const int4_t*>(ents)) + size_t(qq) * kNearEntries;
-    const int32_t leaf0 = uniform(groups[qq].leaf0), nleaf = uniform(groups[qq].nleaf);
-    const int32_t ne = uniform(groups[qq].ne);
+    const cptr<NearGroup> R = as_const(groups + qq);
+    const int32_t leaf0 = R->leaf0, ne = R->ne;
     int ls = 0;
     while ((int64_t(1) << ls) < side) ++ls;
-    const int32_t t0 = uniform(box_pt0[leaf0]), t_end = uniform(box_pt1[leaf0 + nleaf - 1]);
-    const int32_t k_inst = uniform(box_inst[leaf0]);
-    const bool far = far_inst[k_inst] != 0;
-    const ExecPtrs eio = tab_ptrs ? tab_ptrs[k_inst] : single;
+    // first points of the group's leaves, to find each target's leaf
+    const int32_t t0 = R->bnd[0], bnd1 = R->bnd[1], bnd2 = R->bnd[2], bnd3 = R->bnd[3], t_end = R->bnd[4];
+    const bool far = R->far != 0;
+    const ExecPtrs eio = tab_ptrs ? tab_ptrs[R->inst] : single;
     double* u = eio.u;
     const bool sorted_out = eio.sorted != 0;   // u indexed by sorted point
     const int32_t tgt0 = eio.tgt0;
-    // first points of the group's leaves, to find each target's leaf
-    int32_t bnd1 = t_end, bnd2 = t_end, bnd3 = t_end;
-    if (nleaf > 1) bnd1 = uniform(box_pt0[leaf0 + 1]);
-    if (nleaf > 2) bnd2 = uniform(box_pt0[leaf0 + 2]);
-    if (nleaf > 3) bnd3 = uniform(box_pt0[leaf0 + 3]);
     // entries: start offset of each range in the concatenated source list
     int32_t e_p0[kNearEntries], e_off[kNearEntries + 1];
     e_off[0] = 0;
@@ -2260,14 +2310,11 @@ void launch_m2l_bf16(const BoxTile* tiles, const int32_t* ntiles_dev, int32_t ma
                        box_list, il27, ops, Qb, qs, zrow, U);
 }
 
-void launch_near(int32_t q0, int32_t q1, const NearGroup* groups, const int4* ents, const int32_t* box_pt0,
-                 const int32_t* box_pt1, const uint64_t* box_key, const int32_t* box_inst, int64_t side,
-                 const int32_t* pts, const uint32_t* pkey, const double* fs, const int32_t* perm_local,
-                 const ExecPtrs* tab, const ExecPtrs& single, const double* U, const double* leafT,
-                 const double* leafTt, const uint8_t* far_inst, const double* phi_oct, const PhiFar* phi_far,
-                 hipStream_t st) {
+void launch_near(int32_t q0, int32_t q1, const NearGroup* groups, const int4* ents, int64_t side, const int32_t* pts,
+                 const uint32_t* pkey, const double* fs, const int32_t* perm_local, const ExecPtrs* tab,
+                 const ExecPtrs& single, const double* U, const double* leafT, const double* phi_oct,
+                 const PhiFar* phi_far, hipStream_t st) {
     if (q1 <= q0) return;
-    if (side <= 32 && leafTt == nullptr) throw std::logic_error("near field without its coefficient-major T_ofs");
     // with an LDS table: persistent blocks, as many as fit on the device at once, so that
     // each builds its table once and then walks many groups; else one group per wave
     auto grid = [&](const void* fn, int threads, size_t lds, bool persistent) {
@@ -2288,25 +2335,22 @@ void launch_near(int32_t q0, int32_t q1, const NearGroup* groups, const int4* en
         if (W * W > kNearTabMax) throw std::logic_error("near-field window table larger than its array");
         constexpr int nt = near_threads(kWindow);
         const unsigned g = grid(reinterpret_cast<const void*>(&k_near<kRankPad, kWindow>), nt, lds, true);
-        hipLaunchKernelGGL((k_near<kRankPad, kWindow>), dim3(g), dim3(nt), lds, st, q0, q1, groups, ents,
-                           box_pt0, box_pt1, box_key, box_inst, side, W, p2, pkey, fs, perm_local, tab, single, U,
-                           leafT, leafTt, far_inst, phi_oct, phi_far);
+        hipLaunchKernelGGL((k_near<kRankPad, kWindow>), dim3(g), dim3(nt), lds, st, q0, q1, groups, ents, side, W, p2, pkey, fs, perm_local, tab, single, U,
+                           leafT, phi_oct, phi_far);
     } else if (side <= 32) {
-        const int W = int(2 * side);
+        const int W = 64;   // rows: offsets of sides up to 32
         const size_t lds = 0;
-        if (W * W > kNearTabMax) throw std::logic_error("near-field quadrant table larger than its array");
+        if (W * kQuadRow > kNearTabMax || 2 * side > W) throw std::logic_error("near-field quadrant table larger than its array");
         constexpr int nt = near_threads(kQuad);
         const unsigned g = grid(reinterpret_cast<const void*>(&k_near<kRankPad, kQuad>), nt, lds, true);
-        hipLaunchKernelGGL((k_near<kRankPad, kQuad>), dim3(g), dim3(nt), lds, st, q0, q1, groups, ents,
-                           box_pt0, box_pt1, box_key, box_inst, side, W, p2, pkey, fs, perm_local, tab, single, U,
-                           leafT, leafTt, far_inst, phi_oct, phi_far);
+        hipLaunchKernelGGL((k_near<kRankPad, kQuad>), dim3(g), dim3(nt), lds, st, q0, q1, groups, ents, side, W, p2, pkey, fs, perm_local, tab, single, U,
+                           leafT, phi_oct, phi_far);
     } else {
         // every near offset (at most 2 side - 1 <= 255) lies inside the device octant table
         if (2 * side - 1 > kPhiDeviceRadius) throw std::logic_error("leaf wider than the near-field table allows");
         const unsigned g = unsigned((q1 - q0 + kStagedWaves - 1) / kStagedWaves);
-        hipLaunchKernelGGL(k_near_staged<kRankPad>, dim3(g), dim3(64 * kStagedWaves), 0, st, q0, q1, groups, ents,
-                           box_pt0, box_pt1, box_key, box_inst, side, p2, fs, perm_local, tab, single,
-                           U, leafT, far_inst, phi_oct);
+        hipLaunchKernelGGL(k_near_staged<kRankPad>, dim3(g), dim3(64 * kStagedWaves), 0, st, q0, q1, groups, ents, side, p2, fs, perm_local, tab, single,
+                           U, leafT, phi_oct);
     }
 }
 

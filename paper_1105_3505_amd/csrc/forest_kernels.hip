@@ -729,7 +729,8 @@ __global__ void k_point_boxes(const int32_t* box_pt0, const int32_t* box_pt1, in
 // so do the two cells above them and the two below (near by y alone).
 __global__ void k_near_groups(int32_t q0, int32_t h1_start, int32_t h1_count, const int32_t* roots, int32_t nroots,
                               const int32_t* box_child, const int32_t* nb9, const int32_t* box_pt0,
-                              const int32_t* box_pt1, const uint64_t* box_key, NearGroup* groups, int4* ents) {
+                              const int32_t* box_pt1, const uint64_t* box_key, const int32_t* box_inst,
+                              const InstInfo* inst, NearGroup* groups, int4* ents) {
     const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     const int32_t q = int32_t(t >> 4);
     const int j = int(threadIdx.x & 15), lane = int(threadIdx.x & 63);
@@ -777,22 +778,34 @@ __global__ void k_near_groups(int32_t q0, int32_t h1_start, int32_t h1_count, co
         rank += (bi >= 0 && bi < b) ? 1 : 0;
     }
     if (!active) return;
-    if (b >= 0 && own) {
-        ents[size_t(q0 + q) * kNearEntries + rank] = make_int4(box_pt0[b], box_pt1[b + nleaf - 1], kNearAll, kNearAll);
-    } else if (b >= 0 && rowpair) {
-        ents[size_t(q0 + q) * kNearEntries + rank] =
-            make_int4(box_pt0[b], box_pt1[b_end], kNearAll, int32_t(compact_bits(box_key[b] >> 1)));
-    } else if (b >= 0) {
-        const uint64_t key = box_key[b];
-        ents[size_t(q0 + q) * kNearEntries + rank] =
-            make_int4(box_pt0[b], box_pt1[b], int32_t(compact_bits(key)), int32_t(compact_bits(key >> 1)));
+    if (b >= 0) {
+        // child c of the group is near the cell when neither coordinate is two cells off (root
+        // leaves: position 0 alone)
+        int32_t mask = 15;
+        if (q < h1_count)
+            for (int c = 0; c < 4; ++c) {
+                const int dx = (j & 3) - 1 - (c & 1), dy = (j >> 2) - 1 - (c >> 1);
+                if (dx < -1 || dx > 1 || dy < -1 || dy > 1) mask &= ~(1 << c);
+            }
+        const int32_t last = own ? b + nleaf - 1 : b_end;   // last box of the entry
+        ents[size_t(q0 + q) * kNearEntries + rank] = make_int4(box_pt0[b], box_pt1[last], mask, 0);
     }
     if (j == 0) {
         NearGroup G;
         G.leaf0 = leaf0;
         G.nleaf = nleaf;
         G.ne = cnt;
-        G.pad = 0;
+        G.inst = box_inst[leaf0];
+        const int32_t end = box_pt1[leaf0 + nleaf - 1];
+        const uint64_t key0 = box_key[leaf0];
+        G.cpos = 0;
+        for (int k = 0; k < 5; ++k) G.bnd[k] = k < nleaf ? box_pt0[leaf0 + k] : end;
+        for (int k = 0; k < 4; ++k)
+            if (k < nleaf) G.cpos |= int32_t(box_key[leaf0 + k] & 3ull) << (2 * k);
+        G.lx = int32_t(compact_bits(key0) & ~1u);
+        G.ly = int32_t(compact_bits(key0 >> 1) & ~1u);
+        G.far = inst[G.inst].L >= 2 ? 1 : 0;
+        G.pad0 = G.pad1 = G.pad2 = 0;
         groups[q0 + q] = G;
     }
 }
@@ -1361,13 +1374,13 @@ void launch_point_boxes(const int32_t* box_pt0, const int32_t* box_pt1, int32_t 
 
 void launch_near_groups(int32_t q0, int32_t h1_start, int32_t h1_count, const int32_t* roots, int32_t nroots,
                         const int32_t* box_child, const int32_t* nb9, const int32_t* box_pt0,
-                        const int32_t* box_pt1, const uint64_t* box_key, NearGroup* groups, int4* ents,
-                        hipStream_t st) {
+                        const int32_t* box_pt1, const uint64_t* box_key, const int32_t* box_inst,
+                        const InstInfo* inst, NearGroup* groups, int4* ents, hipStream_t st) {
     const int32_t n = h1_count + nroots;
     if (n <= 0) return;
     hipLaunchKernelGGL(k_near_groups, dim3(grid_for(int64_t(n) * 16)), dim3(kBlock), 0, st, q0, h1_start, h1_count,
                        roots, nroots,
-                       box_child, nb9, box_pt0, box_pt1, box_key, groups, ents);
+                       box_child, nb9, box_pt0, box_pt1, box_key, box_inst, inst, groups, ents);
 }
 
 }  // namespace lfmm

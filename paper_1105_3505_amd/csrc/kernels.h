@@ -64,10 +64,6 @@ struct DevOps {
     int64_t leaf_side = 0;
     int nlev = 0;                  // heights 0 .. nlev-1
     double* leafT = nullptr;       // [side^2][kRankPad]: T_ofs column of each cell, cell-major
-    // sides up to 32 (the near-field kernel with an LDS phi table): the same entries
-    // coefficient-major in pairs, [kRankPad / 2][side^2][2], so that lanes evaluating the far
-    // field at different cells read one pair each from a span of 16 side^2 bytes
-    double* leafTt = nullptr;
     // [nlev][4] operators in the fragment order of ifo below: T_ofo (M2M, rows = parent
     // skeleton) and T_ofo^T (L2L, rows = child skeleton)
     double* ofo_rm = nullptr;
@@ -112,16 +108,18 @@ struct PhiFar {
 };
 
 // Near-field group: the leaves leaf0 .. leaf0 + nleaf - 1 (the children of one parent box,
-// or a root that is a leaf), whose sources are the ne point ranges listed for the group.
+// or a root that is a leaf), whose sources are the ne point ranges listed for the group.  One
+// record of 16 words, so that a wave reads all it needs to know of a group in one load.
 struct NearGroup {
-    int32_t leaf0, nleaf, ne, pad;
+    int32_t leaf0, nleaf, ne, inst;
+    int32_t bnd[5];             // first point of each leaf; entries nleaf .. 4: end of the last
+    int32_t lx, ly;             // leaf coordinates of the parent's child position 0
+    int32_t cpos;               // child position c = x bit + 2 y bit of leaf k in bits 2 k, 2 k + 1
+    int32_t far, pad0, pad1, pad2;   // far: the instance's tree has a far field (leaf level >= 2)
 };
 // At most 16 source leaves per group (the 4 x 4 block around a parent's children); entry
-// (first point, end point, leaf x, leaf y) in leaf coordinates of the group's level.
+// (first point, end point, bits of the child positions near to it, 0).
 constexpr int kNearEntries = 16;
-// leaf coordinate of a near-field entry that matches every target of its group: both for the
-// group's own leaves (one run of points), x alone for the two cells above or below them
-constexpr int32_t kNearAll = -(1 << 30);
 
 // Per-execute load/potential pointers of each instance, with the roles of its points: an
 // instance's points are its sources followed by its targets (the same points when targets =
@@ -272,8 +270,8 @@ void launch_point_boxes(const int32_t* box_pt0, const int32_t* box_pt1, int32_t 
 // h1_start .. h1_start + h1_count - 1, then the root leaves roots[0 .. nroots)
 void launch_near_groups(int32_t q0, int32_t h1_start, int32_t h1_count, const int32_t* roots, int32_t nroots,
                         const int32_t* box_child, const int32_t* nb9, const int32_t* box_pt0,
-                        const int32_t* box_pt1, const uint64_t* box_key, NearGroup* groups, int4* ents,
-                        hipStream_t st);
+                        const int32_t* box_pt1, const uint64_t* box_key, const int32_t* box_inst,
+                        const InstInfo* inst, NearGroup* groups, int4* ents, hipStream_t st);
 
 // ---- evaluation passes (fmm_kernels.hip) ---------------------------------------------------
 // P2M of the leaves [leaf0, leaf1); reads the loads (tab per instance, or single for a
@@ -308,12 +306,10 @@ void launch_m2l_mixed(const BoxTile* tiles, const int32_t* ntiles_dev, int32_t m
                       const float* Qh, const float* Ql, const double* qs, int32_t zrow, double* U,
                       hipStream_t st);
 // L2P + near field + un-permutation for the groups [q0, q1) of one leaf side
-void launch_near(int32_t q0, int32_t q1, const NearGroup* groups, const int4* ents, const int32_t* box_pt0,
-                 const int32_t* box_pt1, const uint64_t* box_key, const int32_t* box_inst, int64_t side,
-                 const int32_t* pts, const uint32_t* pkey, const double* fs, const int32_t* perm_local,
-                 const ExecPtrs* tab, const ExecPtrs& single, const double* U, const double* leafT,
-                 const double* leafTt, const uint8_t* far_inst, const double* phi_oct, const PhiFar* phi_far,
-                 hipStream_t st);
+void launch_near(int32_t q0, int32_t q1, const NearGroup* groups, const int4* ents, int64_t side, const int32_t* pts,
+                 const uint32_t* pkey, const double* fs, const int32_t* perm_local, const ExecPtrs* tab,
+                 const ExecPtrs& single, const double* U, const double* leafT, const double* phi_oct,
+                 const PhiFar* phi_far, hipStream_t st);
 // Adaptive tree passes.  P2L (X lists): u-hat of box tau += phi(skeleton of tau - x_j) f_j over
 // the points of its X leaves, for the nx boxes xitems.  Near field of the adaptive leaves
 // (items): U-list sources, W-list skeletons with their q-hat (M2P), L2P at each point's finest
