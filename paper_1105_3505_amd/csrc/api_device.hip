@@ -1621,15 +1621,43 @@ lfmm_status lfmm::root_bits_of(lfmm_ctx* ctx, int32_t K, const int64_t* n, const
     return guarded([&]() -> lfmm_status {
         LFMM_HIP(hipSetDevice(ctx->device));
         hipStream_t st = as_stream(stream);
+        std::vector<const int32_t*> ptr(xy, xy + K);
+        std::vector<Chunk> chunks;
+        std::vector<int32_t> first(size_t(K) + 1, 0);
+        for (int32_t k = 0; k < K; ++k) {
+            first[size_t(k)] = int32_t(chunks.size());
+            for (int64_t b = 0; b < n[k]; b += kChunk)
+                chunks.push_back(Chunk{k, int32_t(b), int32_t(std::min<int64_t>(b + kChunk, n[k])), 0});
+        }
+        first[size_t(K)] = int32_t(chunks.size());
         Arena a(&ctx->pool);
-        a.reserve(size_t(K) * 16);
+        a.reserve(size_t(K) * sizeof(void*));
+        a.reserve(chunks.size() * sizeof(Chunk));
+        a.reserve(first.size() * 4);
+        a.reserve(chunks.size() * 16);
         a.allocate();
-        int32_t* box = a.take<int32_t>(size_t(K) * 4);
-        launch_extents(K, n, xy, box, st);
+        const int32_t** d_ptr = a.take<const int32_t*>(size_t(K));
+        Chunk* d_chunks = a.take<Chunk>(chunks.size());
+        int32_t* d_first = a.take<int32_t>(first.size());
+        int32_t* part = a.take<int32_t>(chunks.size() * 4);
+        Stager stage(ctx);
+        stage.add(d_ptr, ptr);
+        stage.add(d_chunks, chunks);
+        stage.add(d_first, first);
+        // the boxes are written to pinned host memory by the kernel
+        struct Pinned {
+            lfmm_ctx* c;
+            size_t cls = 0;
+            int32_t* p;
+            Pinned(lfmm_ctx* ctx, size_t bytes) : c(ctx), p(static_cast<int32_t*>(ctx->pinned.acquire(bytes, &cls))) {}
+            ~Pinned() { c->pinned.release(p, cls); }
+        } box(ctx, size_t(K) * 16);
+        SyncOnUnwind unwind;
+        stage.flush(st);
+        launch_extents(K, d_ptr, d_chunks, int32_t(chunks.size()), d_first, part, box.p, st);
         LFMM_HIP(hipGetLastError());
-        std::vector<int32_t> h(size_t(K) * 4);
-        LFMM_HIP(hipMemcpyAsync(h.data(), box, h.size() * 4, hipMemcpyDeviceToHost, st));
         LFMM_HIP(hipStreamSynchronize(st));
+        const std::vector<int32_t> h(box.p, box.p + size_t(K) * 4);
         a.release();
         for (int32_t k = 0; k < K; ++k) {
             const int64_t ext = std::max(int64_t(h[4 * size_t(k) + 2]) - h[4 * size_t(k)],

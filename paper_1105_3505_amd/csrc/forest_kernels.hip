@@ -76,40 +76,6 @@ __global__ void k_concat(int32_t K, const int2* const* xy_tab, const int32_t* pt
     xyc[i] = xy_tab[k][i - pt_off[k]];
 }
 
-// {min x, min y, max x, max y} of n points into box (device), by atomics; box is set to the
-// empty box first by k_extent_init on the same stream.
-__global__ void k_extent_init(int32_t* box, int32_t nbox) {
-    const int32_t i = int32_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i < nbox) {
-        box[4 * i] = INT_MAX;
-        box[4 * i + 1] = INT_MAX;
-        box[4 * i + 2] = INT_MIN;
-        box[4 * i + 3] = INT_MIN;
-    }
-}
-
-__global__ void k_extent(const int2* xy, int64_t n, int32_t* box) {
-    int v[4] = {INT_MAX, INT_MAX, INT_MIN, INT_MIN};
-    for (int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < n; i += int64_t(gridDim.x) * blockDim.x) {
-        const int2 p = xy[i];
-        v[0] = min(v[0], p.x); v[1] = min(v[1], p.y);
-        v[2] = max(v[2], p.x); v[3] = max(v[3], p.y);
-    }
-    #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        v[0] = min(v[0], __shfl_xor(v[0], o, 64));
-        v[1] = min(v[1], __shfl_xor(v[1], o, 64));
-        v[2] = max(v[2], __shfl_xor(v[2], o, 64));
-        v[3] = max(v[3], __shfl_xor(v[3], o, 64));
-    }
-    if ((threadIdx.x & 63) == 0) {
-        atomicMin(&box[0], v[0]);
-        atomicMin(&box[1], v[1]);
-        atomicMax(&box[2], v[2]);
-        atomicMax(&box[3], v[3]);
-    }
-}
-
 // v = {min x, min y, max x, max y} over the block: wave shuffles, then the four waves
 // through LDS; thread 0 gets the result in v and true
 __device__ inline bool block_minmax4(int v[4]) {
@@ -134,17 +100,16 @@ __device__ inline bool block_minmax4(int v[4]) {
     return true;
 }
 
-__global__ void k_bbox_chunks(const int2* xy, const Chunk* chunks, int32_t* part, int32_t* dmax) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) *dmax = 0;   // the deepest root box, raised by k_bbox_final
-    const Chunk c = chunks[blockIdx.x];
+// Box of the points begin .. end - 1 of xy into part[4 * blockIdx.x ..]; at most kChunk points, one block.
+__device__ inline void chunk_box(const int2* xy, int32_t begin, int32_t end, int32_t* part) {
     int v[4] = {INT_MAX, INT_MAX, INT_MIN, INT_MIN};
     // all of the thread's points loaded before any is used (one wait, not one per point)
     constexpr int kIt = kChunk / kBlock;
     int2 q[kIt];
     #pragma unroll
     for (int it = 0; it < kIt; ++it) {
-        const int32_t i = c.begin + it * kBlock + int32_t(threadIdx.x);
-        q[it] = i < c.end ? xy[i] : xy[c.begin];   // a chunk's first point stands in past its end
+        const int32_t i = begin + it * kBlock + int32_t(threadIdx.x);
+        q[it] = i < end ? xy[i] : xy[begin];   // a chunk's first point stands in past its end
     }
     #pragma unroll
     for (int it = 0; it < kIt; ++it) {
@@ -155,6 +120,38 @@ __global__ void k_bbox_chunks(const int2* xy, const Chunk* chunks, int32_t* part
         for (int q = 0; q < 4; ++q) part[size_t(blockIdx.x) * 4 + q] = v[q];
 }
 
+// v = box of the partial boxes first .. last - 1, by one block; thread 0 gets the result and true
+__device__ inline bool parts_box(const int32_t* part, int32_t first, int32_t last, int v[4]) {
+    v[0] = v[1] = INT_MAX;
+    v[2] = v[3] = INT_MIN;
+    for (int32_t c = first + int32_t(threadIdx.x); c < last; c += kBlock) {
+        v[0] = min(v[0], part[4 * c]); v[1] = min(v[1], part[4 * c + 1]);
+        v[2] = max(v[2], part[4 * c + 2]); v[3] = max(v[3], part[4 * c + 3]);
+    }
+    return block_minmax4(v);
+}
+
+// Boxes of several point sets (of the server's queued requests), a block per chunk and then a block
+// per set: with one launch per set and an atomic per wave on the set's four words, 48 sets took
+// 2.5 ms, the atomics of each queuing on one line.
+__global__ void k_extent_chunks(const int2* const* xy_tab, const Chunk* chunks, int32_t* part) {
+    const Chunk c = chunks[blockIdx.x];
+    chunk_box(xy_tab[c.inst], c.begin, c.end, part);
+}
+
+__global__ void k_extent_final(const int32_t* part, const int32_t* chunk_first, int32_t* box) {
+    int v[4];
+    const int32_t k = int32_t(blockIdx.x);
+    if (parts_box(part, chunk_first[k], chunk_first[k + 1], v))
+        for (int q = 0; q < 4; ++q) box[4 * size_t(k) + q] = v[q];
+}
+
+__global__ void k_bbox_chunks(const int2* xy, const Chunk* chunks, int32_t* part, int32_t* dmax) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) *dmax = 0;   // the deepest root box, raised by k_bbox_final
+    const Chunk c = chunks[blockIdx.x];
+    chunk_box(xy, c.begin, c.end, part);
+}
+
 // One block per instance: its chunks' partial boxes reduced by the block, written to bbox
 // (host memory) and as the instance's root box, depth D (the smallest with 2^D >= extent),
 // point range and N_leaf (max_leaf, or 0 when the host sets it later) into inst, for the
@@ -162,12 +159,8 @@ __global__ void k_bbox_chunks(const int2* xy, const Chunk* chunks, int32_t* part
 __global__ void k_bbox_final(const int32_t* part, const int32_t* chunk_first, const int32_t* pt_off,
                              int32_t max_leaf, int32_t* bbox, InstInfo* inst, int32_t* dmax) {
     const int32_t k = int32_t(blockIdx.x);
-    int v[4] = {INT_MAX, INT_MAX, INT_MIN, INT_MIN};
-    for (int32_t c = chunk_first[k] + int32_t(threadIdx.x); c < chunk_first[k + 1]; c += kBlock) {
-        v[0] = min(v[0], part[4 * c]); v[1] = min(v[1], part[4 * c + 1]);
-        v[2] = max(v[2], part[4 * c + 2]); v[3] = max(v[3], part[4 * c + 3]);
-    }
-    if (!block_minmax4(v)) return;
+    int v[4];
+    if (!parts_box(part, chunk_first[k], chunk_first[k + 1], v)) return;
     for (int q = 0; q < 4; ++q) bbox[size_t(k) * 4 + q] = v[q];
     const int64_t extent = max(int64_t(v[2]) - v[0], int64_t(v[3]) - v[1]) + 1;
     int D = 0;
@@ -1247,13 +1240,11 @@ void launch_upload(void* dst, const void* pinned_src, size_t len, hipStream_t st
                        static_cast<uint64_t*>(dst), int64_t(len));
 }
 
-void launch_extents(int32_t K, const int64_t* n, const int32_t* const* xy, int32_t* box, hipStream_t st) {
-    hipLaunchKernelGGL(k_extent_init, dim3(grid_for(K)), dim3(kBlock), 0, st, box, K);
-    for (int32_t k = 0; k < K; ++k) {
-        const unsigned g = std::min<unsigned>(grid_for(n[k]), 1024u);
-        hipLaunchKernelGGL(k_extent, dim3(g), dim3(kBlock), 0, st, reinterpret_cast<const int2*>(xy[k]), n[k],
-                           box + 4 * size_t(k));
-    }
+void launch_extents(int32_t K, const int32_t* const* xy_tab, const Chunk* chunks, int32_t nchunks,
+                    const int32_t* chunk_first, int32_t* part, int32_t* box, hipStream_t st) {
+    hipLaunchKernelGGL(k_extent_chunks, dim3(unsigned(nchunks)), dim3(kBlock), 0, st,
+                       reinterpret_cast<const int2* const*>(xy_tab), chunks, part);
+    hipLaunchKernelGGL(k_extent_final, dim3(unsigned(K)), dim3(kBlock), 0, st, part, chunk_first, box);
 }
 
 void launch_concat(int32_t K, const int32_t* const* xy_tab, const int32_t* pt_off, int64_t n, int32_t* xyc,

@@ -183,9 +183,11 @@ void scan_rows(const int32_t* in, int32_t* out, int64_t n, int rows, int32_t* to
 struct Chunk { int32_t inst, begin, end, pad; };   // <= kChunk points of one instance
 constexpr int32_t kChunk = 2048;
 
-// {min x, min y, max x, max y} of each of K point sets (n[k] points at xy[k], device; n and xy
-// host arrays) into box[4 K] (device)
-void launch_extents(int32_t K, const int64_t* n, const int32_t* const* xy, int32_t* box, hipStream_t st);
+// {min x, min y, max x, max y} of each of K point sets (xy_tab on the device) into box[4 K], device or
+// pinned host memory; chunks of at most kChunk points of one set each (inst: the set, indices within
+// it), those of set k from chunk_first[k] on (K + 1 entries); part: 4 words per chunk
+void launch_extents(int32_t K, const int32_t* const* xy_tab, const Chunk* chunks, int32_t nchunks,
+                    const int32_t* chunk_first, int32_t* part, int32_t* box, hipStream_t st);
 void launch_concat(int32_t K, const int32_t* const* xy_tab, const int32_t* pt_off, int64_t n,
                    int32_t* xyc, hipStream_t st);
 // partial root boxes per chunk; also zeroes *dmax
