@@ -130,7 +130,7 @@ def _roofline(dom: str, dom_ms: float, info: dict, n: int, precision: str, workl
         side = info["leaf_side"]
         kernel = "k_near<48, %d>" % (0 if side <= 16 else (1 if side <= 32 else 2))
         if side >= 64:
-            kernel = "k_near_staged<48>"
+            kernel = "k_near_wide<48>"
         return {"kernel": kernel, "bound": "alu", "achieved": achieved,
                 "peak": PEAK_FP64_TFLOPS, "unit": "TFLOP/s", "frac": achieved / PEAK_FP64_TFLOPS,
                 "traffic": measured_traffic(workload, kernel), "work_per_launch": flops,

@@ -324,6 +324,7 @@ struct lfmm_ctx {
     Arena table_mem;
     double* phi_oct = nullptr;   // octant table, radius kPhiDeviceRadius
     PhiFar* phi_far = nullptr;   // far-field expansion coefficients of the context's operator
+    PhiFast* phi_fast = nullptr; // and in the form the near field of wide leaves evaluates
     std::map<int64_t, CachedOps*> ops;                // deepest operator set per leaf side
     std::vector<std::unique_ptr<CachedOps>> all_ops;  // every set built; plans may hold any
     std::map<std::pair<int, int>, int32_t> tuned;     // (size class, density class) -> N_leaf
@@ -399,7 +400,7 @@ struct lfmm_plan {
     int32_t* list_off = nullptr;            // [3][nbox + 1] row starts of the U, W, X lists
     int32_t* list_ent[3] = {};              // their entries
     int64_t list_len[3] = {};
-    int32_t* ad_leaves = nullptr;           // adaptive leaves (near-field items)
+    AdLeaf* ad_recs = nullptr;              // adaptive leaves (near-field items)
     int32_t* ad_xboxes = nullptr;           // boxes with a non-empty X list (P2L items)
     int32_t n_ad_leaves = 0, n_ad_xboxes = 0;
     int32_t* pt_box = nullptr;              // finest box of every point
@@ -733,6 +734,15 @@ struct InstanceInput {
 };
 
 namespace {
+
+AdaptiveLists adaptive_lists(const lfmm_plan* pl) {
+    AdaptiveLists lists{};
+    for (int r = 0; r < 3; ++r) {
+        lists.off[r] = pl->list_off + size_t(r) * size_t(pl->nbox + 1);
+        lists.ent[r] = pl->list_ent[r];
+    }
+    return lists;
+}
 
 // Builds the forest of K point sets: Section 6 tree of every instance, lists of Definition 6.1,
 // operator sets for every leaf side used, and the tiles of the matrix passes.  An instance with
@@ -1321,15 +1331,19 @@ void build_forest(lfmm_plan* pl, int32_t K, const InstanceInput* in, int32_t max
         }
         pl->n_ad_leaves = tot[4];
         pl->n_ad_xboxes = tot[6];
-        ma.reserve(size_t(std::max(tot[4], 1)) * 4);
+        ma.reserve(size_t(std::max(tot[4], 1)) * 4);     // their box indices
+        ma.reserve(size_t(std::max(tot[4], 1)) * sizeof(AdLeaf));
         ma.reserve(size_t(std::max(tot[6], 1)) * 4);
         ma.allocate();
         for (int r = 0; r < 3; ++r) pl->list_ent[r] = ma.take<int32_t>(size_t(std::max(tot[r], 1)));
-        pl->ad_leaves = ma.take<int32_t>(size_t(std::max(tot[4], 1)));
+        int32_t* ad_leaves = ma.take<int32_t>(size_t(std::max(tot[4], 1)));
+        pl->ad_recs = ma.take<AdLeaf>(size_t(std::max(tot[4], 1)));
         pl->ad_xboxes = ma.take<int32_t>(size_t(std::max(tot[6], 1)));
         launch_adaptive_lists(true, pl->box_key, pl->box_parent, pl->box_child, pl->box_lev, pl->role, pl->nb9,
                               pl->box_pt0, pl->box_pt1, nb, nullptr, pl->list_off, pl->list_ent, st);
-        launch_compact_positive(lcnt, lpos, nb, pl->ad_leaves, st);
+        launch_compact_positive(lcnt, lpos, nb, ad_leaves, st);
+        launch_ad_records(pl->n_ad_leaves, ad_leaves, adaptive_lists(pl), pl->box_pt0, pl->box_pt1, pl->box_inst,
+                          pl->ad_recs, st);
         launch_compact_positive(lcnt + 2 * nb1, lpos + 2 * nb1, nb, pl->ad_xboxes, st);
     }
     LFMM_HIP(hipGetLastError());
@@ -1399,10 +1413,7 @@ void enqueue_passes(lfmm_plan* pl, const ExecPtrs* tab, const double* f1, double
     mark(4);
     AdaptiveLists lists{};
     if (pl->adaptive) {
-        for (int r = 0; r < 3; ++r) {
-            lists.off[r] = pl->list_off + size_t(r) * size_t(pl->nbox + 1);
-            lists.ent[r] = pl->list_ent[r];
-        }
+        lists = adaptive_lists(pl);
         // P2L of the X lists (after M2L wrote the incoming expansions, before L2L reads
         // them), timed with the downward pass
         launch_p2l(pl->n_ad_xboxes, pl->ad_xboxes, lists, pl->box_pt0, pl->box_pt1, pl->box_key, pl->box_lev,
@@ -1416,17 +1427,16 @@ void enqueue_passes(lfmm_plan* pl, const ExecPtrs* tab, const double* f1, double
     }
     mark(5);
     if (pl->adaptive) {
-        launch_near_adaptive(pl->n_ad_leaves, pl->ad_leaves, lists, pl->box_pt0, pl->box_pt1, pl->box_key,
-                             pl->box_lev, pl->box_inst, pl->d_inst, pl->d_ops, pl->pts, pl->fs, pl->Q, pl->pt_box,
-                             pl->U, pl->perm, tab, single, pl->d_far, pl->ctx->phi_oct, pl->ctx->phi_far,
-                             st);
+        launch_near_adaptive(pl->n_ad_leaves, pl->ad_recs, lists, pl->box_pt0, pl->box_pt1, pl->box_key, pl->box_lev,
+                             pl->d_inst, pl->d_ops, pl->pts, pl->fs, pl->Q, pl->pt_box, pl->U, pl->perm, tab, single,
+                             pl->d_far, pl->ctx->phi_oct, pl->ctx->phi_fast, st);
         mark(6);
         return;
     }
     for (size_t o = 0; o < pl->ops.size(); ++o) {
         const TileRange& r = pl->near_of_ops[o];
         launch_near(r.t0, r.t0 + r.n, pl->groups, pl->ents, pl->ops[o]->dev.leaf_side, pl->pts, pl->pkey, pl->fs,
-                    pl->perm, tab, single, pl->U, pl->ops[o]->dev.leafT, pl->ctx->phi_oct, pl->ctx->phi_far, st);
+                    pl->perm, tab, single, pl->U, pl->ops[o]->dev.leafT, pl->ctx->phi_oct, pl->ctx->phi_fast, st);
     }
     mark(6);
 }
@@ -1704,9 +1714,18 @@ lfmm_status lfmm_ctx_create(int32_t device, const lfmm_options* opt, lfmm_ctx** 
             for (int j = 0; j < 4; ++j) far.c[k][j] = sten.c[k][j];
         ctx->table_mem.reserve(kPhiDeviceEntries * sizeof(double));
         ctx->table_mem.reserve(sizeof(PhiFar));
+        ctx->table_mem.reserve(sizeof(PhiFast));
         ctx->table_mem.allocate();
         ctx->phi_oct = ctx->table_mem.take<double>(kPhiDeviceEntries);
         ctx->phi_far = ctx->table_mem.take<PhiFar>(1);
+        ctx->phi_fast = ctx->table_mem.take<PhiFast>(1);
+        static_assert(kNearRadius == int(kFarRadius) && kFarOctEntries == kFarOcts * kFarPerOct &&
+                          kFarMantEntries == kFarMant, "host and device forms of the expansion");
+        auto fast = std::make_unique<PhiFast>();
+        std::copy(std::begin(far_phi(o.stencil).a), std::end(far_phi(o.stencil).a), fast->a);
+        std::copy(std::begin(far_phi(o.stencil).log), std::end(far_phi(o.stencil).log), fast->log);
+        far_phi_tables(o.stencil, &fast->oct[0][0], &fast->mant[0][0]);
+        LFMM_HIP(hipMemcpy(ctx->phi_fast, fast.get(), sizeof(PhiFast), hipMemcpyHostToDevice));
         LFMM_HIP(hipMemcpy(ctx->phi_oct, tab.data(), tab.size() * sizeof(double), hipMemcpyHostToDevice));
         LFMM_HIP(hipMemcpy(ctx->phi_far, &far, sizeof(PhiFar), hipMemcpyHostToDevice));
         launch_phi_extend(ctx->phi_oct, 128, kPhiDeviceRadius, ctx->phi_far, nullptr);

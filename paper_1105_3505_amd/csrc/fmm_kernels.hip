@@ -1384,16 +1384,13 @@ __global__ __launch_bounds__(kFineThreads) void k_m2l_bf16_fine(const BoxTile* t
 //     each point carries the key K = 8 (y W + x) mod 2^32 (W = 4s - 1), so the byte offset of
 //     phi(x_i - x_j) is K_i - K_j plus a constant: one subtraction per pair.
 //   QUAD (side 32): a table over |dx|, |dy| < 64; a pair's address is two sums of absolute differences.
-//   GLOBAL (side >= 64): the device octant table (radius kPhiDeviceRadius) in global memory,
-//     eq. (3.1) beyond.
-enum LeafMode { kWindow = 0, kQuad = 1, kGlobal = 2 };
+enum LeafMode { kWindow = 0, kQuad = 1 };
 constexpr int kNearXcdChunk = 512;     // most groups per chunk of the near field's XCD-aware walk
 constexpr int kQuadRow = 65;           // doubles a row of the quad table (odd: rows start on different banks)
 constexpr int kNearTabMax = 64 * kQuadRow;   // doubles: the quad table (side 32); W^2 = 63^2 of the window (side 16)
-// Block size per mode.  With an LDS phi table, 512-thread blocks share one table among eight
-// waves and run persistently (each builds its table once); with the global table, 256-thread
-// blocks take one group per wave and the hardware balances uneven groups.
-constexpr int near_threads(int mode) { return mode == kGlobal ? 256 : 512; }
+// Block size: 512 threads share one table among eight waves and run persistently (each block builds
+// its table once).
+constexpr int kNearBlock = 512;
 
 // |a - b| + c in one instruction (spelled out, the compiler rearranges it into five); b uniform
 __device__ inline uint32_t sad(uint32_t a, uint32_t b, uint32_t c) {
@@ -1475,8 +1472,7 @@ __device__ inline void near_group(int32_t rec, int4 ent, int64_t side, int W, co
                                   uint32_t kofs, const int2* pts,
                                   const uint32_t* pkey, const double* fs, const int32_t* perm_local,
                                   const ExecPtrs* tab_ptrs, ExecPtrs single, const double* U,
-                                  const double* leafT, double* sfar, const double* phi_oct_tab,
-                                  const PhiFar* phi_far) {
+                                  const double* leafT, double* sfar) {
     const int lane = threadIdx.x & 63;
     const cptr<uint32_t> SK = as_const(pkey);
     const cptr<double> SF = as_const(fs);
@@ -1525,8 +1521,7 @@ __device__ inline void near_group(int32_t rec, int4 ent, int64_t side, int W, co
                     return *reinterpret_cast<const double*>(
                         tb + sad(qy, uint32_t(pj.y - gy) * (8u * kQuadRow), sad(qx, uint32_t(pj.x - gx) * 8u, 0u)));
                 const int dx = abs(pi.x - pj.x), dy = abs(pi.y - pj.y);
-                if (MODE == kQuad) return tab[dy * kQuadRow + dx];
-                return phi_oct(dx, dy, phi_oct_tab, phi_far);
+                return tab[dy * kQuadRow + dx];
             };
             auto src_key = [&](int32_t j) -> uint32_t {
                 if (MODE != kWindow) return 0u;
@@ -1612,17 +1607,17 @@ __device__ inline void near_group(int32_t rec, int4 ent, int64_t side, int W, co
 // Four waves per SIMD: six spill scalar registers (16-source steps hold 48 of them) and measured
 // 115 against 93 us.
 template <int P, int MODE>
-__global__ __launch_bounds__(near_threads(MODE), 4) void k_near(
+__global__ __launch_bounds__(kNearBlock, 4) void k_near(
     int32_t q0, int32_t q1, const NearGroup* groups, const int4* ents, int64_t side, int W, const int2* pts,
     const uint32_t* pkey, const double* fs, const int32_t* perm_local, const ExecPtrs* tab_ptrs, ExecPtrs single,
-    const double* U, const double* leafT, const double* phi_oct_tab, const PhiFar* phi_far) {
-    constexpr int kNearBlock = near_threads(MODE), kNearWaves = kNearBlock / 64;
+    const double* U, const double* leafT, const double* phi_oct_tab) {
+    constexpr int kNearWaves = kNearBlock / 64;
     // fixed-size table (largest window: side 32), so that its base is a compile-time constant
     // and folds into the address of every read
-    __shared__ double tab[MODE == kGlobal ? 1 : kNearTabMax];
+    __shared__ double tab[kNearTabMax];
     __shared__ double sfar[kNearWaves][64];   // far fields of each wave's targets
     const int tid = threadIdx.x, wave = tid >> 6;
-    if (MODE != kGlobal) {
+    {
         const int c = (MODE == kWindow) ? int(2 * side - 1) : 0, n = (MODE == kWindow) ? W * W : W * kQuadRow;
         const int row = (MODE == kWindow) ? W : kQuadRow;
         constexpr int kU = 9;   // loads in flight per thread: the whole table in one round
@@ -1684,14 +1679,13 @@ __global__ __launch_bounds__(near_threads(MODE), 4) void k_near(
         fetch(q);
         asm volatile("" ::: "memory");   // the next group's loads go out here
         const int32_t nt = __builtin_amdgcn_readlane(r, 8) - __builtin_amdgcn_readlane(r, 4);
-        // group mode when half a wave or more is busy and phi comes from an LDS table; leaf by
-        // leaf otherwise (the octant table in global memory is read faster a leaf at a time)
-        if (MODE != kGlobal && nt > 32)
+        // group mode when half a wave or more is busy, leaf by leaf otherwise
+        if (nt > 32)
             near_group<P, MODE, false>(r, en, side, W, tab, tb, kofs, pts, pkey, fs, perm_local, tab_ptrs, single, U,
-                                       leafT, sfar[wave], phi_oct_tab, phi_far);
+                                       leafT, sfar[wave]);
         else
             near_group<P, MODE, true>(r, en, side, W, tab, tb, kofs, pts, pkey, fs, perm_local, tab_ptrs, single, U,
-                                      leafT, sfar[wave], phi_oct_tab, phi_far);
+                                      leafT, sfar[wave]);
     }
 }
 
@@ -1745,139 +1739,299 @@ __global__ void k_load_stats_final(const double* part, double* out) {
     out[2] = bad;
 }
 
-// Leaf pass for leaf sides >= 64 (phi from the device octant table: every offset
-// of a near pair, at most 2 side - 1 = 255, is a table entry).  Such leaves are the sparse
-// ones of widely spread or clustered inputs: a group (the up to four leaves of one parent) holds
-// a few dozen targets and its 4 x 4 block of source leaves a few hundred sources.  A wave takes
-// one group.  It first copies the sources of all the group's ranges into LDS (coordinates and
-// loads; the ranges' loads are independent, so their latencies overlap), then sums from LDS:
-// the group's targets take T lanes each (T the power of two at or above their count, at most
-// 64) of S = 64 / T slices, slice s taking every S-th staged source; a pair counts when the
-// source's leaf neighbours the target's (leaf coordinates from the point coordinates), and its
-// phi is a gather from the table.  The slices' sums meet by xor shuffles.  Groups with more
-// than kStageCap sources are summed in chunks of that many.  L2P (T_tfi = T_ofs^T) and the
-// caller-order write are as in k_near.
-constexpr int kStageCap = 512;
-constexpr int kStagedWaves = 4;
-constexpr int kStageRound = 8;   // staged elements per lane with their loads in flight together
+// phi from radius kNearRadius on (PhiFast), the table below it: in LDS, both built by every block.
+struct FastTab {
+    static constexpr int kRow = kNearRadius + 1;   // doubles a row of the near table (odd)
+    double near[kNearRadius * kRow];
+};
+
+struct FastCoef {
+    double a[14], log[5];
+};
+
+__device__ inline void load_near_tab(FastTab& t, const double* phi_oct_tab, int tid, int nt) {
+    for (int i = tid; i < kNearRadius * FastTab::kRow; i += nt) {
+        const int dy = i / FastTab::kRow, dx = i - dy * FastTab::kRow;
+        const int hi = max(dx, dy), lo = min(dx, dy);
+        t.near[i] = phi_oct_tab[hi * (hi + 1) / 2 + lo];
+    }
+}
+
+// uniform loads of the coefficients (scalar registers)
+__device__ inline FastCoef fast_coef(const PhiFast* fast) {
+    const cptr<double> p = as_const(reinterpret_cast<const double*>(fast));
+    FastCoef c;
+    #pragma unroll
+    for (int k = 0; k < 14; ++k) c.a[k] = p[k];
+    #pragma unroll
+    for (int k = 0; k < 5; ++k) c.log[k] = p[14 + k];
+    return c;
+}
+
+// an unsigned integer below 2^32 as a double plus 2^52 (differences of two are exact): no conversion
+__device__ inline double biased(uint32_t v) { return __builtin_bit_cast(double, int2_t{int(v), 0x43300000}); }
+
+// lead + the terms in 1 / r^2: z and v (see FarPhi) of r2, s = dx dy, lead = -(1/4pi) log(1/v) - C/2pi
+// (and the exponent's share), ir2 = 1 / r2
+__device__ inline double phi_terms(double z, double lead, double ir2, double s, const FastCoef& c) {
+    double p = c.log[4];
+    #pragma unroll
+    for (int k = 3; k >= 0; --k) p = fma(p, z, c.log[k]);
+    const double q = s * ir2, w = q * q;
+    const double t1 = fma(c.a[1], w, c.a[0]);
+    const double t2 = fma(fma(c.a[4], w, c.a[3]), w, c.a[2]);
+    const double t3 = fma(fma(fma(c.a[8], w, c.a[7]), w, c.a[6]), w, c.a[5]);
+    const double t4 = fma(fma(fma(fma(c.a[13], w, c.a[12]), w, c.a[11]), w, c.a[10]), w, c.a[9]);
+    const double b = fma(fma(fma(t4, ir2, t3), ir2, t2), ir2, t1);
+    return fma(b, ir2, fma(p, z, lead));
+}
+
+// phi at an offset below 2^8 in both coordinates (dx, dy exact): r2 in [2^11, 2^17) after clamping
+__device__ inline double phi_fast_oct(double dx, double dy, uint32_t adx, uint32_t ady, const FastTab& t,
+                                      const double2_t* oct, const FastCoef& c) {
+    constexpr double kMin = double(kNearRadius) * kNearRadius;
+    const double r2 = fma(dx, dx, dy * dy), r = fmax(r2, kMin);
+    // entry by exponent (modulo 8: 11 is 2 above a multiple) and the mantissa's first eight bits
+    const uint32_t hi = uint32_t(__builtin_bit_cast(int2_t, r).y);
+    const double2_t e = oct[int((hi >> 12) & 2047u) - 512];
+    const double z = fma(r, e.x, -1.0);
+    const double ir2 = e.x * fma(-z, fma(-z, 1.0 - z, 1.0), 1.0);   // |z| <= 2^-9: to 2^-36
+    double ph = phi_terms(z, e.y, ir2, dx * dy, c);
+    if (r2 < kMin) ph = t.near[ady * FastTab::kRow + adx];
+    return ph;
+}
+
+// phi at any offset (coordinates below 2^31)
+__device__ inline double phi_fast_any(double dx, double dy, uint32_t adx, uint32_t ady, const FastTab& t,
+                                      const double2_t* mant, const FastCoef& c) {
+    constexpr double kMin = double(kNearRadius) * kNearRadius;
+    constexpr double kLn2 = -0.69314718055994530942 / (4.0 * kPi);
+    const double r2 = fma(dx, dx, dy * dy), r = fmax(r2, kMin);
+    const int2_t w = __builtin_bit_cast(int2_t, r);
+    const double2_t e = mant[(uint32_t(w.y) >> 12) & 255u];
+    const double m = __builtin_bit_cast(double, int2_t{w.x, int((uint32_t(w.y) & 0xfffffu) | 0x3ff00000u)});
+    const double z = fma(m, e.x, -1.0);
+    const double ex = double(int(uint32_t(w.y) >> 20) - 1023);
+    const double scale = __builtin_bit_cast(double, int2_t{0, int(0x7fe00000u - (uint32_t(w.y) & 0x7ff00000u))});
+    const double ir2 = e.x * fma(-z, fma(-z, 1.0 - z, 1.0), 1.0) * scale;
+    double ph = phi_terms(z, fma(ex, kLn2, e.y), ir2, dx * dy, c);
+    if (r2 < kMin) ph = t.near[ady * FastTab::kRow + adx];
+    return ph;
+}
+
+__device__ inline double bperm_d(int from4, int2_t v) {
+    return __builtin_bit_cast(double, int2_t{__builtin_amdgcn_ds_bpermute(from4, v.x), __builtin_amdgcn_ds_bpermute(from4, v.y)});
+}
+
+// Lane t's entry among the lanes' consecutive ranges for list position base + t: lane e holds range
+// e's start `beg` (increasing; ranges e < ne), e0 is the number of ranges that start before base, and is
+// moved on past the chunk of C positions.  A bit per start in the chunk, counted up to the lane.
+template <int C>
+__device__ inline int chunk_entry(int32_t beg, int32_t ne, int32_t base, int& e0) {
+    const int before = e0;
+    uint64_t starts = 0;
+    while (e0 < ne) {
+        const int32_t b = __builtin_amdgcn_readlane(beg, e0) - base;
+        if (b >= C) break;
+        starts |= 1ull << b;
+        ++e0;
+    }
+    const int lane = int(threadIdx.x) & 63;
+    const uint64_t upto = starts & (~0ull >> (63 - lane));
+    return before + __popcll(upto) - 1;
+}
+
+// x of every lane of a 16-lane row summed over the lanes up to it
+__device__ inline int32_t row_inclusive_scan(int32_t x) {
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, true);   // row_shr:1, 2, 4, 8
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, true);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, true);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, true);
+    return x;
+}
+
+// Work item k of a persistent block, whose waves draw the k in increasing order from a counter in LDS:
+// runs of 64 items go to the XCDs in turn (as blocks do), a run's items to the XCD's blocks in turn.
+// The weights of clustered inputs' leaves differ by two orders and a wave takes only about 30: dealt
+// out to the waves in a fixed order they left the CUs idle for 45 % of k_near_wide (1152 -> 830 us).
+__device__ inline int32_t xcd_item(int32_t k) {
+    const int32_t i = int32_t(blockIdx.x >> 3) + k * int32_t(gridDim.x >> 3);
+    return ((i >> 6) * 8 + int32_t(blockIdx.x & 7)) * 64 + (i & 63);
+}
+
+// The wave's next k (uniform)
+__device__ inline int32_t draw(int32_t* counter) {
+    int32_t k = 0;
+    if ((threadIdx.x & 63) == 0) k = atomicAdd(counter, 1);
+    return __builtin_amdgcn_readfirstlane(k);
+}
+
+// A wave's lanes for n targets (1 .. 64): S = 64 / n slices of n lanes each; lanes past the last slice
+// repeat it and are left out of the sums
+struct Slices {
+    int S, sl, t, raw;   // slices (uniform); this lane's slice, target, and slice before clamping
+};
+// (i + 1/2) / n lies 1/128 or more off every integer
+__device__ inline int slice_count(int n) { return uniform(int(64.5f * __builtin_amdgcn_rcpf(float(n)))); }
+__device__ inline Slices slices(int n, int lane) {
+    const float inv = __builtin_amdgcn_rcpf(float(n));
+    Slices r;
+    r.S = slice_count(n);
+    r.raw = int((float(lane) + 0.5f) * inv);
+    r.t = lane - r.raw * n;
+    r.sl = min(r.raw, r.S - 1);
+    return r;
+}
+// Sum over the slices, to the lanes of slice 0
+__device__ inline double sum_slices(double a, int n, int S, int raw) {
+    for (int o = 1; o < S; o <<= 1) {
+        const double v = __shfl(a, ((int(threadIdx.x) & 63) + o * n) & 63, 64);
+        if (raw + o < S) a += v;
+    }
+    return a;
+}
+
+// Leaf pass for leaf sides 64 and 128.  Such leaves are the sparse ones of widely spread or
+// clustered inputs: a group (the up to four leaves of one parent) holds a few dozen targets and its
+// 4 x 4 block of source leaves a few hundred sources.  A wave takes one group; its record and entries
+// were loaded a group ahead.  The sources of its ranges are read as one list, 60 at a time, one per
+// lane, the next 60 in flight.  For each leaf of the group the sources near to it are moved to the
+// first lanes; its n targets take n lanes each of S = 64 / n slices, and slice s takes every S-th
+// source from its lane by shuffles (60 rounded up to a multiple of any such S is at most 64), so that
+// nearly every lane does useful work (over the group at once, a target adds 9 of the block's 16 leaves).
+// phi is computed (PhiFast, about 42 instructions): random 8-byte gathers from the 4.2-MB table bound
+// the pass at half an L2 request per cycle and compute unit, 3e11 pairs/s.  2e6 points in 64 clusters:
+// 1097 -> 764 us, 60 % of it VALU issue.  Each target's sum depends on its group alone.
+constexpr int kWideWaves = 8, kWideChunk = 60;
 
 template <int P>
-__global__ __launch_bounds__(64 * kStagedWaves) void k_near_staged(
+__global__ __launch_bounds__(64 * kWideWaves, 4) void k_near_wide(
     int32_t q0, int32_t q1, const NearGroup* groups, const int4* ents, int64_t side, const int2* pts, const double* fs,
     const int32_t* perm_local, const ExecPtrs* tab_ptrs, ExecPtrs single, const double* U, const double* leafT,
-    const double* phi_oct_tab) {
-    __shared__ int2 s_xy[kStagedWaves][kStageCap];
-    __shared__ double s_f[kStagedWaves][kStageCap];
-    const int lane = int(threadIdx.x) & 63, wave = int(threadIdx.x) >> 6;
-    const int32_t q = q0 + int32_t(blockIdx.x) * kStagedWaves + wave;
-    if (q >= q1) return;   // uniform over the wave; no block-wide barrier below
-    const int32_t qq = uniform(q);
-    int2* sxy = s_xy[wave];
-    double* sf = s_f[wave];
-    const cptr<int4_t> E = as_const(reinterpret_cast<const int4_t*>(ents)) + size_t(qq) * kNearEntries;
-    const cptr<NearGroup> R = as_const(groups + qq);
-    const int32_t leaf0 = R->leaf0, ne = R->ne;
-    int ls = 0;
-    while ((int64_t(1) << ls) < side) ++ls;
-    // first points of the group's leaves, to find each target's leaf
-    const int32_t t0 = R->bnd[0], bnd1 = R->bnd[1], bnd2 = R->bnd[2], bnd3 = R->bnd[3], t_end = R->bnd[4];
-    const bool far = R->far != 0;
-    const ExecPtrs eio = tab_ptrs ? tab_ptrs[R->inst] : single;
-    double* u = eio.u;
-    const bool sorted_out = eio.sorted != 0;   // u indexed by sorted point
-    const int32_t tgt0 = eio.tgt0;
-    // entries: start offset of each range in the concatenated source list
-    int32_t e_p0[kNearEntries], e_off[kNearEntries + 1];
-    e_off[0] = 0;
-    #pragma unroll
-    for (int e = 0; e < kNearEntries; ++e) {
-        int32_t a = 0, b = 0;
-        if (e < ne) {
-            const int4_t en = E[e];
-            a = en.x;
-            b = en.y;
+    const double* phi_oct_tab, const PhiFast* fast) {
+    __shared__ FastTab tab;
+    __shared__ double2_t oct[kFarOctEntries];
+    const int tid = int(threadIdx.x), lane = tid & 63, wave = tid >> 6, rl = tid & 15;
+    __shared__ int32_t next;
+    int32_t q = q0 + xcd_item(wave), rec = 0;
+    int4 ent = make_int4(0, 0, 0, 0);
+    auto fetch = [&](int32_t g) {   // word l of group g's record in lane l, entry l in lane l (of each row)
+        if (g < q1) {
+            rec = reinterpret_cast<const int32_t*>(groups)[size_t(g) * 16 + rl];
+            ent = ents[size_t(g) * kNearEntries + rl];
         }
-        e_p0[e] = a;
-        e_off[e + 1] = e_off[e] + (b - a);
+    };
+    fetch(q);
+    {
+        const double2_t* src = reinterpret_cast<const double2_t*>(&fast->oct[0][0]);
+        for (int i = tid; i < kFarOctEntries; i += 64 * kWideWaves) oct[i] = src[i];
+        if (tid == 0) next = kWideWaves;
+        load_near_tab(tab, phi_oct_tab, tid, 64 * kWideWaves);
     }
-    const int32_t ns = e_off[kNearEntries];
-    const int32_t nt = t_end - t0;
-    int T = 1;
-    while (T < nt && T < 64) T <<= 1;
-    const int S = 64 / T, tl = lane & (T - 1), sl = lane / T;
-    for (int32_t i0 = t0; i0 < t_end; i0 += T) {
-        const int32_t i = i0 + tl;
-        const bool valid = i < t_end;
-        const int32_t ii = valid ? i : t0;
-        const int2 pi = pts[ii];
-        const int tlx = pi.x >> ls, tly = pi.y >> ls;
-        double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
-        for (int32_t c0 = 0; c0 < ns; c0 += kStageCap) {
-            const int32_t c1 = min(ns, c0 + kStageCap);
-            // stage sources [c0, c1) of the concatenated list (after the wave's reads of the
-            // previous chunk: other lanes' reads, so a fence and not only program order)
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            // eight elements per lane and round, every load issued before the stores: element t of
-            // the concatenated list is point t + (e_p0[e] - e_off[e]) of the range e holding it
-            for (int32_t base = c0; base < c1; base += 64 * kStageRound) {
-                int2 v[kStageRound];
-                double w[kStageRound];
-                #pragma unroll
-                for (int r = 0; r < kStageRound; ++r) {
-                    const int32_t t = base + r * 64 + lane;
-                    int32_t shift = e_p0[0] - e_off[0];
-                    #pragma unroll
-                    for (int e = 1; e < kNearEntries; ++e)
-                        if (t >= e_off[e]) shift = e_p0[e] - e_off[e];
-                    const int32_t j = t < c1 ? t + shift : t0;
-                    v[r] = pts[j];
-                    w[r] = fs[j];
-                }
-                #pragma unroll
-                for (int r = 0; r < kStageRound; ++r) {
-                    const int32_t t = base + r * 64 + lane;
-                    if (t < c1) {
-                        sxy[t - c0] = v[r];
-                        sf[t - c0] = w[r];
-                    }
-                }
+    __syncthreads();
+    const FastCoef coef = fast_coef(fast);
+    const int32_t sd = int32_t(side);
+    while (q < q1) {
+        auto word = [&](int k) -> int32_t { return __builtin_amdgcn_readlane(rec, k); };   // of the NearGroup
+        const int32_t leaf0 = word(0), nleaf = word(1), ne = word(2), cposs = word(11);
+        const int32_t bnd[5] = {word(4), word(5), word(6), word(7), word(8)};
+        const int32_t gx = (word(9) - 1) * sd, gy = (word(10) - 1) * sd;   // corner of the 4 x 4 leaves
+        const bool far = word(12) != 0;
+        const ExecPtrs eio = tab_ptrs ? tab_ptrs[word(3)] : single;
+        const int32_t len = rl < ne ? ent.y - ent.x : 0;
+        const int32_t end = row_inclusive_scan(len), beg = end - len;
+        const int32_t shift = ent.x - beg, bits = ent.z;   // point index less list position, near children
+        const int32_t ns = __builtin_amdgcn_readlane(end, 15);
+        q = q0 + xcd_item(draw(&next));
+        fetch(q);
+        asm volatile("" ::: "memory");   // the next group's loads go out here
+        const int32_t most = max(max(bnd[1] - bnd[0], bnd[2] - bnd[1]), max(bnd[3] - bnd[2], bnd[4] - bnd[3]));
+        for (int32_t p0 = 0; p0 < most; p0 += 64) {
+            // per leaf: this lane's target (coordinates relative to the block, 10 bits each) and slice, the
+            // target's place, the lane's sum
+            uint32_t txy[4];
+            int32_t pout[4];
+            double acc[4];
+            #pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const int32_t n = bnd[c + 1] - bnd[c] - p0;   // 0 or less: none left (skipped below)
+                const Slices z = slices(max(min(n, 64), 1), lane);
+                const int32_t i = n > 0 ? bnd[c] + p0 + z.t : bnd[0];
+                const int2 p = pts[i];
+                pout[c] = perm_local[i];
+                txy[c] = uint32_t(p.x - gx) | (uint32_t(p.y - gy) << 10) | (uint32_t(z.sl) << 20);
+                acc[c] = 0.0;
             }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            const int32_t m = c1 - c0;
-            auto pair = [&](int32_t j) -> double {
-                const int2 pj = sxy[j];
-                const int dlx = (pj.x >> ls) - tlx, dly = (pj.y >> ls) - tly;
-                const bool nb = dlx >= -1 && dlx <= 1 && dly >= -1 && dly <= 1;
-                const int dx = abs(pi.x - pj.x), dy = abs(pi.y - pj.y);
-                const int hi = max(dx, dy), lo = min(dx, dy);
-                const double ph = nb ? phi_oct_tab[hi * (hi + 1) / 2 + lo] : 0.0;
-                return ph * sf[j];
+            int e0 = 0;
+            int2 pn;
+            double fn;
+            uint32_t bn;
+            auto load = [&](int32_t base) {
+                const int e = 4 * chunk_entry<kWideChunk>(beg, ne, base, e0);
+                const int32_t j = min(base + min(lane, kWideChunk - 1), ns - 1) + __builtin_amdgcn_ds_bpermute(e, shift);
+                pn = pts[j];
+                fn = fs[j];
+                const uint32_t be = uint32_t(__builtin_amdgcn_ds_bpermute(e, bits));   // by every lane
+                bn = lane < kWideChunk && base + lane < ns ? be : 0u;
             };
-            int32_t j = sl;
-            for (; j + 3 * S < m; j += 4 * S) {
-                a0 += pair(j);
-                a1 += pair(j + S);
-                a2 += pair(j + 2 * S);
-                a3 += pair(j + 3 * S);
+            load(0);
+            if (far) {
+                #pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    if (c >= nleaf || bnd[c + 1] - bnd[c] <= p0) continue;   // uniform
+                    const int32_t lx = int32_t(txy[c]) & (sd - 1), ly = int32_t(txy[c] >> 10) & (sd - 1);
+                    const double* tlp = leafT + size_t(lx + sd * ly) * P;   // the cell of its leaf
+                    const double* uh = U + size_t(leaf0 + c) * P;
+                    const int S = slice_count(min(bnd[c + 1] - bnd[c] - p0, 64));
+                    for (int p = int(txy[c] >> 20); p < P; p += S) acc[c] += tlp[p] * uh[p];
+                }
             }
-            for (; j < m; j += S) a0 += pair(j);
+            for (int32_t base = 0; base < ns; base += kWideChunk) {
+                const uint32_t src = uint32_t(pn.x - gx) | (uint32_t(pn.y - gy) << 16);
+                const double f = fn;
+                const uint32_t near = bn;
+                if (base + kWideChunk < ns) load(base + kWideChunk);
+                #pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    if (c >= nleaf || bnd[c + 1] - bnd[c] <= p0) continue;   // uniform
+                    const int cpos = (cposs >> (2 * c)) & 3;
+                    const bool on = (near >> cpos) & 1u;
+                    const uint64_t m = __ballot(on);
+                    const int cnt = __popcll(m);
+                    if (cnt == 0) continue;
+                    // the near sources to lanes 0 .. cnt - 1 in order; behind them zero loads at the leaf's
+                    // corner (every offset evaluated is one between near leaves)
+                    const uint32_t corner = uint32_t((1 + (cpos & 1)) * sd) | (uint32_t((1 + (cpos >> 1)) * sd) << 16);
+                    const int below = __builtin_amdgcn_mbcnt_hi(uint32_t(m >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(m), 0));
+                    const int to = 4 * (on ? below : cnt + lane - below);
+                    const int2_t f2 = __builtin_bit_cast(int2_t, on ? f : 0.0);
+                    const int cs = __builtin_amdgcn_ds_permute(to, int(on ? src : corner));
+                    const int2_t cf = {__builtin_amdgcn_ds_permute(to, f2.x), __builtin_amdgcn_ds_permute(to, f2.y)};
+                    const int S = slice_count(min(bnd[c + 1] - bnd[c] - p0, 64)), first = 4 * int(txy[c] >> 20);
+                    const uint32_t tx = txy[c] & 1023u, ty = (txy[c] >> 10) & 1023u;
+                    const double xd = biased(tx), yd = biased(ty);
+                    double a = acc[c];
+                    for (int k = 0; k < cnt; k += S) {
+                        const int from = 4 * k + first;
+                        const uint32_t w = uint32_t(__builtin_amdgcn_ds_bpermute(from, cs));
+                        const double fk = bperm_d(from, cf);
+                        const uint32_t sx = w & 0xffffu, sy = w >> 16;
+                        a = fma(phi_fast_oct(xd - biased(sx), yd - biased(sy), uint32_t(abs(int(tx) - int(sx))),
+                                             uint32_t(abs(int(ty) - int(sy))), tab, oct, coef), fk, a);
+                    }
+                    acc[c] = a;
+                }
+            }
+            #pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const int32_t n = min(bnd[c + 1] - bnd[c] - p0, 64);
+                if (c >= nleaf || n <= 0) continue;
+                const Slices z = slices(n, lane);
+                const double a = sum_slices(acc[c], n, z.S, z.raw);
+                if (z.raw == 0 && pout[c] >= eio.tgt0)
+                    eio.u[eio.sorted ? int64_t(bnd[c] + p0 + lane) : int64_t(pout[c] - eio.tgt0)] = a;
+            }
         }
-        if (far) {
-            const int c = (ii >= bnd1) + (ii >= bnd2) + (ii >= bnd3);
-            const int32_t leaf = leaf0 + c;
-            const int64_t loc = int64_t(pi.x - tlx * side) + side * int64_t(pi.y - tly * side);
-            const double* tlp = leafT + loc * P;
-            const double* uh = U + size_t(leaf) * P;
-            for (int p = sl; p < P; p += S) a1 += tlp[p] * uh[p];
-        }
-        double acc = (a0 + a1) + (a2 + a3);
-        for (int o = T; o < 64; o <<= 1) acc += __shfl_xor(acc, o, 64);
-        const int32_t pout = perm_local[ii];
-        if (valid && sl == 0 && pout >= tgt0) u[sorted_out ? int64_t(ii) : int64_t(pout - tgt0)] = acc;
     }
 }
 
@@ -1944,164 +2098,149 @@ __global__ __launch_bounds__(kBlock) void k_p2l(int32_t nx, const int32_t* xitem
 }
 
 // Near field of the adaptive leaves (Section 8.2 step 5 on the adaptive tree), one wave per
-// leaf tau: the sources are the points of the U-list leaves and, for the W-list boxes, their
-// skeleton points carrying their outgoing expansions (M2P: phi(x_i - y_p) q_p).  The wave
-// first writes a descriptor of each list entry into LDS (up to 64 at a time: kind, start,
-// corner, and the prefix sum of the entry lengths), then copies the sources into LDS in
-// chunks of kStageCap, each lane finding an element's entry by bisection over the prefix sums
-// and keeping kStageRound loads in flight, and sums from LDS as k_near_staged does (T lanes per
-// target, S slices).  L2P runs at each point's finest box (its incoming expansion holds those
-// of the adaptive leaf relayed by L2L), then the caller-order write.
-constexpr int kAdWaves = 4;
-
-struct AdWaveLds {
-    int2 xy[kStageCap];
-    double f[kStageCap];
-    int32_t off[65];   // prefix sums of the entry lengths of the batch
-    int32_t a[64];     // U entry: first point; W entry: box
-    int32_t h[64];     // W entry: height of the box (its skeleton); U entry: -1
-    int2 c[64];        // W entry: corner of the box
-};
+// leaf: the sources are the points of the U-list leaves and, for the W-list boxes, their skeleton
+// points carrying their outgoing expansions (M2P: phi(x_i - y_p) q_p).  Lane e holds entry e of a batch
+// of 64 list entries (start and length; the next leaf's record and first entries are loaded a leaf
+// ahead), and the batch's sources are read as one list, 60 at a time, one per lane, the next 60 in
+// flight.  The n targets take n lanes each of S = 64 / n slices; slice s takes every S-th source from
+// its lane by shuffles.  phi is computed as in k_near_wide, for any offset: 2e6 clustered points
+// 1842 -> 1043 us (gathers from the 4.2-MB table, and a bisection over the entries for every source,
+// before).  L2P runs at each point's finest box (its incoming expansion holds those of the adaptive
+// leaf relayed by L2L), then the caller-order write.
+constexpr int kAdWaves = 8, kAdChunk = kWideChunk;
 
 template <int P>
-__global__ __launch_bounds__(64 * kAdWaves) void k_near_adaptive(
-    int32_t nitems, const int32_t* items, AdaptiveLists L, const int32_t* box_pt0, const int32_t* box_pt1,
-    const uint64_t* box_key, const int8_t* box_lev, const int32_t* box_inst, const InstInfo* inst,
-    const OpsPtrs* ops, const int2* pts, const double* fs, const double* Q, const int32_t* pt_box, const double* U,
-    const int32_t* perm_local, const ExecPtrs* tab_ptrs, ExecPtrs single,
-    const uint8_t* far_inst, const double* phi_oct_tab, const PhiFar* phi_far) {
-    __shared__ AdWaveLds s_w[kAdWaves];
-    const int lane = int(threadIdx.x) & 63, wave = int(threadIdx.x) >> 6;
-    const int32_t q = int32_t(blockIdx.x) * kAdWaves + wave;
-    if (q >= nitems) return;   // uniform over the wave; no block-wide barrier below
-    AdWaveLds& S = s_w[wave];
-    const int32_t tau = uniform(items[q]);
-    const int32_t k_inst = uniform(box_inst[tau]);
-    const int D = uniform(inst[k_inst].D), Lf = uniform(inst[k_inst].L), opi = uniform(inst[k_inst].ops);
-    const OpsPtrs& O = ops[opi];
-    const int32_t side0 = int32_t(O.side);
-    const double* leafT = O.leafT;
-    const int32_t* skel = O.skel;
-    const bool far = far_inst[k_inst] != 0;
-    const ExecPtrs eio = tab_ptrs ? tab_ptrs[k_inst] : single;
-    double* u = eio.u;
-    const bool sorted_out = eio.sorted != 0;   // u indexed by sorted point
-    const int32_t tgt0 = eio.tgt0;
-    const int32_t t0 = uniform(box_pt0[tau]), t_end = uniform(box_pt1[tau]);
-    const int32_t u0 = uniform(L.off[0][tau]), nu = uniform(L.off[0][tau + 1]) - u0;
-    const int32_t w0 = uniform(L.off[1][tau]), nw = uniform(L.off[1][tau + 1]) - w0;
-    const int32_t ne = nu + nw;
-    const int32_t nt = t_end - t0;
-    int T = 1;
-    while (T < nt && T < 64) T <<= 1;
-    const int Sl = 64 / T, tl = lane & (T - 1), sl = lane / T;
-    auto wave_sync = [] {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+__global__ __launch_bounds__(64 * kAdWaves, 4) void k_near_adaptive(
+    int32_t nitems, const AdLeaf* recs, AdaptiveLists L, const int32_t* box_pt0, const int32_t* box_pt1,
+    const uint64_t* box_key, const int8_t* box_lev, const InstInfo* inst, const OpsPtrs* ops, const int2* pts,
+    const double* fs, const double* Q, const int32_t* pt_box, const double* U, const int32_t* perm_local,
+    const ExecPtrs* tab_ptrs, ExecPtrs single, const uint8_t* far_inst, const double* phi_oct_tab,
+    const PhiFast* fast) {
+    __shared__ FastTab tab;
+    __shared__ double2_t mant[kFarMantEntries];
+    const int tid = int(threadIdx.x), lane = tid & 63, wave = tid >> 6;
+    __shared__ int32_t next;
+    static_assert(sizeof(AdLeaf) == 32, "8 words");
+    int32_t q = xcd_item(wave), q1 = xcd_item(kAdWaves + wave);
+    // word l of leaf i's record in lane l
+    auto record = [&](int32_t i) -> int32_t {
+        return i < nitems ? reinterpret_cast<const int32_t*>(recs)[size_t(i) * 8 + (lane & 7)] : 0;
     };
-    for (int32_t i0 = t0; i0 < t_end; i0 += T) {
-        const int32_t i = i0 + tl;
-        const bool valid = i < t_end;
-        const int32_t ii = valid ? i : t0;
-        const int2 pi = pts[ii];
-        double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
-        for (int32_t eb = 0; eb < ne; eb += 64) {
-            // descriptors of entries eb .. eb + 63
-            const int32_t e = eb + lane;
-            int32_t len = 0, a = 0, hh = -1;
-            int2 cc = make_int2(0, 0);
-            if (e < nu) {
-                const int32_t sg = L.ent[0][u0 + e];
-                a = box_pt0[sg];
-                len = box_pt1[sg] - a;
-            } else if (e < ne) {
-                const int32_t d = L.ent[1][w0 + e - nu];
-                hh = Lf - int(box_lev[d]);
-                len = O.rank[hh];
-                a = d;
-                cc = box_corner(box_key, box_lev, d, D);
-            }
-            int32_t incl = len;
-            #pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const int32_t v = __shfl_up(incl, o, 64);
-                if (lane >= o) incl += v;
-            }
-            const int32_t total = __builtin_amdgcn_readlane(incl, 63);
-            wave_sync();   // the previous batch's reads of the descriptors are done
-            S.off[lane] = incl - len;
-            if (lane == 63) S.off[64] = total;
-            S.a[lane] = a;
-            S.h[lane] = hh;
-            S.c[lane] = cc;
-            for (int32_t c0 = 0; c0 < total; c0 += kStageCap) {
-                const int32_t c1 = min(total, c0 + kStageCap);
-                wave_sync();   // descriptors written; the previous chunk's sums are done
-                for (int32_t base = c0; base < c1; base += 64 * kStageRound) {
-                    int2 v[kStageRound];
-                    double w[kStageRound];
-                    #pragma unroll
-                    for (int r = 0; r < kStageRound; ++r) {
-                        const int32_t t = base + r * 64 + lane;
-                        v[r] = make_int2(0, 0);
-                        w[r] = 0.0;
-                        if (t < c1) {
-                            int lo = 0, hi = 63;   // last entry starting at or before t
-                            while (lo < hi) {
-                                const int mid = (lo + hi + 1) >> 1;
-                                if (S.off[mid] <= t) lo = mid;
-                                else hi = mid - 1;
-                            }
-                            const int32_t k = t - S.off[lo];
-                            const int32_t hk = S.h[lo];
-                            if (hk < 0) {
-                                v[r] = pts[S.a[lo] + k];
-                                w[r] = fs[S.a[lo] + k];
-                            } else {
-                                const int32_t* sk = skel + (size_t(hk) * P + k) * 2;
-                                const int2 c = S.c[lo];
-                                v[r] = make_int2(c.x + sk[0], c.y + sk[1]);
-                                w[r] = Q[size_t(S.a[lo]) * P + k];
-                            }
-                        }
-                    }
-                    #pragma unroll
-                    for (int r = 0; r < kStageRound; ++r) {
-                        const int32_t t = base + r * 64 + lane;
-                        if (t < c1) {
-                            S.xy[t - c0] = v[r];
-                            S.f[t - c0] = w[r];
-                        }
+    // box of list entry eb + lane of a leaf (U entries, then W entries)
+    auto entry = [&](int32_t u0, int32_t nu, int32_t w0, int32_t nw, int32_t eb) -> int32_t {
+        const int32_t e = eb + lane;
+        return e < nu ? L.ent[0][u0 + e] : e < nu + nw ? L.ent[1][w0 + e - nu] : -1;
+    };
+    int32_t rec = record(q), rec1 = record(q1);
+    {
+        const double2_t* src = reinterpret_cast<const double2_t*>(&fast->mant[0][0]);
+        for (int i = tid; i < kFarMantEntries; i += 64 * kAdWaves) mant[i] = src[i];
+        if (tid == 0) next = 2 * kAdWaves;
+        load_near_tab(tab, phi_oct_tab, tid, 64 * kAdWaves);
+    }
+    __syncthreads();   // no block-wide barrier below
+    const FastCoef coef = fast_coef(fast);
+    auto word = [](int32_t r, int k) -> int32_t { return __builtin_amdgcn_readlane(r, k); };
+    int32_t sg = q < nitems ? entry(word(rec, 2), word(rec, 3), word(rec, 4), word(rec, 5), 0) : -1;
+    while (q < nitems) {
+        const int32_t t0 = word(rec, 0), t_end = word(rec, 1), u0 = word(rec, 2), nu = word(rec, 3), w0 = word(rec, 4);
+        const int32_t nw = word(rec, 5), k_inst = word(rec, 6), ne = nu + nw;
+        const int32_t sg0 = sg;   // the first batch of entries
+        // the next leaf's entries and the record after it
+        q = q1;
+        q1 = xcd_item(draw(&next));
+        rec = rec1;
+        if (q < nitems) sg = entry(word(rec, 2), word(rec, 3), word(rec, 4), word(rec, 5), 0);
+        rec1 = record(q1);
+        asm volatile("" ::: "memory");   // these loads go out here
+        const InstInfo& I = inst[k_inst];
+        const int D = uniform(I.D), Lf = uniform(I.L);
+        const OpsPtrs& O = ops[uniform(I.ops)];
+        const int32_t side0 = int32_t(O.side);
+        const bool far = far_inst[k_inst] != 0;
+        const ExecPtrs eio = tab_ptrs ? tab_ptrs[k_inst] : single;
+        for (int32_t i0 = t0; i0 < t_end; i0 += 64) {
+            const int32_t n = min(t_end - i0, 64);
+            const Slices z = slices(n, lane);
+            const int S = z.S, sl = z.sl;
+            const int32_t ii = i0 + z.t;
+            const int2 pi = pts[ii];
+            const int32_t pout = perm_local[ii];
+            const double xd = biased(uint32_t(pi.x)), yd = biased(uint32_t(pi.y));   // root coordinates: not negative
+            double acc = 0.0;
+            for (int32_t eb = 0; eb < ne; eb += 64) {
+                // this lane's entry: U (first point, length) or W (box, rank, height, corner)
+                const int32_t d = eb == 0 ? sg0 : entry(u0, nu, w0, nw, eb);
+                const bool is_w = eb + lane >= nu;
+                int32_t a = 0, len = 0, hh = -1;
+                int2 cc = make_int2(0, 0);
+                if (d >= 0) {
+                    if (!is_w) {
+                        a = box_pt0[d];
+                        len = box_pt1[d] - a;
+                    } else {
+                        hh = Lf - int(box_lev[d]);
+                        len = O.rank[hh];
+                        a = d;
+                        cc = box_corner(box_key, box_lev, d, D);
                     }
                 }
-                wave_sync();
-                const int32_t m = c1 - c0;
-                auto pair = [&](int32_t j) -> double {
-                    const int2 pj = S.xy[j];
-                    return phi_oct(abs(pi.x - pj.x), abs(pi.y - pj.y), phi_oct_tab, phi_far) * S.f[j];
+                int32_t end = len;
+                #pragma unroll
+                for (int o = 1; o < 64; o <<= 1) {
+                    const int32_t v = __shfl_up(end, o, 64);
+                    if (lane >= o) end += v;
+                }
+                const int32_t beg = end - len, total = __builtin_amdgcn_readlane(end, 63);
+                const int32_t m = min(64, ne - eb);
+                int e0 = 0;
+                int2 pn;
+                double fn;
+                auto load = [&](int32_t base) {
+                    const int e = 4 * chunk_entry<kAdChunk>(beg, m, base, e0);
+                    const int32_t k = min(base + min(lane, kAdChunk - 1), total - 1) - __builtin_amdgcn_ds_bpermute(e, beg);
+                    const int32_t ae = __builtin_amdgcn_ds_bpermute(e, a), he = __builtin_amdgcn_ds_bpermute(e, hh);
+                    if (eb + 64 <= nu || __ballot(he >= 0) == 0) {   // U entries alone
+                        pn = pts[ae + k];
+                        fn = fs[ae + k];
+                    } else {
+                        const int2 c = make_int2(__builtin_amdgcn_ds_bpermute(e, cc.x), __builtin_amdgcn_ds_bpermute(e, cc.y));
+                        if (he < 0) {
+                            pn = pts[ae + k];
+                            fn = fs[ae + k];
+                        } else {
+                            const int32_t* sk = O.skel + (size_t(he) * P + k) * 2;
+                            pn = make_int2(c.x + sk[0], c.y + sk[1]);
+                            fn = Q[size_t(ae) * P + k];
+                        }
+                    }
                 };
-                int32_t j = sl;
-                for (; j + 3 * Sl < m; j += 4 * Sl) {
-                    a0 += pair(j);
-                    a1 += pair(j + Sl);
-                    a2 += pair(j + 2 * Sl);
-                    a3 += pair(j + 3 * Sl);
+                load(0);
+                for (int32_t base = 0; base < total; base += kAdChunk) {
+                    const int sx = pn.x, sy = pn.y;
+                    const int cnt = min(kAdChunk, total - base);
+                    const int2_t sf = __builtin_bit_cast(int2_t, lane < cnt ? fn : 0.0);
+                    if (base + kAdChunk < total) load(base + kAdChunk);
+                    for (int k = 0; k < cnt; k += S) {   // slots past the chunk's last hold a zero load
+                        const int from = 4 * (k + sl);
+                        const int x = __builtin_amdgcn_ds_bpermute(from, sx), y = __builtin_amdgcn_ds_bpermute(from, sy);
+                        const double fk = bperm_d(from, sf);
+                        acc = fma(phi_fast_any(xd - biased(uint32_t(x)), yd - biased(uint32_t(y)), uint32_t(abs(pi.x - x)),
+                                               uint32_t(abs(pi.y - y)), tab, mant, coef), fk, acc);
+                    }
                 }
-                for (; j < m; j += Sl) a0 += pair(j);
             }
+            if (far) {
+                const int32_t b = pt_box[ii];
+                const int64_t loc = int64_t(pi.x & (side0 - 1)) + int64_t(side0) * int64_t(pi.y & (side0 - 1));
+                const double* tlp = O.leafT + loc * P;
+                const double* uh = U + size_t(b) * P;
+                for (int p = sl; p < P; p += S) acc += tlp[p] * uh[p];
+            }
+            acc = sum_slices(acc, n, S, z.raw);
+            if (z.raw == 0 && pout >= eio.tgt0)
+                eio.u[eio.sorted ? int64_t(ii) : int64_t(pout - eio.tgt0)] = acc;
         }
-        if (far) {
-            const int32_t b = pt_box[ii];
-            const int64_t loc = int64_t(pi.x & (side0 - 1)) + int64_t(side0) * int64_t(pi.y & (side0 - 1));
-            const double* tlp = leafT + loc * P;
-            const double* uh = U + size_t(b) * P;
-            for (int p = sl; p < P; p += Sl) a1 += tlp[p] * uh[p];
-        }
-        double acc = (a0 + a1) + (a2 + a3);
-        for (int o = T; o < 64; o <<= 1) acc += __shfl_xor(acc, o, 64);
-        const int32_t pout = perm_local[ii];
-        if (valid && sl == 0 && pout >= tgt0) u[sorted_out ? int64_t(ii) : int64_t(pout - tgt0)] = acc;
     }
 }
 
@@ -2310,47 +2449,48 @@ void launch_m2l_bf16(const BoxTile* tiles, const int32_t* ntiles_dev, int32_t ma
                        box_list, il27, ops, Qb, qs, zrow, U);
 }
 
+// blocks of `threads` for `waves` work items of a wave each, as many as fit on the device at once
+static unsigned persistent_grid(const void* fn, int threads, int64_t waves) {
+    const int64_t want = (waves + threads / 64 - 1) / (threads / 64);
+    const int cus = p2m_device().cus;
+    int per = 0;
+    int64_t g = std::min<int64_t>(want, 8192);
+    if (cus > 0 && hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, fn, threads, 0) == hipSuccess && per > 0)
+        g = std::min<int64_t>(want, int64_t(cus) * per);
+    else
+        (void)hipGetLastError();
+    return unsigned(std::max<int64_t>(g, 1));
+}
+
+// the same in whole rounds of the XCDs, for xcd_item
+static unsigned xcd_grid(const void* fn, int threads, int64_t waves) {
+    return (persistent_grid(fn, threads, waves) + 7u) & ~7u;
+}
+
 void launch_near(int32_t q0, int32_t q1, const NearGroup* groups, const int4* ents, int64_t side, const int32_t* pts,
                  const uint32_t* pkey, const double* fs, const int32_t* perm_local, const ExecPtrs* tab,
                  const ExecPtrs& single, const double* U, const double* leafT, const double* phi_oct,
-                 const PhiFar* phi_far, hipStream_t st) {
+                 const PhiFast* fast, hipStream_t st) {
     if (q1 <= q0) return;
-    // with an LDS table: persistent blocks, as many as fit on the device at once, so that
-    // each builds its table once and then walks many groups; else one group per wave
-    auto grid = [&](const void* fn, int threads, size_t lds, bool persistent) {
-        unsigned g = std::min<unsigned>(grid_for(q1 - q0, threads / 64), 8192u);
-        const int cus = p2m_device().cus;
-        int per = 0;
-        if (!persistent) return g;
-        if (cus > 0 && hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, fn, threads, lds) == hipSuccess && per > 0)
-            g = std::min<unsigned>(g, unsigned(cus) * unsigned(per));
-        else
-            (void)hipGetLastError();
-        return std::max(g, 1u);
-    };
     const int2* p2 = reinterpret_cast<const int2*>(pts);
     if (side <= 16) {
         const int W = int(4 * side - 1);
-        const size_t lds = 0;   // the table is a fixed-size shared array
         if (W * W > kNearTabMax) throw std::logic_error("near-field window table larger than its array");
-        constexpr int nt = near_threads(kWindow);
-        const unsigned g = grid(reinterpret_cast<const void*>(&k_near<kRankPad, kWindow>), nt, lds, true);
-        hipLaunchKernelGGL((k_near<kRankPad, kWindow>), dim3(g), dim3(nt), lds, st, q0, q1, groups, ents, side, W, p2, pkey, fs, perm_local, tab, single, U,
-                           leafT, phi_oct, phi_far);
+        const unsigned g = persistent_grid(reinterpret_cast<const void*>(&k_near<kRankPad, kWindow>), kNearBlock, q1 - q0);
+        hipLaunchKernelGGL((k_near<kRankPad, kWindow>), dim3(g), dim3(kNearBlock), 0, st, q0, q1, groups, ents, side, W,
+                           p2, pkey, fs, perm_local, tab, single, U, leafT, phi_oct);
     } else if (side <= 32) {
         const int W = 64;   // rows: offsets of sides up to 32
-        const size_t lds = 0;
         if (W * kQuadRow > kNearTabMax || 2 * side > W) throw std::logic_error("near-field quadrant table larger than its array");
-        constexpr int nt = near_threads(kQuad);
-        const unsigned g = grid(reinterpret_cast<const void*>(&k_near<kRankPad, kQuad>), nt, lds, true);
-        hipLaunchKernelGGL((k_near<kRankPad, kQuad>), dim3(g), dim3(nt), lds, st, q0, q1, groups, ents, side, W, p2, pkey, fs, perm_local, tab, single, U,
-                           leafT, phi_oct, phi_far);
+        const unsigned g = persistent_grid(reinterpret_cast<const void*>(&k_near<kRankPad, kQuad>), kNearBlock, q1 - q0);
+        hipLaunchKernelGGL((k_near<kRankPad, kQuad>), dim3(g), dim3(kNearBlock), 0, st, q0, q1, groups, ents, side, W, p2,
+                           pkey, fs, perm_local, tab, single, U, leafT, phi_oct);
     } else {
-        // every near offset (at most 2 side - 1 <= 255) lies inside the device octant table
-        if (2 * side - 1 > kPhiDeviceRadius) throw std::logic_error("leaf wider than the near-field table allows");
-        const unsigned g = unsigned((q1 - q0 + kStagedWaves - 1) / kStagedWaves);
-        hipLaunchKernelGGL(k_near_staged<kRankPad>, dim3(g), dim3(64 * kStagedWaves), 0, st, q0, q1, groups, ents, side, p2, fs, perm_local, tab, single,
-                           U, leafT, phi_oct);
+        // near offsets are at most 2 side - 1, so that their squared length fits the octave table
+        if (2 * side > 256) throw std::logic_error("leaf wider than the near-field table allows");
+        const unsigned g = xcd_grid(reinterpret_cast<const void*>(&k_near_wide<kRankPad>), 64 * kWideWaves, q1 - q0);
+        hipLaunchKernelGGL(k_near_wide<kRankPad>, dim3(g), dim3(64 * kWideWaves), 0, st, q0, q1, groups, ents, side, p2,
+                           fs, perm_local, tab, single, U, leafT, phi_oct, fast);
     }
 }
 
@@ -2377,17 +2517,17 @@ void launch_p2l(int32_t nx, const int32_t* xitems, const AdaptiveLists& lists, c
                        box_inst, inst, ops, reinterpret_cast<const int2*>(pts), fs, U, phi_oct, phi_far);
 }
 
-void launch_near_adaptive(int32_t nitems, const int32_t* items, const AdaptiveLists& lists, const int32_t* box_pt0,
+void launch_near_adaptive(int32_t nitems, const AdLeaf* recs, const AdaptiveLists& lists, const int32_t* box_pt0,
                           const int32_t* box_pt1, const uint64_t* box_key, const int8_t* box_lev,
-                          const int32_t* box_inst, const InstInfo* inst, const OpsPtrs* ops, const int32_t* pts,
+                          const InstInfo* inst, const OpsPtrs* ops, const int32_t* pts,
                           const double* fs, const double* Q, const int32_t* pt_box, const double* U,
                           const int32_t* perm_local, const ExecPtrs* tab, const ExecPtrs& single,
-                          const uint8_t* far_inst, const double* phi_oct, const PhiFar* phi_far, hipStream_t st) {
+                          const uint8_t* far_inst, const double* phi_oct, const PhiFast* fast, hipStream_t st) {
     if (nitems <= 0) return;
-    const unsigned g = unsigned((nitems + kAdWaves - 1) / kAdWaves);
-    hipLaunchKernelGGL(k_near_adaptive<kRankPad>, dim3(g), dim3(64 * kAdWaves), 0, st, nitems, items, lists, box_pt0,
-                       box_pt1, box_key, box_lev, box_inst, inst, ops, reinterpret_cast<const int2*>(pts), fs, Q,
-                       pt_box, U, perm_local, tab, single, far_inst, phi_oct, phi_far);
+    const unsigned g = xcd_grid(reinterpret_cast<const void*>(&k_near_adaptive<kRankPad>), 64 * kAdWaves, nitems);
+    hipLaunchKernelGGL(k_near_adaptive<kRankPad>, dim3(g), dim3(64 * kAdWaves), 0, st, nitems, recs, lists, box_pt0,
+                       box_pt1, box_key, box_lev, inst, ops, reinterpret_cast<const int2*>(pts), fs, Q, pt_box, U,
+                       perm_local, tab, single, far_inst, phi_oct, fast);
 }
 
 void launch_direct(int64_t nt, const int32_t* txy, int64_t ns, const int32_t* sxy, const double* f,

@@ -704,6 +704,23 @@ __global__ void k_compact_positive(const int32_t* cnt, const int32_t* pos, int64
     if (g < nbox && cnt[g] > 0) items[pos[g]] = int32_t(g);
 }
 
+__global__ void k_ad_records(int32_t nitems, const int32_t* items, AdaptiveLists L, const int32_t* box_pt0,
+                             const int32_t* box_pt1, const int32_t* box_inst, AdLeaf* recs) {
+    const int32_t i = int32_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (i >= nitems) return;
+    const int32_t g = items[i];
+    AdLeaf r;
+    r.t0 = box_pt0[g];
+    r.t1 = box_pt1[g];
+    r.u0 = L.off[0][g];
+    r.nu = L.off[0][g + 1] - r.u0;
+    r.w0 = L.off[1][g];
+    r.nw = L.off[1][g + 1] - r.w0;
+    r.inst = box_inst[g];
+    r.pad = 0;
+    recs[i] = r;
+}
+
 // finest box of every point: a thread per finest box (their blocks follow the instance order
 // of the height blocks, not the point order) writes its index over its points
 __global__ void k_point_boxes(const int32_t* box_pt0, const int32_t* box_pt1, int32_t nleaf, int32_t* pt_box) {
@@ -1355,6 +1372,13 @@ void launch_adaptive_lists(bool fill, const uint64_t* box_key, const int32_t* bo
 void launch_compact_positive(const int32_t* cnt, const int32_t* pos, int64_t nbox, int32_t* items, hipStream_t st) {
     if (nbox <= 0) return;
     hipLaunchKernelGGL(k_compact_positive, dim3(grid_for(nbox)), dim3(kBlock), 0, st, cnt, pos, nbox, items);
+}
+
+void launch_ad_records(int32_t nitems, const int32_t* items, const AdaptiveLists& lists, const int32_t* box_pt0,
+                       const int32_t* box_pt1, const int32_t* box_inst, AdLeaf* recs, hipStream_t st) {
+    if (nitems <= 0) return;
+    hipLaunchKernelGGL(k_ad_records, dim3(grid_for(nitems)), dim3(kBlock), 0, st, nitems, items, lists, box_pt0, box_pt1,
+                       box_inst, recs);
 }
 
 void launch_point_boxes(const int32_t* box_pt0, const int32_t* box_pt1, int32_t nleaf, int32_t* pt_box,

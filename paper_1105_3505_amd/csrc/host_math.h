@@ -73,6 +73,24 @@ std::vector<double> build_phi_table(const Stencil& st, int radius);
 // Process-wide table of radius kPhiTableRadius of operator id, built on first use.
 const std::vector<double>& phi_table(int id);
 
+// phi for |m| >= kFarRadius as the kernels evaluate it, without a logarithm or a division:
+//   phi = -(1/4pi) log r^2 - C/2pi + sum_{k=1..4} r^-2k sum_{j=0..k} a_kj w^j,  w = (x y / r^2)^2,
+// r^2 = (1 + z) / v with v = 1 / c rounded for the centre c of r^2's interval (a table), |z| small, so
+// that -(1/4pi) log(1 + z) is a polynomial in z and 1 / r^2 = v (1 - z + z^2 - ...).  One term more
+// than eq. (3.1) and its |m|^-6 continuation: it matches the quadrature table to its rounding (1e-15)
+// from |m| = kFarRadius on.
+constexpr double kFarRadius = 48.0;
+constexpr int kFarOct0 = 11, kFarOcts = 6, kFarPerOct = 256;   // table by octaves: r^2 in [2^11, 2^17)
+constexpr int kFarMant = 256;                                  // table by mantissa: any r^2
+struct FarPhi {
+    double a[14];   // a_10, a_11, a_20, a_21, a_22, ..., a_44
+    double log[5];  // coefficients of z .. z^5 of -(1/4pi) log(1 + z), |z| <= 2^-9
+};
+const FarPhi& far_phi(int id);
+// (v, -(1/4pi) log(1/v) - C/2pi) of every interval: kFarOcts * kFarPerOct of r^2 itself, and kFarMant of
+// its mantissa in [1, 2)
+void far_phi_tables(int id, double* oct, double* mant);
+
 // phi of operator id at an integer offset: table inside the radius, expansion outside.
 double phi(int id, int64_t m1, int64_t m2);
 

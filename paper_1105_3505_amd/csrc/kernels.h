@@ -107,6 +107,15 @@ struct PhiFar {
     double c[3][4];
 };
 
+// The expansion from radius kNearRadius on as the near field of wide and adaptive leaves evaluates it
+// (coefficients and tables of FarPhi, host_math.h); below it, a table over |dx|, |dy| < kNearRadius.
+constexpr int kNearRadius = 48;
+constexpr int kFarOctEntries = 6 * 256, kFarMantEntries = 256;
+struct PhiFast {
+    double a[14], log[5], pad;
+    double oct[kFarOctEntries][2], mant[kFarMantEntries][2];
+};
+
 // Near-field group: the leaves leaf0 .. leaf0 + nleaf - 1 (the children of one parent box,
 // or a root that is a leaf), whose sources are the ne point ranges listed for the group.  One
 // record of 16 words, so that a wave reads all it needs to know of a group in one load.
@@ -311,21 +320,30 @@ void launch_m2l_mixed(const BoxTile* tiles, const int32_t* ntiles_dev, int32_t m
 void launch_near(int32_t q0, int32_t q1, const NearGroup* groups, const int4* ents, int64_t side, const int32_t* pts,
                  const uint32_t* pkey, const double* fs, const int32_t* perm_local, const ExecPtrs* tab,
                  const ExecPtrs& single, const double* U, const double* leafT, const double* phi_oct,
-                 const PhiFar* phi_far, hipStream_t st);
+                 const PhiFast* fast, hipStream_t st);
+// Near field of the adaptive leaves: what a wave needs to know of a leaf, in one record
+struct AdLeaf {
+    int32_t t0, t1;        // its points
+    int32_t u0, nu;        // its U list in ent[0]
+    int32_t w0, nw;        // its W list in ent[1]
+    int32_t inst, pad;
+};
+void launch_ad_records(int32_t nitems, const int32_t* items, const AdaptiveLists& lists, const int32_t* box_pt0,
+                       const int32_t* box_pt1, const int32_t* box_inst, AdLeaf* recs, hipStream_t st);
 // Adaptive tree passes.  P2L (X lists): u-hat of box tau += phi(skeleton of tau - x_j) f_j over
 // the points of its X leaves, for the nx boxes xitems.  Near field of the adaptive leaves
-// (items): U-list sources, W-list skeletons with their q-hat (M2P), L2P at each point's finest
+// (records): U-list sources, W-list skeletons with their q-hat (M2P), L2P at each point's finest
 // box, un-permutation.
 void launch_p2l(int32_t nx, const int32_t* xitems, const AdaptiveLists& lists, const int32_t* box_pt0,
                 const int32_t* box_pt1, const uint64_t* box_key, const int8_t* box_lev, const int32_t* box_inst,
                 const InstInfo* inst, const OpsPtrs* ops, const int32_t* pts, const double* fs, double* U,
                 const double* phi_oct, const PhiFar* phi_far, hipStream_t st);
-void launch_near_adaptive(int32_t nitems, const int32_t* items, const AdaptiveLists& lists, const int32_t* box_pt0,
+void launch_near_adaptive(int32_t nitems, const AdLeaf* recs, const AdaptiveLists& lists, const int32_t* box_pt0,
                           const int32_t* box_pt1, const uint64_t* box_key, const int8_t* box_lev,
-                          const int32_t* box_inst, const InstInfo* inst, const OpsPtrs* ops, const int32_t* pts,
+                          const InstInfo* inst, const OpsPtrs* ops, const int32_t* pts,
                           const double* fs, const double* Q, const int32_t* pt_box, const double* U,
                           const int32_t* perm_local, const ExecPtrs* tab, const ExecPtrs& single,
-                          const uint8_t* far_inst, const double* phi_oct, const PhiFar* phi_far, hipStream_t st);
+                          const uint8_t* far_inst, const double* phi_oct, const PhiFast* fast, hipStream_t st);
 // Radius of the device phi table: the host's quadrature table (radius 128) followed by the
 // far-field expansion for the octant entries up to this radius, filled by
 // launch_phi_extend(oct, 128, radius).  4.2 MB: near-field offsets between the wide leaves of

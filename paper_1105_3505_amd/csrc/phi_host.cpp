@@ -144,7 +144,33 @@ namespace {
 struct StencilData {
     Stencil st;
     std::vector<double> table;
+    FarPhi far;
 };
+
+// The kernels' expansion (FarPhi): least squares over the table entries with |m| >= 40 of
+// phi + (log|m| + C) / (2 pi), columns (40 / |m|)^2k (4 w)^j.
+void fit_far_phi(StencilData& d) {
+    std::vector<std::pair<int, int>> pts;
+    for (int a = 0; a <= kPhiTableRadius; ++a)
+        for (int b = 0; b <= a; ++b)
+            if (double(a) * a + double(b) * b >= 40.0 * 40.0) pts.emplace_back(a, b);
+    const int ncol = 14;
+    Mat A(int(pts.size()), ncol), B(int(pts.size()), 1);
+    for (size_t i = 0; i < pts.size(); ++i) {
+        const double a = pts[i].first, b = pts[i].second, r2 = a * a + b * b, u = 1600.0 / r2;
+        const double w = a * b / r2 * (a * b / r2);
+        int col = 0;
+        for (int k = 1; k <= 4; ++k)
+            for (int j = 0; j <= k; ++j) A(int(i), col++) = std::pow(u, k) * std::pow(4.0 * w, j);
+        B(int(i), 0) = d.table[size_t(octant_index(pts[i].first, pts[i].second))] +
+                       (0.5 * std::log(r2) + d.st.C) / (2.0 * kPi);
+    }
+    const Mat X = least_squares(A, B);
+    int col = 0;
+    for (int k = 1; k <= 4; ++k)
+        for (int j = 0; j <= k; ++j, ++col) d.far.a[col] = X(col, 0) * std::pow(1600.0, k) * std::pow(4.0, j);
+    for (int k = 1; k <= 5; ++k) d.far.log[k - 1] = (k & 1 ? -1.0 : 1.0) / (4.0 * kPi * k);
+}
 
 // The |m|^-6 terms of the 5-point expansion, which eq. (3.1) stops short of: least squares over
 // the table entries with |m| >= 40 of phi minus the eq. (3.1) value, columns |m|^-6 cos(4 j theta)
@@ -227,6 +253,7 @@ const StencilData& stencil_data(int id) {
             d.table = build_phi_table(st, kPhiTableRadius);
             fit_far_field(d);
         }
+        fit_far_phi(d);
     });
     return data[id];
 }
@@ -236,6 +263,21 @@ const StencilData& stencil_data(int id) {
 const Stencil& stencil(int id) { return stencil_data(id).st; }
 
 const std::vector<double>& phi_table(int id) { return stencil_data(id).table; }
+
+const FarPhi& far_phi(int id) { return stencil_data(id).far; }
+
+void far_phi_tables(int id, double* oct, double* mant) {
+    const long double pi = 3.14159265358979323846264338327950288L;
+    const long double lead = -(long double)(stencil_data(id).st.C) / (2.0L * pi);
+    auto entry = [&](double* t, long double centre) {
+        t[0] = double(1.0L / centre);
+        t[1] = double(lead + std::log((long double)(t[0])) / (4.0L * pi));
+    };
+    for (int o = 0; o < kFarOcts; ++o)
+        for (int i = 0; i < kFarPerOct; ++i)
+            entry(oct + 2 * (o * kFarPerOct + i), std::ldexp(1.0L + (i + 0.5L) / kFarPerOct, kFarOct0 + o));
+    for (int i = 0; i < kFarMant; ++i) entry(mant + 2 * i, 1.0L + (i + 0.5L) / kFarMant);
+}
 
 double phi(int id, int64_t m1, int64_t m2) {
     int64_t a = std::llabs(m1), b = std::llabs(m2);
