@@ -19,6 +19,7 @@
 #include <functional>
 #include <limits>
 #include <memory>
+#include <numeric>
 #include <string>
 #include <unordered_map>
 #include <vector>
@@ -31,40 +32,134 @@ using namespace lfmm;
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kDotBlocks = 256;
 
 inline unsigned blocks_for(int64_t n) { return unsigned(std::max<int64_t>(1, (n + kThreads - 1) / kThreads)); }
 
 // ---- vector kernels -------------------------------------------------------------------------
 
-// Partial dot products of w with the k vectors V[j] (stride ldv) over fixed slices of [0, n),
-// one slice per block, reduced in a fixed order: part[j * kDotBlocks + block].
-__global__ __launch_bounds__(kThreads) void k_dots_part(const double* V, int64_t ldv, int k, const double* w,
-                                                        int64_t n, double* part) {
-    __shared__ double red[kThreads];
-    const int64_t per = (n + kDotBlocks - 1) / kDotBlocks;
-    const int64_t i0 = int64_t(blockIdx.x) * per, i1 = min(n, i0 + per);
-    for (int j = 0; j < k; ++j) {
-        const double* v = V + size_t(j) * size_t(ldv);
-        double s = 0.0;
-        for (int64_t i = i0 + threadIdx.x; i < i1; i += kThreads) s += v[i] * w[i];
-        red[threadIdx.x] = s;
-        __syncthreads();
-        for (int o = kThreads / 2; o > 0; o >>= 1) {
-            if (int(threadIdx.x) < o) red[threadIdx.x] += red[threadIdx.x + o];
+typedef double double2_t __attribute__((ext_vector_type(2)));
+
+constexpr int kGsThreads = 1024, kGsWaves = kGsThreads / 64;
+constexpr int kGsTile = 512;     // elements: 32 a wave
+constexpr int kGsBlocks = 256;   // at most: one per CU
+
+// One step of the Gram-Schmidt passes: a block's slice [per * block, per * (block + 1)) of the vectors.
+// UPDATE: w -= V h with the k coefficients h summed from part_in (the nb blocks' partials of a step before;
+// block 0 writes them to h_out).  Then NORM: the slice's share of |w|^2 into part_out[block]; otherwise
+// its shares of V^T w into part_out[block * kp + j], j < k.
+//
+// V has rows of ld elements, ld a multiple of the tile, and its rows and w are zero from n on (NORM: w
+// may end at n).  For V^T w, lane l of a wave holds row l % 16 of a group of V, eight consecutive
+// elements at a time, so that nothing is exchanged between lanes before the end.  (On the matrix cores,
+// with w as the other operand, 15 of 16 columns are idle: 2.6 us of FP64 pipe a step against 0.2.)
+// A step is bound by reading V, from L2 up to some 10 MB.
+// Before, a kernel for the partials (V row by row, nine barriers a row), one that added a vector's 256
+// partials in turn and one for the update took 17 + 7 + 7 us on 50,000 elements and 18 vectors; now
+// 5.8 us for V^T w, 9.4 with the update before it, 6.7 for the update and |w|^2.
+// The order of the sums depends on n and k alone.
+template <bool UPDATE, bool NORM>
+__global__ __launch_bounds__(kGsThreads) void k_gs(const double* V, int64_t ld, int k, int kp, double* w, int64_t n,
+                                                   int64_t per, int nb, const double* part_in, double* h_out,
+                                                   double* part_out) {
+    __shared__ double hs[576];   // restart + 1 <= 513 coefficients, in whole rounds of 64
+    __shared__ double red[kGsWaves][64];
+    const int tid = int(threadIdx.x), lane = tid & 63, wave = tid >> 6;
+    const int64_t i0 = int64_t(blockIdx.x) * per, i1 = i0 + per < ld ? i0 + per : ld;
+    if (UPDATE) {
+        for (int j0 = 0; j0 < k; j0 += 64) {
+            double a = 0.0;
+            #pragma unroll 4
+            for (int b = wave; b < nb; b += kGsWaves) a += part_in[size_t(b) * kp + j0 + lane];
+            red[wave][lane] = a;
+            __syncthreads();
+            if (tid < 64) {
+                double h = 0.0;
+                for (int q = 0; q < kGsWaves; ++q) h += red[q][tid];
+                hs[j0 + tid] = h;
+                if (blockIdx.x == 0 && j0 + tid < k) h_out[j0 + tid] = h;
+            }
             __syncthreads();
         }
-        if (threadIdx.x == 0) part[size_t(j) * kDotBlocks + blockIdx.x] = red[0];
+    }
+    double sq = 0.0;
+    if (UPDATE || NORM) {
+        // two threads an element: the even and the odd vectors
+        const int e = tid & (kGsTile - 1), odd = tid / kGsTile;
+        for (int64_t t0 = i0; t0 < i1; t0 += kGsTile) {
+            const int64_t i = t0 + e;
+            double a = 0.0;
+            if (UPDATE) {
+                const double* v = V + size_t(i);
+                #pragma unroll 8
+                for (int j = odd; j < k; j += 2) a += hs[j] * v[size_t(j) * size_t(ld)];
+                double* sum = &red[0][0];
+                if (odd) sum[e] = a;
+                __syncthreads();
+                a += sum[e];
+            }
+            if (!odd && i < n) {
+                const double x = UPDATE ? w[i] - a : w[i];
+                if (UPDATE) w[i] = x;
+                sq += x * x;
+            }
+            __syncthreads();   // w is read by the block's other waves below, the sums' array written again
+        }
+    }
+    if (NORM) {
+        red[wave][lane] = sq;
         __syncthreads();
+        if (tid < 64) {
+            double a = 0.0;
+            for (int q = 0; q < kGsWaves; ++q) a += red[q][tid];
+            for (int o = 32; o > 0; o >>= 1) a += __shfl_xor(a, o, 64);
+            if (tid == 0) part_out[blockIdx.x] = a;
+        }
+    } else {
+        for (int j0 = 0; j0 < k; j0 += 64) {   // up to four groups of 16 vectors a pass
+            const int groups = (min(k - j0, 64) + 15) / 16;
+            // waves: group wave % G of G = 1, 2 or 4 and an equal part of the tile
+            const int G = groups > 2 ? 4 : groups, g = wave & (G - 1), len = 32 * G;
+            const int row = min(j0 + 16 * g + (lane & 15), k - 1);   // rows past the last repeat it
+            const int64_t first = i0 + (wave / G) * len + 8 * (lane >> 4);
+            const double2_t* v = reinterpret_cast<const double2_t*>(V + size_t(row) * size_t(ld) + first);
+            const double2_t* x = reinterpret_cast<const double2_t*>(w + first);
+            double a0 = 0.0, a1 = 0.0;
+            if (g < groups)
+                for (int64_t t0 = i0; t0 < i1; t0 += kGsTile) {
+                    #pragma unroll 2
+                    for (int q = 0; q < len; q += 32) {
+                        double2_t a[4], b[4];
+                        #pragma unroll
+                        for (int u = 0; u < 4; ++u) {
+                            a[u] = v[q / 2 + u];
+                            b[u] = x[q / 2 + u];
+                        }
+                        #pragma unroll
+                        for (int u = 0; u < 4; ++u) {
+                            a0 = fma(a[u].x, b[u].x, a0);
+                            a1 = fma(a[u].y, b[u].y, a1);
+                        }
+                    }
+                    v += kGsTile / 2;
+                    x += kGsTile / 2;
+                }
+            red[wave][lane] = a0 + a1;
+            __syncthreads();
+            if (tid < 16 * groups) {   // vector j0 + tid: its group's waves, four lanes each
+                double h = 0.0;
+                for (int q = tid >> 4; q < kGsWaves; q += G)
+                    for (int u = 0; u < 4; ++u) h += red[q][16 * u + (tid & 15)];
+                part_out[size_t(blockIdx.x) * kp + j0 + tid] = h;
+            }
+            __syncthreads();
+        }
     }
 }
 
-__global__ void k_dots_final(const double* part, int k, double* out) {
-    const int j = int(blockIdx.x) * blockDim.x + int(threadIdx.x);
-    if (j >= k) return;
-    double s = 0.0;
-    for (int b = 0; b < kDotBlocks; ++b) s += part[size_t(j) * kDotBlocks + b];
-    out[j] = s;
+// zero elements n .. ld - 1 of the rows of V
+__global__ void k_pad_rows(double* V, int64_t ld, int64_t n) {
+    const int64_t i = n + int64_t(threadIdx.x);
+    if (i < ld) V[size_t(blockIdx.x) * size_t(ld) + size_t(i)] = 0.0;
 }
 
 // w += sign * sum_j h[j] V[j]
@@ -173,30 +268,70 @@ struct Status {
 struct Gmres {
     int64_t n = 0;
     int m = 0;
-    DevBuf<double> V, w, part, h, r;
+    int64_t ld = 0, per = 0;   // elements of a row of V, of a block's slice
+    int kp = 0, nb = 0;        // coefficients a block's partials hold room for; blocks
+    // V: m + 1 rows and w; part, part2: the blocks' shares of either pass's coefficients
+    DevBuf<double> V, part, part2, y, r;
+    double* w = nullptr;
+    // pinned, written by the kernels: coefficients of both passes and the blocks' shares of |w|^2 (a
+    // copy to pageable memory behind them left the device idle for 30 us more an iteration)
+    double* h = nullptr;
 
-    void setup(int64_t n_, int m_) {
-        n = n_;
-        m = m_;
-        V.alloc(size_t(m + 1) * size_t(n));
-        w.alloc(size_t(n));
-        r.alloc(size_t(n));
-        part.alloc(size_t(m + 2) * kDotBlocks);
-        h.alloc(size_t(2 * (m + 2)));
+    Gmres() = default;
+    Gmres(const Gmres&) = delete;
+    Gmres& operator=(const Gmres&) = delete;
+    ~Gmres() { release(); }
+
+    void release() {
+        V.free();
+        part.free();
+        part2.free();
+        y.free();
+        r.free();
+        if (h) (void)hipHostFree(h);
+        h = nullptr;
+        n = 0;
     }
 
-    // out[0..k) = V[0..k)^T x
-    void dots(const double* Vb, int k, const double* x, double* out, hipStream_t st) {
-        hipLaunchKernelGGL(k_dots_part, dim3(kDotBlocks), dim3(kThreads), 0, st, Vb, n, k, x, n, part.p);
-        hipLaunchKernelGGL(k_dots_final, dim3(1), dim3(64), 0, st, part.p, k, out);
+    // The buffers belong to the solver's object, whose solves share its other buffers as well; a basis
+    // of more than kKeepBytes is given back after the solve.  (Allocated and freed on every solve, and
+    // with the copies named above, 35 iterations on 50,000 elements took 7.1 ms, now 6.2.)
+    static constexpr size_t kKeepBytes = size_t(256) << 20;
+    void trim() {
+        if (V.n * sizeof(double) > kKeepBytes) release();
+    }
+
+    void setup(int64_t n_, int m_, hipStream_t st) {
+        if (n == n_ && m == m_) return;
+        release();
+        m = m_;
+        const int64_t tiles = (n_ + kGsTile - 1) / kGsTile;
+        ld = tiles * kGsTile;
+        per = (tiles + kGsBlocks - 1) / kGsBlocks * kGsTile;
+        nb = int((ld + per - 1) / per);
+        kp = (m + 1 + 63) / 64 * 64;
+        V.alloc(size_t(m + 2) * size_t(ld));
+        w = V.p + size_t(m + 1) * size_t(ld);
+        r.alloc(size_t(n_));
+        y.alloc(size_t(m));
+        part.alloc(size_t(nb) * size_t(kp));
+        part2.alloc(size_t(nb) * size_t(kp));
+        SOLVER_HIP(hipHostMalloc(reinterpret_cast<void**>(&h), size_t(2 * kp + nb) * sizeof(double), 0));
+        hipLaunchKernelGGL(k_pad_rows, dim3(unsigned(m + 2)), dim3(kGsTile), 0, st, V.p, ld, n_);
+        n = n_;
+    }
+
+    // part = the blocks' shares of V[0..k)^T w
+    void dots(int k, hipStream_t st) {
+        hipLaunchKernelGGL((k_gs<false, false>), dim3(unsigned(nb)), dim3(kGsThreads), 0, st, V.p, ld, k, kp, w, n, per,
+                           nb, nullptr, nullptr, part.p);
     }
 
     double norm(const double* x, hipStream_t st) {
-        dots(x, 1, x, h.p, st);
-        double v = 0.0;
-        SOLVER_HIP(hipMemcpyAsync(&v, h.p, sizeof(double), hipMemcpyDeviceToHost, st));
+        hipLaunchKernelGGL((k_gs<false, true>), dim3(unsigned(nb)), dim3(kGsThreads), 0, st, V.p, ld, 0, kp,
+                           const_cast<double*>(x), n, per, nb, nullptr, nullptr, h);
         SOLVER_HIP(hipStreamSynchronize(st));
-        return std::sqrt(std::max(v, 0.0));
+        return std::sqrt(std::max(std::accumulate(h, h + nb, 0.0), 0.0));
     }
 
     lfmm_solver_stats run(const std::function<void(const double*, double*)>& apply, const double* b, double* x,
@@ -208,7 +343,7 @@ struct Gmres {
             out.converged = 1;
             return out;
         }
-        std::vector<double> H(size_t(m + 1) * m), cs(m), sn(m), g(m + 1), hv(size_t(2 * (m + 2)));
+        std::vector<double> H(size_t(m + 1) * m), cs(m), sn(m), g(m + 1);
         auto Hat = [&](int i, int j) -> double& { return H[size_t(i) * m + size_t(j)]; };
         SOLVER_HIP(hipMemcpyAsync(r.p, b, size_t(n) * sizeof(double), hipMemcpyDeviceToDevice, st));
         double beta = bn;
@@ -220,28 +355,22 @@ struct Gmres {
             g[0] = beta;
             int j = 0;
             for (; j < m; ++j) {
-                double* vj = V.p + size_t(j) * size_t(n);
-                apply(vj, w.p);
+                apply(V.p + size_t(j) * size_t(ld), w);
                 // classical Gram-Schmidt, twice: h = V^T w; w -= V h (both passes summed); the
                 // two coefficient sets and |w|^2 come back in one read
-                double* h1 = h.p;
-                double* h2 = h.p + (m + 2);
-                dots(V.p, j + 1, w.p, h1, st);
-                hipLaunchKernelGGL(k_combine, dim3(blocks_for(n)), dim3(kThreads), 0, st, V.p, n, j + 1, h1, -1.0,
-                                   w.p, n);
-                dots(V.p, j + 1, w.p, h2, st);
-                hipLaunchKernelGGL(k_combine, dim3(blocks_for(n)), dim3(kThreads), 0, st, V.p, n, j + 1, h2, -1.0,
-                                   w.p, n);
-                dots(w.p, 1, w.p, h.p + (2 * m + 3), st);
-                SOLVER_HIP(hipMemcpyAsync(hv.data(), h.p, hv.size() * sizeof(double), hipMemcpyDeviceToHost, st));
+                dots(j + 1, st);
+                hipLaunchKernelGGL((k_gs<true, false>), dim3(unsigned(nb)), dim3(kGsThreads), 0, st, V.p, ld, j + 1, kp,
+                                   w, n, per, nb, part.p, h, part2.p);
+                hipLaunchKernelGGL((k_gs<true, true>), dim3(unsigned(nb)), dim3(kGsThreads), 0, st, V.p, ld, j + 1, kp,
+                                   w, n, per, nb, part2.p, h + kp, h + 2 * kp);
                 SOLVER_HIP(hipStreamSynchronize(st));
                 SOLVER_HIP(hipGetLastError());
-                const double wn = std::sqrt(std::max(hv[size_t(2 * m + 3)], 0.0));
-                for (int i = 0; i <= j; ++i) Hat(i, j) = hv[size_t(i)] + hv[size_t(m + 2 + i)];
+                const double wn = std::sqrt(std::max(std::accumulate(h + 2 * kp, h + 2 * kp + nb, 0.0), 0.0));
+                for (int i = 0; i <= j; ++i) Hat(i, j) = h[i] + h[kp + i];
                 Hat(j + 1, j) = wn;
                 if (wn > 0.0)
-                    hipLaunchKernelGGL(k_scale_copy, dim3(blocks_for(n)), dim3(kThreads), 0, st, w.p, 1.0 / wn,
-                                       V.p + size_t(j + 1) * size_t(n), n);
+                    hipLaunchKernelGGL(k_scale_copy, dim3(blocks_for(n)), dim3(kThreads), 0, st, w, 1.0 / wn,
+                                       V.p + size_t(j + 1) * size_t(ld), n);
                 // previous rotations, then a new one that zeroes H(j+1, j)
                 for (int i = 0; i < j; ++i) {
                     const double a = Hat(i, j), c = Hat(i + 1, j);
@@ -265,17 +394,17 @@ struct Gmres {
             }
             if (!done) j = m;
             // y = H(0..j, 0..j)^-1 g; x += V y
-            std::vector<double> y(size_t(j), 0.0);
+            std::vector<double> c(size_t(j), 0.0);
             for (int i = j - 1; i >= 0; --i) {
                 double s = g[size_t(i)];
-                for (int k = i + 1; k < j; ++k) s -= Hat(i, k) * y[size_t(k)];
-                y[size_t(i)] = Hat(i, i) != 0.0 ? s / Hat(i, i) : 0.0;
+                for (int k = i + 1; k < j; ++k) s -= Hat(i, k) * c[size_t(k)];
+                c[size_t(i)] = Hat(i, i) != 0.0 ? s / Hat(i, i) : 0.0;
             }
-            SOLVER_HIP(hipMemcpyAsync(h.p, y.data(), size_t(j) * sizeof(double), hipMemcpyHostToDevice, st));
-            hipLaunchKernelGGL(k_combine, dim3(blocks_for(n)), dim3(kThreads), 0, st, V.p, n, j, h.p, 1.0, x, n);
+            SOLVER_HIP(hipMemcpyAsync(y.p, c.data(), size_t(j) * sizeof(double), hipMemcpyHostToDevice, st));
+            hipLaunchKernelGGL(k_combine, dim3(blocks_for(n)), dim3(kThreads), 0, st, V.p, ld, j, y.p, 1.0, x, n);
             // true residual r = b - A x (also the next cycle's start)
-            apply(x, w.p);
-            hipLaunchKernelGGL(k_sub, dim3(blocks_for(n)), dim3(kThreads), 0, st, b, w.p, r.p, n);
+            apply(x, w);
+            hipLaunchKernelGGL(k_sub, dim3(blocks_for(n)), dim3(kThreads), 0, st, b, w, r.p, n);
             beta = norm(r.p, st);
             if (beta <= tol * bn) done = true;
             if (iters >= max_iter) done = true;
@@ -330,7 +459,8 @@ struct lfmm_inclusions {
     int64_t nn = 0;                       // nodes touched by the bars (Omega_inc)
     std::vector<int32_t> nodes;           // host copy, [nn][2]
     DevBuf<int32_t> xy, rowptr, col;
-    DevBuf<double> dlt, v, s, t;
+    DevBuf<double> dlt, v, s, t, rhs;
+    Gmres gm;
     lfmm_plan* plan = nullptr;            // the nodes, targets = sources: S on Omega_inc
     ~lfmm_inclusions() {
         if (plan) lfmm_plan_destroy(plan);
@@ -344,6 +474,7 @@ struct lfmm_dirichlet {
     DevBuf<int32_t> src;                  // [2n][2]: n + nu(n) first, then n
     DevBuf<int32_t> gam;                  // [n][2]
     DevBuf<double> f2;                    // dipole loads
+    Gmres gm;
     lfmm_plan* plan = nullptr;            // sources: the dipole ends; targets: the boundary
     ~lfmm_dirichlet() {
         if (plan) lfmm_plan_destroy(plan);
@@ -437,24 +568,24 @@ lfmm_status lfmm_inclusions_solve(lfmm_inclusions* inc, double c1, double c2, co
         const unsigned gb = blocks_for(nn);
         const int2* xy = reinterpret_cast<const int2*>(inc->xy.p);
         // right-hand side of eq. 10.4: -B S B v
-        DevBuf<double> rhs;
-        rhs.alloc(size_t(nn));
+        if (!inc->rhs.p) inc->rhs.alloc(size_t(nn));
         hipLaunchKernelGGL(k_linear, dim3(gb), dim3(kThreads), 0, st, xy, c1, c2, inc->v.p, nn);
         hipLaunchKernelGGL(k_bars, dim3(gb), dim3(kThreads), 0, st, inc->rowptr.p, inc->col.p, inc->dlt.p, inc->v.p,
                            nullptr, 0.0, 1.0, inc->t.p, nn);
         check(lfmm_execute(inc->plan, inc->t.p, inc->s.p, stream));
         hipLaunchKernelGGL(k_bars, dim3(gb), dim3(kThreads), 0, st, inc->rowptr.p, inc->col.p, inc->dlt.p, inc->s.p,
-                           nullptr, 0.0, -1.0, rhs.p, nn);
+                           nullptr, 0.0, -1.0, inc->rhs.p, nn);
         // operator: mu -> mu + B S mu
         auto apply = [&](const double* in, double* o) {
             check(lfmm_execute(inc->plan, in, inc->s.p, stream));
             hipLaunchKernelGGL(k_bars, dim3(gb), dim3(kThreads), 0, st, inc->rowptr.p, inc->col.p, inc->dlt.p,
                                inc->s.p, in, 1.0, 1.0, o, nn);
         };
-        Gmres gm;
-        gm.setup(nn, std::min<int>(restart, int(std::max<int64_t>(nn, 1))));
-        const lfmm_solver_stats r = gm.run(apply, rhs.p, mu_dev, tol, max_iter, st);
+        Gmres& gm = inc->gm;
+        gm.setup(nn, std::min<int>(restart, int(std::max<int64_t>(nn, 1))), st);
+        const lfmm_solver_stats r = gm.run(apply, inc->rhs.p, mu_dev, tol, max_iter, st);
         SOLVER_HIP(hipStreamSynchronize(st));
+        gm.trim();
         if (stats) *stats = r;
         return LFMM_OK;
     });
@@ -556,10 +687,11 @@ lfmm_status lfmm_dirichlet_solve(lfmm_dirichlet* dir, const double* g_dev, const
             hipLaunchKernelGGL(k_dipole_loads, dim3(blocks_for(dir->n)), dim3(kThreads), 0, st, in, dir->f2.p, dir->n);
             check(lfmm_execute(dir->plan, dir->f2.p, o, stream));
         };
-        Gmres gm;
-        gm.setup(dir->n, std::min<int>(restart, int(std::max<int64_t>(dir->n, 1))));
+        Gmres& gm = dir->gm;
+        gm.setup(dir->n, std::min<int>(restart, int(std::max<int64_t>(dir->n, 1))), st);
         const lfmm_solver_stats r = gm.run(apply, g_dev, q_dev, tol, max_iter, st);
         SOLVER_HIP(hipStreamSynchronize(st));
+        gm.trim();
         if (stats) *stats = r;
         return LFMM_OK;
     });
