@@ -1436,7 +1436,8 @@ void enqueue_passes(lfmm_plan* pl, const ExecPtrs* tab, const double* f1, double
     for (size_t o = 0; o < pl->ops.size(); ++o) {
         const TileRange& r = pl->near_of_ops[o];
         launch_near(r.t0, r.t0 + r.n, pl->groups, pl->ents, pl->ops[o]->dev.leaf_side, pl->pts, pl->pkey, pl->fs,
-                    pl->perm, tab, single, pl->U, pl->ops[o]->dev.leafT, pl->ctx->phi_oct, pl->ctx->phi_fast, st);
+                    pl->perm, tab, single, pl->U, pl->ops[o]->dev.leafT, pl->ctx->phi_oct, pl->ctx->phi_fast,
+                    pl->leaf_of_ops[o].n, st);
     }
     mark(6);
 }

@@ -1823,11 +1823,12 @@ __device__ inline double bperm_d(int from4, int2_t v) {
     return __builtin_bit_cast(double, int2_t{__builtin_amdgcn_ds_bpermute(from4, v.x), __builtin_amdgcn_ds_bpermute(from4, v.y)});
 }
 
-// Lane t's entry among the lanes' consecutive ranges for list position base + t: lane e holds range
-// e's start `beg` (increasing; ranges e < ne), e0 is the number of ranges that start before base, and is
-// moved on past the chunk of C positions.  A bit per start in the chunk, counted up to the lane.
+// Lane t's entry among the lanes' consecutive ranges for list position base + t, t < C: lane e holds
+// range e's start `beg` (ranges e < ne, none empty), e0 counts ranges that start before some earlier base
+// and is moved on past the chunk.  A bit per start in the chunk, counted up to the lane.
 template <int C>
 __device__ inline int chunk_entry(int32_t beg, int32_t ne, int32_t base, int& e0) {
+    while (e0 < ne && __builtin_amdgcn_readlane(beg, e0) <= base) ++e0;
     const int before = e0;
     uint64_t starts = 0;
     while (e0 < ne) {
@@ -1840,6 +1841,66 @@ __device__ inline int chunk_entry(int32_t beg, int32_t ne, int32_t base, int& e0
     const uint64_t upto = starts & (~0ull >> (63 - lane));
     return before + __popcll(upto) - 1;
 }
+
+// A chunk's cnt sources, one per lane, added up for the lanes' targets: slice s of S takes sources s,
+// s + S, ..., two at a time (two chains of dependent instructions); first = 4 s, and
+// term(4 lane, a) = a + the term of that lane's source
+template <class T>
+__device__ inline double chunk_sum(int cnt, int S, int first, T term) {
+    double a0 = 0.0, a1 = 0.0;
+    int k = 0;
+    for (; k + S < cnt; k += 2 * S) {
+        a0 = term(4 * k + first, a0);
+        a1 = term(4 * (k + S) + first, a1);
+    }
+    if (k < cnt) a0 = term(4 * k + first, a0);
+    return a0 + a1;
+}
+
+// Slice sl's share of L2P for a lane's target: rows tl of the operator, uh of the expansion
+template <int P>
+__device__ inline double far_share(const double* tl, const double* uh, int sl, int S) {
+    const double2_t* t2 = reinterpret_cast<const double2_t*>(tl);
+    const double2_t* u2 = reinterpret_cast<const double2_t*>(uh);
+    double a = 0.0;
+    for (int p = sl; p < P / 2; p += 4 * S) {
+        double2_t t[4], u[4];
+        #pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int q = min(p + k * S, P / 2 - 1);
+            t[k] = t2[q];
+            u[k] = u2[q];
+        }
+        #pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (p + k * S < P / 2) a = fma(t[k].y, u[k].y, fma(t[k].x, u[k].x, a));
+    }
+    return a;
+}
+
+// The sums of a leaf's chunks are kept in four parts, chunk i in part i % 4, added as (0 + 1) + (2 + 3),
+// so that one wave, or four with a part each, come to the same result.  One wave turns the parts
+// round: the next chunk's part is always the first.
+struct Parts {
+    double a[4] = {0.0, 0.0, 0.0, 0.0};
+    __device__ void add(double v) {
+        const double t = a[0] + v;
+        a[0] = a[1];
+        a[1] = a[2];
+        a[2] = a[3];
+        a[3] = t;
+    }
+    __device__ double sum(int chunks) {
+        for (int r = chunks & 3; r != 0 && r < 4; ++r) {   // to part 0 first again
+            const double t = a[0];
+            a[0] = a[1];
+            a[1] = a[2];
+            a[2] = a[3];
+            a[3] = t;
+        }
+        return (a[0] + a[1]) + (a[2] + a[3]);
+    }
+};
 
 // x of every lane of a 16-lane row summed over the lanes up to it
 __device__ inline int32_t row_inclusive_scan(int32_t x) {
@@ -1893,27 +1954,42 @@ __device__ inline double sum_slices(double a, int n, int S, int raw) {
 
 // Leaf pass for leaf sides 64 and 128.  Such leaves are the sparse ones of widely spread or
 // clustered inputs: a group (the up to four leaves of one parent) holds a few dozen targets and its
-// 4 x 4 block of source leaves a few hundred sources.  A wave takes one group; its record and entries
-// were loaded a group ahead.  The sources of its ranges are read as one list, 60 at a time, one per
-// lane, the next 60 in flight.  For each leaf of the group the sources near to it are moved to the
-// first lanes; its n targets take n lanes each of S = 64 / n slices, and slice s takes every S-th
-// source from its lane by shuffles (60 rounded up to a multiple of any such S is at most 64), so that
-// nearly every lane does useful work (over the group at once, a target adds 9 of the block's 16 leaves).
-// phi is computed (PhiFast, about 42 instructions): random 8-byte gathers from the 4.2-MB table bound
-// the pass at half an L2 request per cycle and compute unit, 3e11 pairs/s.  2e6 points in 64 clusters:
-// 1097 -> 764 us, 60 % of it VALU issue.  Each target's sum depends on its group alone.
-constexpr int kWideWaves = 8, kWideChunk = 60;
+// 4 x 4 block of source leaves a few hundred sources.  A wave takes one group, leaf by leaf; its
+// record and entries were loaded a group ahead.  The ranges near to the leaf are read as one list, 60
+// sources at a time, one per lane, the next 60 in flight.  The leaf's n targets take n lanes each of
+// S = 64 / n slices, and slice s takes every S-th source from its lane by shuffles (60 rounded up to a
+// multiple of any such S is at most 64).  phi is computed (PhiFast, about 42 instructions): random
+// 8-byte gathers from the 4.2-MB table bound the pass at half an L2 request per cycle and compute unit,
+// 3e11 pairs/s.  2e6 points in 64 clusters: 1097 -> 695 us.
+// SPLIT: a block of four waves per leaf, a part of the chunks (see Parts) in each, for plans of few
+// leaves, where a wave would work through a group's pairs alone (kSplitLeaves).
+// Each target's sum depends on its group alone.
+constexpr int kWideWaves = 8, kWideChunk = 60, kSplitWaves = 4;
+// What a wave takes, by the number of units (child positions of the groups): a quarter of a leaf up to
+// kSplitLeaves, a leaf up to kWaveLeaves, and up to kWaveLeavesFull where the groups hold 9/4 leaves or more on
+// average, otherwise a group.  Measured (quarter / leaf / group; gathers from the table, us), on uniform points and
+// clusters: 784 units 13 / 40 / 261; 83, 1.9e3 32 / 38 / 80; 88, 1.5e4 77 / 61 / 96; 108, 9.8e4
+// 419 / 179 / 219; 254, 5.2e5 - / 762 / 695; 1097; on curves, whose groups hold two leaves: 984 units
+// 22 / 19 / 53; 26, 3.9e3 44 / 26 / 33; 27, 2.5e4 198 / 88 / 72; 87.
+constexpr int64_t kSplitLeaves = 2048, kWaveLeaves = 8192, kWaveLeavesFull = 196608;
+// The same for adaptive leaves (quarter / leaf; gathers): 97 leaves 45 / 320; 88, 2.2e3 134 / 248; 479,
+// 1.4e4 581 / 626; 1022, 7.4e4 2401 / 2030; 2997.
+constexpr int32_t kSplitAdaptive = 16384;
 
-template <int P>
-__global__ __launch_bounds__(64 * kWideWaves, 4) void k_near_wide(
+template <int P, bool SPLIT>
+__global__ __launch_bounds__(64 * (SPLIT ? kSplitWaves : kWideWaves), SPLIT ? 3 : 4) void k_near_wide(
     int32_t q0, int32_t q1, const NearGroup* groups, const int4* ents, int64_t side, const int2* pts, const double* fs,
     const int32_t* perm_local, const ExecPtrs* tab_ptrs, ExecPtrs single, const double* U, const double* leafT,
-    const double* phi_oct_tab, const PhiFast* fast) {
+    const double* phi_oct_tab, const PhiFast* fast, int by_leaf) {
+    constexpr int W = SPLIT ? kSplitWaves : kWideWaves;
     __shared__ FastTab tab;
     __shared__ double2_t oct[kFarOctEntries];
-    const int tid = int(threadIdx.x), lane = tid & 63, wave = tid >> 6, rl = tid & 15;
+    __shared__ double part[SPLIT ? kSplitWaves + 1 : 1][64];
     __shared__ int32_t next;
-    int32_t q = q0 + xcd_item(wave), rec = 0;
+    const int tid = int(threadIdx.x), lane = tid & 63, wave = tid >> 6, rl = tid & 15;
+    // by_leaf: leaf unit & 3 of group unit >> 2
+    int32_t unit = SPLIT ? int32_t(blockIdx.x) : xcd_item(wave);
+    int32_t q = q0 + (by_leaf ? unit >> 2 : unit), rec = 0;
     int4 ent = make_int4(0, 0, 0, 0);
     auto fetch = [&](int32_t g) {   // word l of group g's record in lane l, entry l in lane l (of each row)
         if (g < q1) {
@@ -1924,112 +2000,88 @@ __global__ __launch_bounds__(64 * kWideWaves, 4) void k_near_wide(
     fetch(q);
     {
         const double2_t* src = reinterpret_cast<const double2_t*>(&fast->oct[0][0]);
-        for (int i = tid; i < kFarOctEntries; i += 64 * kWideWaves) oct[i] = src[i];
+        for (int i = tid; i < kFarOctEntries; i += 64 * W) oct[i] = src[i];
         if (tid == 0) next = kWideWaves;
-        load_near_tab(tab, phi_oct_tab, tid, 64 * kWideWaves);
+        load_near_tab(tab, phi_oct_tab, tid, 64 * W);
     }
     __syncthreads();
     const FastCoef coef = fast_coef(fast);
     const int32_t sd = int32_t(side);
     while (q < q1) {
-        auto word = [&](int k) -> int32_t { return __builtin_amdgcn_readlane(rec, k); };   // of the NearGroup
+        const int32_t r = rec, mine = unit & 3;
+        const int4 en = ent;
+        auto word = [&](int k) -> int32_t { return __builtin_amdgcn_readlane(r, k); };   // of the NearGroup
+        unit = SPLIT ? unit + int32_t(gridDim.x) : xcd_item(draw(&next));
+        q = q0 + (by_leaf ? unit >> 2 : unit);
+        fetch(q);
+        asm volatile("" ::: "memory");   // the next group's loads go out here
         const int32_t leaf0 = word(0), nleaf = word(1), ne = word(2), cposs = word(11);
-        const int32_t bnd[5] = {word(4), word(5), word(6), word(7), word(8)};
         const int32_t gx = (word(9) - 1) * sd, gy = (word(10) - 1) * sd;   // corner of the 4 x 4 leaves
         const bool far = word(12) != 0;
         const ExecPtrs eio = tab_ptrs ? tab_ptrs[word(3)] : single;
-        const int32_t len = rl < ne ? ent.y - ent.x : 0;
-        const int32_t end = row_inclusive_scan(len), beg = end - len;
-        const int32_t shift = ent.x - beg, bits = ent.z;   // point index less list position, near children
-        const int32_t ns = __builtin_amdgcn_readlane(end, 15);
-        q = q0 + xcd_item(draw(&next));
-        fetch(q);
-        asm volatile("" ::: "memory");   // the next group's loads go out here
-        const int32_t most = max(max(bnd[1] - bnd[0], bnd[2] - bnd[1]), max(bnd[3] - bnd[2], bnd[4] - bnd[3]));
-        for (int32_t p0 = 0; p0 < most; p0 += 64) {
-            // per leaf: this lane's target (coordinates relative to the block, 10 bits each) and slice, the
-            // target's place, the lane's sum
-            uint32_t txy[4];
-            int32_t pout[4];
-            double acc[4];
-            #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const int32_t n = bnd[c + 1] - bnd[c] - p0;   // 0 or less: none left (skipped below)
-                const Slices z = slices(max(min(n, 64), 1), lane);
-                const int32_t i = n > 0 ? bnd[c] + p0 + z.t : bnd[0];
-                const int2 p = pts[i];
-                pout[c] = perm_local[i];
-                txy[c] = uint32_t(p.x - gx) | (uint32_t(p.y - gy) << 10) | (uint32_t(z.sl) << 20);
-                acc[c] = 0.0;
-            }
-            int e0 = 0;
-            int2 pn;
-            double fn;
-            uint32_t bn;
-            auto load = [&](int32_t base) {
-                const int e = 4 * chunk_entry<kWideChunk>(beg, ne, base, e0);
-                const int32_t j = min(base + min(lane, kWideChunk - 1), ns - 1) + __builtin_amdgcn_ds_bpermute(e, shift);
-                pn = pts[j];
-                fn = fs[j];
-                const uint32_t be = uint32_t(__builtin_amdgcn_ds_bpermute(e, bits));   // by every lane
-                bn = lane < kWideChunk && base + lane < ns ? be : 0u;
-            };
-            load(0);
-            if (far) {
-                #pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    if (c >= nleaf || bnd[c + 1] - bnd[c] <= p0) continue;   // uniform
-                    const int32_t lx = int32_t(txy[c]) & (sd - 1), ly = int32_t(txy[c] >> 10) & (sd - 1);
-                    const double* tlp = leafT + size_t(lx + sd * ly) * P;   // the cell of its leaf
-                    const double* uh = U + size_t(leaf0 + c) * P;
-                    const int S = slice_count(min(bnd[c + 1] - bnd[c] - p0, 64));
-                    for (int p = int(txy[c] >> 20); p < P; p += S) acc[c] += tlp[p] * uh[p];
-                }
-            }
-            for (int32_t base = 0; base < ns; base += kWideChunk) {
-                const uint32_t src = uint32_t(pn.x - gx) | (uint32_t(pn.y - gy) << 16);
-                const double f = fn;
-                const uint32_t near = bn;
-                if (base + kWideChunk < ns) load(base + kWideChunk);
-                #pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    if (c >= nleaf || bnd[c + 1] - bnd[c] <= p0) continue;   // uniform
-                    const int cpos = (cposs >> (2 * c)) & 3;
-                    const bool on = (near >> cpos) & 1u;
-                    const uint64_t m = __ballot(on);
-                    const int cnt = __popcll(m);
-                    if (cnt == 0) continue;
-                    // the near sources to lanes 0 .. cnt - 1 in order; behind them zero loads at the leaf's
-                    // corner (every offset evaluated is one between near leaves)
-                    const uint32_t corner = uint32_t((1 + (cpos & 1)) * sd) | (uint32_t((1 + (cpos >> 1)) * sd) << 16);
-                    const int below = __builtin_amdgcn_mbcnt_hi(uint32_t(m >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(m), 0));
-                    const int to = 4 * (on ? below : cnt + lane - below);
-                    const int2_t f2 = __builtin_bit_cast(int2_t, on ? f : 0.0);
-                    const int cs = __builtin_amdgcn_ds_permute(to, int(on ? src : corner));
-                    const int2_t cf = {__builtin_amdgcn_ds_permute(to, f2.x), __builtin_amdgcn_ds_permute(to, f2.y)};
-                    const int S = slice_count(min(bnd[c + 1] - bnd[c] - p0, 64)), first = 4 * int(txy[c] >> 20);
-                    const uint32_t tx = txy[c] & 1023u, ty = (txy[c] >> 10) & 1023u;
-                    const double xd = biased(tx), yd = biased(ty);
-                    double a = acc[c];
-                    for (int k = 0; k < cnt; k += S) {
-                        const int from = 4 * k + first;
-                        const uint32_t w = uint32_t(__builtin_amdgcn_ds_bpermute(from, cs));
-                        const double fk = bperm_d(from, cf);
-                        const uint32_t sx = w & 0xffffu, sy = w >> 16;
-                        a = fma(phi_fast_oct(xd - biased(sx), yd - biased(sy), uint32_t(abs(int(tx) - int(sx))),
-                                             uint32_t(abs(int(ty) - int(sy))), tab, oct, coef), fk, a);
-                    }
-                    acc[c] = a;
-                }
-            }
-            #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const int32_t n = min(bnd[c + 1] - bnd[c] - p0, 64);
-                if (c >= nleaf || n <= 0) continue;
+        for (int c = by_leaf ? mine : 0; c < (by_leaf ? min(mine + 1, nleaf) : nleaf); ++c) {
+            const int32_t t0 = word(4 + c), t_end = word(5 + c);
+            // the ranges near to leaf c to the first lanes, in order
+            const bool on = lane < 16 && lane < ne && ((en.z >> ((cposs >> (2 * c)) & 3)) & 1);
+            const uint32_t m = uint32_t(__ballot(on));
+            const int nr = __popc(m), below = __popc(m & ((1u << rl) - 1u));
+            const int to = lane < 16 ? 4 * (on ? below : nr + rl - below) : 4 * lane;
+            const int32_t start = __builtin_amdgcn_ds_permute(to, en.x);
+            const int32_t len = __builtin_amdgcn_ds_permute(to, on ? en.y - en.x : 0);
+            const int32_t end = row_inclusive_scan(len), beg = end - len, shift = start - beg;
+            const int32_t ns = __builtin_amdgcn_readlane(end, 15), chunks = (ns + kWideChunk - 1) / kWideChunk;
+            for (int32_t p0 = t0; p0 < t_end; p0 += 64) {
+                const int32_t n = min(t_end - p0, 64);
                 const Slices z = slices(n, lane);
-                const double a = sum_slices(acc[c], n, z.S, z.raw);
-                if (z.raw == 0 && pout[c] >= eio.tgt0)
-                    eio.u[eio.sorted ? int64_t(bnd[c] + p0 + lane) : int64_t(pout[c] - eio.tgt0)] = a;
+                const int2 pi = pts[p0 + z.t];
+                int e0 = 0;
+                int2 pn = make_int2(0, 0);
+                double fn = 0.0;
+                auto load = [&](int32_t i) {   // chunk i: its source of this lane
+                    const int32_t base = i * kWideChunk;
+                    const int e = 4 * chunk_entry<kWideChunk>(beg, nr, base, e0);
+                    const int32_t k = min(base + min(lane, kWideChunk - 1), ns - 1) + __builtin_amdgcn_ds_bpermute(e, shift);
+                    pn = pts[k];
+                    fn = fs[k];
+                };
+                const int32_t i0 = SPLIT ? wave : 0, step = SPLIT ? kSplitWaves : 1;
+                if (i0 < chunks) load(i0);
+                const int32_t pout = perm_local[p0 + z.t];
+                double fa = 0.0;
+                if (far && (!SPLIT || wave == kSplitWaves - 1))
+                    fa = far_share<P>(leafT + size_t((pi.x & (sd - 1)) + sd * (pi.y & (sd - 1))) * P,   // its cell of the leaf
+                                      U + size_t(leaf0 + c) * P, z.sl, z.S);
+                const uint32_t tx = uint32_t(pi.x - gx), ty = uint32_t(pi.y - gy);
+                const double xd = biased(tx), yd = biased(ty);
+                Parts parts;
+                for (int32_t i = i0; i < chunks; i += step) {
+                    const int cnt = min(kWideChunk, ns - i * kWideChunk);
+                    const int w = int(uint32_t(pn.x - gx) | (uint32_t(pn.y - gy) << 16));
+                    const int2_t f = __builtin_bit_cast(int2_t, lane < cnt ? fn : 0.0);   // slots past the last: zero loads
+                    if (i + step < chunks) load(i + step);
+                    const double v = chunk_sum(cnt, z.S, 4 * z.sl, [&](int from, double a) -> double {
+                        const uint32_t b = uint32_t(__builtin_amdgcn_ds_bpermute(from, w));
+                        const double fk = bperm_d(from, f);
+                        const uint32_t sx = b & 0xffffu, sy = b >> 16;
+                        return fma(phi_fast_oct(xd - biased(sx), yd - biased(sy), uint32_t(abs(int(tx) - int(sx))),
+                                                uint32_t(abs(int(ty) - int(sy))), tab, oct, coef), fk, a);
+                    });
+                    if (SPLIT) parts.a[0] += v;
+                    else parts.add(v);
+                }
+                double acc;
+                if (SPLIT) {
+                    part[wave][lane] = parts.a[0];
+                    if (wave == kSplitWaves - 1) part[kSplitWaves][lane] = fa;
+                    __syncthreads();
+                    acc = ((part[0][lane] + part[1][lane]) + (part[2][lane] + part[3][lane])) + part[4][lane];
+                    __syncthreads();
+                } else {
+                    acc = parts.sum(chunks) + fa;
+                }
+                acc = sum_slices(acc, n, z.S, z.raw);
+                if ((!SPLIT || wave == 0) && z.raw == 0 && pout >= eio.tgt0)
+                    eio.u[eio.sorted ? int64_t(p0 + z.t) : int64_t(pout - eio.tgt0)] = acc;
             }
         }
     }
@@ -2104,24 +2156,28 @@ __global__ __launch_bounds__(kBlock) void k_p2l(int32_t nx, const int32_t* xitem
 // ahead), and the batch's sources are read as one list, 60 at a time, one per lane, the next 60 in
 // flight.  The n targets take n lanes each of S = 64 / n slices; slice s takes every S-th source from
 // its lane by shuffles.  phi is computed as in k_near_wide, for any offset: 2e6 clustered points
-// 1842 -> 1043 us (gathers from the 4.2-MB table, and a bisection over the entries for every source,
+// 1842 -> 1039 us (gathers from the 4.2-MB table, and a bisection over the entries for every source,
 // before).  L2P runs at each point's finest box (its incoming expansion holds those of the adaptive
 // leaf relayed by L2L), then the caller-order write.
+// SPLIT: as in k_near_wide, four waves per leaf.
 constexpr int kAdWaves = 8, kAdChunk = kWideChunk;
 
-template <int P>
-__global__ __launch_bounds__(64 * kAdWaves, 4) void k_near_adaptive(
+template <int P, bool SPLIT>
+__global__ __launch_bounds__(64 * (SPLIT ? kSplitWaves : kAdWaves), SPLIT ? 3 : 4) void k_near_adaptive(
     int32_t nitems, const AdLeaf* recs, AdaptiveLists L, const int32_t* box_pt0, const int32_t* box_pt1,
     const uint64_t* box_key, const int8_t* box_lev, const InstInfo* inst, const OpsPtrs* ops, const int2* pts,
     const double* fs, const double* Q, const int32_t* pt_box, const double* U, const int32_t* perm_local,
     const ExecPtrs* tab_ptrs, ExecPtrs single, const uint8_t* far_inst, const double* phi_oct_tab,
     const PhiFast* fast) {
+    constexpr int W = SPLIT ? kSplitWaves : kAdWaves;
     __shared__ FastTab tab;
     __shared__ double2_t mant[kFarMantEntries];
-    const int tid = int(threadIdx.x), lane = tid & 63, wave = tid >> 6;
+    __shared__ double part[SPLIT ? kSplitWaves + 1 : 1][64];
     __shared__ int32_t next;
+    const int tid = int(threadIdx.x), lane = tid & 63, wave = tid >> 6;
     static_assert(sizeof(AdLeaf) == 32, "8 words");
-    int32_t q = xcd_item(wave), q1 = xcd_item(kAdWaves + wave);
+    int32_t q = SPLIT ? int32_t(blockIdx.x) : xcd_item(wave);
+    int32_t q1 = SPLIT ? q + int32_t(gridDim.x) : xcd_item(kAdWaves + wave);
     // word l of leaf i's record in lane l
     auto record = [&](int32_t i) -> int32_t {
         return i < nitems ? reinterpret_cast<const int32_t*>(recs)[size_t(i) * 8 + (lane & 7)] : 0;
@@ -2134,11 +2190,11 @@ __global__ __launch_bounds__(64 * kAdWaves, 4) void k_near_adaptive(
     int32_t rec = record(q), rec1 = record(q1);
     {
         const double2_t* src = reinterpret_cast<const double2_t*>(&fast->mant[0][0]);
-        for (int i = tid; i < kFarMantEntries; i += 64 * kAdWaves) mant[i] = src[i];
+        for (int i = tid; i < kFarMantEntries; i += 64 * W) mant[i] = src[i];
         if (tid == 0) next = 2 * kAdWaves;
-        load_near_tab(tab, phi_oct_tab, tid, 64 * kAdWaves);
+        load_near_tab(tab, phi_oct_tab, tid, 64 * W);
     }
-    __syncthreads();   // no block-wide barrier below
+    __syncthreads();
     const FastCoef coef = fast_coef(fast);
     auto word = [](int32_t r, int k) -> int32_t { return __builtin_amdgcn_readlane(r, k); };
     int32_t sg = q < nitems ? entry(word(rec, 2), word(rec, 3), word(rec, 4), word(rec, 5), 0) : -1;
@@ -2148,7 +2204,7 @@ __global__ __launch_bounds__(64 * kAdWaves, 4) void k_near_adaptive(
         const int32_t sg0 = sg;   // the first batch of entries
         // the next leaf's entries and the record after it
         q = q1;
-        q1 = xcd_item(draw(&next));
+        q1 = SPLIT ? q1 + int32_t(gridDim.x) : xcd_item(draw(&next));
         rec = rec1;
         if (q < nitems) sg = entry(word(rec, 2), word(rec, 3), word(rec, 4), word(rec, 5), 0);
         rec1 = record(q1);
@@ -2162,12 +2218,12 @@ __global__ __launch_bounds__(64 * kAdWaves, 4) void k_near_adaptive(
         for (int32_t i0 = t0; i0 < t_end; i0 += 64) {
             const int32_t n = min(t_end - i0, 64);
             const Slices z = slices(n, lane);
-            const int S = z.S, sl = z.sl;
             const int32_t ii = i0 + z.t;
             const int2 pi = pts[ii];
             const int32_t pout = perm_local[ii];
             const double xd = biased(uint32_t(pi.x)), yd = biased(uint32_t(pi.y));   // root coordinates: not negative
-            double acc = 0.0;
+            Parts parts;
+            int32_t done = 0;   // chunks of the batches before
             for (int32_t eb = 0; eb < ne; eb += 64) {
                 // this lane's entry: U (first point, length) or W (box, rank, height, corner)
                 const int32_t d = eb == 0 ? sg0 : entry(u0, nu, w0, nw, eb);
@@ -2192,11 +2248,12 @@ __global__ __launch_bounds__(64 * kAdWaves, 4) void k_near_adaptive(
                     if (lane >= o) end += v;
                 }
                 const int32_t beg = end - len, total = __builtin_amdgcn_readlane(end, 63);
-                const int32_t m = min(64, ne - eb);
+                const int32_t m = min(64, ne - eb), chunks = (total + kAdChunk - 1) / kAdChunk;
                 int e0 = 0;
-                int2 pn;
-                double fn;
-                auto load = [&](int32_t base) {
+                int2 pn = make_int2(0, 0);
+                double fn = 0.0;
+                auto load = [&](int32_t i) {   // chunk i: its source of this lane
+                    const int32_t base = i * kAdChunk;
                     const int e = 4 * chunk_entry<kAdChunk>(beg, m, base, e0);
                     const int32_t k = min(base + min(lane, kAdChunk - 1), total - 1) - __builtin_amdgcn_ds_bpermute(e, beg);
                     const int32_t ae = __builtin_amdgcn_ds_bpermute(e, a), he = __builtin_amdgcn_ds_bpermute(e, hh);
@@ -2215,30 +2272,40 @@ __global__ __launch_bounds__(64 * kAdWaves, 4) void k_near_adaptive(
                         }
                     }
                 };
-                load(0);
-                for (int32_t base = 0; base < total; base += kAdChunk) {
+                const int32_t c0 = SPLIT ? (wave - done) & 3 : 0, step = SPLIT ? kSplitWaves : 1;
+                if (c0 < chunks) load(c0);
+                for (int32_t i = c0; i < chunks; i += step) {
                     const int sx = pn.x, sy = pn.y;
-                    const int cnt = min(kAdChunk, total - base);
-                    const int2_t sf = __builtin_bit_cast(int2_t, lane < cnt ? fn : 0.0);
-                    if (base + kAdChunk < total) load(base + kAdChunk);
-                    for (int k = 0; k < cnt; k += S) {   // slots past the chunk's last hold a zero load
-                        const int from = 4 * (k + sl);
+                    const int cnt = min(kAdChunk, total - i * kAdChunk);
+                    const int2_t sf = __builtin_bit_cast(int2_t, lane < cnt ? fn : 0.0);   // slots past the last: zero loads
+                    if (i + step < chunks) load(i + step);
+                    const double v = chunk_sum(cnt, z.S, 4 * z.sl, [&](int from, double acc) -> double {
                         const int x = __builtin_amdgcn_ds_bpermute(from, sx), y = __builtin_amdgcn_ds_bpermute(from, sy);
                         const double fk = bperm_d(from, sf);
-                        acc = fma(phi_fast_any(xd - biased(uint32_t(x)), yd - biased(uint32_t(y)), uint32_t(abs(pi.x - x)),
-                                               uint32_t(abs(pi.y - y)), tab, mant, coef), fk, acc);
-                    }
+                        return fma(phi_fast_any(xd - biased(uint32_t(x)), yd - biased(uint32_t(y)), uint32_t(abs(pi.x - x)),
+                                                uint32_t(abs(pi.y - y)), tab, mant, coef), fk, acc);
+                    });
+                    if (SPLIT) parts.a[0] += v;
+                    else parts.add(v);
                 }
+                done += chunks;
             }
-            if (far) {
-                const int32_t b = pt_box[ii];
-                const int64_t loc = int64_t(pi.x & (side0 - 1)) + int64_t(side0) * int64_t(pi.y & (side0 - 1));
-                const double* tlp = O.leafT + loc * P;
-                const double* uh = U + size_t(b) * P;
-                for (int p = sl; p < P; p += S) acc += tlp[p] * uh[p];
+            double fa = 0.0;
+            if (far && (!SPLIT || wave == kSplitWaves - 1))
+                fa = far_share<P>(O.leafT + (int64_t(pi.x & (side0 - 1)) + int64_t(side0) * int64_t(pi.y & (side0 - 1))) * P,
+                                  U + size_t(pt_box[ii]) * P, z.sl, z.S);
+            double acc;
+            if (SPLIT) {
+                part[wave][lane] = parts.a[0];
+                if (wave == kSplitWaves - 1) part[kSplitWaves][lane] = fa;
+                __syncthreads();
+                acc = ((part[0][lane] + part[1][lane]) + (part[2][lane] + part[3][lane])) + part[4][lane];
+                __syncthreads();
+            } else {
+                acc = parts.sum(done) + fa;
             }
-            acc = sum_slices(acc, n, S, z.raw);
-            if (z.raw == 0 && pout >= eio.tgt0)
+            acc = sum_slices(acc, n, z.S, z.raw);
+            if ((!SPLIT || wave == 0) && z.raw == 0 && pout >= eio.tgt0)
                 eio.u[eio.sorted ? int64_t(ii) : int64_t(pout - eio.tgt0)] = acc;
         }
     }
@@ -2470,7 +2537,7 @@ static unsigned xcd_grid(const void* fn, int threads, int64_t waves) {
 void launch_near(int32_t q0, int32_t q1, const NearGroup* groups, const int4* ents, int64_t side, const int32_t* pts,
                  const uint32_t* pkey, const double* fs, const int32_t* perm_local, const ExecPtrs* tab,
                  const ExecPtrs& single, const double* U, const double* leafT, const double* phi_oct,
-                 const PhiFast* fast, hipStream_t st) {
+                 const PhiFast* fast, int32_t nleaf, hipStream_t st) {
     if (q1 <= q0) return;
     const int2* p2 = reinterpret_cast<const int2*>(pts);
     if (side <= 16) {
@@ -2488,9 +2555,19 @@ void launch_near(int32_t q0, int32_t q1, const NearGroup* groups, const int4* en
     } else {
         // near offsets are at most 2 side - 1, so that their squared length fits the octave table
         if (2 * side > 256) throw std::logic_error("leaf wider than the near-field table allows");
-        const unsigned g = xcd_grid(reinterpret_cast<const void*>(&k_near_wide<kRankPad>), 64 * kWideWaves, q1 - q0);
-        hipLaunchKernelGGL(k_near_wide<kRankPad>, dim3(g), dim3(64 * kWideWaves), 0, st, q0, q1, groups, ents, side, p2,
-                           fs, perm_local, tab, single, U, leafT, phi_oct, fast);
+        const int64_t units = 4 * int64_t(q1 - q0);
+        if (units <= kSplitLeaves) {
+            const unsigned g = persistent_grid(reinterpret_cast<const void*>(&k_near_wide<kRankPad, true>),
+                                               64 * kSplitWaves, units * kSplitWaves);
+            hipLaunchKernelGGL((k_near_wide<kRankPad, true>), dim3(g), dim3(64 * kSplitWaves), 0, st, q0, q1, groups,
+                               ents, side, p2, fs, perm_local, tab, single, U, leafT, phi_oct, fast, 1);
+            return;
+        }
+        const int by_leaf = units <= kWaveLeaves || (units <= kWaveLeavesFull && 16 * int64_t(nleaf) >= 9 * units);
+        const unsigned g = xcd_grid(reinterpret_cast<const void*>(&k_near_wide<kRankPad, false>), 64 * kWideWaves,
+                                    by_leaf ? units : q1 - q0);
+        hipLaunchKernelGGL((k_near_wide<kRankPad, false>), dim3(g), dim3(64 * kWideWaves), 0, st, q0, q1, groups, ents,
+                           side, p2, fs, perm_local, tab, single, U, leafT, phi_oct, fast, by_leaf);
     }
 }
 
@@ -2524,10 +2601,19 @@ void launch_near_adaptive(int32_t nitems, const AdLeaf* recs, const AdaptiveList
                           const int32_t* perm_local, const ExecPtrs* tab, const ExecPtrs& single,
                           const uint8_t* far_inst, const double* phi_oct, const PhiFast* fast, hipStream_t st) {
     if (nitems <= 0) return;
-    const unsigned g = xcd_grid(reinterpret_cast<const void*>(&k_near_adaptive<kRankPad>), 64 * kAdWaves, nitems);
-    hipLaunchKernelGGL(k_near_adaptive<kRankPad>, dim3(g), dim3(64 * kAdWaves), 0, st, nitems, recs, lists, box_pt0,
-                       box_pt1, box_key, box_lev, inst, ops, reinterpret_cast<const int2*>(pts), fs, Q, pt_box, U,
-                       perm_local, tab, single, far_inst, phi_oct, fast);
+    const int2* p2 = reinterpret_cast<const int2*>(pts);
+    if (nitems <= kSplitAdaptive) {
+        const unsigned g = persistent_grid(reinterpret_cast<const void*>(&k_near_adaptive<kRankPad, true>),
+                                           64 * kSplitWaves, int64_t(nitems) * kSplitWaves);
+        hipLaunchKernelGGL((k_near_adaptive<kRankPad, true>), dim3(g), dim3(64 * kSplitWaves), 0, st, nitems, recs,
+                           lists, box_pt0, box_pt1, box_key, box_lev, inst, ops, p2, fs, Q, pt_box, U, perm_local, tab,
+                           single, far_inst, phi_oct, fast);
+        return;
+    }
+    const unsigned g = xcd_grid(reinterpret_cast<const void*>(&k_near_adaptive<kRankPad, false>), 64 * kAdWaves, nitems);
+    hipLaunchKernelGGL((k_near_adaptive<kRankPad, false>), dim3(g), dim3(64 * kAdWaves), 0, st, nitems, recs, lists,
+                       box_pt0, box_pt1, box_key, box_lev, inst, ops, p2, fs, Q, pt_box, U, perm_local, tab, single,
+                       far_inst, phi_oct, fast);
 }
 
 void launch_direct(int64_t nt, const int32_t* txy, int64_t ns, const int32_t* sxy, const double* f,
