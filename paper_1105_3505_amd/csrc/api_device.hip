@@ -356,6 +356,19 @@ struct TileRange {
     int32_t t0 = 0, n = 0;
 };
 
+// Levels whose M2M and L2L run by subtrees: `depth` heights from h downwards, a block for each of
+// the n boxes of height h
+struct SubStage {
+    int h = 0, depth = 0;
+    int32_t n = 0;
+    SubTree* subs = nullptr;
+    SubOps m2m{}, l2l{};
+};
+// A block for each box of a stage's top level, at most as many as run at once, and at most 16 boxes
+// below each on average: full trees' fourth level has 64, four times the matrix instructions (M2M of
+// 64,000 uniform points in levels 5 to 2: 23 us by four levels, 16.0 by three, 16.8 level by level)
+constexpr int32_t kSubOwners = 256, kSubBoxes = 16;
+
 struct lfmm_plan {
     lfmm_ctx* ctx = nullptr;
     int32_t K = 0;                          // instances
@@ -372,6 +385,7 @@ struct lfmm_plan {
     int32_t nq = 0;
     TileRange m2l;                          // M2L tiles (class-sorted, some empty)
     std::vector<TileRange> m2m, l2l;        // tiles per height
+    std::vector<SubStage> stages;           // from the top of the tree downwards
     int64_t m2l_pairs = 0;
     Arena mem_small, mem_pts, mem_box, mem_ad;
     InstInfo* d_inst = nullptr;
@@ -1121,6 +1135,29 @@ void build_forest(lfmm_plan* pl, int32_t K, const InstanceInput* in, int32_t max
         }
         pl->m2m[size_t(h)].n = int32_t(m2m_tiles.size()) - pl->m2m[size_t(h)].t0;
     }
+    // Stages of M2M and L2L by subtrees, where all trees have the same height and operators (so that a
+    // height is a level), from level 2 down, while a stage's top level has few boxes
+    bool alike = true;
+    for (int32_t k = 0; k < K; ++k)
+        alike = alike && pl->inst[size_t(k)].L == pl->inst[0].L && pl->inst[size_t(k)].ops == pl->inst[0].ops;
+    size_t owners = 0;
+    for (int lev = 2; alike && lev < H; lev = H - (pl->stages.back().h - pl->stages.back().depth)) {
+        SubStage g;
+        g.h = H - lev;
+        g.n = pl->hbase[size_t(g.h) + 1] - pl->hbase[size_t(g.h)];
+        while (g.depth < std::min(kSubLevels, g.h) &&
+               pl->hbase[size_t(g.h - g.depth) + 1] - pl->hbase[size_t(g.h - g.depth)] <= kSubBoxes * g.n)
+            ++g.depth;
+        if (g.depth < 2 || g.n > kSubOwners) break;
+        for (int k = 0; k < g.depth; ++k) {
+            const size_t at = size_t(g.h - k) * 4 * kRankPad * kRankPad;
+            const auto& dev = pl->ops[size_t(pl->inst[0].ops)]->dev;
+            g.m2m.A[k] = dev.ofo_rm + at;
+            g.l2l.A[k] = dev.ofo_cm + at;
+        }
+        owners += size_t(g.n);
+        pl->stages.push_back(g);
+    }
     std::vector<BoxGroup> groups = m2l_groups;
     groups.insert(groups.end(), l2l_groups.begin(), l2l_groups.end());
 
@@ -1158,6 +1195,7 @@ void build_forest(lfmm_plan* pl, int32_t K, const InstanceInput* in, int32_t max
     mb.reserve(size_t(nb) * 4 * kNumInteractions);       // interaction lists
     mb.reserve(size_t(std::max(cls_slots, 1)) * 4);
     mb.reserve(size_t(std::max(tile_slots, 1)) * sizeof(BoxTile));
+    mb.reserve(std::max<size_t>(owners, 1) * sizeof(SubTree));
     mb.reserve(size_t(nb + 1) * P * 8);                  // Q and its zero row
     mb.reserve(size_t(std::max(pl->nq, 1)) * sizeof(NearGroup));
     mb.reserve(size_t(std::max(pl->nq, 1)) * kNearEntries * sizeof(int4));
@@ -1198,6 +1236,7 @@ void build_forest(lfmm_plan* pl, int32_t K, const InstanceInput* in, int32_t max
     pl->il27 = mb.take<int32_t>(size_t(nb) * kNumInteractions);
     pl->cls_box = mb.take<int32_t>(std::max(cls_slots, 1));
     pl->tiles = mb.take<BoxTile>(std::max(tile_slots, 1));
+    SubTree* subs = mb.take<SubTree>(std::max<size_t>(owners, 1));
     pl->Q = mb.take<double>(size_t(nb + 1) * P);
     pl->U = mb.take<double>(size_t(nb + 1) * P);
     pl->groups = mb.take<NearGroup>(size_t(std::max(pl->nq, 1)));
@@ -1285,6 +1324,11 @@ void build_forest(lfmm_plan* pl, int32_t K, const InstanceInput* in, int32_t max
     // also zeroes row nb of Q-hat and U-hat, which the box-matrix kernels read for absent sources
     launch_link_boxes(pl->box_key, pl->box_parent, pl->box_inst, pl->box_lev, pl->d_inst, nb, pl->box_pt0,
                       pl->box_child, pl->box_pt1, pl->Q + size_t(nb) * P, pl->U + size_t(nb) * P, st);
+    for (SubStage& g : pl->stages) {
+        g.subs = subs;
+        launch_subtrees(pl->hbase[size_t(g.h)], g.n, g.depth, pl->box_child, g.subs, st);
+        subs += g.n;
+    }
     launch_lists(pl->box_key, pl->box_parent, pl->box_child, pl->box_inst, pl->box_lev, pl->d_inst, nb, pl->nb9,
                  pl->il27, st);
     const int32_t m2l_slots = pl->m2l.n;
@@ -1388,9 +1432,14 @@ void enqueue_passes(lfmm_plan* pl, const ExecPtrs* tab, const double* f1, double
                    double(pl->n) / double(std::max<int32_t>(pl->nleaf, 1)), st);
     }
     mark(2);
-    for (int h = 1; h <= pl->Hmax; ++h) {
+    const int h_sub = pl->stages.empty() ? pl->Hmax + 1 : pl->stages.back().h - pl->stages.back().depth + 1;
+    for (int h = 1; h < std::min(h_sub, pl->Hmax + 1); ++h) {
         const TileRange& r = pl->m2m[size_t(h)];
         if (r.n > 0) launch_m2m(pl->m2m_tiles + r.t0, r.n, pl->box_child, pl->d_ops, pl->Q, pl->nbox, st);
+    }
+    for (size_t k = pl->stages.size(); k-- > 0;) {
+        const SubStage& g = pl->stages[k];
+        launch_m2m_sub(g.subs, g.n, g.depth, g.m2m, pl->box_child, pl->Q, pl->nbox, st);
     }
     mark(3);
     if (pl->m2l.n > 0) {
@@ -1420,7 +1469,9 @@ void enqueue_passes(lfmm_plan* pl, const ExecPtrs* tab, const double* f1, double
                    pl->box_inst, pl->d_inst, pl->d_ops, pl->pts, pl->fs, pl->U, pl->ctx->phi_oct, pl->ctx->phi_far,
                    st);
     }
-    for (int h = pl->Hmax; h >= 0; --h) {
+    for (const SubStage& g : pl->stages)
+        launch_l2l_sub(g.subs, g.n, g.depth, g.l2l, pl->box_child, pl->U, pl->role, st);
+    for (int h = std::min(pl->Hmax, h_sub - 2); h >= 0; --h) {   // heights of the children
         const TileRange& r = pl->l2l[size_t(h)];
         if (r.n > 0)
             launch_l2l(pl->tiles + r.t0, r.n, pl->cls_box, pl->box_parent, pl->d_ops, pl->U, pl->nbox, pl->role, st);
@@ -2155,7 +2206,8 @@ lfmm_status lfmm_plan_footprint_bytes(const lfmm_ctx* ctx, int64_t n_src, int64_
                          : ctx->opt.precision == LFMM_MIXED_BF16 ? (nb + 1) * (P * 6 + 8) + 2 * al
                                                                  : 0;
     const size_t box = nb * (8 + 20 + 1 + 16 + 36 + 4 * kNumInteractions + 32) + tiles * sizeof(BoxTile) +
-                       2 * (nb + 1) * P * 8 + nl * (sizeof(NearGroup) + kNearEntries * 16) + 14 * al + mixed;
+                       2 * (nb + 1) * P * 8 + nl * (sizeof(NearGroup) + kNearEntries * 16) +
+                       size_t(D / kSubLevels + 1) * kSubOwners * sizeof(SubTree) + 15 * al + mixed;
     const size_t small = sizeof(InstInfo) + 64 * sizeof(OpsPtrs) + 16 + 4 * size_t(D + 2) * sizeof(BoxGroup) +
                          (nb / 64 + size_t(D + 2)) * sizeof(BoxTile) + sizeof(ExecPtrs) + 16 * al;
     // construction temporaries: concatenated points, keys and indices (two copies), common

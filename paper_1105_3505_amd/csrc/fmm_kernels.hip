@@ -676,6 +676,201 @@ __global__ __launch_bounds__(kBlock) void k_l2l_fine(const BoxTile* tiles, const
     boxmat_fine<kModeL2L>(tiles, box_list, box_parent, ops, U, zrow, U, role);
 }
 
+// M2M and L2L over several levels in one launch, for the top of a tree, whose levels of few boxes each
+// lasted a launch's 4.4 us with the kernels above: 2.4 us of it for the launch itself, then a chain of
+// dependent loads, with the device nearly idle.  A block takes one box and all its descendants down to
+// `depth` levels of boxes with children (depth <= kSubLevels; SubTree): level k of them is kept in LDS
+// for the next, at most 4^k rows, so that a level costs its products and one or two barriers.  Twelve
+// waves: wave w takes child position w % 4 and row block w / 4, as in the kernels above and with the same
+// sums.  The children's indices and (L2L) their M2L results are loaded before the first product, a
+// level's operators while the one before runs.  A level is bound by its matrix instructions, 1 us for
+// up to 16 boxes: four levels of a curve's tree take 10.4 us (M2M) and 12.7 us (L2L), before 15 and 17.
+constexpr int kSubThreads = 768, kSubRow = kRankPad + 2;
+__device__ inline constexpr int sub_base(int k) { return k == 3 ? 0 : k == 2 ? 64 : k == 1 ? 80 : 84; }
+constexpr int kSubRows = 85;
+static_assert(kSubLevels == 4, "sub_base");
+
+struct SubChildren {   // this lane's children, by level and unit of 16 boxes
+    int32_t ch[3], ch3[4];
+};
+__device__ inline SubChildren sub_children(const SubTree& s, int depth, const int32_t* box_child, int c, int n) {
+    SubChildren r;
+    #pragma unroll
+    for (int k = 0; k < 3; ++k)
+        r.ch[k] = k < depth && n < s.count[k] ? box_child[size_t(s.first[k] + n) * 4 + c] : -1;
+    #pragma unroll
+    for (int q = 0; q < 4; ++q)
+        r.ch3[q] = depth == 4 && 16 * q + n < s.count[3] ? box_child[size_t(s.first[3] + 16 * q + n) * 4 + c] : -1;
+    return r;
+}
+__device__ inline SubTree sub_tree(const SubTree* subs) {
+    const cptr<int32_t> p = as_const(reinterpret_cast<const int32_t*>(subs + blockIdx.x));
+    SubTree s;
+    #pragma unroll
+    for (int k = 0; k < kSubLevels; ++k) {
+        s.first[k] = p[k];
+        s.count[k] = p[kSubLevels + k];
+    }
+    return s;
+}
+
+__global__ __launch_bounds__(kSubThreads, 3) void k_m2m_sub(const SubTree* subs, int depth, SubOps A,
+                                                            const int32_t* box_child, double* Q, int32_t zrow) {
+    constexpr int P = kRankPad, KQ = P / 4, NJ = KQ / 2, A2 = P * P / 2;
+    __shared__ __align__(16) double qs[kSubRows][kSubRow];
+    __shared__ double red[4][12][64];
+    const int tid = int(threadIdx.x), wave = tid >> 6, lane = tid & 63;
+    const int n = lane & 15, g = lane >> 4, c = wave & 3, m = wave >> 2;
+    const SubTree s = sub_tree(subs);
+    const SubChildren ch = sub_children(s, depth, box_child, c, n);
+    auto load_a = [&](int k, double2_t (&a)[NJ]) {
+        const gptr<double2_t> p = global(reinterpret_cast<const double2_t*>(A.A[k])) + size_t(c) * A2 + size_t(m * NJ) * 64 + lane;
+        #pragma unroll
+        for (int j = 0; j < NJ; ++j) a[j] = p[j * 64];
+    };
+    auto load_q = [&](int32_t child, double2_t (&x)[NJ]) {   // an expansion of an earlier kernel
+        const gptr<double2_t> p = reinterpret_cast<gptr<double2_t>>(global(Q) + size_t(child < 0 ? zrow : child) * P + g * KQ);
+        #pragma unroll
+        for (int j = 0; j < NJ; ++j) x[j] = p[j];
+    };
+    double2_t a[NJ], an[NJ], x[2][NJ];
+    load_a(depth - 1, a);
+    if (depth == 4) {
+        load_q(ch.ch3[0], x[0]);
+        if (16 < s.count[3]) load_q(ch.ch3[1], x[1]);
+    } else {
+        load_q(depth == 3 ? ch.ch[2] : depth == 2 ? ch.ch[1] : ch.ch[0], x[0]);
+    }
+    #pragma unroll
+    for (int k = kSubLevels - 1; k >= 0; --k) {
+        if (k >= depth) continue;                          // uniform
+        if (k < depth - 1) {
+            #pragma unroll
+            for (int j = 0; j < NJ; ++j) a[j] = an[j];
+        }
+        if (k > 0) load_a(k > 0 ? k - 1 : 0, an);          // the next level's
+        asm volatile("" ::: "memory");
+        #pragma unroll
+        for (int q = 0; q < (k == 3 ? 4 : 1); ++q) {
+            if (16 * q >= s.count[k]) continue;            // uniform
+            if (k < depth - 1) {
+                const int32_t child = ch.ch[k < 3 ? k : 0];
+                const double2_t* p = reinterpret_cast<const double2_t*>(
+                    &qs[sub_base(k + 1) + max(child - s.first[k < 3 ? k + 1 : 3], 0)][g * KQ]);
+                #pragma unroll
+                for (int j = 0; j < NJ; ++j) x[0][j] = child < 0 ? double2_t{0.0, 0.0} : p[j];
+            }
+            double4_t acc = {0.0, 0.0, 0.0, 0.0};
+            #pragma unroll
+            for (int j = 0; j < NJ; ++j) {
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[j].x, x[q & 1][j].x, acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[j].y, x[q & 1][j].y, acc, 0, 0, 0);
+            }
+            if (k == 3 && q < 2 && 16 * (q + 2) < s.count[3]) load_q(ch.ch3[q < 2 ? q + 2 : 0], x[q & 1]);
+            #pragma unroll
+            for (int i = 0; i < 4; ++i) red[c][4 * m + i][lane] = acc[i];
+            __syncthreads();
+            // wave w writes element w of every lane's twelve
+            const double v = ((red[0][wave][lane] + red[1][wave][lane]) + red[2][wave][lane]) + red[3][wave][lane];
+            const int row = 16 * (wave >> 2) + g + 4 * (wave & 3), b = 16 * q + n;
+            if (b < s.count[k]) {
+                qs[sub_base(k) + b][row] = v;
+                Q[size_t(s.first[k] + b) * P + row] = v;
+            }
+            __syncthreads();
+        }
+    }
+}
+
+__global__ __launch_bounds__(kSubThreads, 3) void k_l2l_sub(const SubTree* subs, int depth, SubOps A,
+                                                            const int32_t* box_child, double* U, const int8_t* role) {
+    constexpr int P = kRankPad, KQ = P / 4, NJ = KQ / 2, A2 = P * P / 2;
+    __shared__ __align__(16) double us[kSubRows][kSubRow];
+    const int tid = int(threadIdx.x), wave = tid >> 6, lane = tid & 63;
+    const int n = lane & 15, g = lane >> 4, c = wave & 3, m = wave >> 2;
+    const SubTree s = sub_tree(subs);
+    const SubChildren ch = sub_children(s, depth, box_child, c, n);
+    // Row 4 i + g of the row block is given row 12 g + 4 m + i of the operator, so that lane (g, n) ends up
+    // with four consecutive elements of its child's expansion
+    const int arow = 12 * (n & 3) + 4 * m + (n >> 2);
+    auto load_a = [&](int k, double2_t (&a)[NJ]) {
+        const gptr<double2_t> p = global(reinterpret_cast<const double2_t*>(A.A[k])) + size_t(c) * A2 +
+                                  size_t(arow >> 4) * NJ * 64 + 16 * g + (arow & 15);
+        #pragma unroll
+        for (int j = 0; j < NJ; ++j) a[j] = p[j * 64];
+    };
+    // M2L's result; a pruned box of the adaptive tree has none: it takes its parent's alone
+    auto load_old = [&](int32_t child, double2_t (&o)[2]) {
+        const bool add = child >= 0 && !(role != nullptr && role[child] == kRolePruned);
+        const double2_t* p = reinterpret_cast<const double2_t*>(U + size_t(add ? child : s.first[0]) * P + g * KQ + 4 * m);
+        #pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const double2_t v = p[j];
+            o[j] = add ? v : double2_t{0.0, 0.0};
+        }
+    };
+    double2_t a[NJ], an[NJ], x[NJ], old[3][2], old3[4][2];
+    load_a(0, a);
+    {
+        const gptr<double2_t> p = reinterpret_cast<gptr<double2_t>>(global(static_cast<const double*>(U)) + size_t(s.first[0]) * P + g * KQ);
+        #pragma unroll
+        for (int j = 0; j < NJ; ++j) x[j] = p[j];
+    }
+    #pragma unroll
+    for (int k = 0; k < 3; ++k)
+        if (k < depth) load_old(ch.ch[k], old[k]);
+    #pragma unroll
+    for (int k = 0; k < kSubLevels; ++k) {
+        if (k >= depth) continue;                          // uniform
+        if (k > 0) {
+            #pragma unroll
+            for (int j = 0; j < NJ; ++j) a[j] = an[j];
+        }
+        if (k + 1 < depth) load_a(k < 3 ? k + 1 : 0, an);  // the next level's
+        if (k == 2) {
+            #pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (depth == 4 && 16 * q < s.count[3]) load_old(ch.ch3[q], old3[q]);
+        }
+        asm volatile("" ::: "memory");
+        #pragma unroll
+        for (int q = 0; q < (k == 3 ? 4 : 1); ++q) {
+            if (16 * q >= s.count[k]) continue;            // uniform
+            if (k > 0) {
+                const double2_t* p = reinterpret_cast<const double2_t*>(&us[sub_base(k) + min(16 * q + n, s.count[k] - 1)][g * KQ]);
+                #pragma unroll
+                for (int j = 0; j < NJ; ++j) x[j] = p[j];
+            }
+            double4_t acc[4];
+            #pragma unroll
+            for (int r = 0; r < 4; ++r) acc[r] = double4_t{0.0, 0.0, 0.0, 0.0};
+            #pragma unroll
+            for (int t = 0; t < 3; ++t)                    // part r of the sum: steps 3 r .. 3 r + 2
+                #pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int e = 3 * r + t;
+                    acc[r] = __builtin_amdgcn_mfma_f64_16x16x4f64(e & 1 ? a[e >> 1].y : a[e >> 1].x,
+                                                                  e & 1 ? x[e >> 1].y : x[e >> 1].x, acc[r], 0, 0, 0);
+                }
+            const int32_t child = k == 3 ? ch.ch3[q] : ch.ch[k < 3 ? k : 0];
+            if (child >= 0) {
+                double2_t* out = reinterpret_cast<double2_t*>(U + size_t(child) * P + g * KQ + 4 * m);
+                double2_t* row = reinterpret_cast<double2_t*>(
+                    &us[k + 1 < depth ? sub_base(k + 1) + child - s.first[k < 3 ? k + 1 : 3] : 0][g * KQ + 4 * m]);
+                #pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    const double2_t o = k == 3 ? old3[q][j] : old[k < 3 ? k : 0][j];
+                    const double2_t v = {o.x + (((acc[0][2 * j] + acc[1][2 * j]) + acc[2][2 * j]) + acc[3][2 * j]),
+                                         o.y + (((acc[0][2 * j + 1] + acc[1][2 * j + 1]) + acc[2][2 * j + 1]) + acc[3][2 * j + 1])};
+                    out[j] = v;
+                    if (k + 1 < depth) row[j] = v;
+                }
+            }
+        }
+        __syncthreads();
+    }
+}
+
 // Mixed-precision operands of the outgoing expansions, once per box: q-hat split into FP32
 // hi + lo parts (hi = fl32(q), lo = fl32(q - hi), so that hi + lo equals q to about 2^-48) and
 // its charge sum in FP64, for boxes [0, nrows) (the all-zero row included).
@@ -2450,6 +2645,18 @@ void launch_l2l(const BoxTile* tiles, int32_t ntiles, const int32_t* box_list, c
     g = std::max<int64_t>(8, (g + 7) / 8 * 8);
     hipLaunchKernelGGL(k_l2l, dim3(static_cast<unsigned>(g)), dim3(kBlock), 0, st, tiles, ntiles, box_list,
                        box_parent, ops, U, zrow, role);
+}
+
+void launch_m2m_sub(const SubTree* subs, int32_t n, int depth, const SubOps& A, const int32_t* box_child, double* Q,
+                    int32_t zrow, hipStream_t st) {
+    if (n <= 0) return;
+    hipLaunchKernelGGL(k_m2m_sub, dim3(unsigned(n)), dim3(kSubThreads), 0, st, subs, depth, A, box_child, Q, zrow);
+}
+
+void launch_l2l_sub(const SubTree* subs, int32_t n, int depth, const SubOps& A, const int32_t* box_child, double* U,
+                    const int8_t* role, hipStream_t st) {
+    if (n <= 0) return;
+    hipLaunchKernelGGL(k_l2l_sub, dim3(unsigned(n)), dim3(kSubThreads), 0, st, subs, depth, A, box_child, U, role);
 }
 
 // Tiles weighted by the expected share of their interaction lists that exists: boxes with `children`

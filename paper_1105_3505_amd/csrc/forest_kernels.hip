@@ -704,6 +704,28 @@ __global__ void k_compact_positive(const int32_t* cnt, const int32_t* pos, int64
     if (g < nbox && cnt[g] > 0) items[pos[g]] = int32_t(g);
 }
 
+__global__ void k_subtrees(int32_t box0, int32_t n, int depth, const int32_t* box_child, SubTree* subs) {
+    const int32_t i = int32_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    SubTree s{};
+    int32_t a = box0 + i, b = a;   // a level's first and last box; boxes above the leaves have children
+    for (int k = 0; k < depth; ++k) {
+        s.first[k] = a;
+        s.count[k] = b - a + 1;
+        if (k + 1 == depth) break;
+        const int32_t* ca = box_child + size_t(a) * 4;
+        const int32_t* cb = box_child + size_t(b) * 4;
+        int32_t na = -1, nb = -1;
+        for (int c = 0; c < 4; ++c) {
+            if (na < 0) na = ca[c];
+            nb = max(nb, cb[c]);
+        }
+        a = na;
+        b = nb;
+    }
+    subs[i] = s;
+}
+
 __global__ void k_ad_records(int32_t nitems, const int32_t* items, AdaptiveLists L, const int32_t* box_pt0,
                              const int32_t* box_pt1, const int32_t* box_inst, AdLeaf* recs) {
     const int32_t i = int32_t(blockIdx.x) * blockDim.x + threadIdx.x;
@@ -1372,6 +1394,11 @@ void launch_adaptive_lists(bool fill, const uint64_t* box_key, const int32_t* bo
 void launch_compact_positive(const int32_t* cnt, const int32_t* pos, int64_t nbox, int32_t* items, hipStream_t st) {
     if (nbox <= 0) return;
     hipLaunchKernelGGL(k_compact_positive, dim3(grid_for(nbox)), dim3(kBlock), 0, st, cnt, pos, nbox, items);
+}
+
+void launch_subtrees(int32_t box0, int32_t n, int depth, const int32_t* box_child, SubTree* subs, hipStream_t st) {
+    if (n <= 0) return;
+    hipLaunchKernelGGL(k_subtrees, dim3(grid_for(n)), dim3(kBlock), 0, st, box0, n, depth, box_child, subs);
 }
 
 void launch_ad_records(int32_t nitems, const int32_t* items, const AdaptiveLists& lists, const int32_t* box_pt0,

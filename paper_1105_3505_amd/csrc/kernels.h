@@ -300,6 +300,22 @@ void launch_m2m(const BoxTile* tiles, int32_t ntiles, const int32_t* box_child, 
 // kRolePruned (role non-null) take the parent's expansion alone (no M2L wrote theirs)
 void launch_l2l(const BoxTile* tiles, int32_t ntiles, const int32_t* box_list, const int32_t* box_parent,
                 const OpsPtrs* ops, double* U, int32_t zrow, const int8_t* role, hipStream_t st);
+// A box and its descendants, down to kSubLevels levels of boxes with children: level k of them is boxes
+// first[k] .. first[k] + count[k] - 1 (k = 0: the box itself)
+constexpr int kSubLevels = 4;
+struct SubTree {
+    int32_t first[kSubLevels], count[kSubLevels];
+};
+struct SubOps {
+    const double* A[kSubLevels];   // the four operators (ofo_rm or ofo_cm) of level k's boxes
+};
+// Subtrees of the n boxes from `box0` on, depth levels each
+void launch_subtrees(int32_t box0, int32_t n, int depth, const int32_t* box_child, SubTree* subs, hipStream_t st);
+// M2M into, and L2L out of, all boxes of the n subtrees (same sums as launch_m2m and launch_l2l)
+void launch_m2m_sub(const SubTree* subs, int32_t n, int depth, const SubOps& A, const int32_t* box_child, double* Q,
+                    int32_t zrow, hipStream_t st);
+void launch_l2l_sub(const SubTree* subs, int32_t n, int depth, const SubOps& A, const int32_t* box_child, double* U,
+                    const int8_t* role, hipStream_t st);
 // M2L over the class-sorted tiles, *ntiles_dev of them (max_tiles at most); Q row zrow is all
 // zeros (read for absent sources); children, the mean number of children of a box above the
 // leaves, and max_tiles pick the kernel (same results bit for bit)
