@@ -1428,8 +1428,7 @@ void enqueue_passes(lfmm_plan* pl, const ExecPtrs* tab, const double* f1, double
     for (size_t o = 0; o < pl->ops.size(); ++o) {
         const TileRange& r = pl->leaf_of_ops[o];
         launch_p2m(r.t0, r.t0 + r.n, pl->box_pt0, pl->box_pt1, pl->box_key, pl->ops[o]->dev.leaf_side, pl->pts, tab,
-                   single, pl->perm, pl->pinst, pl->fs, pl->ops[o]->dev.leafT, pl->Q,
-                   double(pl->n) / double(std::max<int32_t>(pl->nleaf, 1)), st);
+                   single, pl->perm, pl->box_inst, pl->fs, pl->ops[o]->dev.leafT, pl->Q, st);
     }
     mark(2);
     const int h_sub = pl->stages.empty() ? pl->Hmax + 1 : pl->stages.back().h - pl->stages.back().depth + 1;

@@ -97,19 +97,13 @@ inline unsigned grid_for(int64_t n, int per_block = kBlock) {
     return unsigned(g < 1 ? 1 : g);
 }
 
-// Load of sorted point s: in the caller's order, the instance-local index perm_local[s] of
-// instance pinst[s]; with sorted loads, index s itself (coalesced); zero for a point that is a
-// target only.  Also stored at fs[s] for the near field: P2M visits every point once.
-__device__ inline double gather_f(const ExecPtrs* tab, const ExecPtrs& single, const int32_t* perm_local,
-                                  const int32_t* pinst, int64_t s, double* fs) {
-    const ExecPtrs e = tab ? tab[pinst[s]] : single;
-    const double* f = e.f;
-    const int32_t nsrc = e.nsrc;
-    const bool sorted = e.sorted != 0;
-    const int32_t j = perm_local[s];
-    const double v = j < nsrc ? f[sorted ? s : int64_t(j)] : 0.0;
-    fs[s] = v;
-    return v;
+__device__ inline int32_t uniform(int32_t v) { return __builtin_amdgcn_readfirstlane(v); }
+
+// Load of sorted point s of an instance with arrays e: in the caller's order, that of the
+// instance-local index perm_local[s] = j; with sorted loads, of index s itself (coalesced); zero for a
+// point that is a target only.  Also stored at fs[s] for the near field: P2M visits every point once.
+__device__ inline double load_f(const ExecPtrs& e, int32_t j, int32_t s) {
+    return j < e.nsrc ? e.f[e.sorted != 0 ? s : j] : 0.0;
 }
 
 // P2M with the dense-model operator (Remark 8.2): q-hat[p] = sum_j T[loc(j)][p] f_j; one
@@ -117,17 +111,18 @@ __device__ inline double gather_f(const ExecPtrs* tab, const ExecPtrs& single, c
 // per lane (coalesced), and handed to all lanes by shuffles, so the only memory reads in the
 // loop are the operator rows, whose addresses are known in advance and can be in flight
 // together.  Each entry is one sum over the leaf's points in order, as in k_p2m_lds: which of
-// the two kernels a launch takes depends on the plan (the mean points per leaf), so a leaf must
+// the two kernels a launch takes depends on the plan (its number of leaves), so a leaf must
 // get the same bits from both for an instance alone and in a forest to agree.
 template <int P>
 __global__ __launch_bounds__(kBlock) void k_p2m(int32_t leaf0, int32_t leaf1, const int32_t* box_pt0,
                                                  const int32_t* box_pt1, const uint64_t* box_key, int64_t side,
                                                  const int2* pts, const ExecPtrs* tab, ExecPtrs single,
-                                                 const int32_t* perm_local, const int32_t* pinst,
+                                                 const int32_t* perm_local, const int32_t* box_inst,
                                                  double* fs, const double* leafT, double* Q) {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int32_t g = leaf0 + int32_t(blockIdx.x) * kWaves + wave;
     if (g >= leaf1) return;
+    const ExecPtrs e = tab ? tab[box_inst[g]] : single;
     const int32_t p0 = box_pt0[g], p1 = box_pt1[g];
     const uint64_t key = box_key[g];
     const int32_t cx = int32_t(compact_bits(key) * side), cy = int32_t(compact_bits(key >> 1) * side);
@@ -140,21 +135,20 @@ __global__ __launch_bounds__(kBlock) void k_p2m(int32_t leaf0, int32_t leaf1, co
         if (j < p1) {
             const int2 q = pts[j];
             loc = int32_t(int64_t(q.x - cx) + side * int64_t(q.y - cy));
-            f = gather_f(tab, single, perm_local, pinst, j, fs);
+            f = load_f(e, perm_local[j], j);
+            fs[j] = f;
         }
         const int cnt = min(64, p1 - c0);
-        for (int k = 0; k < cnt; k += 4) {   // k + 3 < 64: the tail reads the zero-load lanes
-            const int32_t l0 = __shfl(loc, k, 64), l1 = __shfl(loc, k + 1, 64);
-            const int32_t l2 = __shfl(loc, k + 2, 64), l3 = __shfl(loc, k + 3, 64);
-            const double f0 = __shfl(f, k, 64), f1 = __shfl(f, k + 1, 64);
-            const double f2 = __shfl(f, k + 2, 64), f3 = __shfl(f, k + 3, 64);
-            // the four rows are loaded together; the sum takes them in point order
-            const double t0 = leafT[int64_t(l0) * P + l], t1 = leafT[int64_t(l1) * P + l];
-            const double t2 = leafT[int64_t(l2) * P + l], t3 = leafT[int64_t(l3) * P + l];
-            a += t0 * f0;
-            a += t1 * f1;
-            a += t2 * f2;
-            a += t3 * f3;
+        for (int k = 0; k < cnt; k += 8) {   // k + 7 < 64: the tail reads the zero-load lanes
+            // the eight rows are loaded together; the sum takes them in point order
+            double t[8], fk[8];
+            #pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                t[u] = leafT[int64_t(__shfl(loc, k + u, 64)) * P + l];
+                fk[u] = __shfl(f, k + u, 64);
+            }
+            #pragma unroll
+            for (int u = 0; u < 8; ++u) a += t[u] * fk[u];
         }
     }
     if (lane < P) Q[size_t(g) * P + lane] = a;
@@ -162,95 +156,157 @@ __global__ __launch_bounds__(kBlock) void k_p2m(int32_t leaf0, int32_t leaf1, co
 
 // P2M with the leaf operator staged in LDS (leaf sides whose T_ofs fits: side^2 P doubles):
 // persistent blocks of kP2mThreads copy T_ofs once, then each wave takes 8 leaves at a time,
-// one per 8-lane group; lane l of a group accumulates rows l, l + 8, ..., l + 40 of Q-hat over
-// the leaf's points, which the group loads 8 at a time and broadcasts by shuffles.  A group
-// past the others' point counts adds zero loads at cell 0.  The next leaves' box data are
-// loaded while the current ones are summed.
-constexpr int kP2mThreads = 1024;
+// one per 8-lane group, eight points of each at a time (a chunk); lane l of a group accumulates entries
+// 2 l + 16 r and 2 l + 16 r + 1 of Q-hat over the leaf's points, which the group loads one per lane and
+// hands round by shuffles.  A group past the others' point counts adds zero loads at cell 0.
+// What bounds it is the chain box -> points and order -> loads -> rows, a few dependent trips to
+// memory per chunk: the points and their order are loaded two chunks ahead and the loads one, across
+// leaves, and the boxes two steps ahead (16,384 leaves of 15 points, side 16: 20.4 -> 16.9 us; 8.9e6
+// points in 512 trees 338 -> 273; 2e6 in 64 clusters, side 128, 183 -> 153).  From 1e6 points on the rows
+// bound it: 384 bytes a point, from LDS, or from L2 and beyond (5 TB/s).
+constexpr int kP2mThreads = 1024, kP2mFreeThreads = 512;   // with and without the staged operator
 constexpr int kP2mGroup = 8;                   // lanes per leaf
 constexpr int kP2mLeaves = 64 / kP2mGroup;     // leaves per wave and step
-// leaves with T_ofs too large for LDS take the grouped kernel (global T_ofs) when they hold
-// at most this many points on average, else one wave each
-constexpr int kP2mSparsePoints = 16;
+// A wave per leaf (k_p2m) for plans of at most this many leaves, whose waves all run at once: a leaf's
+// points, loads and rows then take one trip to memory each, not one a chunk.  Measured (k_p2m / grouped,
+// us): side 8, 15 points a leaf, 1,024 leaves 6.6 / 13.2, 4,096 9.6 / 14.7, 16,384 20.0 / 16.1; side 32, 25 points,
+// 1,024 leaves 7.2 / 17.5, 4,096 11.4 / 17.5, 16,384 26.3 / 21.9.
+constexpr int32_t kP2mWaveLeaves = 8192;
 
-// STAGED false: the same grouping for leaves whose T_ofs is too large for LDS but that hold few
-// points each (the sparse leaves of clustered inputs): the operator rows come from global memory
-// (L2-resident), eight lanes reading one 384-byte row together.
-template <int P, bool STAGED = true>
-__global__ __launch_bounds__(kP2mThreads) void k_p2m_lds(int32_t leaf0, int32_t leaf1, const int32_t* box_pt0,
-                                                        const int32_t* box_pt1, const uint64_t* box_key, int64_t side,
+// STAGED false: the same for leaves whose T_ofs is too large for LDS: the operator rows come from global
+// memory (L2-resident), eight lanes reading one 384-byte row together.
+template <int P, bool STAGED>
+__global__ __launch_bounds__(STAGED ? kP2mThreads : kP2mFreeThreads) void k_p2m_lds(int32_t leaf0, int32_t leaf1, const int32_t* box_pt0,
+                                                        const int32_t* box_pt1, int64_t side,
                                                         const int2* pts, const ExecPtrs* tab, ExecPtrs single,
-                                                        const int32_t* perm_local,
-                                                        const int32_t* pinst, double* fs, const double* leafT,
-                                                        double* Q) {
-    constexpr int R = P / kP2mGroup;   // rows per lane
-    static_assert(P % kP2mGroup == 0, "rows split evenly over a group");
-    extern __shared__ double sT_lds[];
-    const int ncell = int(side * side);
+                                                        const int32_t* perm_local, const int32_t* box_inst,
+                                                        double* fs, const double* leafT, double* Q) {
+    constexpr int W = (STAGED ? kP2mThreads : kP2mFreeThreads) / 64;
+    constexpr int R = P / (2 * kP2mGroup);   // pairs of entries per lane
+    static_assert(P % (2 * kP2mGroup) == 0, "entries split evenly over a group");
+    extern __shared__ __align__(16) double sT_lds[];
+    const int ncell = int(side * side), sd = int(side);
+    const int wave = int(threadIdx.x) >> 6, lane = int(threadIdx.x) & 63, l = lane % kP2mGroup;
+    const int grp = lane / kP2mGroup;
+    const int32_t nleaf = leaf1 - leaf0;
+    const int32_t stride = int32_t(gridDim.x) * W * kP2mLeaves;
+    struct Box {
+        int32_t p0, npt, inst;
+    };
+    auto box = [&](int32_t q) {   // of this lane's leaf at step q
+        Box b = {0, 0, 0};
+        if (q + grp < nleaf) {
+            const int32_t g = leaf0 + q + grp;
+            b.p0 = box_pt0[g];
+            b.npt = box_pt1[g] - b.p0;
+            if (tab) b.inst = box_inst[g];
+        }
+        return b;
+    };
+    // the chunk whose points are loaded next: chunk c of step q, its boxes, and the next step's
+    int32_t q = (int32_t(blockIdx.x) * W + wave) * kP2mLeaves, c = 0, most = 0;
+    Box cur = box(q), nxt = box(q + stride);
+    ExecPtrs e = single;
+    auto open = [&]() {   // step q's leaves
+        if (tab) e = tab[cur.inst];
+        most = cur.npt;
+        #pragma unroll
+        for (int o = kP2mGroup; o < 64; o <<= 1) most = max(most, __shfl_xor(most, o, 64));
+        most = uniform(most);
+    };
+    struct Chunk {
+        int32_t s, perm, q, pts;   // this lane's point (-1: none) and its place; step; points per leaf; pts < 0: none
+        int2 xy;
+        bool last;
+        const double* f;
+        int32_t nsrc, sorted;
+    };
+    auto fetch = [&]() {
+        Chunk k;
+        k.pts = -1;
+        k.s = -1;
+        k.q = q;
+        k.perm = 0;
+        k.xy = make_int2(0, 0);
+        k.last = true;
+        k.f = e.f;
+        k.nsrc = e.nsrc;
+        k.sorted = e.sorted;
+        if (q >= nleaf) return k;
+        if (c + l < cur.npt) {
+            k.s = cur.p0 + c + l;
+            k.xy = pts[k.s];
+            k.perm = perm_local[k.s];
+        }
+        k.pts = min(most - c, kP2mGroup);
+        c += kP2mGroup;
+        if (c >= most) {
+            q += stride;
+            c = 0;
+            cur = nxt;
+            nxt = box(q + stride);
+            if (q < nleaf) open();
+        } else {
+            k.last = false;
+        }
+        return k;
+    };
+    open();
+    Chunk ahead = fetch();
     if (STAGED) {
         const double2* src = reinterpret_cast<const double2*>(leafT);
         double2* dst = reinterpret_cast<double2*>(sT_lds);
         for (int i = int(threadIdx.x); i < ncell * P / 2; i += kP2mThreads) dst[i] = src[i];
     }
-    const double* sT = STAGED ? sT_lds : leafT;
-    const int wave = int(threadIdx.x) >> 6, lane = int(threadIdx.x) & 63, l = lane % kP2mGroup;
-    const int grp = lane / kP2mGroup;
-    const int32_t nleaf = leaf1 - leaf0;
-    const int32_t stride = int32_t(gridDim.x) * (kP2mThreads / 64) * kP2mLeaves;
-    int32_t q = (int32_t(blockIdx.x) * (kP2mThreads / 64) + wave) * kP2mLeaves;
-    // box data of this lane's leaf at step q
-    auto box = [&](int32_t qq, int32_t& p0, int32_t& npt, int32_t& cx, int32_t& cy) {
-        p0 = 0;
-        npt = 0;
-        cx = cy = 0;
-        if (qq + grp < nleaf) {
-            const int32_t g = leaf0 + qq + grp;
-            p0 = box_pt0[g];
-            npt = box_pt1[g] - p0;
-            const uint64_t key = box_key[g];
-            cx = int32_t(compact_bits(key) * side);
-            cy = int32_t(compact_bits(key >> 1) * side);
+    const double2_t* sT = reinterpret_cast<const double2_t*>(STAGED ? sT_lds : leafT);
+    // the chunk whose loads are in flight
+    int32_t n_s, n_q, n_pts, n_loc;
+    bool n_last;
+    double n_f;
+    auto gather = [&](const Chunk& k) {
+        n_s = k.s;
+        n_q = k.q;
+        n_pts = k.pts;
+        n_last = k.last;
+        n_loc = 0;
+        n_f = 0.0;
+        if (k.s >= 0) {
+            n_loc = (k.xy.x & (sd - 1)) + sd * (k.xy.y & (sd - 1));   // the cell of its leaf: sides are powers of two
+            if (k.perm < k.nsrc) n_f = k.f[k.sorted != 0 ? k.s : k.perm];
         }
     };
-    int32_t p0, npt, cx, cy;
-    box(q, p0, npt, cx, cy);
+    gather(ahead);
+    ahead = fetch();
     __syncthreads();
-    for (; q < nleaf; q += stride) {
-        int32_t np0, nnpt, ncx, ncy;
-        box(q + stride, np0, nnpt, ncx, ncy);
-        int32_t nmax = npt;
+    double2_t a[R];
+    #pragma unroll
+    for (int r = 0; r < R; ++r) a[r] = double2_t{0.0, 0.0};
+    while (n_pts >= 0) {   // uniform
+        const int32_t loc = n_loc, npt = n_pts, cq = n_q;
+        const double f = n_f;
+        const bool last = n_last;
+        if (n_s >= 0) fs[n_s] = f;
+        gather(ahead);
+        ahead = fetch();
+        asm volatile("" ::: "memory");   // these loads go out here
         #pragma unroll
-        for (int o = kP2mGroup; o < 64; o <<= 1) nmax = max(nmax, __shfl_xor(nmax, o, 64));
-        double a[R];
-        #pragma unroll
-        for (int r = 0; r < R; ++r) a[r] = 0.0;
-        for (int32_t c0 = 0; c0 < nmax; c0 += kP2mGroup) {
-            int32_t loc = 0;
-            double f = 0.0;
-            if (c0 + l < npt) {
-                const int2 pt = pts[p0 + c0 + l];
-                loc = int32_t(int64_t(pt.x - cx) + side * int64_t(pt.y - cy));
-                f = gather_f(tab, single, perm_local, pinst, p0 + c0 + l, fs);
-            }
+        for (int k = 0; k < kP2mGroup; ++k) {
+            if (k >= npt) break;         // uniform
+            const int src = (lane & ~(kP2mGroup - 1)) | k;
+            const double2_t* row = sT + __shfl(loc, src, 64) * (P / 2) + l;
+            const double fk = __shfl(f, src, 64);
             #pragma unroll
-            for (int k = 0; k < kP2mGroup; ++k) {
-                const int src = (lane & ~(kP2mGroup - 1)) | k;
-                const int32_t lk = __shfl(loc, src, 64);
-                const double fk = __shfl(f, src, 64);
-                const double* row = sT + lk * P + l;
+            for (int r = 0; r < R; ++r) a[r] += row[kP2mGroup * r] * fk;
+        }
+        if (last) {
+            if (cq + grp < nleaf) {
+                double2_t* out = reinterpret_cast<double2_t*>(Q + size_t(leaf0 + cq + grp) * P) + l;
                 #pragma unroll
-                for (int r = 0; r < R; ++r) a[r] += row[kP2mGroup * r] * fk;
+                for (int r = 0; r < R; ++r) out[kP2mGroup * r] = a[r];
             }
-        }
-        if (q + grp < nleaf) {
-            double* out = Q + size_t(leaf0 + q + grp) * P + l;
             #pragma unroll
-            for (int r = 0; r < R; ++r) out[kP2mGroup * r] = a[r];
+            for (int r = 0; r < R; ++r) a[r] = double2_t{0.0, 0.0};
         }
-        p0 = np0;
-        npt = nnpt;
-        cx = ncx;
-        cy = ncy;
     }
 }
 
@@ -279,7 +335,6 @@ __device__ inline int32_t xcd_tile(int32_t b, int32_t G, int32_t step, int32_t n
 //
 // FP64: 16x16x4 instruction, step kk of row block m takes column g * 12 + kk in lane group
 // g = lane / 16; element i of lane (g, n) is row 16 m + g + 4 i, column n.
-__device__ inline int32_t uniform(int32_t v) { return __builtin_amdgcn_readfirstlane(v); }
 
 // Pointers into global memory by address space, so that loads through them are global (not
 // flat) loads: flat loads also count as LDS operations, and waiting for the LDS reads of a
@@ -2578,7 +2633,7 @@ P2mDevice p2m_device() {
         int cus = 0, lds = 0;
         if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, d) != hipSuccess ||
             hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, d) != hipSuccess ||
-            hipFuncSetAttribute(reinterpret_cast<const void*>(&k_p2m_lds<kRankPad>),
+            hipFuncSetAttribute(reinterpret_cast<const void*>(&k_p2m_lds<kRankPad, true>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess) {
             (void)hipGetLastError();
             return;   // the unstaged kernel serves every side
@@ -2588,35 +2643,44 @@ P2mDevice p2m_device() {
     return dev[d];
 }
 
+// blocks of `threads` for `waves` work items of a wave each, as many as fit on the device at once
+static unsigned persistent_grid(const void* fn, int threads, int64_t waves) {
+    const int64_t want = (waves + threads / 64 - 1) / (threads / 64);
+    const int cus = p2m_device().cus;
+    int per = 0;
+    int64_t g = std::min<int64_t>(want, 8192);
+    if (cus > 0 && hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, fn, threads, 0) == hipSuccess && per > 0)
+        g = std::min<int64_t>(want, int64_t(cus) * per);
+    else
+        (void)hipGetLastError();
+    return unsigned(std::max<int64_t>(g, 1));
+}
+
 void launch_p2m(int32_t leaf0, int32_t leaf1, const int32_t* box_pt0, const int32_t* box_pt1, const uint64_t* box_key,
                 int64_t side, const int32_t* pts, const ExecPtrs* tab, const ExecPtrs& single,
-                const int32_t* perm_local, const int32_t* pinst, double* fs, const double* leafT, double* Q,
-                double avg_pts, hipStream_t st) {
-    if (leaf1 <= leaf0) return;
+                const int32_t* perm_local, const int32_t* box_inst, double* fs, const double* leafT, double* Q,
+                hipStream_t st) {
+    const int32_t nleaf = leaf1 - leaf0;
+    if (nleaf <= 0) return;
+    const int2* p2 = reinterpret_cast<const int2*>(pts);
+    if (nleaf <= kP2mWaveLeaves) {
+        hipLaunchKernelGGL(k_p2m<kRankPad>, dim3(grid_for(nleaf, kWaves)), dim3(kBlock), 0, st, leaf0, leaf1, box_pt0,
+                           box_pt1, box_key, side, p2, tab, single, perm_local, box_inst, fs, leafT, Q);
+        return;
+    }
     const size_t lds = size_t(side * side) * kRankPad * sizeof(double);
     const P2mDevice dv = p2m_device();
     if (dv.cus > 0 && lds <= size_t(dv.lds)) {
-        const int per_cu = std::max(1, std::min(2, int(size_t(dv.lds) / lds)));
         const int64_t per_block = (kP2mThreads / 64) * kP2mLeaves;
-        const int64_t want = (int64_t(leaf1 - leaf0) + per_block - 1) / per_block;
-        const int64_t grid = std::max<int64_t>(1, std::min<int64_t>(want, int64_t(dv.cus) * per_cu));
-        hipLaunchKernelGGL(k_p2m_lds<kRankPad>, dim3(unsigned(grid)), dim3(kP2mThreads), lds, st, leaf0, leaf1,
-                           box_pt0, box_pt1, box_key, side, reinterpret_cast<const int2*>(pts), tab, single,
-                           perm_local, pinst, fs, leafT, Q);
+        const int64_t grid = std::min<int64_t>((int64_t(nleaf) + per_block - 1) / per_block, dv.cus);
+        hipLaunchKernelGGL((k_p2m_lds<kRankPad, true>), dim3(unsigned(grid)), dim3(kP2mThreads), lds, st, leaf0, leaf1,
+                           box_pt0, box_pt1, side, p2, tab, single, perm_local, box_inst, fs, leafT, Q);
         return;
     }
-    if (avg_pts <= double(kP2mSparsePoints)) {
-        // few points per leaf: eight leaves per wave, T_ofs rows from global memory
-        const int64_t per_block = (kP2mThreads / 64) * kP2mLeaves;
-        const int64_t grid = std::max<int64_t>(1, (int64_t(leaf1 - leaf0) + per_block - 1) / per_block);
-        hipLaunchKernelGGL((k_p2m_lds<kRankPad, false>), dim3(unsigned(grid)), dim3(kP2mThreads), 0, st, leaf0, leaf1,
-                           box_pt0, box_pt1, box_key, side, reinterpret_cast<const int2*>(pts), tab, single,
-                           perm_local, pinst, fs, leafT, Q);
-        return;
-    }
-    hipLaunchKernelGGL(k_p2m<kRankPad>, dim3(grid_for(leaf1 - leaf0, kWaves)), dim3(kBlock), 0, st, leaf0, leaf1,
-                       box_pt0, box_pt1, box_key, side, reinterpret_cast<const int2*>(pts), tab, single,
-                       perm_local, pinst, fs, leafT, Q);
+    const unsigned grid = persistent_grid(reinterpret_cast<const void*>(&k_p2m_lds<kRankPad, false>), kP2mFreeThreads,
+                                          (int64_t(nleaf) + kP2mLeaves - 1) / kP2mLeaves);
+    hipLaunchKernelGGL((k_p2m_lds<kRankPad, false>), dim3(grid), dim3(kP2mFreeThreads), 0, st, leaf0, leaf1, box_pt0,
+                       box_pt1, side, p2, tab, single, perm_local, box_inst, fs, leafT, Q);
 }
 
 void launch_m2m(const BoxTile* tiles, int32_t ntiles, const int32_t* box_child, const OpsPtrs* ops, double* Q,
@@ -2721,19 +2785,6 @@ void launch_m2l_bf16(const BoxTile* tiles, const int32_t* ntiles_dev, int32_t ma
     g = std::max<int64_t>(8, (g + 7) / 8 * 8);
     hipLaunchKernelGGL(k_m2l_bf16, dim3(static_cast<unsigned>(g)), dim3(kBf16Block), 0, st, tiles, ntiles_dev,
                        box_list, il27, ops, Qb, qs, zrow, U);
-}
-
-// blocks of `threads` for `waves` work items of a wave each, as many as fit on the device at once
-static unsigned persistent_grid(const void* fn, int threads, int64_t waves) {
-    const int64_t want = (waves + threads / 64 - 1) / (threads / 64);
-    const int cus = p2m_device().cus;
-    int per = 0;
-    int64_t g = std::min<int64_t>(want, 8192);
-    if (cus > 0 && hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, fn, threads, 0) == hipSuccess && per > 0)
-        g = std::min<int64_t>(want, int64_t(cus) * per);
-    else
-        (void)hipGetLastError();
-    return unsigned(std::max<int64_t>(g, 1));
 }
 
 // the same in whole rounds of the XCDs, for xcd_item
