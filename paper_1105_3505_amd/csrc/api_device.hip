@@ -394,7 +394,7 @@ struct lfmm_plan {
     ExecPtrs* d_exec = nullptr;
     BoxTile* m2m_tiles = nullptr;           // M2M tiles (pl->m2m ranges index them)
     int32_t* d_m2l_ntiles = nullptr;
-    int32_t *pts = nullptr, *perm = nullptr, *pinst = nullptr;
+    int32_t *pts = nullptr, *perm = nullptr;
     uint32_t* pkey = nullptr;
     double* fs = nullptr;
     uint64_t* box_key = nullptr;
@@ -780,7 +780,7 @@ void build_forest(lfmm_plan* pl, int32_t K, const InstanceInput* in, int32_t max
     pl->nout.assign(size_t(K), 0);
     // coordinate segments in point order: the sources of an instance, then its own targets
     std::vector<const int32_t*> seg_ptr;
-    std::vector<int32_t> seg_off{0};
+    std::vector<int32_t> seg_off{0}, seg_inst, first_seg;
     for (int32_t k = 0; k < K; ++k) {
         const InstanceInput& I = in[k];
         const int64_t nk = I.n_src + (I.tgt ? I.n_tgt : 0);
@@ -788,11 +788,14 @@ void build_forest(lfmm_plan* pl, int32_t K, const InstanceInput* in, int32_t max
         pl->nsrc[size_t(k)] = int32_t(I.n_src);
         pl->tgt0[size_t(k)] = I.tgt ? int32_t(I.n_src) : 0;
         pl->nout[size_t(k)] = I.tgt ? int32_t(I.n_tgt) : int32_t(I.n_src);
+        first_seg.push_back(int32_t(seg_ptr.size()));
         if (I.n_src > 0) {
+            seg_inst.push_back(k);
             seg_ptr.push_back(I.src);
             seg_off.push_back(seg_off.back() + int32_t(I.n_src));
         }
         if (I.tgt && I.n_tgt > 0) {
+            seg_inst.push_back(k);
             seg_ptr.push_back(I.tgt);
             seg_off.push_back(seg_off.back() + int32_t(I.n_tgt));
         }
@@ -806,8 +809,11 @@ void build_forest(lfmm_plan* pl, int32_t K, const InstanceInput* in, int32_t max
     std::vector<int32_t> chunk_first(static_cast<size_t>(K) + 1, 0);
     for (int32_t k = 0; k < K; ++k) {
         chunk_first[size_t(k)] = int32_t(chunks.size());
-        for (int32_t b = pl->pt_off[size_t(k)]; b < pl->pt_off[size_t(k) + 1]; b += kChunk)
-            chunks.push_back(Chunk{k, b, std::min(b + kChunk, pl->pt_off[size_t(k) + 1]), 0});
+        int32_t seg = first_seg[size_t(k)];
+        for (int32_t b = pl->pt_off[size_t(k)]; b < pl->pt_off[size_t(k) + 1]; b += kChunk) {
+            while (seg_off[size_t(seg) + 1] <= b) ++seg;
+            chunks.push_back(Chunk{k, b, std::min(b + kChunk, pl->pt_off[size_t(k) + 1]), seg});
+        }
     }
     chunk_first[size_t(K)] = int32_t(chunks.size());
     const int32_t nch = int32_t(chunks.size());
@@ -817,6 +823,7 @@ void build_forest(lfmm_plan* pl, int32_t K, const InstanceInput* in, int32_t max
     Arena tmp(&ctx->pool, sreg);
     tmp.reserve(size_t(nseg) * sizeof(void*));  // coordinate segments
     tmp.reserve(size_t(nseg + 1) * 4);          // segment offsets
+    tmp.reserve(size_t(nseg) * 4);              // and instances
     tmp.reserve(size_t(K + 1) * 4);             // pt_off
     tmp.reserve(size_t(nch) * sizeof(Chunk));
     tmp.reserve(size_t(K + 1) * 4);             // chunk_first
@@ -828,27 +835,29 @@ void build_forest(lfmm_plan* pl, int32_t K, const InstanceInput* in, int32_t max
     for (int32_t k = 0; k < K; ++k)
         max_chunks = std::max(max_chunks, chunk_first[size_t(k) + 1] - chunk_first[size_t(k)]);
     const int32_t stat_copies = std::min(kLevelStatsCopies, std::max(1, max_chunks / 32));
-    tmp.reserve(size_t(stat_copies) * K * (kMaxLevels + 3) * 4 + 4);   // level histograms, look-ahead maxima, counter
+    // level histograms, look-ahead maxima, counters
+    const int32_t ndone = kDoneStride * (1 + level_stats_counters(nch));
+    tmp.reserve((size_t(stat_copies) * K * (kMaxLevels + 3) + ndone) * 4);
     tmp.reserve(4);                             // deepest root box
-    tmp.reserve(nseg > 1 ? size_t(n) * 8 : 0);  // concatenated points
     tmp.reserve(size_t(n) * 8);                 // keys
     tmp.reserve(size_t(n) * 8);                 // keys_tmp
     tmp.reserve(size_t(n) * 4);                 // vals
     tmp.reserve(size_t(n) * 4);                 // vals_tmp
     tmp.reserve(size_t(n));                     // cl
     tmp.reserve(radix_scratch_bytes(n));
-    tmp.reserve(scan_scratch_bytes(n, 1));
+    tmp.reserve(leaf_starts_scratch_bytes(nch));
     tmp.allocate();
     SyncOnUnwind unwind_tmp;
     const int32_t** d_xytab = tmp.take<const int32_t*>(nseg);
     int32_t* d_segoff = tmp.take<int32_t>(nseg + 1);
+    int32_t* d_seginst = tmp.take<int32_t>(nseg);
     int32_t* d_ptoff = tmp.take<int32_t>(K + 1);
     Chunk* d_chunks = tmp.take<Chunk>(nch);
     int32_t* d_chfirst = tmp.take<int32_t>(K + 1);
     int32_t* d_part = tmp.take<int32_t>(size_t(nch) * 4);
     InstInfo* d_inst0 = tmp.take<InstInfo>(K);
     const int32_t nstats = stat_copies * K * (kMaxLevels + 3);
-    int32_t* d_stats = tmp.take<int32_t>(size_t(nstats) + 1);   // zeroed by the key kernel
+    int32_t* d_stats = tmp.take<int32_t>(size_t(nstats) + ndone);   // zeroed by the key kernel
     int32_t* d_dmax = tmp.take<int32_t>(1);
     // results of the two read-backs: pinned host memory that the kernels write (the root boxes
     // by the kernel itself, the level statistics by one copy); in the static workspace, device
@@ -868,27 +877,23 @@ void build_forest(lfmm_plan* pl, int32_t K, const InstanceInput* in, int32_t max
     std::vector<int32_t> rb_host(sreg ? rb_words : 0);
     int32_t* bb = rb;                      // [K][4] root boxes
     int32_t* stats = rb + size_t(K) * 4;   // [K][34] histograms, then [K] maxima
-    int32_t* d_xyc = (nseg > 1) ? tmp.take<int32_t>(size_t(n) * 2) : nullptr;
     uint64_t* keys = tmp.take<uint64_t>(n);
     uint64_t* keys_tmp = tmp.take<uint64_t>(n);
     uint32_t* vals = tmp.take<uint32_t>(n);
     uint32_t* vals_tmp = tmp.take<uint32_t>(n);
     int8_t* cl = tmp.take<int8_t>(n);
     void* rscr = tmp.take<char>(radix_scratch_bytes(n));
-    void* sscr = tmp.take<char>(scan_scratch_bytes(n, 1));
+    void* sscr = tmp.take<char>(leaf_starts_scratch_bytes(nch));
 
     Stager stage_a(ctx, sreg != nullptr);
     stage_a.add(d_xytab, seg_ptr);
     stage_a.add(d_segoff, seg_off);
+    stage_a.add(d_seginst, seg_inst);
     stage_a.add(d_ptoff, pl->pt_off);
     stage_a.add(d_chunks, chunks);
     stage_a.add(d_chfirst, chunk_first);
     stage_a.flush(st);
-    const int32_t* xy = seg_ptr[0];
-    if (nseg > 1) {
-        launch_concat(nseg, d_xytab, d_segoff, n, d_xyc, st);
-        xy = d_xyc;
-    }
+    const PointSegs segs{seg_ptr[0], d_xytab, d_segoff, d_seginst, nseg};
 
     // N_leaf of every instance: the caller's, else the options', else the tuned value for
     // the instance's size and density (known after the root boxes), else the default
@@ -899,7 +904,7 @@ void build_forest(lfmm_plan* pl, int32_t K, const InstanceInput* in, int32_t max
     }
 
     // ---- root boxes ----------------------------------------------------------------------
-    launch_bbox_chunks(xy, d_chunks, nch, d_part, d_dmax, st);
+    launch_bbox_chunks(segs, d_chunks, nch, d_part, d_dmax, st);
     // root boxes straight to pinned host memory, and the instance table of the next kernels
     // (N_leaf too when there is one for all) straight to the device
     launch_bbox_final(d_part, d_chfirst, d_ptoff, K, std::max(ml_all, 0), bb, d_inst0, d_dmax, st);
@@ -909,7 +914,7 @@ void build_forest(lfmm_plan* pl, int32_t K, const InstanceInput* in, int32_t max
     // host reads the root boxes: the keys need only the device's instance table, and distinct
     // points need at least 16 key bits once there are 2^16 of them (a pass over digits that
     // are zero everywhere would change nothing either).
-    launch_keys(xy, d_ptoff, K, d_inst0, d_dmax, n, keys, vals, d_stats, nstats + 1, n > 1 ? rscr : nullptr, st);
+    launch_keys(segs, K, d_inst0, d_dmax, n, keys, vals, d_stats, nstats + ndone, n > 1 ? rscr : nullptr, st);
     const int early_passes = (n >= (int64_t(1) << 16)) ? 2 : 0;
     int which = radix_sort_passes(keys, vals, keys_tmp, vals_tmp, n, 0, early_passes, true, rscr, st);
     // point storage, taken while the device works
@@ -917,13 +922,11 @@ void build_forest(lfmm_plan* pl, int32_t K, const InstanceInput* in, int32_t max
     mp.set_pool(&ctx->pool, sreg);
     mp.reserve(size_t(n) * 8);                  // pts
     mp.reserve(size_t(n) * 4);                  // perm
-    mp.reserve(size_t(n) * 4);                  // pinst
     mp.reserve(size_t(n) * 4);                  // pkey
     mp.reserve(size_t(n) * 8);                  // fs
     mp.allocate();
     pl->pts = mp.take<int32_t>(size_t(n) * 2);
     pl->perm = mp.take<int32_t>(n);
-    pl->pinst = mp.take<int32_t>(n);
     pl->pkey = mp.take<uint32_t>(n);
     pl->fs = mp.take<double>(n);
     if (sreg) {
@@ -973,7 +976,7 @@ void build_forest(lfmm_plan* pl, int32_t K, const InstanceInput* in, int32_t max
     uint32_t* svals = which ? vals_tmp : vals;
 
     // ---- leaf levels and box counts ---------------------------------------------------------
-    launch_level_stats(skeys, svals, d_chunks, nch, d_inst0, Dmax, K, pl->pts, pl->perm, pl->pinst, cl, d_stats,
+    launch_level_stats(skeys, svals, d_chunks, nch, d_inst0, Dmax, K, pl->pts, pl->perm, cl, d_stats,
                        stat_copies, d_stats + nstats, stats, st);
     if (sreg) {
         LFMM_HIP(hipMemcpyAsync(rb_host.data() + size_t(K) * 4, stats, (rb_words - size_t(K) * 4) * 4,
@@ -1316,8 +1319,8 @@ void build_forest(lfmm_plan* pl, int32_t K, const InstanceInput* in, int32_t max
     }
 
     // leaves (and the window keys of the points) straight from the scan of the leaf starts
-    scan_leaf_starts(cl, pl->pinst, pl->d_inst, n, skeys, Dmax, pl->pts, pl->pkey, leaf_pt0, leaf_key, leaf_cl,
-                     leaf_inst, sscr, st);
+    launch_leaf_starts(d_chunks, nch, cl, pl->d_inst, skeys, Dmax, pl->pts, pl->pkey, leaf_pt0, leaf_key, leaf_cl,
+                       leaf_inst, sscr, st);
     if (Lmax > 0) scan_level_starts(leaf_cl, leaf_inst, pl->d_inst, nl, Lmax, lscan, lscr, st);
     launch_build_boxes(lscan, leaf_cl, leaf_pt0, leaf_key, leaf_inst, pl->d_inst, nl, Lmax, pl->box_key, pl->box_pt0,
                        pl->box_parent, pl->box_child, pl->box_inst, pl->box_lev, st);
@@ -2195,8 +2198,8 @@ lfmm_status lfmm_plan_footprint_bytes(const lfmm_ctx* ctx, int64_t n_src, int64_
     const size_t nl = size_t(std::min<int64_t>(n, int64_t(nb)));
     const size_t P = kRankPad, al = 256;
     auto block = [](size_t b) { return 2 * b + (size_t(1) << 16); };
-    // points: coordinates, permutation, instance, window key, loads
-    const size_t pts = size_t(n) * 28 + 5 * al;
+    // points: coordinates, permutation, window key, loads
+    const size_t pts = size_t(n) * 24 + 4 * al;
     // boxes: key, four int32 fields and a pad, level, children, neighbour and interaction lists,
     // class lists (M2L and L2L groups, four slots per box each), tiles, Q and U with their zero
     // rows, near-field groups and their 16 entries
@@ -2209,12 +2212,12 @@ lfmm_status lfmm_plan_footprint_bytes(const lfmm_ctx* ctx, int64_t n_src, int64_
                        size_t(D / kSubLevels + 1) * kSubOwners * sizeof(SubTree) + 15 * al + mixed;
     const size_t small = sizeof(InstInfo) + 64 * sizeof(OpsPtrs) + 16 + 4 * size_t(D + 2) * sizeof(BoxGroup) +
                          (nb / 64 + size_t(D + 2)) * sizeof(BoxTile) + sizeof(ExecPtrs) + 16 * al;
-    // construction temporaries: concatenated points, keys and indices (two copies), common
+    // construction temporaries: keys and indices (two copies), common
     // levels, sort and scan scratch; then per leaf: first point, key, level, instance and one
     // scan row per level; per box: class scans
     const size_t chunks = size_t(n) / kChunk + 1;   // each: its range and box partials
-    const size_t tmp = size_t(n) * (8 + 16 + 8 + 1) + radix_scratch_bytes(n) + scan_scratch_bytes(n, 1) +
-                       chunks * 2 * 16 + (kMaxLevels + 10) * 4 * 4 * kLevelStatsCopies + 24 * al;
+    const size_t tmp = size_t(n) * (16 + 8 + 1) + radix_scratch_bytes(n) + leaf_starts_scratch_bytes(int32_t(chunks)) +
+                       chunks * 2 * 16 + (kMaxLevels + 10) * 4 * 4 * kLevelStatsCopies + kDoneStride * 65 * 4 + 25 * al;
     const size_t rows = size_t(std::max(D, 1));
     const size_t tmp2 = nl * (4 + 8 + 1 + 4 + 4 * rows) + scan_scratch_bytes(int64_t(nl), int(rows)) + nb * 16 + 64 +
                         scan_scratch_bytes(int64_t(nb), 4) + 10 * al;

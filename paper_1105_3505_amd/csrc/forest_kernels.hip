@@ -69,13 +69,6 @@ inline unsigned grid_for(int64_t n, int per_block = kBlock) {
     return unsigned(g < 1 ? 1 : g);
 }
 
-__global__ void k_concat(int32_t K, const int2* const* xy_tab, const int32_t* pt_off, int64_t n, int2* xyc) {
-    const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const int32_t k = find_inst(pt_off, K, i);
-    xyc[i] = xy_tab[k][i - pt_off[k]];
-}
-
 // v = {min x, min y, max x, max y} over the block: wave shuffles, then the four waves
 // through LDS; thread 0 gets the result in v and true
 __device__ inline bool block_minmax4(int v[4]) {
@@ -100,8 +93,9 @@ __device__ inline bool block_minmax4(int v[4]) {
     return true;
 }
 
-// Box of the points begin .. end - 1 of xy into part[4 * blockIdx.x ..]; at most kChunk points, one block.
-__device__ inline void chunk_box(const int2* xy, int32_t begin, int32_t end, int32_t* part) {
+// Box of the points load(begin) .. load(end - 1) into part[4 * blockIdx.x ..]; at most kChunk points, one block.
+template <class Load>
+__device__ inline void chunk_box(Load load, int32_t begin, int32_t end, int32_t* part) {
     int v[4] = {INT_MAX, INT_MAX, INT_MIN, INT_MIN};
     // all of the thread's points loaded before any is used (one wait, not one per point)
     constexpr int kIt = kChunk / kBlock;
@@ -109,7 +103,7 @@ __device__ inline void chunk_box(const int2* xy, int32_t begin, int32_t end, int
     #pragma unroll
     for (int it = 0; it < kIt; ++it) {
         const int32_t i = begin + it * kBlock + int32_t(threadIdx.x);
-        q[it] = i < end ? xy[i] : xy[begin];   // a chunk's first point stands in past its end
+        q[it] = load(i < end ? i : begin);   // a chunk's first point stands in past its end
     }
     #pragma unroll
     for (int it = 0; it < kIt; ++it) {
@@ -136,7 +130,8 @@ __device__ inline bool parts_box(const int32_t* part, int32_t first, int32_t las
 // 2.5 ms, the atomics of each queuing on one line.
 __global__ void k_extent_chunks(const int2* const* xy_tab, const Chunk* chunks, int32_t* part) {
     const Chunk c = chunks[blockIdx.x];
-    chunk_box(xy_tab[c.inst], c.begin, c.end, part);
+    const int2* xy = xy_tab[c.inst];
+    chunk_box([&](int32_t i) { return xy[i]; }, c.begin, c.end, part);
 }
 
 __global__ void k_extent_final(const int32_t* part, const int32_t* chunk_first, int32_t* box) {
@@ -146,10 +141,19 @@ __global__ void k_extent_final(const int32_t* part, const int32_t* chunk_first, 
         for (int q = 0; q < 4; ++q) box[4 * size_t(k) + q] = v[q];
 }
 
-__global__ void k_bbox_chunks(const int2* xy, const Chunk* chunks, int32_t* part, int32_t* dmax) {
+__global__ void k_bbox_chunks(PointSegs segs, const Chunk* chunks, int32_t* part, int32_t* dmax) {
     if (blockIdx.x == 0 && threadIdx.x == 0) *dmax = 0;   // the deepest root box, raised by k_bbox_final
     const Chunk c = chunks[blockIdx.x];
-    chunk_box(xy, c.begin, c.end, part);
+    if (segs.n == 1) {
+        const int2* xy = reinterpret_cast<const int2*>(segs.one);
+        chunk_box([&](int32_t i) { return xy[i]; }, c.begin, c.end, part);
+        return;
+    }
+    // the segment of the chunk's first point and the one after it (an instance's sources, then its targets)
+    const int32_t off = segs.off[c.seg], next = segs.off[c.seg + 1];
+    const int2* a = reinterpret_cast<const int2*>(segs.ptr[c.seg]);
+    const int2* b = next < c.end ? reinterpret_cast<const int2*>(segs.ptr[c.seg + 1]) : nullptr;
+    chunk_box([&](int32_t i) { return i < next ? a[i - off] : b[i - next]; }, c.begin, c.end, part);
 }
 
 // One block per instance: its chunks' partial boxes reduced by the block, written to bbox
@@ -200,27 +204,49 @@ __device__ inline void rs_count_tile(const uint32_t (&dg)[kRsItems], uint32_t* C
 
 // Morton key (instance above it) and index of every point, one tile of kRsTile points per
 // block, with the tile's counts of the lowest digit when C is given; also zeroes the nzero
-// counters that the level statistics accumulate into.
-__global__ void k_keys(const int2* xy, const int32_t* pt_off, int32_t K, const InstInfo* inst, const int32_t* dmax,
+// counters that the level statistics accumulate into.  The points are read from the callers' arrays
+// (segments), found once per tile and by bisection among the tile's segments if there are several: a
+// copy of all points one after another, with a bisection over all segments for each, took another 130 us of
+// a plan of 512 trees (8.9e6 points; 90 us here).
+__global__ void k_keys(PointSegs segs, int32_t K, const InstInfo* inst, const int32_t* dmax,
                        int64_t n, uint64_t* keys, uint32_t* vals, int32_t* zero, int32_t nzero, uint32_t* C,
                        int64_t ntiles, bool digit_major) {
     const int64_t g = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     const int Dmax = (K > 1) ? *dmax : 0;   // instance bits sit above the deepest Morton code
     for (int64_t z = g; z < nzero; z += int64_t(gridDim.x) * blockDim.x) zero[z] = 0;
+    const int64_t base = int64_t(blockIdx.x) * kRsTile;
+    int32_t lo = 0, hi = 0;   // segments of the tile's first and last point
+    if (segs.n > 1) {
+        lo = find_inst(segs.off, segs.n, base);
+        hi = find_inst(segs.off, segs.n, min(base + kRsTile, n) - 1);
+    }
+    const int2* one = reinterpret_cast<const int2*>(segs.n > 1 ? segs.ptr[lo] : segs.one);
+    const int64_t off = segs.n > 1 ? segs.off[lo] : 0;
     // all loads of the tile first (few waves per SIMD: the latency is hidden by loads in flight)
     int2 pt[kRsItems];
+    int32_t ki[kRsItems];   // instances
     #pragma unroll
     for (int it = 0; it < kRsItems; ++it) {
-        const int64_t i = int64_t(blockIdx.x) * kRsTile + int64_t(it) * kBlock + threadIdx.x;
-        pt[it] = i < n ? xy[i] : make_int2(0, 0);
+        const int64_t i = base + int64_t(it) * kBlock + threadIdx.x;
+        pt[it] = make_int2(0, 0);
+        ki[it] = 0;
+        if (i >= n) continue;
+        if (lo == hi) {
+            pt[it] = one[i - off];
+            if (K > 1) ki[it] = segs.inst[lo];
+        } else {
+            const int32_t sg = lo + find_inst(segs.off + lo, hi - lo + 1, i);
+            pt[it] = reinterpret_cast<const int2*>(segs.ptr[sg])[i - segs.off[sg]];
+            ki[it] = segs.inst[sg];
+        }
     }
     uint32_t dg[kRsItems];
     #pragma unroll
     for (int it = 0; it < kRsItems; ++it) {
-        const int64_t i = int64_t(blockIdx.x) * kRsTile + int64_t(it) * kBlock + threadIdx.x;
+        const int64_t i = base + int64_t(it) * kBlock + threadIdx.x;
         dg[it] = 256u;
         if (i >= n) continue;
-        const int32_t k = (K > 1) ? find_inst(pt_off, K, i) : 0;
+        const int32_t k = ki[it];
         const int2 p = pt[it];
         const uint32_t x = uint32_t(int64_t(p.x) - inst[k].ox), y = uint32_t(int64_t(p.y) - inst[k].oy);
         const uint64_t m = spread_bits(x) | (spread_bits(y) << 1);
@@ -233,20 +259,22 @@ __global__ void k_keys(const int2* xy, const int32_t* pt_off, int32_t K, const I
 }
 
 // One block per chunk of one instance.  Per sorted point: its coordinates in the instance's
-// root box decoded from the Morton key (no gather of the input), its instance-local index
-// and instance; the number of levels its box shares with the previous point's (-1 at the
+// root box decoded from the Morton key (no gather of the input) and its instance-local
+// index; the number of levels its box shares with the previous point's (-1 at the
 // instance's first point), a histogram of those counts (equal values of a wave are counted
 // with ballots, one LDS add per distinct value), and the levels shared with the point N_leaf
 // positions ahead (a box of that level would hold more than N_leaf points).  The block adds
 // its non-zero counts and its maximum to the instance's totals with device-scope atomics
 // (hist: [K][kMaxLevels + 2], then maxc: [K]; zero before the launch), and the last block
-// to finish (counter *done, zero before the launch) copies the totals to host memory.  Each
+// to finish (counters done, zero before the launch) copies the totals to host memory; with many
+// blocks, the last of every 16 or more with a counter of their own counts in the first (not all of them
+// on one line).  Each
 // thread waits for its own atomics (vector memory count zero) before the barrier that
 // precedes the counter, and the totals are read back with atomics, so no device-wide fence
 // is needed.
 __global__ void k_level_stats(const uint64_t* keys, const uint32_t* vals, const Chunk* chunks,
                               const InstInfo* inst, int Dmax, int32_t K, int2* pts, int32_t* perm_local,
-                              int32_t* pinst, int8_t* cl, int32_t* hist, int32_t R, int32_t* done,
+                              int8_t* cl, int32_t* hist, int32_t R, int32_t* done, int32_t ndone,
                               int32_t* host_out) {
     constexpr int NH = kMaxLevels + 2;
     __shared__ int32_t h[NH];
@@ -282,7 +310,6 @@ __global__ void k_level_stats(const uint64_t* keys, const uint32_t* vals, const 
             const uint64_t m = kk[it] & morton_mask(Dmax);
             pts[s] = make_int2(int32_t(compact_bits(m)), int32_t(compact_bits(m >> 1)));
             perm_local[s] = int32_t(ix[it]) - I.pt0;
-            pinst[s] = c.inst;
             v = (s == I.pt0) ? -1 : common_levels(kk[it], kp[it], Dmax) - shift;
             cl[s] = int8_t(v);
             if (s + nleaf < I.pt1) mc = max(mc, common_levels(kk[it], ka[it], Dmax) - shift);
@@ -308,7 +335,14 @@ __global__ void k_level_stats(const uint64_t* keys, const uint32_t* vals, const 
     if (threadIdx.x < NH && h[threadIdx.x] != 0) atomicAdd(&hc[size_t(c.inst) * NH + threadIdx.x], h[threadIdx.x]);
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
-    if (threadIdx.x == 0) is_last = atomicAdd(done, 1) == int(gridDim.x) - 1;
+    if (threadIdx.x == 0) {
+        if (ndone == 0) {
+            is_last = atomicAdd(done, 1) == int(gridDim.x) - 1;
+        } else {
+            const int32_t q = int32_t(blockIdx.x) % ndone, size = (int32_t(gridDim.x) - q + ndone - 1) / ndone;
+            is_last = atomicAdd(&done[kDoneStride * (1 + q)], 1) == size - 1 && atomicAdd(done, 1) == ndone - 1;
+        }
+    }
     __syncthreads();
     if (is_last)
         for (size_t i = threadIdx.x; i < per; i += blockDim.x) {
@@ -1018,12 +1052,6 @@ struct RowsArray {   // values from an array, row stride n
     int64_t n;
     __device__ int32_t operator()(int r, int64_t i) const { return in[size_t(r) * n + i]; }
 };
-struct LeafStart {   // 1 where a leaf of its instance starts at Morton-ordered point i
-    const int8_t* cl;
-    const int32_t* pinst;
-    const InstInfo* inst;
-    __device__ int32_t operator()(int, int64_t i) const { return cl[i] < inst[pinst[i]].L ? 1 : 0; }
-};
 struct LevelStart {   // row lev: 1 where leaf b starts a box of level lev < L of its instance
     const int8_t* leaf_cl;
     const int32_t* leaf_inst;
@@ -1091,38 +1119,84 @@ struct StoreSink {
     int64_t n;
     __device__ void operator()(int row, int64_t i, int32_t x, int32_t) const { out[size_t(row) * n + i] = x; }
 };
-// Leaf starts: the point that starts leaf x writes that leaf's first point, key, level count
-// and instance; every point of a leaf side of at most 16 also gets its window key
-// K = 8 (y W + x) mod 2^32 (W = 4 side - 1) for the near field.
-struct LeafSink {
-    const uint64_t* keys;
-    const int8_t* cl;
-    const int32_t* pinst;
-    const InstInfo* inst;
-    int Dmax;
-    const int2* pts;
-    uint32_t* pkey;
-    int32_t* leaf_pt0;
-    uint64_t* leaf_key;
-    int8_t* leaf_cl;
-    int32_t* leaf_inst;
-    __device__ void operator()(int, int64_t s, int32_t r, int32_t flag) const {
-        const int32_t k = pinst[s];
-        const InstInfo& I = inst[k];
-        if (flag) {
-            leaf_pt0[r] = int32_t(s);
-            leaf_key[r] = (keys[s] & morton_mask(Dmax)) >> (2 * (I.D - I.L));
-            leaf_cl[r] = cl[s];
-            leaf_inst[r] = k;
-        }
-        const int64_t side = int64_t(1) << (I.D - I.L);
-        if (side <= 16) {
-            const int2 p = pts[s];
-            const uint32_t W = uint32_t(4 * side - 1);
-            pkey[s] = 8u * (uint32_t(p.y) * W + uint32_t(p.x));   // modulo 2^32 on purpose
-        }
+// Leaf starts, a block per chunk of one instance: counts of a chunk, then the leaves' numbers and what
+// they hold.  The point that starts leaf x writes that leaf's first point, key, level count and
+// instance; every point of a leaf side of at most 16 also gets its window key K = 8 (y W + x) mod 2^32
+// (W = 4 side - 1) for the near field.  Points are visited a row of the block at a time, so that every
+// access is to consecutive words (eight consecutive points per thread of a scan over all points, with the
+// instance of each: 37 + 279 us for 8.9e6 points of 512 trees, now 15 + 68).
+__global__ void k_leaf_count(const Chunk* chunks, const int8_t* cl, const InstInfo* inst, int32_t* count) {
+    const Chunk c = chunks[blockIdx.x];
+    const int L = inst[c.inst].L;
+    int32_t v = 0;
+    #pragma unroll
+    for (int it = 0; it < kChunk / kBlock; ++it) {
+        const int32_t s = c.begin + it * kBlock + int32_t(threadIdx.x);
+        v += s < c.end && cl[s] < L ? 1 : 0;
     }
-};
+    v = block_sum(v);
+    if (threadIdx.x == 0) count[blockIdx.x] = v;
+}
+
+// before: count of the chunks before each, or null (added up here)
+__global__ void k_leaf_starts(const Chunk* chunks, const int32_t* count, const int32_t* before, const int8_t* cl,
+                              const InstInfo* inst, const uint64_t* keys, int Dmax, const int2* pts, uint32_t* pkey,
+                              int32_t* leaf_pt0, uint64_t* leaf_key, int8_t* leaf_cl, int32_t* leaf_inst) {
+    constexpr int kIt = kChunk / kBlock, kW = kBlock / 64;
+    __shared__ int32_t wcnt[kIt * kW];
+    const Chunk c = chunks[blockIdx.x];
+    const InstInfo& I = inst[c.inst];
+    const int L = I.L, shift = 2 * (I.D - I.L);
+    const uint32_t side = 1u << min(I.D - I.L, 31);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int8_t v[kIt];
+    int2 p[kIt];
+    #pragma unroll
+    for (int it = 0; it < kIt; ++it) {
+        const int32_t s = c.begin + it * kBlock + int32_t(threadIdx.x);
+        v[it] = s < c.end ? cl[s] : int8_t(127);
+        p[it] = side <= 16 && s < c.end ? pts[s] : make_int2(0, 0);
+    }
+    int32_t pre = 0;
+    if (before) {
+        pre = before[blockIdx.x];
+    } else {
+        for (int t = threadIdx.x; t < int(blockIdx.x); t += kBlock) pre += count[t];
+        pre = block_sum(pre);
+    }
+    int32_t rank[kIt];   // among the row's of this wave
+    #pragma unroll
+    for (int it = 0; it < kIt; ++it) {
+        const uint64_t m = __ballot(v[it] < L);
+        rank[it] = __popcll(m & ((1ull << lane) - 1ull));
+        if (lane == 0) wcnt[it * kW + wave] = __popcll(m);
+    }
+    __syncthreads();
+    if (threadIdx.x < 64) {
+        const int32_t x = lane < kIt * kW ? wcnt[lane] : 0;
+        int32_t y = x;
+        #pragma unroll
+        for (int o = 1; o < kIt * kW; o <<= 1) {
+            const int32_t z = __shfl_up(y, o, 64);
+            if (lane >= o) y += z;
+        }
+        if (lane < kIt * kW) wcnt[lane] = y - x;
+    }
+    __syncthreads();
+    const uint32_t W = 4 * side - 1;
+    #pragma unroll
+    for (int it = 0; it < kIt; ++it) {
+        const int32_t s = c.begin + it * kBlock + int32_t(threadIdx.x);
+        if (v[it] < L) {
+            const int32_t r = pre + wcnt[it * kW + wave] + rank[it];
+            leaf_pt0[r] = s;
+            leaf_key[r] = (keys[s] & morton_mask(Dmax)) >> shift;
+            leaf_cl[r] = v[it];
+            leaf_inst[r] = c.inst;
+        }
+        if (side <= 16 && s < c.end) pkey[s] = 8u * (uint32_t(p[it].y) * W + uint32_t(p[it].x));   // modulo 2^32 on purpose
+    }
+}
 
 template <class Src, class Sink>
 __global__ void k_scan_apply(Src src, Sink sink, int64_t n, const int32_t* bsum, int nblk, int32_t* totals) {
@@ -1176,13 +1250,22 @@ void scan_rows(const int32_t* in, int32_t* out, int64_t n, int rows, int32_t* to
     scan_source(RowsArray{in, n}, out, n, rows, totals, scratch, st);
 }
 
-void scan_leaf_starts(const int8_t* cl, const int32_t* pinst, const InstInfo* inst, int64_t n, const uint64_t* keys,
-                      int Dmax, const int32_t* pts, uint32_t* pkey, int32_t* leaf_pt0, uint64_t* leaf_key,
-                      int8_t* leaf_cl, int32_t* leaf_inst, void* scratch, hipStream_t st) {
-    scan_sink(LeafStart{cl, pinst, inst},
-              LeafSink{keys, cl, pinst, inst, Dmax, reinterpret_cast<const int2*>(pts), pkey, leaf_pt0, leaf_key,
-                       leaf_cl, leaf_inst},
-              n, 1, nullptr, scratch, st);
+size_t leaf_starts_scratch_bytes(int32_t nchunks) {
+    return size_t(nchunks) * 8 + scan_scratch_bytes(nchunks, 1);
+}
+
+void launch_leaf_starts(const Chunk* chunks, int32_t nchunks, const int8_t* cl, const InstInfo* inst,
+                        const uint64_t* keys, int Dmax, const int32_t* pts, uint32_t* pkey, int32_t* leaf_pt0,
+                        uint64_t* leaf_key, int8_t* leaf_cl, int32_t* leaf_inst, void* scratch, hipStream_t st) {
+    int32_t* count = static_cast<int32_t*>(scratch);
+    int32_t* before = nullptr;
+    hipLaunchKernelGGL(k_leaf_count, dim3(unsigned(nchunks)), dim3(kBlock), 0, st, chunks, cl, inst, count);
+    if (nchunks > 8192) {   // a block would read more than 32 counts a thread
+        before = count + nchunks;
+        scan_rows(count, before, nchunks, 1, nullptr, before + nchunks, st);
+    }
+    hipLaunchKernelGGL(k_leaf_starts, dim3(unsigned(nchunks)), dim3(kBlock), 0, st, chunks, count, before, cl, inst, keys,
+                       Dmax, reinterpret_cast<const int2*>(pts), pkey, leaf_pt0, leaf_key, leaf_cl, leaf_inst);
 }
 
 void scan_level_starts(const int8_t* leaf_cl, const int32_t* leaf_inst, const InstInfo* inst, int64_t nleaf,
@@ -1286,16 +1369,9 @@ void launch_extents(int32_t K, const int32_t* const* xy_tab, const Chunk* chunks
     hipLaunchKernelGGL(k_extent_final, dim3(unsigned(K)), dim3(kBlock), 0, st, part, chunk_first, box);
 }
 
-void launch_concat(int32_t K, const int32_t* const* xy_tab, const int32_t* pt_off, int64_t n, int32_t* xyc,
-                   hipStream_t st) {
-    hipLaunchKernelGGL(k_concat, dim3(grid_for(n)), dim3(kBlock), 0, st, K,
-                       reinterpret_cast<const int2* const*>(xy_tab), pt_off, n, reinterpret_cast<int2*>(xyc));
-}
-
-void launch_bbox_chunks(const int32_t* xy, const Chunk* chunks, int32_t nchunks, int32_t* part, int32_t* dmax,
+void launch_bbox_chunks(const PointSegs& segs, const Chunk* chunks, int32_t nchunks, int32_t* part, int32_t* dmax,
                         hipStream_t st) {
-    hipLaunchKernelGGL(k_bbox_chunks, dim3(unsigned(nchunks)), dim3(kBlock), 0, st, reinterpret_cast<const int2*>(xy),
-                       chunks, part, dmax);
+    hipLaunchKernelGGL(k_bbox_chunks, dim3(unsigned(nchunks)), dim3(kBlock), 0, st, segs, chunks, part, dmax);
 }
 
 void launch_bbox_final(const int32_t* part, const int32_t* chunk_first, const int32_t* pt_off, int32_t K,
@@ -1304,22 +1380,25 @@ void launch_bbox_final(const int32_t* part, const int32_t* chunk_first, const in
                        max_leaf, bbox, inst, dmax);
 }
 
-void launch_keys(const int32_t* xy, const int32_t* pt_off, int32_t K, const InstInfo* inst, const int32_t* dmax,
+void launch_keys(const PointSegs& segs, int32_t K, const InstInfo* inst, const int32_t* dmax,
                  int64_t n, uint64_t* keys, uint32_t* vals, int32_t* zero, int32_t nzero, void* radix_scratch,
                  hipStream_t st) {
     const int64_t nt = radix_tiles(n);
-    hipLaunchKernelGGL(k_keys, dim3(unsigned(nt)), dim3(kBlock), 0, st, reinterpret_cast<const int2*>(xy), pt_off, K,
+    hipLaunchKernelGGL(k_keys, dim3(unsigned(nt)), dim3(kBlock), 0, st, segs, K,
                        inst, dmax, n, keys, vals, zero, nzero,
                        radix_scratch ? radix_counts(radix_scratch) : static_cast<uint32_t*>(nullptr), nt,
                        radix_digit_major(n));
 }
 
+int32_t level_stats_counters(int32_t nchunks) { return nchunks < 64 ? 0 : std::min(nchunks / 16, 64); }
+
 void launch_level_stats(const uint64_t* keys, const uint32_t* vals, const Chunk* chunks, int32_t nchunks,
-                        const InstInfo* inst, int Dmax, int32_t K, int32_t* pts, int32_t* perm_local, int32_t* pinst,
+                        const InstInfo* inst, int Dmax, int32_t K, int32_t* pts, int32_t* perm_local,
                         int8_t* cl, int32_t* hist, int32_t copies, int32_t* done, int32_t* host_out,
                         hipStream_t st) {
     hipLaunchKernelGGL(k_level_stats, dim3(unsigned(nchunks)), dim3(kBlock), 0, st, keys, vals, chunks, inst, Dmax, K,
-                       reinterpret_cast<int2*>(pts), perm_local, pinst, cl, hist, std::max(copies, 1), done,
+                       reinterpret_cast<int2*>(pts), perm_local, cl, hist, std::max(copies, 1), done,
+                       level_stats_counters(nchunks),
                        host_out);
 }
 

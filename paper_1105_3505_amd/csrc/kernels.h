@@ -189,18 +189,26 @@ size_t scan_scratch_bytes(int64_t n, int rows);
 void scan_rows(const int32_t* in, int32_t* out, int64_t n, int rows, int32_t* totals,
                void* scratch, hipStream_t st);
 
-struct Chunk { int32_t inst, begin, end, pad; };   // <= kChunk points of one instance
+// <= kChunk points of one instance; seg: the segment of the first of them
+struct Chunk { int32_t inst, begin, end, seg; };
 constexpr int32_t kChunk = 2048;
+
+// The points of all instances, in the callers' arrays: segment s holds points off[s] .. off[s + 1] - 1, of
+// instance inst[s] (device tables; an instance's sources, then its targets); a single segment is `one`
+struct PointSegs {
+    const int32_t* one;
+    const int32_t* const* ptr;
+    const int32_t *off, *inst;
+    int32_t n;
+};
 
 // {min x, min y, max x, max y} of each of K point sets (xy_tab on the device) into box[4 K], device or
 // pinned host memory; chunks of at most kChunk points of one set each (inst: the set, indices within
 // it), those of set k from chunk_first[k] on (K + 1 entries); part: 4 words per chunk
 void launch_extents(int32_t K, const int32_t* const* xy_tab, const Chunk* chunks, int32_t nchunks,
                     const int32_t* chunk_first, int32_t* part, int32_t* box, hipStream_t st);
-void launch_concat(int32_t K, const int32_t* const* xy_tab, const int32_t* pt_off, int64_t n,
-                   int32_t* xyc, hipStream_t st);
 // partial root boxes per chunk; also zeroes *dmax
-void launch_bbox_chunks(const int32_t* xy, const Chunk* chunks, int32_t nchunks, int32_t* part,
+void launch_bbox_chunks(const PointSegs& segs, const Chunk* chunks, int32_t nchunks, int32_t* part,
                         int32_t* dmax, hipStream_t st);
 // one block per instance: root boxes to bbox, and the instances' root boxes, depths, point
 // ranges and N_leaf (max_leaf, 0 if not positive) into inst; the deepest depth into *dmax
@@ -209,25 +217,28 @@ void launch_bbox_final(const int32_t* part, const int32_t* chunk_first, const in
 // keys and indices of the points (root boxes from inst, the deepest depth from *dmax);
 // zeroes zero[0, nzero); with radix_scratch (of radix_scratch_bytes(n)) also the sort's tile
 // counts of the lowest digit
-void launch_keys(const int32_t* xy, const int32_t* pt_off, int32_t K, const InstInfo* inst,
+void launch_keys(const PointSegs& segs, int32_t K, const InstInfo* inst,
                  const int32_t* dmax, int64_t n, uint64_t* keys, uint32_t* vals, int32_t* zero,
                  int32_t nzero, void* radix_scratch, hipStream_t st);
-// sorted points (coordinates in the root box, decoded from the keys), instance-local indices
-// and instances; per-level box counts and look-ahead maxima of every instance into hist
-// ([K][kMaxLevels + 2] counts, then [K] maxima; zero before the launch), copied to host_out
-// (host memory) by the last block; *done counts finished blocks (zero before the launch)
-// hist: `copies` zeroed copies of [K][kMaxLevels + 2] histograms and K maxima, added up into
-// host_out by the last block
-constexpr int kLevelStatsCopies = 16;
+// sorted points (coordinates in the root box, decoded from the keys) and instance-local
+// indices; per-level box counts and look-ahead maxima of every instance into hist (`copies` copies of
+// [K][kMaxLevels + 2] counts, then [K] maxima; zero before the launch), added up into host_out
+// (host memory) by the last block; done: kDoneStride (1 + level_stats_counters(nchunks)) words that
+// count finished blocks (zero before the launch)
+constexpr int kLevelStatsCopies = 16, kDoneStride = 32;
+int32_t level_stats_counters(int32_t nchunks);
 void launch_level_stats(const uint64_t* keys, const uint32_t* vals, const Chunk* chunks, int32_t nchunks,
-                        const InstInfo* inst, int Dmax, int32_t K, int32_t* pts, int32_t* perm_local, int32_t* pinst,
+                        const InstInfo* inst, int Dmax, int32_t K, int32_t* pts, int32_t* perm_local,
                         int8_t* cl, int32_t* hist, int32_t copies, int32_t* done, int32_t* host_out,
                         hipStream_t st);
-// exclusive scans of the flags "a leaf starts here" (per point), "leaf b starts a box of
-// level lev" (row lev, per leaf) and "box g is child c of its parent" (row c, per box)
-void scan_leaf_starts(const int8_t* cl, const int32_t* pinst, const InstInfo* inst, int64_t n,
-                      const uint64_t* keys, int Dmax, const int32_t* pts, uint32_t* pkey, int32_t* leaf_pt0,
-                      uint64_t* leaf_key, int8_t* leaf_cl, int32_t* leaf_inst, void* scratch, hipStream_t st);
+// the leaves that start in the chunks' points (sorted; cl: levels shared with the point before), numbered
+// in order, and the points' window keys; scratch of leaf_starts_scratch_bytes(nchunks)
+size_t leaf_starts_scratch_bytes(int32_t nchunks);
+void launch_leaf_starts(const Chunk* chunks, int32_t nchunks, const int8_t* cl, const InstInfo* inst,
+                        const uint64_t* keys, int Dmax, const int32_t* pts, uint32_t* pkey, int32_t* leaf_pt0,
+                        uint64_t* leaf_key, int8_t* leaf_cl, int32_t* leaf_inst, void* scratch, hipStream_t st);
+// exclusive scans of the flags "leaf b starts a box of level lev" (row lev, per leaf) and "box
+// g is child c of its parent" (row c, per box)
 void scan_level_starts(const int8_t* leaf_cl, const int32_t* leaf_inst, const InstInfo* inst, int64_t nleaf,
                        int Lmax, int32_t* out, void* scratch, hipStream_t st);
 void scan_child_classes(const uint64_t* box_key, int64_t nbox, int32_t* out, int32_t* totals, void* scratch,
