@@ -315,6 +315,29 @@ std::mutex g_static_mu[64];   // calls on one device take turns (they share its 
 }  // namespace
 static __device__ __align__(256) char scratch[kStaticScratchBytes];
 
+// A stream of the library's own beside a caller's, forked from it and joined to it by events
+struct SideStream {
+    hipStream_t s = nullptr;
+    hipEvent_t fork = nullptr, join = nullptr;
+    bool create() {
+        if (hipStreamCreateWithFlags(&s, hipStreamNonBlocking) == hipSuccess &&
+            hipEventCreateWithFlags(&fork, hipEventDisableTiming) == hipSuccess &&
+            hipEventCreateWithFlags(&join, hipEventDisableTiming) == hipSuccess)
+            return true;
+        (void)hipGetLastError();
+        destroy();
+        return false;
+    }
+    void destroy() {
+        if (join) (void)hipEventDestroy(join);
+        if (fork) (void)hipEventDestroy(fork);
+        if (s) (void)hipStreamDestroy(s);
+        s = nullptr;
+        fork = join = nullptr;
+    }
+};
+constexpr int kMaxSides = 8;
+
 struct lfmm_ctx {
     int device = 0;
     void* static_scratch = nullptr;   // device address of `scratch` on this context's device
@@ -329,6 +352,10 @@ struct lfmm_ctx {
     std::vector<std::unique_ptr<CachedOps>> all_ops;  // every set built; plans may hold any
     std::map<std::pair<int, int>, int32_t> tuned;     // (size class, density class) -> N_leaf
     hipStream_t capture = nullptr;                    // stream that graph captures record on
+    // streams beside the callers', lent to plans; at most kMaxSides are made
+    std::vector<SideStream> sides;
+    int sides_made = 0;
+    std::mutex side_mu;
     std::mutex mu;
     // live plans and servers, destroyed with the context if the caller has not done so
     std::set<lfmm_plan*> plans;
@@ -336,6 +363,24 @@ struct lfmm_ctx {
     std::mutex reg_mu;
     ~lfmm_ctx() {
         if (capture) (void)hipStreamDestroy(capture);
+        for (SideStream& s : sides) s.destroy();
+    }
+    // a side stream without an owner, or one with s == null
+    SideStream lend_side() {
+        std::lock_guard<std::mutex> lock(side_mu);
+        SideStream x;
+        if (!sides.empty()) {
+            x = sides.back();
+            sides.pop_back();
+        } else if (sides_made < kMaxSides && x.create()) {
+            ++sides_made;
+        }
+        return x;
+    }
+    void take_back(const SideStream& x) {
+        if (!x.s) return;
+        std::lock_guard<std::mutex> lock(side_mu);
+        sides.push_back(x);
     }
 };
 
@@ -386,6 +431,7 @@ struct lfmm_plan {
     TileRange m2l;                          // M2L tiles (class-sorted, some empty)
     std::vector<TileRange> m2m, l2l;        // tiles per height
     std::vector<SubStage> stages;           // from the top of the tree downwards
+    SideStream side;                        // lent by the context at the first execute that overlaps
     int64_t m2l_pairs = 0;
     Arena mem_small, mem_pts, mem_box, mem_ad;
     InstInfo* d_inst = nullptr;
@@ -451,6 +497,7 @@ struct lfmm_plan {
         for (hipEvent_t e : exec_copied)
             if (e) (void)hipEventDestroy(e);
         if (h_exec) ctx->pinned.release(h_exec, h_exec_cls);
+        ctx->take_back(side);
     }
 };
 
@@ -1414,6 +1461,35 @@ void build_forest(lfmm_plan* pl, int32_t K, const InstanceInput* in, int32_t max
     stage_c.retire(pl->built);
 }
 
+// Whether the plan's near field runs beside its far field on st: from kOverlapLeaves[0] to [1] leaves.  With
+// fewer, the passes are shorter than the fork and the join (some 10 us); with more, they fill the
+// device by themselves and L2P alone costs more than within the near field.  Execute of uniform points, in turn / beside
+// (us): 49 leaves 64 / 64, 169 80 / 71, 652 113 / 92, 2,555 135 / 104, 9,801 176 / 164, 19,600 257 / 262; mixed
+// precision 78 / 65, 96 / 75, 128 / 93, 160 / 117, 243 / 225, 371 / 353; a curve, 100 leaves 64 / 65, 396 88 / 74.
+// The near field has to be worth it as well: a wave takes about 0.9 us for each of its group's ranges of
+// sources (16 where all leaves are there, a quarter of that on curves) and pass of 64 targets, twice that with
+// the quadrant table of side 32 (a curve, side 32, 8: gains as above); below kOverlapRanges of them
+// (16,384 boundary nodes, side 16: 6, the near field 14 us), in turn is faster (a solve of 26
+// iterations 4.09 / 4.25 ms).
+constexpr int32_t kOverlapLeaves[2] = {128, 16384};
+constexpr double kOverlapRanges = 7.0;
+bool beside(lfmm_plan* pl, hipStream_t st) {
+    if (pl->adaptive || pl->nleaf < kOverlapLeaves[0] || pl->nleaf > kOverlapLeaves[1] || pl->m2l.n <= 0) return false;
+    int64_t side = 0;
+    for (const CachedOps* o : pl->ops) side = std::max(side, int64_t(o->dev.leaf_side));
+    const double groups = pl->nq, fill = double(pl->nleaf) / (4.0 * groups);
+    const double ranges = std::max(1.0, double(pl->n) / (64.0 * groups)) * 16.0 * fill * fill * (side > 16 ? 2.0 : 1.0);
+    if (side > 32 || ranges < kOverlapRanges) return false;
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &status) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    if (status != hipStreamCaptureStatusNone) return false;
+    if (!pl->side.s) pl->side = pl->ctx->lend_side();
+    return pl->side.s != nullptr;
+}
+
 // Enqueues the evaluation passes (Section 8.2) on st.  tab = per-instance load/potential
 // pointers on the device, or null with f1/u1 those of the single instance (in the plan's
 // Morton order when sorted).
@@ -1434,6 +1510,38 @@ void enqueue_passes(lfmm_plan* pl, const ExecPtrs* tab, const double* f1, double
                    single, pl->perm, pl->box_inst, pl->fs, pl->ops[o]->dev.leafT, pl->Q, st);
     }
     mark(2);
+    // The pairs of the near field need the loads alone: for plans that leave the device partly idle they run on a
+    // side stream beside the far field's passes, and L2P follows both (same bits).  Not under capture (the
+    // side stream would belong to the capture until it ends) and not while phases are timed.
+    const bool overlap = marks == 0 && beside(pl, st);
+    struct Join {
+        hipStream_t st;
+        SideStream side;
+        bool open = false;
+        void close() {
+            open = false;
+            const hipError_t a = hipEventRecord(side.join, side.s), b = hipStreamWaitEvent(st, side.join, 0);
+            LFMM_HIP(a);
+            LFMM_HIP(b);
+        }
+        ~Join() {
+            if (open && hipEventRecord(side.join, side.s) == hipSuccess) (void)hipStreamWaitEvent(st, side.join, 0);
+        }
+    } join{st, pl->side};
+    auto near = [&](int far_on, hipStream_t on) {
+        for (size_t o = 0; o < pl->ops.size(); ++o) {
+            const TileRange& r = pl->near_of_ops[o];
+            launch_near(r.t0, r.t0 + r.n, pl->groups, pl->ents, pl->ops[o]->dev.leaf_side, pl->pts, pl->pkey, pl->fs,
+                        pl->perm, tab, single, pl->U, pl->ops[o]->dev.leafT, pl->ctx->phi_oct, pl->ctx->phi_fast,
+                        pl->leaf_of_ops[o].n, far_on, on);
+        }
+    };
+    if (overlap) {
+        LFMM_HIP(hipEventRecord(pl->side.fork, st));
+        LFMM_HIP(hipStreamWaitEvent(pl->side.s, pl->side.fork, 0));
+        join.open = true;
+        near(0, pl->side.s);
+    }
     const int h_sub = pl->stages.empty() ? pl->Hmax + 1 : pl->stages.back().h - pl->stages.back().depth + 1;
     for (int h = 1; h < std::min(h_sub, pl->Hmax + 1); ++h) {
         const TileRange& r = pl->m2m[size_t(h)];
@@ -1486,11 +1594,15 @@ void enqueue_passes(lfmm_plan* pl, const ExecPtrs* tab, const double* f1, double
         mark(6);
         return;
     }
-    for (size_t o = 0; o < pl->ops.size(); ++o) {
-        const TileRange& r = pl->near_of_ops[o];
-        launch_near(r.t0, r.t0 + r.n, pl->groups, pl->ents, pl->ops[o]->dev.leaf_side, pl->pts, pl->pkey, pl->fs,
-                    pl->perm, tab, single, pl->U, pl->ops[o]->dev.leafT, pl->ctx->phi_oct, pl->ctx->phi_fast,
-                    pl->leaf_of_ops[o].n, st);
+    if (overlap) {
+        join.close();
+        for (size_t o = 0; o < pl->ops.size(); ++o) {
+            const TileRange& r = pl->near_of_ops[o];
+            launch_l2p(r.t0, r.t0 + r.n, pl->groups, pl->ops[o]->dev.leaf_side, pl->pts, pl->perm, tab, single, pl->U,
+                       pl->ops[o]->dev.leafT, st);
+        }
+    } else {
+        near(1, st);
     }
     mark(6);
 }

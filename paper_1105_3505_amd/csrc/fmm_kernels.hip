@@ -1722,7 +1722,7 @@ __device__ inline void near_group(int32_t rec, int4 ent, int64_t side, int W, co
                                   uint32_t kofs, const int2* pts,
                                   const uint32_t* pkey, const double* fs, const int32_t* perm_local,
                                   const ExecPtrs* tab_ptrs, ExecPtrs single, const double* U,
-                                  const double* leafT, double* sfar) {
+                                  const double* leafT, double* sfar, int far_on) {
     const int lane = threadIdx.x & 63;
     const cptr<uint32_t> SK = as_const(pkey);
     const cptr<double> SF = as_const(fs);
@@ -1732,9 +1732,14 @@ __device__ inline void near_group(int32_t rec, int4 ent, int64_t side, int W, co
     const int32_t bnd[5] = {word(4), word(5), word(6), word(7), word(8)};
     const int32_t lx0 = word(9), ly0 = word(10), cposs = word(11);
     const int32_t t_end = bnd[4];
-    const bool far = word(12) != 0;
+    const bool far = word(12) != 0 && far_on;
     const ExecPtrs eio = tab_ptrs ? tab_ptrs[word(3)] : single;
     double* u = eio.u;
+    if (SLICED && far) {   // of all the group's targets, into sfar
+        const int2 p = pts[min(bnd[0] + lane, t_end - 1)];
+        far_rows<P>(leaf0, nleaf, bnd, bnd[0], (p.x & int32_t(side - 1)) + int32_t(side) * (p.y & int32_t(side - 1)), leafT,
+                    U, sfar);
+    }
     const bool sorted_out = eio.sorted != 0;   // u indexed by sorted point
     const int32_t tgt0 = eio.tgt0;   // first target index
     // passes: the whole group once (group mode) or each leaf in turn (sliced mode)
@@ -1753,9 +1758,7 @@ __device__ inline void near_group(int32_t rec, int4 ent, int64_t side, int W, co
             const int32_t ii = valid ? i : p0;
             // leaves past the last start at t_end, after every point
             const int c = SLICED ? c0 : (ii >= bnd[1]) + (ii >= bnd[2]) + (ii >= bnd[3]);
-            const int32_t leaf = leaf0 + c;
             const int cpos = (cposs >> (2 * c)) & 3;
-            const int32_t tx = lx0 + (cpos & 1), ty = ly0 + (cpos >> 1);
             const int2 pi = pts[ii];
             // the window centre's byte offset is folded into the target's key once, so that a
             // pair costs one subtraction for its table address
@@ -1836,19 +1839,14 @@ __device__ inline void near_group(int32_t rec, int4 ent, int64_t side, int W, co
                     }
                 }
             }
-            if (far) {
-                const int32_t loc = pi.x - tx * int32_t(side) + int32_t(side) * (pi.y - ty * int32_t(side));
-                if (SLICED) {
-                    const double* tlp = leafT + size_t(loc) * P;
-                    const double* uh = U + size_t(leaf) * P;
-                    for (int p = sl; p < P; p += S) a1 += tlp[p] * uh[p];
-                } else {
-                    a1 += far_rows<P>(leaf0, nleaf, bnd, i0, loc, leafT, U, sfar);
-                }
-            }
             double acc = (a0 + a1) + (a2 + a3);
             if (SLICED)
                 for (int o = T; o < 64; o <<= 1) acc += __shfl_xor(acc, o, 64);
+            // the far field last, as when k_l2p adds it
+            if (far)
+                acc += SLICED ? sfar[ii - bnd[0]]
+                              : far_rows<P>(leaf0, nleaf, bnd, i0, (pi.x & int32_t(side - 1)) +
+                                                int32_t(side) * (pi.y & int32_t(side - 1)), leafT, U, sfar);
             if (valid && sl == 0 && pout >= tgt0) u[sorted_out ? int64_t(ii) : int64_t(pout - tgt0)] = acc;
         }
     }
@@ -1860,7 +1858,7 @@ template <int P, int MODE>
 __global__ __launch_bounds__(kNearBlock, 4) void k_near(
     int32_t q0, int32_t q1, const NearGroup* groups, const int4* ents, int64_t side, int W, const int2* pts,
     const uint32_t* pkey, const double* fs, const int32_t* perm_local, const ExecPtrs* tab_ptrs, ExecPtrs single,
-    const double* U, const double* leafT, const double* phi_oct_tab) {
+    const double* U, const double* leafT, const double* phi_oct_tab, int far_on) {
     constexpr int kNearWaves = kNearBlock / 64;
     // fixed-size table (largest window: side 32), so that its base is a compile-time constant
     // and folds into the address of every read
@@ -1932,10 +1930,10 @@ __global__ __launch_bounds__(kNearBlock, 4) void k_near(
         // group mode when half a wave or more is busy, leaf by leaf otherwise
         if (nt > 32)
             near_group<P, MODE, false>(r, en, side, W, tab, tb, kofs, pts, pkey, fs, perm_local, tab_ptrs, single, U,
-                                       leafT, sfar[wave]);
+                                       leafT, sfar[wave], far_on);
         else
             near_group<P, MODE, true>(r, en, side, W, tab, tb, kofs, pts, pkey, fs, perm_local, tab_ptrs, single, U,
-                                      leafT, sfar[wave]);
+                                      leafT, sfar[wave], far_on);
     }
 }
 
@@ -1987,6 +1985,35 @@ __global__ void k_load_stats_final(const double* part, double* out) {
     out[0] = s;
     out[1] = a;
     out[2] = bad;
+}
+
+// L2P alone, for groups whose pairs k_near adds up beside the passes before this one: adds the far field to
+// u, a wave per group (same bits as k_near with L2P, which adds it last).  Bound by the launch and three
+// dependent loads, 5 to 6 us for plans of up to some thousand groups.
+template <int P>
+__global__ __launch_bounds__(kBlock) void k_l2p(int32_t q0, int32_t q1, const NearGroup* groups, int32_t side,
+                                                 const int2* pts, const int32_t* perm_local, const ExecPtrs* tab_ptrs,
+                                                 ExecPtrs single, const double* U, const double* leafT) {
+    __shared__ double sfar[kWaves][64];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    for (int32_t q = q0 + int32_t(blockIdx.x) * kWaves + wave; q < q1; q += int32_t(gridDim.x) * kWaves) {
+        const int32_t rec = reinterpret_cast<const int32_t*>(groups)[size_t(q) * 16 + (lane & 15)];
+        auto word = [&](int k) -> int32_t { return __builtin_amdgcn_readlane(rec, k); };   // of the NearGroup
+        if (word(12) == 0) continue;
+        const int32_t bnd[5] = {word(4), word(5), word(6), word(7), word(8)};
+        const ExecPtrs eio = tab_ptrs ? tab_ptrs[word(3)] : single;
+        for (int32_t i0 = bnd[0]; i0 < bnd[4]; i0 += 64) {
+            const int32_t i = min(i0 + lane, bnd[4] - 1);
+            const int2 p = pts[i];
+            const int32_t pout = perm_local[i];
+            const bool on = i0 + lane < bnd[4] && pout >= eio.tgt0;
+            double* u = eio.u + (eio.sorted ? int64_t(i) : int64_t(pout - eio.tgt0));
+            const double old = on ? *u : 0.0;
+            const double v = far_rows<P>(word(0), word(1), bnd, i0, (p.x & (side - 1)) + side * (p.y & (side - 1)), leafT, U,
+                                         sfar[wave]);
+            if (on) *u = old + v;
+        }
+    }
 }
 
 // phi from radius kNearRadius on (PhiFast), the table below it: in LDS, both built by every block.
@@ -2795,21 +2822,22 @@ static unsigned xcd_grid(const void* fn, int threads, int64_t waves) {
 void launch_near(int32_t q0, int32_t q1, const NearGroup* groups, const int4* ents, int64_t side, const int32_t* pts,
                  const uint32_t* pkey, const double* fs, const int32_t* perm_local, const ExecPtrs* tab,
                  const ExecPtrs& single, const double* U, const double* leafT, const double* phi_oct,
-                 const PhiFast* fast, int32_t nleaf, hipStream_t st) {
+                 const PhiFast* fast, int32_t nleaf, int far_on, hipStream_t st) {
     if (q1 <= q0) return;
+    if (!far_on && side > 32) throw std::logic_error("the kernel for wide leaves has no pass without L2P");
     const int2* p2 = reinterpret_cast<const int2*>(pts);
     if (side <= 16) {
         const int W = int(4 * side - 1);
         if (W * W > kNearTabMax) throw std::logic_error("near-field window table larger than its array");
         const unsigned g = persistent_grid(reinterpret_cast<const void*>(&k_near<kRankPad, kWindow>), kNearBlock, q1 - q0);
         hipLaunchKernelGGL((k_near<kRankPad, kWindow>), dim3(g), dim3(kNearBlock), 0, st, q0, q1, groups, ents, side, W,
-                           p2, pkey, fs, perm_local, tab, single, U, leafT, phi_oct);
+                           p2, pkey, fs, perm_local, tab, single, U, leafT, phi_oct, far_on);
     } else if (side <= 32) {
         const int W = 64;   // rows: offsets of sides up to 32
         if (W * kQuadRow > kNearTabMax || 2 * side > W) throw std::logic_error("near-field quadrant table larger than its array");
         const unsigned g = persistent_grid(reinterpret_cast<const void*>(&k_near<kRankPad, kQuad>), kNearBlock, q1 - q0);
         hipLaunchKernelGGL((k_near<kRankPad, kQuad>), dim3(g), dim3(kNearBlock), 0, st, q0, q1, groups, ents, side, W, p2,
-                           pkey, fs, perm_local, tab, single, U, leafT, phi_oct);
+                           pkey, fs, perm_local, tab, single, U, leafT, phi_oct, far_on);
     } else {
         // near offsets are at most 2 side - 1, so that their squared length fits the octave table
         if (2 * side > 256) throw std::logic_error("leaf wider than the near-field table allows");
@@ -2827,6 +2855,15 @@ void launch_near(int32_t q0, int32_t q1, const NearGroup* groups, const int4* en
         hipLaunchKernelGGL((k_near_wide<kRankPad, false>), dim3(g), dim3(64 * kWideWaves), 0, st, q0, q1, groups, ents,
                            side, p2, fs, perm_local, tab, single, U, leafT, phi_oct, fast, by_leaf);
     }
+}
+
+void launch_l2p(int32_t q0, int32_t q1, const NearGroup* groups, int64_t side, const int32_t* pts,
+                const int32_t* perm_local, const ExecPtrs* tab, const ExecPtrs& single, const double* U,
+                const double* leafT, hipStream_t st) {
+    if (q1 <= q0) return;
+    const unsigned g = persistent_grid(reinterpret_cast<const void*>(&k_l2p<kRankPad>), kBlock, q1 - q0);
+    hipLaunchKernelGGL(k_l2p<kRankPad>, dim3(g), dim3(kBlock), 0, st, q0, q1, groups, int32_t(side),
+                       reinterpret_cast<const int2*>(pts), perm_local, tab, single, U, leafT);
 }
 
 size_t load_stats_scratch_bytes() { return size_t(kStatBlocks) * 3 * sizeof(double); }

@@ -346,7 +346,11 @@ void launch_m2l_mixed(const BoxTile* tiles, const int32_t* ntiles_dev, int32_t m
 void launch_near(int32_t q0, int32_t q1, const NearGroup* groups, const int4* ents, int64_t side, const int32_t* pts,
                  const uint32_t* pkey, const double* fs, const int32_t* perm_local, const ExecPtrs* tab,
                  const ExecPtrs& single, const double* U, const double* leafT, const double* phi_oct,
-                 const PhiFast* fast, int32_t nleaf, hipStream_t st);
+                 const PhiFast* fast, int32_t nleaf, int far_on, hipStream_t st);
+// L2P alone into u, for sides up to 32 whose near field was added up with far_on = 0
+void launch_l2p(int32_t q0, int32_t q1, const NearGroup* groups, int64_t side, const int32_t* pts,
+                const int32_t* perm_local, const ExecPtrs* tab, const ExecPtrs& single, const double* U,
+                const double* leafT, hipStream_t st);
 // Near field of the adaptive leaves: what a wave needs to know of a leaf, in one record
 struct AdLeaf {
     int32_t t0, t1;        // its points
