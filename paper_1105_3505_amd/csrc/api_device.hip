@@ -1379,8 +1379,11 @@ void build_forest(lfmm_plan* pl, int32_t K, const InstanceInput* in, int32_t max
         launch_subtrees(pl->hbase[size_t(g.h)], g.n, g.depth, pl->box_child, g.subs, st);
         subs += g.n;
     }
+    // adaptive trees: roles, and V lists (interaction lists without pruned boxes) in place of the full ones
+    if (adaptive)
+        launch_roles(pl->box_pt0, pl->box_pt1, pl->box_parent, pl->box_lev, pl->box_inst, pl->d_inst, nb, pl->role, st);
     launch_lists(pl->box_key, pl->box_parent, pl->box_child, pl->box_inst, pl->box_lev, pl->d_inst, nb, pl->nb9,
-                 pl->il27, st);
+                 pl->il27, adaptive ? pl->role : nullptr, st);
     const int32_t m2l_slots = pl->m2l.n;
     const int32_t n_m2l_groups = int32_t(m2l_groups.size());
     if (!adaptive) {
@@ -1392,11 +1395,8 @@ void build_forest(lfmm_plan* pl, int32_t K, const InstanceInput* in, int32_t max
         launch_class_lists(d_groups, int32_t(groups.size()), 0, tile_slots, cscan, ctotal, pl->box_key, pl->box_lev,
                            nullptr, nb, pl->cls_box, pl->tiles, st);
     } else {
-        // roles, V lists (interaction lists without pruned boxes) and the M2L tiles over the
-        // boxes that take part; L2L keeps every box (pruned ones relay expansions)
-        launch_roles(pl->box_pt0, pl->box_pt1, pl->box_parent, pl->box_lev, pl->box_inst, pl->d_inst, nb, pl->role,
-                     st);
-        launch_filter_interactions(pl->role, nb, pl->il27, st);
+        // the M2L tiles over the boxes that take part; L2L keeps every box (pruned ones relay
+        // expansions)
         scan_child_classes_active(pl->box_key, pl->box_lev, pl->role, nb, cscan_v, ctotal_v, cscr, st);
         launch_class_lists(d_groups, n_m2l_groups, 0, m2l_slots, cscan_v, ctotal_v, pl->box_key, pl->box_lev,
                            pl->role, nb, pl->cls_box, pl->tiles, st);

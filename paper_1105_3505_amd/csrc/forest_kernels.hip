@@ -423,19 +423,30 @@ __device__ inline int32_t find_box(const uint64_t* box_key, int32_t lo, int32_t 
     return (lo < end && box_key[lo] == key) ? lo : -1;
 }
 
+// Element index / N of this thread of a grid over elements of N slots each, and the slot: a division of 64 bits
+// per block and one of 32 per thread
+template <int N>
+__device__ inline int32_t split_index(int& slot) {
+    const int64_t base = int64_t(blockIdx.x) * blockDim.x, g0 = base / N;
+    const uint32_t r = uint32_t(base - g0 * N) + threadIdx.x, d = r / uint32_t(N);
+    slot = int(r - d * uint32_t(N));
+    return int32_t(g0) + int32_t(d);
+}
+
 __device__ inline uint64_t morton2(uint32_t x, uint32_t y) { return spread_bits(x) | (spread_bits(y) << 1); }
 
 // 3 x 3 neighbourhood of every box (slot (dy + 1) * 3 + dx + 1), one thread per (box, slot):
 // the box of that cell found by search among the boxes of its level, or directly when the
 // level holds every cell (its boxes are then the cells in Morton order).  No dependence
-// between levels, so one launch covers all of them.
+// between levels, so one launch covers all of them.  (A search outwards from the box in doubling
+// steps took 274 us for 1.5e6 boxes, this one 190: a wave waits for its farthest neighbour.)
 __global__ void k_neighbours(const uint64_t* box_key, const int32_t* box_inst, const int8_t* box_lev,
                              const InstInfo* inst, int64_t nbox, int32_t* nb9) {
     const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (t >= nbox * 9) return;
-    const int64_t g = t / 9;
-    const int q = int(t - g * 9);
-    int32_t r = int32_t(g);
+    int q;
+    const int32_t g = split_index<9>(q);
+    int32_t r = g;
     if (q != 4) {
         const int lev = box_lev[g];
         const InstInfo& I = inst[box_inst[g]];
@@ -455,15 +466,16 @@ __global__ void k_neighbours(const uint64_t* box_key, const int32_t* box_inst, c
 // interaction list of every box of level >= 2 (Definition 6.1), one thread per (box, slot):
 // the children of its parent's neighbours that are not its own neighbours, slot k being the
 // k-th such cell in row-major order of the 6 x 6 block they cover (which depends on the box's
-// position in its parent)
+// position in its parent); with role, V lists: pruned boxes have none and are in none
 __global__ void k_interactions(const uint64_t* box_key, const int32_t* box_parent, const int32_t* box_child,
-                               const int8_t* box_lev, int64_t nbox, const int32_t* nb9, int32_t* il27) {
+                               const int8_t* box_lev, const int8_t* role, int64_t nbox, const int32_t* nb9,
+                               int32_t* il27) {
     const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (t >= nbox * kNumInteractions) return;
-    const int64_t g = t / kNumInteractions;
-    const int k = int(t - g * kNumInteractions);
+    int k;
+    const int32_t g = split_index<kNumInteractions>(k);
     int32_t r = -1;
-    if (box_lev[g] >= 2) {
+    if (box_lev[g] >= 2 && !(role != nullptr && role[g] == kRolePruned)) {
         const uint64_t key = box_key[g];
         const int32_t bx = int32_t(compact_bits(key)), by = int32_t(compact_bits(key >> 1));
         const int cx = bx & 1, cy = by & 1;
@@ -490,6 +502,7 @@ __global__ void k_interactions(const uint64_t* box_key, const int32_t* box_paren
             if (q >= 0) r = box_child[size_t(q) * 4 + size_t((x & 1) + 2 * (y & 1))];
         }
     }
+    if (role != nullptr && r >= 0 && role[r] == kRolePruned) r = -1;
     il27[t] = r;
 }
 
@@ -594,14 +607,6 @@ __global__ void k_roles(const int32_t* box_pt0, const int32_t* box_pt1, const in
     role[g] = member ? (leaf ? kRoleLeaf : kRoleInner) : kRolePruned;
 }
 
-__global__ void k_filter_interactions(const int8_t* role, int64_t nbox, int32_t* il27) {
-    const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (t >= nbox * kNumInteractions) return;
-    const int64_t g = t / kNumInteractions;
-    const int32_t r = il27[t];
-    if (r >= 0 && (role[g] == kRolePruned || role[r] == kRolePruned)) il27[t] = -1;
-}
-
 // Box (level, x, y), x and y in units of its level.
 struct BoxAt {
     int lev;
@@ -643,6 +648,25 @@ struct ListOut {
 // siblings waiting, over at most kMaxLevels levels.
 constexpr int kListStack = 3 * kMaxLevels + 4;
 
+// The eight neighbours of a box and their roles, each in one round of loads (kRolePruned where there is none); a
+// chain of two loads per neighbour and ancestor was most of the lists' time (2e6 points in 64 clusters: count
+// and fill 412 -> 317 us)
+struct Ring {
+    int32_t c[8];
+    int8_t role[8];
+};
+__device__ inline Ring ring(const int32_t* nb9, const int8_t* role, int32_t b) {
+    Ring r;
+    #pragma unroll
+    for (int q = 0; q < 8; ++q) r.c[q] = nb9[size_t(b) * 9 + (q < 4 ? q : q + 1)];
+    #pragma unroll
+    for (int q = 0; q < 8; ++q) r.role[q] = role[max(r.c[q], 0)];
+    #pragma unroll
+    for (int q = 0; q < 8; ++q)
+        if (r.c[q] < 0) r.role[q] = kRolePruned;
+    return r;
+}
+
 // X entries of box a (level >= 2): the leaves coarser than a that touch a's parent but not a,
 // among the neighbours of a's ancestors; out(list, entry) takes each.
 template <class Out>
@@ -651,14 +675,18 @@ __device__ inline void x_entries(int32_t a, const uint64_t* box_key, const int32
     const BoxAt ab = box_at(box_key, box_lev, a);
     const int32_t p = box_parent[a];
     const BoxAt par = box_at(box_key, box_lev, p);
-    for (int32_t b = p; b >= 0 && box_lev[b] >= 1; b = box_parent[b])
-        for (int q = 0; q < 9; ++q) {
-            if (q == 4) continue;
-            const int32_t c = nb9[size_t(b) * 9 + q];
-            if (c < 0 || role[c] != kRoleLeaf) continue;
-            const BoxAt cb = box_at(box_key, box_lev, c);
-            if (touches(par, cb) && !touches(ab, cb)) out(c);
+    int lev = par.lev;
+    for (int32_t b = p; b >= 0 && lev >= 1; --lev) {
+        const int32_t up = box_parent[b];
+        const Ring r = ring(nb9, role, b);
+        #pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            if (r.role[q] != kRoleLeaf) continue;
+            const BoxAt cb = box_at(box_key, box_lev, r.c[q]);
+            if (touches(par, cb) && !touches(ab, cb)) out(r.c[q]);
         }
+        b = up;
+    }
 }
 
 // U and W of every adaptive leaf and X of every box of the adaptive tree, one thread per box.
@@ -692,34 +720,57 @@ __global__ void k_adaptive_lists(const uint64_t* box_key, const int32_t* box_par
         o.put(0, g, nu, g);
         int32_t stack[kListStack];
         int sp = 0;
-        for (int q = 0; q < 9; ++q) {
-            if (q == 4) continue;
-            const int32_t c = nb9[size_t(g) * 9 + q];
-            if (c < 0 || role[c] == kRolePruned) continue;
-            if (role[c] == kRoleLeaf) {
+        const Ring rt = ring(nb9, role, g);
+        for (int q = 0; q < 8; ++q) {
+            int32_t c = -1;
+            int8_t rc = kRolePruned;
+            #pragma unroll
+            for (int k = 0; k < 8; ++k)   // element q, in registers
+                if (k == q) {
+                    c = rt.c[k];
+                    rc = rt.role[k];
+                }
+            if (rc == kRolePruned) continue;
+            if (rc == kRoleLeaf) {
                 o.put(0, g, nu, c);
                 continue;
             }
             stack[sp++] = c;
             while (sp > 0) {
                 const int32_t b = stack[--sp];
+                const int4 kids = reinterpret_cast<const int4*>(box_child)[b];
+                const int32_t ds[4] = {kids.x, kids.y, kids.z, kids.w};
+                BoxAt at[4];
+                int8_t rd[4];
+                int32_t np[4];
+                #pragma unroll
+                for (int k = 0; k < 4; ++k) {   // all of the four's data in flight together
+                    const int32_t d = max(ds[k], 0);
+                    at[k] = box_at(box_key, box_lev, d);
+                    rd[k] = role[d];
+                    np[k] = box_pt1[d] - box_pt0[d];
+                }
+                #pragma unroll
                 for (int k = 3; k >= 0; --k) {   // pushed in reverse: children visited in order
-                    const int32_t d = box_child[size_t(b) * 4 + k];
+                    const int32_t d = ds[k];
                     if (d < 0) continue;
-                    if (!touches(tau, box_at(box_key, box_lev, d))) {
-                        if (box_pt1[d] - box_pt0[d] <= kDirectMax) o.put(0, g, nu, d);
+                    if (!touches(tau, at[k])) {
+                        if (np[k] <= kDirectMax) o.put(0, g, nu, d);
                         else o.put(1, g, nw, d);
-                    } else if (role[d] == kRoleLeaf) o.put(0, g, nu, d);
+                    } else if (rd[k] == kRoleLeaf) o.put(0, g, nu, d);
                     else if (sp < kListStack) stack[sp++] = d;
                 }
             }
         }
-        for (int32_t a = box_parent[g]; a >= 0 && box_lev[a] >= 1; a = box_parent[a])
-            for (int q = 0; q < 9; ++q) {
-                if (q == 4) continue;
-                const int32_t c = nb9[size_t(a) * 9 + q];
-                if (c >= 0 && role[c] == kRoleLeaf && touches(tau, box_at(box_key, box_lev, c))) o.put(0, g, nu, c);
-            }
+        int lev = tau.lev - 1;
+        for (int32_t a = box_parent[g]; a >= 0 && lev >= 1; --lev) {
+            const int32_t up = box_parent[a];
+            const Ring r = ring(nb9, role, a);
+            #pragma unroll
+            for (int q = 0; q < 8; ++q)
+                if (r.role[q] == kRoleLeaf && touches(tau, box_at(box_key, box_lev, r.c[q]))) o.put(0, g, nu, r.c[q]);
+            a = up;
+        }
         // X entries of tau and of its ancestors small enough to keep none (counts grow upwards)
         for (int32_t a = g; a >= 0 && box_lev[a] >= 2 && box_pt1[a] - box_pt0[a] <= kDirectMax; a = box_parent[a])
             x_entries(a, box_key, box_parent, box_lev, role, nb9, [&](int32_t c) { o.put(0, g, nu, c); });
@@ -1420,12 +1471,12 @@ void launch_link_boxes(const uint64_t* box_key, const int32_t* box_parent, const
 
 void launch_lists(const uint64_t* box_key, const int32_t* box_parent, const int32_t* box_child,
                   const int32_t* box_inst, const int8_t* box_lev, const InstInfo* inst, int64_t nbox, int32_t* nb9,
-                  int32_t* il27, hipStream_t st) {
+                  int32_t* il27, const int8_t* role, hipStream_t st) {
     if (nbox <= 0) return;
     hipLaunchKernelGGL(k_neighbours, dim3(grid_for(nbox * 9)), dim3(kBlock), 0, st, box_key, box_inst, box_lev, inst,
                        nbox, nb9);
     hipLaunchKernelGGL(k_interactions, dim3(grid_for(nbox * kNumInteractions)), dim3(kBlock), 0, st, box_key,
-                       box_parent, box_child, box_lev, nbox, nb9, il27);
+                       box_parent, box_child, box_lev, role, nbox, nb9, il27);
 }
 
 void launch_class_lists(const BoxGroup* groups, int32_t ngroups, int32_t slot0, int32_t nslots,
@@ -1445,12 +1496,6 @@ void launch_roles(const int32_t* box_pt0, const int32_t* box_pt1, const int32_t*
     if (nbox <= 0) return;
     hipLaunchKernelGGL(k_roles, dim3(grid_for(nbox)), dim3(kBlock), 0, st, box_pt0, box_pt1, box_parent, box_lev,
                        box_inst, inst, nbox, role);
-}
-
-void launch_filter_interactions(const int8_t* role, int64_t nbox, int32_t* il27, hipStream_t st) {
-    if (nbox <= 0) return;
-    hipLaunchKernelGGL(k_filter_interactions, dim3(grid_for(nbox * kNumInteractions)), dim3(kBlock), 0, st, role,
-                       nbox, il27);
 }
 
 void launch_adaptive_lists(bool fill, const uint64_t* box_key, const int32_t* box_parent, const int32_t* box_child,

@@ -257,7 +257,7 @@ void launch_link_boxes(const uint64_t* box_key, const int32_t* box_parent, const
 // lists from the parents' neighbours
 void launch_lists(const uint64_t* box_key, const int32_t* box_parent, const int32_t* box_child,
                   const int32_t* box_inst, const int8_t* box_lev, const InstInfo* inst, int64_t nbox, int32_t* nb9,
-                  int32_t* il27, hipStream_t st);
+                  int32_t* il27, const int8_t* role, hipStream_t st);
 // class lists (boxes of each group sorted by child position) and the tiles over them;
 // the groups own tile slots [slot0, slot0 + nslots); with role non-null, boxes of role
 // kRolePruned below level 3 are left out (cscan / ctotal must count the same boxes)
@@ -271,8 +271,6 @@ void scan_child_classes_active(const uint64_t* box_key, const int8_t* box_lev, c
 // roles of the boxes of the adaptive tree (N_leaf and leaf level from each box's instance)
 void launch_roles(const int32_t* box_pt0, const int32_t* box_pt1, const int32_t* box_parent, const int8_t* box_lev,
                   const int32_t* box_inst, const InstInfo* inst, int64_t nbox, int8_t* role, hipStream_t st);
-// interaction-list slots naming a pruned box, or of a pruned box, set to -1 (V lists)
-void launch_filter_interactions(const int8_t* role, int64_t nbox, int32_t* il27, hipStream_t st);
 // U, W and X lists: fill = false counts them into cnt[3][nbox + 1] (the last of each row
 // zero); fill = true writes entries at the row starts off[3][nbox + 1] into ent[3]
 void launch_adaptive_lists(bool fill, const uint64_t* box_key, const int32_t* box_parent, const int32_t* box_child,
