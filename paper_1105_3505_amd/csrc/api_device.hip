@@ -1734,6 +1734,19 @@ lfmm_status create_forest(lfmm_ctx* ctx, int32_t K, const InstanceInput* in, int
     });
 }
 
+// Pinned host memory that a kernel writes results to (none for 0 bytes), from the context's pool
+struct PinnedWords {
+    lfmm_ctx* c;
+    size_t cls = 0;
+    void* p;
+    PinnedWords(lfmm_ctx* ctx, size_t bytes) : c(ctx), p(bytes ? ctx->pinned.acquire(bytes, &cls) : nullptr) {}
+    PinnedWords(const PinnedWords&) = delete;
+    PinnedWords& operator=(const PinnedWords&) = delete;
+    ~PinnedWords() {
+        if (p) c->pinned.release(p, cls);
+    }
+};
+
 // Checks of the loads of K instances (f[k] holds nsrc[k] values) before any pass: a NaN or
 // infinite load is an invalid input (LFMM_E_INVAL); a total load that is not zero (|sum f| >
 // 1e-12 sum |f|, the well-posedness condition of Section 1) is reported as LFMM_W_NONZERO_SUM,
@@ -1747,11 +1760,16 @@ lfmm_status check_loads(lfmm_ctx* ctx, int32_t K, const double* const* f, const 
     a.allocate();
     double* scr = a.take<double>(load_stats_scratch_bytes() / sizeof(double));
     double* out = a.take<double>(size_t(K) * 3);
-    for (int32_t k = 0; k < K; ++k) launch_load_stats(f[k], nsrc[k], scr, out + 3 * size_t(k), st);
-    LFMM_HIP(hipGetLastError());
+    // the totals are written to pinned host memory by the kernel; with a static workspace, copied back
     std::vector<double> h(size_t(K) * 3);
-    LFMM_HIP(hipMemcpyAsync(h.data(), out, h.size() * sizeof(double), hipMemcpyDeviceToHost, st));
+    PinnedWords pinned(ctx, sreg ? 0 : h.size() * sizeof(double));
+    SyncOnUnwind unwind;
+    double* to = pinned.p ? static_cast<double*>(pinned.p) : out;
+    for (int32_t k = 0; k < K; ++k) launch_load_stats(f[k], nsrc[k], scr, to + 3 * size_t(k), st);
+    LFMM_HIP(hipGetLastError());
+    if (!pinned.p) LFMM_HIP(hipMemcpyAsync(h.data(), out, h.size() * sizeof(double), hipMemcpyDeviceToHost, st));
     LFMM_HIP(hipStreamSynchronize(st));
+    if (pinned.p) std::memcpy(h.data(), pinned.p, h.size() * sizeof(double));
     a.release();
     lfmm_status res = LFMM_OK;
     for (int32_t k = 0; k < K; ++k) {
@@ -1821,19 +1839,14 @@ lfmm_status lfmm::root_bits_of(lfmm_ctx* ctx, int32_t K, const int64_t* n, const
         stage.add(d_chunks, chunks);
         stage.add(d_first, first);
         // the boxes are written to pinned host memory by the kernel
-        struct Pinned {
-            lfmm_ctx* c;
-            size_t cls = 0;
-            int32_t* p;
-            Pinned(lfmm_ctx* ctx, size_t bytes) : c(ctx), p(static_cast<int32_t*>(ctx->pinned.acquire(bytes, &cls))) {}
-            ~Pinned() { c->pinned.release(p, cls); }
-        } box(ctx, size_t(K) * 16);
+        PinnedWords pinned(ctx, size_t(K) * 16);
+        int32_t* box = static_cast<int32_t*>(pinned.p);
         SyncOnUnwind unwind;
         stage.flush(st);
-        launch_extents(K, d_ptr, d_chunks, int32_t(chunks.size()), d_first, part, box.p, st);
+        launch_extents(K, d_ptr, d_chunks, int32_t(chunks.size()), d_first, part, box, st);
         LFMM_HIP(hipGetLastError());
         LFMM_HIP(hipStreamSynchronize(st));
-        const std::vector<int32_t> h(box.p, box.p + size_t(K) * 4);
+        const std::vector<int32_t> h(box, box + size_t(K) * 4);
         a.release();
         for (int32_t k = 0; k < K; ++k) {
             const int64_t ext = std::max(int64_t(h[4 * size_t(k) + 2]) - h[4 * size_t(k)],

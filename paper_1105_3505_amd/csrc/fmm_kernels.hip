@@ -1974,17 +1974,17 @@ __global__ __launch_bounds__(kBlock) void k_load_stats_part(const double* f, int
     }
 }
 
-__global__ void k_load_stats_final(const double* part, double* out) {
-    if (threadIdx.x != 0) return;
-    double s = 0.0, a = 0.0, bad = 0.0;
-    for (int b = 0; b < kStatBlocks; ++b) {
-        s += part[3 * b];
-        a += part[3 * b + 1];
-        bad += part[3 * b + 2];
+// (the partials come to LDS together: read one after the other from memory they took 9 to 13 us)
+__global__ __launch_bounds__(kBlock) void k_load_stats_final(const double* part, double* out) {
+    __shared__ double p[3][kStatBlocks];
+    for (int i = threadIdx.x; i < 3 * kStatBlocks; i += kBlock) p[i % 3][i / 3] = part[i];
+    __syncthreads();
+    if (threadIdx.x < 3) {
+        double s = 0.0;
+        #pragma unroll 32
+        for (int b = 0; b < kStatBlocks; ++b) s += p[threadIdx.x][b];
+        out[threadIdx.x] = s;
     }
-    out[0] = s;
-    out[1] = a;
-    out[2] = bad;
 }
 
 // L2P alone, for groups whose pairs k_near adds up beside the passes before this one: adds the far field to
@@ -2870,7 +2870,7 @@ size_t load_stats_scratch_bytes() { return size_t(kStatBlocks) * 3 * sizeof(doub
 
 void launch_load_stats(const double* f, int64_t n, double* scratch, double* out3, hipStream_t st) {
     hipLaunchKernelGGL(k_load_stats_part, dim3(kStatBlocks), dim3(kBlock), 0, st, f, n, scratch);
-    hipLaunchKernelGGL(k_load_stats_final, dim3(1), dim3(64), 0, st, scratch, out3);
+    hipLaunchKernelGGL(k_load_stats_final, dim3(1), dim3(kBlock), 0, st, scratch, out3);
 }
 
 void launch_phi_extend(double* oct, int r0, int r1, const PhiFar* far, hipStream_t st) {

@@ -1279,8 +1279,9 @@ void scan_sink(Src src, Sink sink, int64_t n, int rows, int32_t* totals, void* s
     if (n <= 0 || rows <= 0) return;
     const int64_t nb = (n + kScanTile - 1) / kScanTile;
     int32_t* bsum = static_cast<int32_t*>(scratch);
-    hipLaunchKernelGGL(k_scan_sums<Src>, dim3(unsigned(nb), unsigned(rows)), dim3(kBlock), 0, st, src, n, bsum,
-                       int(nb));
+    if (nb > 1)   // a single block adds up no sums before its own
+        hipLaunchKernelGGL(k_scan_sums<Src>, dim3(unsigned(nb), unsigned(rows)), dim3(kBlock), 0, st, src, n, bsum,
+                           int(nb));
     hipLaunchKernelGGL((k_scan_apply<Src, Sink>), dim3(unsigned(nb), unsigned(rows)), dim3(kBlock), 0, st, src, sink,
                        n, bsum, int(nb), totals);
 }
@@ -1310,7 +1311,8 @@ void launch_leaf_starts(const Chunk* chunks, int32_t nchunks, const int8_t* cl, 
                         uint64_t* leaf_key, int8_t* leaf_cl, int32_t* leaf_inst, void* scratch, hipStream_t st) {
     int32_t* count = static_cast<int32_t*>(scratch);
     int32_t* before = nullptr;
-    hipLaunchKernelGGL(k_leaf_count, dim3(unsigned(nchunks)), dim3(kBlock), 0, st, chunks, cl, inst, count);
+    if (nchunks > 1)
+        hipLaunchKernelGGL(k_leaf_count, dim3(unsigned(nchunks)), dim3(kBlock), 0, st, chunks, cl, inst, count);
     if (nchunks > 8192) {   // a block would read more than 32 counts a thread
         before = count + nchunks;
         scan_rows(count, before, nchunks, 1, nullptr, before + nchunks, st);
