@@ -950,20 +950,26 @@ void build_forest(lfmm_plan* pl, int32_t K, const InstanceInput* in, int32_t max
         if (ctx->tuned.empty()) ml_all = kDefaultMaxLeaf;
     }
 
-    // ---- root boxes ----------------------------------------------------------------------
-    launch_bbox_chunks(segs, d_chunks, nch, d_part, d_dmax, st);
-    // root boxes straight to pinned host memory, and the instance table of the next kernels
-    // (N_leaf too when there is one for all) straight to the device
-    launch_bbox_final(d_part, d_chfirst, d_ptoff, K, std::max(ml_all, 0), bb, d_inst0, d_dmax, st);
+    // one small tree takes a single launch up to the level statistics (the static workspace has no
+    // pinned memory to read them from, and its launches are replayed)
+    const bool small = K == 1 && n <= kChunk && ml_all > 0 && !sreg;
     std::unique_ptr<Fence> bb_ready;
-    if (!sreg) bb_ready = std::make_unique<Fence>(st);
-    // Morton keys and, for large inputs, the first two passes of their sort go out before the
-    // host reads the root boxes: the keys need only the device's instance table, and distinct
-    // points need at least 16 key bits once there are 2^16 of them (a pass over digits that
-    // are zero everywhere would change nothing either).
-    launch_keys(segs, K, d_inst0, d_dmax, n, keys, vals, d_stats, nstats + ndone, n > 1 ? rscr : nullptr, st);
-    const int early_passes = (n >= (int64_t(1) << 16)) ? 2 : 0;
-    int which = radix_sort_passes(keys, vals, keys_tmp, vals_tmp, n, 0, early_passes, true, rscr, st);
+    int early_passes = 0, which = 0;
+    if (!small) {
+        // ---- root boxes ----------------------------------------------------------------------
+        launch_bbox_chunks(segs, d_chunks, nch, d_part, d_dmax, st);
+        // root boxes straight to pinned host memory, and the instance table of the next kernels
+        // (N_leaf too when there is one for all) straight to the device
+        launch_bbox_final(d_part, d_chfirst, d_ptoff, K, std::max(ml_all, 0), bb, d_inst0, d_dmax, st);
+        if (!sreg) bb_ready = std::make_unique<Fence>(st);
+        // Morton keys and, for large inputs, the first two passes of their sort go out before the
+        // host reads the root boxes: the keys need only the device's instance table, and distinct
+        // points need at least 16 key bits once there are 2^16 of them (a pass over digits that
+        // are zero everywhere would change nothing either).
+        launch_keys(segs, K, d_inst0, d_dmax, n, keys, vals, d_stats, nstats + ndone, n > 1 ? rscr : nullptr, st);
+        early_passes = (n >= (int64_t(1) << 16)) ? 2 : 0;
+        which = radix_sort_passes(keys, vals, keys_tmp, vals_tmp, n, 0, early_passes, true, rscr, st);
+    }
     // point storage, taken while the device works
     Arena& mp = pl->mem_pts;
     mp.set_pool(&ctx->pool, sreg);
@@ -976,6 +982,10 @@ void build_forest(lfmm_plan* pl, int32_t K, const InstanceInput* in, int32_t max
     pl->perm = mp.take<int32_t>(n);
     pl->pkey = mp.take<uint32_t>(n);
     pl->fs = mp.take<double>(n);
+    if (small) {
+        launch_small_tree(segs, int32_t(n), ml_all, keys, pl->pts, pl->perm, cl, bb, stats, st);
+        bb_ready = std::make_unique<Fence>(st);
+    }
     if (sreg) {
         LFMM_HIP(hipMemcpyAsync(rb_host.data(), bb, size_t(K) * 16, hipMemcpyDeviceToHost, st));
         LFMM_HIP(hipStreamSynchronize(st));
@@ -1017,14 +1027,16 @@ void build_forest(lfmm_plan* pl, int32_t K, const InstanceInput* in, int32_t max
 
     // ---- Morton order: the rest of the sort ------------------------------------------------
     const int kbits = 2 * Dmax + ibits;
-    which = radix_sort_passes(keys, vals, keys_tmp, vals_tmp, n, early_passes,
-                              std::max(early_passes, (kbits + 7) / 8), true, rscr, st);
+    if (!small)
+        which = radix_sort_passes(keys, vals, keys_tmp, vals_tmp, n, early_passes,
+                                  std::max(early_passes, (kbits + 7) / 8), true, rscr, st);
     uint64_t* skeys = which ? keys_tmp : keys;
     uint32_t* svals = which ? vals_tmp : vals;
 
     // ---- leaf levels and box counts ---------------------------------------------------------
-    launch_level_stats(skeys, svals, d_chunks, nch, d_inst0, Dmax, K, pl->pts, pl->perm, cl, d_stats,
-                       stat_copies, d_stats + nstats, stats, st);
+    if (!small)
+        launch_level_stats(skeys, svals, d_chunks, nch, d_inst0, Dmax, K, pl->pts, pl->perm, cl, d_stats,
+                           stat_copies, d_stats + nstats, stats, st);
     if (sreg) {
         LFMM_HIP(hipMemcpyAsync(rb_host.data() + size_t(K) * 4, stats, (rb_words - size_t(K) * 4) * 4,
                                 hipMemcpyDeviceToHost, st));

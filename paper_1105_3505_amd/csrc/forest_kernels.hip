@@ -360,6 +360,103 @@ __global__ void k_level_stats(const uint64_t* keys, const uint32_t* vals, const 
         }
 }
 
+// Root box, Morton order and level statistics of one tree of at most kChunk points, by one block: what
+// k_bbox_chunks to k_level_stats do in eight launches and two read-backs, of which small plans' building
+// consists (a solve of 1e3 points 206 -> 179 us, of 2e3 229 -> 204).  The sort is bitonic, in LDS, by key and
+// index, the order of the radix sort's; it is most of the kernel's 21 to 31 us, 0.3 us a stage of one barrier
+// and four LDS reads (partners within a wave by shuffles: 21 and 37 us).
+constexpr int kSmallThreads = 1024;
+static_assert(kChunk == 2 * kSmallThreads, "a pair per thread");
+__global__ __launch_bounds__(kSmallThreads) void k_small_tree(PointSegs segs, int32_t n, int32_t max_leaf,
+                                                              uint64_t* keys, int2* pts, int32_t* perm_local,
+                                                              int8_t* cl, int32_t* bbox, int32_t* stats) {
+    constexpr int NH = kMaxLevels + 2, kPer = kChunk / kSmallThreads;
+    __shared__ uint64_t sk[kChunk];
+    __shared__ uint16_t si[kChunk];
+    __shared__ int32_t box[4], h[NH], maxc;
+    const int tid = int(threadIdx.x);
+    if (tid < 2) box[tid] = INT_MAX;
+    else if (tid < 4) box[tid] = INT_MIN;
+    else if (tid == 4) maxc = -1;
+    if (tid < NH) h[tid] = 0;
+    const int2* a = reinterpret_cast<const int2*>(segs.n > 1 ? segs.ptr[0] : segs.one);
+    const int2* b = segs.n > 1 ? reinterpret_cast<const int2*>(segs.ptr[1]) : nullptr;
+    const int32_t na = segs.n > 1 ? segs.off[1] : n;   // points of the first segment
+    int2 p[kPer];
+    int v[4] = {INT_MAX, INT_MAX, INT_MIN, INT_MIN};
+    #pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        const int32_t i = min(tid + k * kSmallThreads, n - 1);
+        p[k] = i < na ? a[i] : b[i - na];
+        v[0] = min(v[0], p[k].x); v[1] = min(v[1], p[k].y);
+        v[2] = max(v[2], p[k].x); v[3] = max(v[3], p[k].y);
+    }
+    #pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        v[0] = min(v[0], __shfl_xor(v[0], o, 64)); v[1] = min(v[1], __shfl_xor(v[1], o, 64));
+        v[2] = max(v[2], __shfl_xor(v[2], o, 64)); v[3] = max(v[3], __shfl_xor(v[3], o, 64));
+    }
+    __syncthreads();
+    if ((tid & 63) == 0) {
+        atomicMin(&box[0], v[0]); atomicMin(&box[1], v[1]);
+        atomicMax(&box[2], v[2]); atomicMax(&box[3], v[3]);
+    }
+    __syncthreads();
+    const int64_t extent = max(int64_t(box[2]) - box[0], int64_t(box[3]) - box[1]) + 1;
+    int D = 0;
+    while (D < 32 && (int64_t(1) << D) < extent) ++D;
+    int N = 64;   // a power of two of sort slots; those past the points hold the greatest pair
+    while (N < n) N <<= 1;
+    #pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        const int i = tid + k * kSmallThreads;
+        if (i < N) {
+            sk[i] = i < n ? spread_bits(uint32_t(int64_t(p[k].x) - box[0])) |
+                                (spread_bits(uint32_t(int64_t(p[k].y) - box[1])) << 1)
+                          : ~0ull;
+            si[i] = uint16_t(i);
+        }
+    }
+    for (int size = 2; size <= N; size <<= 1)
+        for (int o = size >> 1; o > 0; o >>= 1) {
+            __syncthreads();
+            if (tid < N / 2) {   // the pair i, i + o
+                const int i = 2 * tid - (tid & (o - 1)), j = i + o;
+                const uint64_t x = sk[i], y = sk[j];
+                const uint16_t xi = si[i], yi = si[j];
+                const bool greater = x > y || (x == y && xi > yi), up = (i & size) == 0;
+                if (greater == up) {
+                    sk[i] = y;
+                    sk[j] = x;
+                    si[i] = yi;
+                    si[j] = xi;
+                }
+            }
+        }
+    __syncthreads();
+    int mc = -1;
+    #pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        const int s = tid + k * kSmallThreads;
+        if (s >= n) continue;
+        const uint64_t m = sk[s];
+        keys[s] = m;
+        pts[s] = make_int2(int32_t(compact_bits(m)), int32_t(compact_bits(m >> 1)));
+        perm_local[s] = int32_t(si[s]);
+        const int c = s == 0 ? -1 : common_levels(m, sk[s - 1], D);
+        cl[s] = int8_t(c);
+        atomicAdd(&h[c + 1], 1);
+        if (s + max_leaf < n) mc = max(mc, common_levels(m, sk[s + max_leaf], D));
+    }
+    #pragma unroll
+    for (int o = 32; o > 0; o >>= 1) mc = max(mc, __shfl_xor(mc, o, 64));
+    if ((tid & 63) == 0) atomicMax(&maxc, mc);
+    __syncthreads();
+    if (tid < 4) bbox[tid] = box[tid];
+    if (tid < NH) stats[tid] = h[tid];
+    if (tid == NH) stats[NH] = max(maxc, 0);   // zero where no count is taken, as the totals start
+}
+
 // One thread per (leaf, level): the leaf that starts a box of that level writes the box and
 // its parent link.
 __global__ void k_build_boxes(const int32_t* lscan, const int8_t* leaf_cl, const int32_t* leaf_pt0,
@@ -1431,6 +1528,13 @@ void launch_bbox_final(const int32_t* part, const int32_t* chunk_first, const in
                        int32_t max_leaf, int32_t* bbox, InstInfo* inst, int32_t* dmax, hipStream_t st) {
     hipLaunchKernelGGL(k_bbox_final, dim3(static_cast<unsigned>(K)), dim3(kBlock), 0, st, part, chunk_first, pt_off,
                        max_leaf, bbox, inst, dmax);
+}
+
+void launch_small_tree(const PointSegs& segs, int32_t n, int32_t max_leaf, uint64_t* keys, int32_t* pts,
+                       int32_t* perm_local, int8_t* cl, int32_t* bbox, int32_t* stats, hipStream_t st) {
+    if (n > kChunk || segs.n > 2) throw std::logic_error("tree too large for one block");
+    hipLaunchKernelGGL(k_small_tree, dim3(1), dim3(kSmallThreads), 0, st, segs, n, max_leaf, keys,
+                       reinterpret_cast<int2*>(pts), perm_local, cl, bbox, stats);
 }
 
 void launch_keys(const PointSegs& segs, int32_t K, const InstInfo* inst, const int32_t* dmax,

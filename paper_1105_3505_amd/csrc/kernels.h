@@ -214,6 +214,10 @@ void launch_bbox_chunks(const PointSegs& segs, const Chunk* chunks, int32_t nchu
 // ranges and N_leaf (max_leaf, 0 if not positive) into inst; the deepest depth into *dmax
 void launch_bbox_final(const int32_t* part, const int32_t* chunk_first, const int32_t* pt_off, int32_t K,
                        int32_t max_leaf, int32_t* bbox, InstInfo* inst, int32_t* dmax, hipStream_t st);
+// one tree of at most kChunk points, in one or two segments, at once: sorted keys and points, indices, levels shared
+// with the point before (cl), and its root box and level statistics to host memory (as the kernels below)
+void launch_small_tree(const PointSegs& segs, int32_t n, int32_t max_leaf, uint64_t* keys, int32_t* pts,
+                       int32_t* perm_local, int8_t* cl, int32_t* bbox, int32_t* stats, hipStream_t st);
 // keys and indices of the points (root boxes from inst, the deepest depth from *dmax);
 // zeroes zero[0, nzero); with radix_scratch (of radix_scratch_bytes(n)) also the sort's tile
 // counts of the lowest digit
