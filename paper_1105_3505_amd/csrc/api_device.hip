@@ -2373,6 +2373,7 @@ lfmm_status lfmm_plan_destroy(lfmm_plan* pl) {
             pl->mem_small.release_after(done);
             pl->mem_pts.release_after(done);
             pl->mem_box.release_after(done);
+            pl->mem_ad.release_after(done);
             if (pl->h_exec) {
                 pl->ctx->pinned.release_after(pl->h_exec, pl->h_exec_cls, done);
                 pl->h_exec = nullptr;
