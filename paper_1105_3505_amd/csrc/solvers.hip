@@ -60,7 +60,7 @@ constexpr int kGsBlocks = 256;   // at most: one per CU
 template <bool UPDATE, bool NORM>
 __global__ __launch_bounds__(kGsThreads) void k_gs(const double* V, int64_t ld, int k, int kp, double* w, int64_t n,
                                                    int64_t per, int nb, const double* part_in, double* h_out,
-                                                   double* part_out) {
+                                                   double* part_out, double* part_copy) {
     __shared__ double hs[576];   // restart + 1 <= 513 coefficients, in whole rounds of 64
     __shared__ double red[kGsWaves][64];
     const int tid = int(threadIdx.x), lane = tid & 63, wave = tid >> 6;
@@ -112,7 +112,10 @@ __global__ __launch_bounds__(kGsThreads) void k_gs(const double* V, int64_t ld, 
             double a = 0.0;
             for (int q = 0; q < kGsWaves; ++q) a += red[q][tid];
             for (int o = 32; o > 0; o >>= 1) a += __shfl_xor(a, o, 64);
-            if (tid == 0) part_out[blockIdx.x] = a;
+            if (tid == 0) {
+                part_out[blockIdx.x] = a;
+                if (part_copy) part_copy[blockIdx.x] = a;
+            }
         }
     } else {
         for (int j0 = 0; j0 < k; j0 += 64) {   // up to four groups of 16 vectors a pass
@@ -179,6 +182,23 @@ __global__ void k_fill(double* out, double v, int64_t n) {
 __global__ void k_scale_copy(const double* a, double s, double* out, int64_t n) {
     const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (i < n) out[i] = s * a[i];
+}
+
+// out = w / |w|, with |w|^2 the sum of the nb <= kGsBlocks shares sq, added in turn as on the host
+__global__ __launch_bounds__(kThreads) void k_normalise(const double* w, const double* sq, int nb, double* out, int64_t n) {
+    static_assert(kGsBlocks <= kThreads, "a share per thread");
+    __shared__ double p[kGsBlocks], s;
+    if (int(threadIdx.x) < nb) p[threadIdx.x] = sq[threadIdx.x];
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double a = 0.0;
+        #pragma unroll 8
+        for (int b = 0; b < nb; ++b) a += p[b];
+        s = 1.0 / sqrt(max(a, 0.0));
+    }
+    __syncthreads();
+    const int64_t i = int64_t(blockIdx.x) * kThreads + threadIdx.x;
+    if (i < n) out[i] = s * w[i];
 }
 
 // out = a - b
@@ -274,8 +294,10 @@ struct Gmres {
     DevBuf<double> V, part, part2, y, r;
     double* w = nullptr;
     // pinned, written by the kernels: coefficients of both passes and the blocks' shares of |w|^2 (a
-    // copy to pageable memory behind them left the device idle for 30 us more an iteration)
+    // copy to pageable memory behind them left the device idle for 30 us more an iteration), of the even
+    // and of the odd iterations, and what tells that they are there
     double* h = nullptr;
+    hipEvent_t ready[2] = {nullptr, nullptr};
 
     Gmres() = default;
     Gmres(const Gmres&) = delete;
@@ -290,6 +312,10 @@ struct Gmres {
         r.free();
         if (h) (void)hipHostFree(h);
         h = nullptr;
+        for (hipEvent_t& e : ready) {
+            if (e) (void)hipEventDestroy(e);
+            e = nullptr;
+        }
         n = 0;
     }
 
@@ -316,7 +342,8 @@ struct Gmres {
         y.alloc(size_t(m));
         part.alloc(size_t(nb) * size_t(kp));
         part2.alloc(size_t(nb) * size_t(kp));
-        SOLVER_HIP(hipHostMalloc(reinterpret_cast<void**>(&h), size_t(2 * kp + nb) * sizeof(double), 0));
+        SOLVER_HIP(hipHostMalloc(reinterpret_cast<void**>(&h), 2 * size_t(2 * kp + nb) * sizeof(double), 0));
+        for (hipEvent_t& e : ready) SOLVER_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
         hipLaunchKernelGGL(k_pad_rows, dim3(unsigned(m + 2)), dim3(kGsTile), 0, st, V.p, ld, n_);
         n = n_;
     }
@@ -324,18 +351,18 @@ struct Gmres {
     // part = the blocks' shares of V[0..k)^T w
     void dots(int k, hipStream_t st) {
         hipLaunchKernelGGL((k_gs<false, false>), dim3(unsigned(nb)), dim3(kGsThreads), 0, st, V.p, ld, k, kp, w, n, per,
-                           nb, nullptr, nullptr, part.p);
+                           nb, nullptr, nullptr, part.p, nullptr);
     }
 
     double norm(const double* x, hipStream_t st) {
         hipLaunchKernelGGL((k_gs<false, true>), dim3(unsigned(nb)), dim3(kGsThreads), 0, st, V.p, ld, 0, kp,
-                           const_cast<double*>(x), n, per, nb, nullptr, nullptr, h);
+                           const_cast<double*>(x), n, per, nb, nullptr, nullptr, h, nullptr);
         SOLVER_HIP(hipStreamSynchronize(st));
         return std::sqrt(std::max(std::accumulate(h, h + nb, 0.0), 0.0));
     }
 
     lfmm_solver_stats run(const std::function<void(const double*, double*)>& apply, const double* b, double* x,
-                          double tol, int max_iter, hipStream_t st) {
+                          double tol, int max_iter, bool ahead, hipStream_t st) {
         lfmm_solver_stats out{};
         hipLaunchKernelGGL(k_fill, dim3(blocks_for(n)), dim3(kThreads), 0, st, x, 0.0, n);
         const double bn = norm(b, st);
@@ -353,24 +380,38 @@ struct Gmres {
             hipLaunchKernelGGL(k_scale_copy, dim3(blocks_for(n)), dim3(kThreads), 0, st, r.p, 1.0 / beta, V.p, n);
             std::fill(g.begin(), g.end(), 0.0);
             g[0] = beta;
-            int j = 0;
-            for (; j < m; ++j) {
+            // Iteration j's kernels: classical Gram-Schmidt, twice: h = V^T w; w -= V h (both passes
+            // summed); the two coefficient sets and |w|^2 come back together
+            auto enqueue = [&](int j) {
+                double* hj = h + (j & 1) * (2 * kp + nb);
                 apply(V.p + size_t(j) * size_t(ld), w);
-                // classical Gram-Schmidt, twice: h = V^T w; w -= V h (both passes summed); the
-                // two coefficient sets and |w|^2 come back in one read
                 dots(j + 1, st);
                 hipLaunchKernelGGL((k_gs<true, false>), dim3(unsigned(nb)), dim3(kGsThreads), 0, st, V.p, ld, j + 1, kp,
-                                   w, n, per, nb, part.p, h, part2.p);
+                                   w, n, per, nb, part.p, hj, part2.p, nullptr);
                 hipLaunchKernelGGL((k_gs<true, true>), dim3(unsigned(nb)), dim3(kGsThreads), 0, st, V.p, ld, j + 1, kp,
-                                   w, n, per, nb, part2.p, h + kp, h + 2 * kp);
-                SOLVER_HIP(hipStreamSynchronize(st));
+                                   w, n, per, nb, part2.p, hj + kp, hj + 2 * kp, part.p);
+                SOLVER_HIP(hipEventRecord(ready[j & 1], st));
+            };
+            auto enqueue_next = [&](int j) {
+                hipLaunchKernelGGL(k_normalise, dim3(blocks_for(n)), dim3(kThreads), 0, st, w, part.p, nb,
+                                   V.p + size_t(j + 1) * size_t(ld), n);
+                enqueue(j + 1);
+            };
+            enqueue(0);
+            int j = 0;
+            for (; j < m; ++j) {
+                // The next iteration goes out before this one's results are read, so that the device does
+                // not wait for the host (a third of an iteration on 50,000 unknowns), unless the residual's
+                // last step, taken again, would end the solve: then it would be in vain
+                const bool likely_last = j > 0 && g[size_t(j)] * g[size_t(j)] <= tol * bn * std::fabs(g[size_t(j) - 1]);
+                const bool sent = ahead && j + 1 < m && iters + 1 < max_iter && !likely_last;
+                if (sent) enqueue_next(j);
+                const double* hj = h + (j & 1) * (2 * kp + nb);
+                SOLVER_HIP(hipEventSynchronize(ready[j & 1]));
                 SOLVER_HIP(hipGetLastError());
-                const double wn = std::sqrt(std::max(std::accumulate(h + 2 * kp, h + 2 * kp + nb, 0.0), 0.0));
-                for (int i = 0; i <= j; ++i) Hat(i, j) = h[i] + h[kp + i];
+                const double wn = std::sqrt(std::max(std::accumulate(hj + 2 * kp, hj + 2 * kp + nb, 0.0), 0.0));
+                for (int i = 0; i <= j; ++i) Hat(i, j) = hj[i] + hj[kp + i];
                 Hat(j + 1, j) = wn;
-                if (wn > 0.0)
-                    hipLaunchKernelGGL(k_scale_copy, dim3(blocks_for(n)), dim3(kThreads), 0, st, w, 1.0 / wn,
-                                       V.p + size_t(j + 1) * size_t(ld), n);
                 // previous rotations, then a new one that zeroes H(j+1, j)
                 for (int i = 0; i < j; ++i) {
                     const double a = Hat(i, j), c = Hat(i + 1, j);
@@ -391,6 +432,7 @@ struct Gmres {
                     done = true;
                     break;
                 }
+                if (!sent && j + 1 < m) enqueue_next(j);
             }
             if (!done) j = m;
             // y = H(0..j, 0..j)^-1 g; x += V y
@@ -446,6 +488,9 @@ lfmm_status run_guarded(F&& f) {
 void check(lfmm_status s) {
     if (s < 0) throw Status{s, lfmm_last_error()};
 }
+
+// executes that check their loads read them back, and would refuse those of an iteration sent in vain
+bool runs_ahead(const lfmm_ctx* ctx) { return !(ctx_flags(ctx) & LFMM_FLAG_CHECK_LOADS); }
 
 hipStream_t as_stream(void* s) { return reinterpret_cast<hipStream_t>(s); }
 
@@ -583,7 +628,7 @@ lfmm_status lfmm_inclusions_solve(lfmm_inclusions* inc, double c1, double c2, co
         };
         Gmres& gm = inc->gm;
         gm.setup(nn, std::min<int>(restart, int(std::max<int64_t>(nn, 1))), st);
-        const lfmm_solver_stats r = gm.run(apply, inc->rhs.p, mu_dev, tol, max_iter, st);
+        const lfmm_solver_stats r = gm.run(apply, inc->rhs.p, mu_dev, tol, max_iter, runs_ahead(inc->ctx), st);
         SOLVER_HIP(hipStreamSynchronize(st));
         gm.trim();
         if (stats) *stats = r;
@@ -689,7 +734,7 @@ lfmm_status lfmm_dirichlet_solve(lfmm_dirichlet* dir, const double* g_dev, const
         };
         Gmres& gm = dir->gm;
         gm.setup(dir->n, std::min<int>(restart, int(std::max<int64_t>(dir->n, 1))), st);
-        const lfmm_solver_stats r = gm.run(apply, g_dev, q_dev, tol, max_iter, st);
+        const lfmm_solver_stats r = gm.run(apply, g_dev, q_dev, tol, max_iter, runs_ahead(dir->ctx), st);
         SOLVER_HIP(hipStreamSynchronize(st));
         gm.trim();
         if (stats) *stats = r;
