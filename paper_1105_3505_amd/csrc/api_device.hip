@@ -1483,10 +1483,12 @@ void build_forest(lfmm_plan* pl, int32_t K, const InstanceInput* in, int32_t max
 // the quadrant table of side 32 (a curve, side 32, 8: gains as above); below kOverlapRanges of them
 // (16,384 boundary nodes, side 16: 6, the near field 14 us), in turn is faster (a solve of 26
 // iterations 4.09 / 4.25 ms).
+// Never in the static workspace: its solve makes no stream and no event.
 constexpr int32_t kOverlapLeaves[2] = {128, 16384};
 constexpr double kOverlapRanges = 7.0;
 bool beside(lfmm_plan* pl, hipStream_t st) {
-    if (pl->adaptive || pl->nleaf < kOverlapLeaves[0] || pl->nleaf > kOverlapLeaves[1] || pl->m2l.n <= 0) return false;
+    if (pl->sreg || pl->adaptive || pl->nleaf < kOverlapLeaves[0] || pl->nleaf > kOverlapLeaves[1] || pl->m2l.n <= 0)
+        return false;
     int64_t side = 0;
     for (const CachedOps* o : pl->ops) side = std::max(side, int64_t(o->dev.leaf_side));
     const double groups = pl->nq, fill = double(pl->nleaf) / (4.0 * groups);
