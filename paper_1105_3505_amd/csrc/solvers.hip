@@ -16,6 +16,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <exception>
 #include <functional>
 #include <limits>
 #include <memory>
@@ -458,6 +459,19 @@ struct Gmres {
     }
 };
 
+// While an exception passes through: waits for the stream, whose kernels (an iteration sent ahead among
+// them) may still write the solver's buffers, then frees these, so that the next solve starts anew.
+struct ReleaseOnUnwind {
+    Gmres& gm;
+    hipStream_t st;
+    int pending = std::uncaught_exceptions();
+    ~ReleaseOnUnwind() {
+        if (std::uncaught_exceptions() <= pending) return;
+        (void)hipStreamSynchronize(st);
+        gm.release();
+    }
+};
+
 lfmm_status check_solver_options(const lfmm_solver_options* o, double* tol, int* max_iter, int* restart) {
     *tol = 1e-12;
     *max_iter = 500;
@@ -627,6 +641,7 @@ lfmm_status lfmm_inclusions_solve(lfmm_inclusions* inc, double c1, double c2, co
                                inc->s.p, in, 1.0, 1.0, o, nn);
         };
         Gmres& gm = inc->gm;
+        ReleaseOnUnwind unwind{gm, st};
         gm.setup(nn, std::min<int>(restart, int(std::max<int64_t>(nn, 1))), st);
         const lfmm_solver_stats r = gm.run(apply, inc->rhs.p, mu_dev, tol, max_iter, runs_ahead(inc->ctx), st);
         SOLVER_HIP(hipStreamSynchronize(st));
@@ -733,6 +748,7 @@ lfmm_status lfmm_dirichlet_solve(lfmm_dirichlet* dir, const double* g_dev, const
             check(lfmm_execute(dir->plan, dir->f2.p, o, stream));
         };
         Gmres& gm = dir->gm;
+        ReleaseOnUnwind unwind{gm, st};
         gm.setup(dir->n, std::min<int>(restart, int(std::max<int64_t>(dir->n, 1))), st);
         const lfmm_solver_stats r = gm.run(apply, g_dev, q_dev, tol, max_iter, runs_ahead(dir->ctx), st);
         SOLVER_HIP(hipStreamSynchronize(st));
