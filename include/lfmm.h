@@ -421,7 +421,9 @@ lfmm_status lfmm_server_destroy(lfmm_server* srv);
 /* Restarted GMRES (classical Gram-Schmidt run twice) on device vectors; the operator is applied
  * through resident plans.  tol: relative residual |b - A x| / |b| (default 1e-12); max_iter:
  * default 500; restart: Krylov dimension per cycle (default 50, at most 512).  Fields <= 0
- * take the defaults. */
+ * take the defaults.  A solve's vectors (restart + 4 of them, and partial sums) are taken from
+ * the context's cached blocks up to 128 MiB, else allocated; either way they are given back
+ * before it returns, also on an error: between solves an object holds none. */
 typedef struct lfmm_solver_options {
     double tol;
     int32_t max_iter;

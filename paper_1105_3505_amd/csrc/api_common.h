@@ -29,6 +29,10 @@ void plan_destroy_completed(lfmm_plan* plan);
 // for the stream.
 lfmm_status root_bits_of(lfmm_ctx* ctx, int32_t K, const int64_t* n, const int32_t* const* xy, void* stream,
                          int32_t* bits);
+// Device memory, or pinned host memory that kernels address, from a context's pools of cached blocks;
+// given back by ctx_release once the device's work on it is done.
+lfmm_status ctx_acquire(lfmm_ctx* ctx, size_t bytes, bool pinned, void** p, size_t* size_class);
+void ctx_release(lfmm_ctx* ctx, void* p, size_t size_class, bool pinned);
 // Device of a context.
 int ctx_device(const lfmm_ctx* ctx);
 // Option flags of a context (LFMM_FLAG_*).

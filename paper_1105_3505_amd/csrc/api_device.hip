@@ -1871,6 +1871,18 @@ lfmm_status lfmm::root_bits_of(lfmm_ctx* ctx, int32_t K, const int64_t* n, const
     });
 }
 
+lfmm_status lfmm::ctx_acquire(lfmm_ctx* ctx, size_t bytes, bool pinned, void** p, size_t* size_class) {
+    return guarded([&]() -> lfmm_status {
+        *p = pinned ? ctx->pinned.acquire(bytes, size_class) : ctx->pool.acquire(bytes, size_class);
+        return LFMM_OK;
+    });
+}
+
+void lfmm::ctx_release(lfmm_ctx* ctx, void* p, size_t size_class, bool pinned) {
+    if (pinned) ctx->pinned.release(p, size_class);
+    else ctx->pool.release(p, size_class);
+}
+
 extern "C" {
 
 lfmm_status lfmm_ctx_create(int32_t device, const lfmm_options* opt, lfmm_ctx** out) {

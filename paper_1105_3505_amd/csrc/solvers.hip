@@ -16,7 +16,6 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
-#include <exception>
 #include <functional>
 #include <limits>
 #include <memory>
@@ -281,121 +280,131 @@ struct Status {
     std::string msg;
 };
 
+void check(lfmm_status s) {
+    if (s < 0) throw Status{s, lfmm_last_error()};
+}
+
 // ---- restarted GMRES ----------------------------------------------------------------------------
 
 // Solves A x = b (device vectors of n) by GMRES(m) with x0 = 0; apply(in, out) enqueues A in
 // on the stream.  Stops when the relative residual |b - A x| / |b| estimated by the Givens
 // recurrence is <= tol, or after max_iter iterations; then reports the true relative residual.
 struct Gmres {
-    int64_t n = 0;
-    int m = 0;
-    int64_t ld = 0, per = 0;   // elements of a row of V, of a block's slice
-    int kp = 0, nb = 0;        // coefficients a block's partials hold room for; blocks
-    // V: m + 1 rows and w; part, part2: the blocks' shares of either pass's coefficients
-    DevBuf<double> V, part, part2, y, r;
-    double* w = nullptr;
+    lfmm_ctx* ctx;
+    hipStream_t st;
+    int64_t n;
+    int m;
+    int64_t ld, per;   // elements of a row of V, of a block's slice
+    int kp, nb;        // coefficients a block's partials hold room for; blocks
+    // V: m + 1 rows and w; part, part2: the blocks' shares of either pass's coefficients; rhs: room for the
+    // caller's right-hand side
+    double *V = nullptr, *w = nullptr, *part = nullptr, *part2 = nullptr, *y = nullptr, *r = nullptr, *rhs = nullptr;
     // pinned, written by the kernels: coefficients of both passes and the blocks' shares of |w|^2 (a
     // copy to pageable memory behind them left the device idle for 30 us more an iteration), of the even
     // and of the odd iterations, and what tells that they are there
     double* h = nullptr;
     hipEvent_t ready[2] = {nullptr, nullptr};
 
-    Gmres() = default;
-    Gmres(const Gmres&) = delete;
-    Gmres& operator=(const Gmres&) = delete;
-    ~Gmres() { release(); }
+    // The workspace of one solve.  Up to kPooledBytes it is a block of the context's pool, so that solves
+    // one after another, of this object or others, neither allocate (hipMalloc and hipFree on every solve,
+    // with the copies named above: 35 iterations on 50,000 elements 7.1 ms, without 6.2) nor hold more than
+    // one such block between them; above, it is allocated and freed.
+    static constexpr size_t kPooledBytes = size_t(128) << 20;
+    void* dev = nullptr;
+    size_t dev_class = 0, host_class = 0;   // of the pooled blocks; dev_class 0: not pooled
 
-    void release() {
-        V.free();
-        part.free();
-        part2.free();
-        y.free();
-        r.free();
-        if (h) (void)hipHostFree(h);
-        h = nullptr;
-        for (hipEvent_t& e : ready) {
-            if (e) (void)hipEventDestroy(e);
-            e = nullptr;
-        }
-        n = 0;
-    }
-
-    // The buffers belong to the solver's object, whose solves share its other buffers as well; a basis
-    // of more than kKeepBytes is given back after the solve.  (Allocated and freed on every solve, and
-    // with the copies named above, 35 iterations on 50,000 elements took 7.1 ms, now 6.2.)
-    static constexpr size_t kKeepBytes = size_t(256) << 20;
-    void trim() {
-        if (V.n * sizeof(double) > kKeepBytes) release();
-    }
-
-    void setup(int64_t n_, int m_, hipStream_t st) {
-        if (n == n_ && m == m_) return;
-        release();
-        m = m_;
-        const int64_t tiles = (n_ + kGsTile - 1) / kGsTile;
+    Gmres(lfmm_ctx* ctx_, int64_t n_, int restart, hipStream_t st_)
+        : ctx(ctx_), st(st_), n(n_), m(int(std::min<int64_t>(restart, n_))) {
+        const int64_t tiles = (n + kGsTile - 1) / kGsTile;
         ld = tiles * kGsTile;
         per = (tiles + kGsBlocks - 1) / kGsBlocks * kGsTile;
         nb = int((ld + per - 1) / per);
         kp = (m + 1 + 63) / 64 * 64;
-        V.alloc(size_t(m + 2) * size_t(ld));
-        w = V.p + size_t(m + 1) * size_t(ld);
-        r.alloc(size_t(n_));
-        y.alloc(size_t(m));
-        part.alloc(size_t(nb) * size_t(kp));
-        part2.alloc(size_t(nb) * size_t(kp));
-        SOLVER_HIP(hipHostMalloc(reinterpret_cast<void**>(&h), 2 * size_t(2 * kp + nb) * sizeof(double), 0));
-        for (hipEvent_t& e : ready) SOLVER_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
-        hipLaunchKernelGGL(k_pad_rows, dim3(unsigned(m + 2)), dim3(kGsTile), 0, st, V.p, ld, n_);
-        n = n_;
+        const size_t basis = size_t(m + 2) * size_t(ld), share = size_t(nb) * size_t(kp);
+        const size_t bytes = (basis + 2 * share + size_t(kp) + 2 * size_t(ld)) * sizeof(double);
+        try {
+            if (bytes <= kPooledBytes) check(ctx_acquire(ctx, bytes, false, &dev, &dev_class));
+            else SOLVER_HIP(hipMalloc(&dev, bytes));
+            V = static_cast<double*>(dev);   // (all pieces are whole tiles or whole rounds of 64)
+            w = V + size_t(m + 1) * size_t(ld);
+            part = V + basis;
+            part2 = part + share;
+            y = part2 + share;
+            r = y + kp;
+            rhs = r + ld;
+            void* p = nullptr;
+            check(ctx_acquire(ctx, 2 * size_t(2 * kp + nb) * sizeof(double), true, &p, &host_class));
+            h = static_cast<double*>(p);
+            for (hipEvent_t& e : ready) SOLVER_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+        } catch (...) {
+            release();
+            throw;
+        }
+        hipLaunchKernelGGL(k_pad_rows, dim3(unsigned(m + 2)), dim3(kGsTile), 0, st, V, ld, n);
+    }
+    Gmres(const Gmres&) = delete;
+    Gmres& operator=(const Gmres&) = delete;
+    // After an error in a solve, kernels (an iteration sent ahead among them) may still write the workspace
+    ~Gmres() {
+        (void)hipStreamSynchronize(st);
+        release();
+    }
+
+    void release() {
+        for (hipEvent_t e : ready)
+            if (e) (void)hipEventDestroy(e);
+        if (h) ctx_release(ctx, h, host_class, true);
+        if (dev && dev_class) ctx_release(ctx, dev, dev_class, false);
+        else if (dev) (void)hipFree(dev);
     }
 
     // part = the blocks' shares of V[0..k)^T w
-    void dots(int k, hipStream_t st) {
-        hipLaunchKernelGGL((k_gs<false, false>), dim3(unsigned(nb)), dim3(kGsThreads), 0, st, V.p, ld, k, kp, w, n, per,
-                           nb, nullptr, nullptr, part.p, nullptr);
+    void dots(int k) {
+        hipLaunchKernelGGL((k_gs<false, false>), dim3(unsigned(nb)), dim3(kGsThreads), 0, st, V, ld, k, kp, w, n, per,
+                           nb, nullptr, nullptr, part, nullptr);
     }
 
-    double norm(const double* x, hipStream_t st) {
-        hipLaunchKernelGGL((k_gs<false, true>), dim3(unsigned(nb)), dim3(kGsThreads), 0, st, V.p, ld, 0, kp,
+    double norm(const double* x) {
+        hipLaunchKernelGGL((k_gs<false, true>), dim3(unsigned(nb)), dim3(kGsThreads), 0, st, V, ld, 0, kp,
                            const_cast<double*>(x), n, per, nb, nullptr, nullptr, h, nullptr);
         SOLVER_HIP(hipStreamSynchronize(st));
         return std::sqrt(std::max(std::accumulate(h, h + nb, 0.0), 0.0));
     }
 
     lfmm_solver_stats run(const std::function<void(const double*, double*)>& apply, const double* b, double* x,
-                          double tol, int max_iter, bool ahead, hipStream_t st) {
+                          double tol, int max_iter, bool ahead) {
         lfmm_solver_stats out{};
         hipLaunchKernelGGL(k_fill, dim3(blocks_for(n)), dim3(kThreads), 0, st, x, 0.0, n);
-        const double bn = norm(b, st);
+        const double bn = norm(b);
         if (bn == 0.0) {
             out.converged = 1;
             return out;
         }
         std::vector<double> H(size_t(m + 1) * m), cs(m), sn(m), g(m + 1);
         auto Hat = [&](int i, int j) -> double& { return H[size_t(i) * m + size_t(j)]; };
-        SOLVER_HIP(hipMemcpyAsync(r.p, b, size_t(n) * sizeof(double), hipMemcpyDeviceToDevice, st));
+        SOLVER_HIP(hipMemcpyAsync(r, b, size_t(n) * sizeof(double), hipMemcpyDeviceToDevice, st));
         double beta = bn;
         int iters = 0;
         bool done = false;
         while (!done) {
-            hipLaunchKernelGGL(k_scale_copy, dim3(blocks_for(n)), dim3(kThreads), 0, st, r.p, 1.0 / beta, V.p, n);
+            hipLaunchKernelGGL(k_scale_copy, dim3(blocks_for(n)), dim3(kThreads), 0, st, r, 1.0 / beta, V, n);
             std::fill(g.begin(), g.end(), 0.0);
             g[0] = beta;
             // Iteration j's kernels: classical Gram-Schmidt, twice: h = V^T w; w -= V h (both passes
             // summed); the two coefficient sets and |w|^2 come back together
             auto enqueue = [&](int j) {
                 double* hj = h + (j & 1) * (2 * kp + nb);
-                apply(V.p + size_t(j) * size_t(ld), w);
-                dots(j + 1, st);
-                hipLaunchKernelGGL((k_gs<true, false>), dim3(unsigned(nb)), dim3(kGsThreads), 0, st, V.p, ld, j + 1, kp,
-                                   w, n, per, nb, part.p, hj, part2.p, nullptr);
-                hipLaunchKernelGGL((k_gs<true, true>), dim3(unsigned(nb)), dim3(kGsThreads), 0, st, V.p, ld, j + 1, kp,
-                                   w, n, per, nb, part2.p, hj + kp, hj + 2 * kp, part.p);
+                apply(V + size_t(j) * size_t(ld), w);
+                dots(j + 1);
+                hipLaunchKernelGGL((k_gs<true, false>), dim3(unsigned(nb)), dim3(kGsThreads), 0, st, V, ld, j + 1, kp,
+                                   w, n, per, nb, part, hj, part2, nullptr);
+                hipLaunchKernelGGL((k_gs<true, true>), dim3(unsigned(nb)), dim3(kGsThreads), 0, st, V, ld, j + 1, kp,
+                                   w, n, per, nb, part2, hj + kp, hj + 2 * kp, part);
                 SOLVER_HIP(hipEventRecord(ready[j & 1], st));
             };
             auto enqueue_next = [&](int j) {
-                hipLaunchKernelGGL(k_normalise, dim3(blocks_for(n)), dim3(kThreads), 0, st, w, part.p, nb,
-                                   V.p + size_t(j + 1) * size_t(ld), n);
+                hipLaunchKernelGGL(k_normalise, dim3(blocks_for(n)), dim3(kThreads), 0, st, w, part, nb,
+                                   V + size_t(j + 1) * size_t(ld), n);
                 enqueue(j + 1);
             };
             enqueue(0);
@@ -443,12 +452,12 @@ struct Gmres {
                 for (int k = i + 1; k < j; ++k) s -= Hat(i, k) * c[size_t(k)];
                 c[size_t(i)] = Hat(i, i) != 0.0 ? s / Hat(i, i) : 0.0;
             }
-            SOLVER_HIP(hipMemcpyAsync(y.p, c.data(), size_t(j) * sizeof(double), hipMemcpyHostToDevice, st));
-            hipLaunchKernelGGL(k_combine, dim3(blocks_for(n)), dim3(kThreads), 0, st, V.p, ld, j, y.p, 1.0, x, n);
+            SOLVER_HIP(hipMemcpyAsync(y, c.data(), size_t(j) * sizeof(double), hipMemcpyHostToDevice, st));
+            hipLaunchKernelGGL(k_combine, dim3(blocks_for(n)), dim3(kThreads), 0, st, V, ld, j, y, 1.0, x, n);
             // true residual r = b - A x (also the next cycle's start)
             apply(x, w);
-            hipLaunchKernelGGL(k_sub, dim3(blocks_for(n)), dim3(kThreads), 0, st, b, w, r.p, n);
-            beta = norm(r.p, st);
+            hipLaunchKernelGGL(k_sub, dim3(blocks_for(n)), dim3(kThreads), 0, st, b, w, r, n);
+            beta = norm(r);
             if (beta <= tol * bn) done = true;
             if (iters >= max_iter) done = true;
         }
@@ -456,19 +465,6 @@ struct Gmres {
         out.rel_residual = beta / bn;
         out.converged = out.rel_residual <= tol ? 1 : 0;
         return out;
-    }
-};
-
-// While an exception passes through: waits for the stream, whose kernels (an iteration sent ahead among
-// them) may still write the solver's buffers, then frees these, so that the next solve starts anew.
-struct ReleaseOnUnwind {
-    Gmres& gm;
-    hipStream_t st;
-    int pending = std::uncaught_exceptions();
-    ~ReleaseOnUnwind() {
-        if (std::uncaught_exceptions() <= pending) return;
-        (void)hipStreamSynchronize(st);
-        gm.release();
     }
 };
 
@@ -499,10 +495,6 @@ lfmm_status run_guarded(F&& f) {
     }
 }
 
-void check(lfmm_status s) {
-    if (s < 0) throw Status{s, lfmm_last_error()};
-}
-
 // executes that check their loads read them back, and would refuse those of an iteration sent in vain
 bool runs_ahead(const lfmm_ctx* ctx) { return !(ctx_flags(ctx) & LFMM_FLAG_CHECK_LOADS); }
 
@@ -518,8 +510,7 @@ struct lfmm_inclusions {
     int64_t nn = 0;                       // nodes touched by the bars (Omega_inc)
     std::vector<int32_t> nodes;           // host copy, [nn][2]
     DevBuf<int32_t> xy, rowptr, col;
-    DevBuf<double> dlt, v, s, t, rhs;
-    Gmres gm;
+    DevBuf<double> dlt, v, s, t;
     lfmm_plan* plan = nullptr;            // the nodes, targets = sources: S on Omega_inc
     ~lfmm_inclusions() {
         if (plan) lfmm_plan_destroy(plan);
@@ -533,7 +524,6 @@ struct lfmm_dirichlet {
     DevBuf<int32_t> src;                  // [2n][2]: n + nu(n) first, then n
     DevBuf<int32_t> gam;                  // [n][2]
     DevBuf<double> f2;                    // dipole loads
-    Gmres gm;
     lfmm_plan* plan = nullptr;            // sources: the dipole ends; targets: the boundary
     ~lfmm_dirichlet() {
         if (plan) lfmm_plan_destroy(plan);
@@ -627,25 +617,21 @@ lfmm_status lfmm_inclusions_solve(lfmm_inclusions* inc, double c1, double c2, co
         const unsigned gb = blocks_for(nn);
         const int2* xy = reinterpret_cast<const int2*>(inc->xy.p);
         // right-hand side of eq. 10.4: -B S B v
-        if (!inc->rhs.p) inc->rhs.alloc(size_t(nn));
+        Gmres gm(inc->ctx, nn, restart, st);
         hipLaunchKernelGGL(k_linear, dim3(gb), dim3(kThreads), 0, st, xy, c1, c2, inc->v.p, nn);
         hipLaunchKernelGGL(k_bars, dim3(gb), dim3(kThreads), 0, st, inc->rowptr.p, inc->col.p, inc->dlt.p, inc->v.p,
                            nullptr, 0.0, 1.0, inc->t.p, nn);
         check(lfmm_execute(inc->plan, inc->t.p, inc->s.p, stream));
         hipLaunchKernelGGL(k_bars, dim3(gb), dim3(kThreads), 0, st, inc->rowptr.p, inc->col.p, inc->dlt.p, inc->s.p,
-                           nullptr, 0.0, -1.0, inc->rhs.p, nn);
+                           nullptr, 0.0, -1.0, gm.rhs, nn);
         // operator: mu -> mu + B S mu
         auto apply = [&](const double* in, double* o) {
             check(lfmm_execute(inc->plan, in, inc->s.p, stream));
             hipLaunchKernelGGL(k_bars, dim3(gb), dim3(kThreads), 0, st, inc->rowptr.p, inc->col.p, inc->dlt.p,
                                inc->s.p, in, 1.0, 1.0, o, nn);
         };
-        Gmres& gm = inc->gm;
-        ReleaseOnUnwind unwind{gm, st};
-        gm.setup(nn, std::min<int>(restart, int(std::max<int64_t>(nn, 1))), st);
-        const lfmm_solver_stats r = gm.run(apply, inc->rhs.p, mu_dev, tol, max_iter, runs_ahead(inc->ctx), st);
+        const lfmm_solver_stats r = gm.run(apply, gm.rhs, mu_dev, tol, max_iter, runs_ahead(inc->ctx));
         SOLVER_HIP(hipStreamSynchronize(st));
-        gm.trim();
         if (stats) *stats = r;
         return LFMM_OK;
     });
@@ -747,12 +733,9 @@ lfmm_status lfmm_dirichlet_solve(lfmm_dirichlet* dir, const double* g_dev, const
             hipLaunchKernelGGL(k_dipole_loads, dim3(blocks_for(dir->n)), dim3(kThreads), 0, st, in, dir->f2.p, dir->n);
             check(lfmm_execute(dir->plan, dir->f2.p, o, stream));
         };
-        Gmres& gm = dir->gm;
-        ReleaseOnUnwind unwind{gm, st};
-        gm.setup(dir->n, std::min<int>(restart, int(std::max<int64_t>(dir->n, 1))), st);
-        const lfmm_solver_stats r = gm.run(apply, g_dev, q_dev, tol, max_iter, runs_ahead(dir->ctx), st);
+        Gmres gm(dir->ctx, dir->n, restart, st);
+        const lfmm_solver_stats r = gm.run(apply, g_dev, q_dev, tol, max_iter, runs_ahead(dir->ctx));
         SOLVER_HIP(hipStreamSynchronize(st));
-        gm.trim();
         if (stats) *stats = r;
         return LFMM_OK;
     });
