@@ -1518,10 +1518,13 @@ void enqueue_passes(lfmm_plan* pl, const ExecPtrs* tab, const double* f1, double
     };
     mark(0);
     mark(1);   // the loads are gathered into Morton order by P2M itself
+    int32_t max_leaf = 0;
+    for (const InstInfo& I : pl->inst) max_leaf = std::max(max_leaf, I.max_leaf);
     for (size_t o = 0; o < pl->ops.size(); ++o) {
         const TileRange& r = pl->leaf_of_ops[o];
         launch_p2m(r.t0, r.t0 + r.n, pl->box_pt0, pl->box_pt1, pl->box_key, pl->ops[o]->dev.leaf_side, pl->pts, tab,
-                   single, pl->perm, pl->box_inst, pl->fs, pl->ops[o]->dev.leafT, pl->Q, st);
+                   single, pl->perm, pl->box_inst, pl->fs, pl->ops[o]->dev.leafT, pl->Q,
+                   double(pl->n) / double(std::max<int32_t>(pl->nleaf, 1)), max_leaf, st);
     }
     mark(2);
     // The pairs of the near field need the loads alone: for plans that leave the device partly idle they run on a
