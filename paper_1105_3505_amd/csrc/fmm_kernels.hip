@@ -28,11 +28,14 @@ constexpr int kWaves = kBlock / 64;
 constexpr int32_t kFineM2mTiles = 64;
 constexpr int32_t kFineL2lTiles = 256;
 // M2L by tiles of 128 boxes, weighted by how full their interaction lists are (m2l_weighted): the
-// 16-box kernels up to the first three counts, then, in FP64, blocks of 64 boxes, then of 128.
-// Measured on uniform points (16-box / 64-box / 128-box kernel, us): 101 tiles 49 / 53 / 81, 190
-// tiles 86 / 80 / 85, 355 tiles - / 115 / 137, 680 tiles - / 209 / 195; FP32 mixed 355 tiles 307 / - /
-// 336; bf16 101 tiles 58 / - / 75, 190 tiles 86 / - / 78.
-constexpr int32_t kFineM2lTiles = 128, kFineM2lMixedTiles = 384, kFineM2lBf16Tiles = 128, kHalfM2lTiles = 512;
+// 16-box kernels up to the first three counts, then, in FP64, blocks of 64 boxes while all blocks of all
+// (unweighted) tiles run at once (two a tile, three a compute unit), then of 128.  Measured (16-box / 64-box / 128-box
+// kernel, us), uniform points: 120 tiles 53 / 58 / 84, 152 tiles 76 / 82 / 85, 222 tiles 97 / 85 / 87, 353 tiles
+// 140 / 111 / 134, 418 tiles 165 / 159 / 136, 485 tiles 182 / 156 / 137, 677 tiles 244 / 211 / 193; clusters, 244 tiles
+// 99 / 85 / 87; a curve, 303 tiles 66 / 108 / 133; FP32 mixed 353 tiles 300 / - / 336, 418 tiles 369 / - / 345, clusters,
+// 661 tiles 551 / - / 482; bf16 120 tiles 61 / - / 76, 152 tiles 78 / - / 77, clusters, 244 tiles 104 / - / 72, a curve,
+// 303 tiles 73 / - / 82.
+constexpr int32_t kFineM2lTiles = 160, kFineM2lMixedTiles = 384, kFineM2lBf16Tiles = 144, kHalfM2lTiles = 384;
 constexpr double kPi = 3.14159265358979323846;
 constexpr double kEulerGamma = 0.57721566490153286061;
 
@@ -2763,11 +2766,11 @@ void launch_l2l_sub(const SubTree* subs, int32_t n, int depth, const SubOps& A, 
     hipLaunchKernelGGL(k_l2l_sub, dim3(unsigned(n)), dim3(kSubThreads), 0, st, subs, depth, A, box_child, U, role);
 }
 
-// Tiles weighted by the expected share of their interaction lists that exists: boxes with `children`
-// children on average have about (children / 4)^2 of the 27 (a curve's 2 children: a quarter), and the
-// 16-box kernels skip the rest.
+// Tiles weighted by the share of the 27 slots that the 16-box kernels do not skip: those that any of 16 boxes has a
+// source for.  Boxes with `children` children on average have (children / 4)^2 of the 27 each, but three children
+// (clusters) already leave hardly a slot to no box of 16, and a curve's two leave about half of them.
 static int32_t m2l_weighted(int32_t max_tiles, double children) {
-    const double w = std::min(1.0, std::max(0.0, children) / 4.0);
+    const double w = std::min(1.0, std::max(0.0, children) / 3.0);
     return int32_t(double(max_tiles) * w * w);
 }
 
