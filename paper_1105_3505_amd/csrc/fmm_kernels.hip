@@ -1669,48 +1669,73 @@ __device__ inline uint32_t sad(uint32_t a, uint32_t b, uint32_t c) {
 // per lane the 24 loads of a row's pairs each touched about 27 lines (and 64 rows of the cell-major
 // table), and the texture addresser's time on them, 46 us of the pass on 1e6 points, was its largest
 // part (21 us now).  A target's sum: six terms per lane in order, then the eight lanes' by a tree.
+// FEW (groups of at most 32 targets): all of the group's targets in turn, eight a step, each with its own leaf's
+// expansion, so that leaves of one or two targets do not take a step of sixteen each (the pass on 1e6 points of
+// N_leaf 4: 890 -> 628 us, on 7e5 in clusters of N_leaf 8 540 -> 382; with sixteen a step, 85 registers for 79 and a
+// block less per compute unit, 917).  The same bits.
 // sfar: 64 doubles of LDS of this wave.
-template <int P>
+template <int P, bool FEW>
 __device__ inline double far_rows(int32_t leaf0, int32_t nleaf, const int32_t (&bnd)[5], int32_t i0, int32_t loc,
                                   const double* leafT, const double* U, double* sfar) {
     static_assert(P == 48, "three 128-byte lines a row");
     const int lane = int(threadIdx.x) & 63, g8 = lane >> 3, l = lane & 7;
     const gptr<double2_t> T = global(reinterpret_cast<const double2_t*>(leafT)) + l;
+    const gptr<double2_t> X = global(reinterpret_cast<const double2_t*>(U)) + size_t(leaf0) * (P / 2) + l;
     auto dpp_add = [](double v, auto ctrl) -> double {
         const int2_t w = __builtin_bit_cast(int2_t, v);
         return v + __builtin_bit_cast(double, int2_t{__builtin_amdgcn_update_dpp(0, w.x, ctrl(), 0xf, 0xf, true),
                                                      __builtin_amdgcn_update_dpp(0, w.y, ctrl(), 0xf, 0xf, true)});
     };
-    for (int c = 0; c < nleaf; ++c) {
-        const int32_t b0 = c == 0 ? bnd[0] : c == 1 ? bnd[1] : c == 2 ? bnd[2] : bnd[3];
-        const int32_t b1 = c == 0 ? bnd[1] : c == 1 ? bnd[2] : c == 2 ? bnd[3] : bnd[4];
-        const int32_t t0 = max(b0 - i0, 0), t1 = min(b1 - i0, 64);   // its targets among the 64 (uniform)
-        if (t0 >= t1) continue;
-        const gptr<double2_t> u = global(reinterpret_cast<const double2_t*>(U)) + size_t(leaf0 + c) * (P / 2) + l;
-        const double2_t u0 = u[0], u1 = u[8], u2 = u[16];
-        for (int32_t t = t0; t < t1; t += 16) {
-            const int32_t ta = t + g8, tb = t + 8 + g8;
-            const size_t ra = size_t(__shfl(loc, min(ta, 63), 64)) * (P / 2), rb = size_t(__shfl(loc, min(tb, 63), 64)) * (P / 2);
-            const double2_t x0 = T[ra], x1 = T[ra + 8], x2 = T[ra + 16], y0 = T[rb], y1 = T[rb + 8], y2 = T[rb + 16];
-            double a = x0.x * u0.x, b = y0.x * u0.x;
+    auto row = [&](int32_t t) -> size_t { return size_t(__shfl(loc, min(t, 63), 64)) * (P / 2); };
+    auto tree = [&](double v) {                 // the other of the pair, the other pair of the four, the
+        v = dpp_add(v, [] { return 0xB1; });    // other four (mirrored)
+        v = dpp_add(v, [] { return 0x4E; });
+        return dpp_add(v, [] { return 0x141; });
+    };
+    if (FEW) {
+        const int32_t nt = min(bnd[4] - i0, 64);
+        for (int32_t t = 0; t < nt; t += 8) {
+            const int32_t ta = t + g8, i = min(i0 + ta, bnd[4] - 1);   // past the last target the last one's leaf
+            const gptr<double2_t> u = X + size_t((i >= bnd[1]) + (i >= bnd[2]) + (i >= bnd[3])) * (P / 2);
+            const size_t ra = row(ta);
+            const double2_t x0 = T[ra], x1 = T[ra + 8], x2 = T[ra + 16], u0 = u[0], u1 = u[8], u2 = u[16];
+            double a = x0.x * u0.x;
             a += x0.y * u0.y;
-            b += y0.y * u0.y;
             a += x1.x * u1.x;
-            b += y1.x * u1.x;
             a += x1.y * u1.y;
-            b += y1.y * u1.y;
             a += x2.x * u2.x;
-            b += y2.x * u2.x;
             a += x2.y * u2.y;
-            b += y2.y * u2.y;
-            a = dpp_add(a, [] { return 0xB1; });    // the other of the pair, the other pair of the
-            b = dpp_add(b, [] { return 0xB1; });    // four, the other four (mirrored)
-            a = dpp_add(a, [] { return 0x4E; });
-            b = dpp_add(b, [] { return 0x4E; });
-            a = dpp_add(a, [] { return 0x141; });
-            b = dpp_add(b, [] { return 0x141; });
-            if (l == 0 && ta < t1) sfar[ta] = a;
-            if (l == 1 && tb < t1) sfar[tb] = b;
+            a = tree(a);
+            if (l == 0 && ta < nt) sfar[ta] = a;
+        }
+    } else {
+        for (int c = 0; c < nleaf; ++c) {
+            const int32_t b0 = c == 0 ? bnd[0] : c == 1 ? bnd[1] : c == 2 ? bnd[2] : bnd[3];
+            const int32_t b1 = c == 0 ? bnd[1] : c == 1 ? bnd[2] : c == 2 ? bnd[3] : bnd[4];
+            const int32_t t0 = max(b0 - i0, 0), t1 = min(b1 - i0, 64);   // its targets among the 64 (uniform)
+            if (t0 >= t1) continue;
+            const gptr<double2_t> u = X + size_t(c) * (P / 2);
+            const double2_t u0 = u[0], u1 = u[8], u2 = u[16];
+            for (int32_t t = t0; t < t1; t += 16) {
+                const int32_t ta = t + g8, tb = t + 8 + g8;
+                const size_t ra = row(ta), rb = row(tb);
+                const double2_t x0 = T[ra], x1 = T[ra + 8], x2 = T[ra + 16], y0 = T[rb], y1 = T[rb + 8], y2 = T[rb + 16];
+                double a = x0.x * u0.x, b = y0.x * u0.x;
+                a += x0.y * u0.y;
+                b += y0.y * u0.y;
+                a += x1.x * u1.x;
+                b += y1.x * u1.x;
+                a += x1.y * u1.y;
+                b += y1.y * u1.y;
+                a += x2.x * u2.x;
+                b += y2.x * u2.x;
+                a += x2.y * u2.y;
+                b += y2.y * u2.y;
+                a = tree(a);
+                b = tree(b);
+                if (l == 0 && ta < t1) sfar[ta] = a;
+                if (l == 1 && tb < t1) sfar[tb] = b;
+            }
         }
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -1751,7 +1776,7 @@ __device__ inline void near_group(int32_t rec, int4 ent, int64_t side, int W, co
     double* u = eio.u;
     if (SLICED && far) {   // of all the group's targets, into sfar
         const int2 p = pts[min(bnd[0] + lane, t_end - 1)];
-        far_rows<P>(leaf0, nleaf, bnd, bnd[0], (p.x & int32_t(side - 1)) + int32_t(side) * (p.y & int32_t(side - 1)), leafT,
+        far_rows<P, true>(leaf0, nleaf, bnd, bnd[0], (p.x & int32_t(side - 1)) + int32_t(side) * (p.y & int32_t(side - 1)), leafT,
                     U, sfar);
     }
     const bool sorted_out = eio.sorted != 0;   // u indexed by sorted point
@@ -1859,7 +1884,7 @@ __device__ inline void near_group(int32_t rec, int4 ent, int64_t side, int W, co
             // the far field last, as when k_l2p adds it
             if (far)
                 acc += SLICED ? sfar[ii - bnd[0]]
-                              : far_rows<P>(leaf0, nleaf, bnd, i0, (pi.x & int32_t(side - 1)) +
+                              : far_rows<P, false>(leaf0, nleaf, bnd, i0, (pi.x & int32_t(side - 1)) +
                                                 int32_t(side) * (pi.y & int32_t(side - 1)), leafT, U, sfar);
             if (valid && sl == 0 && pout >= tgt0) u[sorted_out ? int64_t(ii) : int64_t(pout - tgt0)] = acc;
         }
@@ -2023,8 +2048,9 @@ __global__ __launch_bounds__(kBlock) void k_l2p(int32_t q0, int32_t q1, const Ne
             const bool on = i0 + lane < bnd[4] && pout >= eio.tgt0;
             double* u = eio.u + (eio.sorted ? int64_t(i) : int64_t(pout - eio.tgt0));
             const double old = on ? *u : 0.0;
-            const double v = far_rows<P>(word(0), word(1), bnd, i0, (p.x & (side - 1)) + side * (p.y & (side - 1)), leafT, U,
-                                         sfar[wave]);
+            const int32_t loc = (p.x & (side - 1)) + side * (p.y & (side - 1));
+            const double v = bnd[4] - bnd[0] <= 32 ? far_rows<P, true>(word(0), word(1), bnd, i0, loc, leafT, U, sfar[wave])
+                                                   : far_rows<P, false>(word(0), word(1), bnd, i0, loc, leafT, U, sfar[wave]);
             if (on) *u = old + v;
         }
     }
