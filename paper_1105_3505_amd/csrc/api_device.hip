@@ -1449,7 +1449,7 @@ void build_forest(lfmm_plan* pl, int32_t K, const InstanceInput* in, int32_t max
                               pl->box_pt0, pl->box_pt1, nb, nullptr, pl->list_off, pl->list_ent, st);
         launch_compact_positive(lcnt, lpos, nb, ad_leaves, st);
         launch_ad_records(pl->n_ad_leaves, ad_leaves, adaptive_lists(pl), pl->box_pt0, pl->box_pt1, pl->box_inst,
-                          pl->ad_recs, st);
+                          pl->box_lev, pl->d_inst, pl->ad_recs, st);
         launch_compact_positive(lcnt + 2 * nb1, lpos + 2 * nb1, nb, pl->ad_xboxes, st);
     }
     LFMM_HIP(hipGetLastError());

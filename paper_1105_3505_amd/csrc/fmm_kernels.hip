@@ -2056,19 +2056,22 @@ __global__ __launch_bounds__(kBlock) void k_l2p(int32_t q0, int32_t q1, const Ne
     }
 }
 
-// phi from radius kNearRadius on (PhiFast), the table below it: in LDS, both built by every block.
+// phi from radius kNearRadius on (PhiFast), the table below it (offsets below R): in LDS, both built by every block.
+template <int R>
 struct FastTab {
-    static constexpr int kRow = kNearRadius + 1;   // doubles a row of the near table (odd)
-    double near[kNearRadius * kRow];
+    static_assert(R >= kNearRadius && R % 2 == 0, "R");
+    static constexpr int kRows = R, kRow = R + 1;   // doubles a row of the near table (odd)
+    double near[R * kRow];
 };
 
 struct FastCoef {
     double a[14], log[5];
 };
 
-__device__ inline void load_near_tab(FastTab& t, const double* phi_oct_tab, int tid, int nt) {
-    for (int i = tid; i < kNearRadius * FastTab::kRow; i += nt) {
-        const int dy = i / FastTab::kRow, dx = i - dy * FastTab::kRow;
+template <class Tab>
+__device__ inline void load_near_tab(Tab& t, const double* phi_oct_tab, int tid, int nt) {
+    for (int i = tid; i < Tab::kRows * Tab::kRow; i += nt) {
+        const int dy = i / Tab::kRow, dx = i - dy * Tab::kRow;
         const int hi = max(dx, dy), lo = min(dx, dy);
         t.near[i] = phi_oct_tab[hi * (hi + 1) / 2 + lo];
     }
@@ -2104,7 +2107,8 @@ __device__ inline double phi_terms(double z, double lead, double ir2, double s, 
 }
 
 // phi at an offset below 2^8 in both coordinates (dx, dy exact): r2 in [2^11, 2^17) after clamping
-__device__ inline double phi_fast_oct(double dx, double dy, uint32_t adx, uint32_t ady, const FastTab& t,
+template <class Tab>
+__device__ inline double phi_fast_oct(double dx, double dy, uint32_t adx, uint32_t ady, const Tab& t,
                                       const double2_t* oct, const FastCoef& c) {
     constexpr double kMin = double(kNearRadius) * kNearRadius;
     const double r2 = fma(dx, dx, dy * dy), r = fmax(r2, kMin);
@@ -2114,12 +2118,13 @@ __device__ inline double phi_fast_oct(double dx, double dy, uint32_t adx, uint32
     const double z = fma(r, e.x, -1.0);
     const double ir2 = e.x * fma(-z, fma(-z, 1.0 - z, 1.0), 1.0);   // |z| <= 2^-9: to 2^-36
     double ph = phi_terms(z, e.y, ir2, dx * dy, c);
-    if (r2 < kMin) ph = t.near[ady * FastTab::kRow + adx];
+    if (r2 < kMin) ph = t.near[ady * Tab::kRow + adx];
     return ph;
 }
 
 // phi at any offset (coordinates below 2^31)
-__device__ inline double phi_fast_any(double dx, double dy, uint32_t adx, uint32_t ady, const FastTab& t,
+template <class Tab>
+__device__ inline double phi_fast_any(double dx, double dy, uint32_t adx, uint32_t ady, const Tab& t,
                                       const double2_t* mant, const FastCoef& c) {
     constexpr double kMin = double(kNearRadius) * kNearRadius;
     constexpr double kLn2 = -0.69314718055994530942 / (4.0 * kPi);
@@ -2132,7 +2137,7 @@ __device__ inline double phi_fast_any(double dx, double dy, uint32_t adx, uint32
     const double scale = __builtin_bit_cast(double, int2_t{0, int(0x7fe00000u - (uint32_t(w.y) & 0x7ff00000u))});
     const double ir2 = e.x * fma(-z, fma(-z, 1.0 - z, 1.0), 1.0) * scale;
     double ph = phi_terms(z, fma(ex, kLn2, e.y), ir2, dx * dy, c);
-    if (r2 < kMin) ph = t.near[ady * FastTab::kRow + adx];
+    if (r2 < kMin) ph = t.near[ady * Tab::kRow + adx];
     return ph;
 }
 
@@ -2299,7 +2304,7 @@ __global__ __launch_bounds__(64 * (SPLIT ? kSplitWaves : kWideWaves), SPLIT ? 3 
     const int32_t* perm_local, const ExecPtrs* tab_ptrs, ExecPtrs single, const double* U, const double* leafT,
     const double* phi_oct_tab, const PhiFast* fast, int by_leaf) {
     constexpr int W = SPLIT ? kSplitWaves : kWideWaves;
-    __shared__ FastTab tab;
+    __shared__ FastTab<kNearRadius> tab;
     __shared__ double2_t oct[kFarOctEntries];
     __shared__ double part[SPLIT ? kSplitWaves + 1 : 1][64];
     __shared__ int32_t next;
@@ -2473,11 +2478,15 @@ __global__ __launch_bounds__(kBlock) void k_p2l(int32_t nx, const int32_t* xitem
 // ahead), and the batch's sources are read as one list, 60 at a time, one per lane, the next 60 in
 // flight.  The n targets take n lanes each of S = 64 / n slices; slice s takes every S-th source from
 // its lane by shuffles.  phi is computed as in k_near_wide, for any offset: 2e6 clustered points
-// 1842 -> 1039 us (gathers from the 4.2-MB table, and a bisection over the entries for every source,
-// before).  L2P runs at each point's finest box (its incoming expansion holds those of the adaptive
+// 1842 -> 960 us (gathers from the 4.2-MB table, and a bisection over the entries for every source,
+// before).  A chunk whose sources are all near to all of a leaf of side up to 64 takes phi from a table
+// instead, in LDS for sides up to 32, the first 67 KB of the octant table for 64 (a third of the
+// instructions; uniform points, N_leaf 64: 300,000 in leaves of side 16 and 32 245 -> 142 us, of side 64
+// 379 -> 239, of which the gathers alone took 239 before).  L2P runs at each point's finest box (its incoming expansion holds those of the adaptive
 // leaf relayed by L2L), then the caller-order write.
 // SPLIT: as in k_near_wide, four waves per leaf.
 constexpr int kAdWaves = 8, kAdChunk = kWideChunk;
+constexpr int kCloseOffsets = 64, kMidOffsets = 128;   // of either table
 
 template <int P, bool SPLIT>
 __global__ __launch_bounds__(64 * (SPLIT ? kSplitWaves : kAdWaves), SPLIT ? 3 : 4) void k_near_adaptive(
@@ -2487,7 +2496,7 @@ __global__ __launch_bounds__(64 * (SPLIT ? kSplitWaves : kAdWaves), SPLIT ? 3 : 
     const ExecPtrs* tab_ptrs, ExecPtrs single, const uint8_t* far_inst, const double* phi_oct_tab,
     const PhiFast* fast) {
     constexpr int W = SPLIT ? kSplitWaves : kAdWaves;
-    __shared__ FastTab tab;
+    __shared__ FastTab<kCloseOffsets> tab;
     __shared__ double2_t mant[kFarMantEntries];
     __shared__ double part[SPLIT ? kSplitWaves + 1 : 1][64];
     __shared__ int32_t next;
@@ -2517,7 +2526,7 @@ __global__ __launch_bounds__(64 * (SPLIT ? kSplitWaves : kAdWaves), SPLIT ? 3 : 
     int32_t sg = q < nitems ? entry(word(rec, 2), word(rec, 3), word(rec, 4), word(rec, 5), 0) : -1;
     while (q < nitems) {
         const int32_t t0 = word(rec, 0), t_end = word(rec, 1), u0 = word(rec, 2), nu = word(rec, 3), w0 = word(rec, 4);
-        const int32_t nw = word(rec, 5), k_inst = word(rec, 6), ne = nu + nw;
+        const int32_t nw = word(rec, 5), k_inst = word(rec, 6), sh = word(rec, 7), ne = nu + nw;
         const int32_t sg0 = sg;   // the first batch of entries
         // the next leaf's entries and the record after it
         q = q1;
@@ -2539,6 +2548,10 @@ __global__ __launch_bounds__(64 * (SPLIT ? kSplitWaves : kAdWaves), SPLIT ? 3 : 
             const int2 pi = pts[ii];
             const int32_t pout = perm_local[ii];
             const double xd = biased(uint32_t(pi.x)), yd = biased(uint32_t(pi.y));   // root coordinates: not negative
+            // leaves of side up to 64: the sources at most `reach` off every point of the leaf in both
+            // coordinates are those with x - near_x and y - near_y in [0, near_w]
+            const int32_t top = (1 << min(sh, 6)) - 1, reach = (sh <= 5 ? kCloseOffsets : kMidOffsets) - 1, near_w = 2 * reach - top;
+            const int32_t near_x = ((uniform(pi.x) >> sh) << sh) + top - reach, near_y = ((uniform(pi.y) >> sh) << sh) + top - reach;
             Parts parts;
             int32_t done = 0;   // chunks of the batches before
             for (int32_t eb = 0; eb < ne; eb += 64) {
@@ -2596,12 +2609,29 @@ __global__ __launch_bounds__(64 * (SPLIT ? kSplitWaves : kAdWaves), SPLIT ? 3 : 
                     const int cnt = min(kAdChunk, total - i * kAdChunk);
                     const int2_t sf = __builtin_bit_cast(int2_t, lane < cnt ? fn : 0.0);   // slots past the last: zero loads
                     if (i + step < chunks) load(i + step);
-                    const double v = chunk_sum(cnt, z.S, 4 * z.sl, [&](int from, double acc) -> double {
-                        const int x = __builtin_amdgcn_ds_bpermute(from, sx), y = __builtin_amdgcn_ds_bpermute(from, sy);
-                        const double fk = bperm_d(from, sf);
-                        return fma(phi_fast_any(xd - biased(uint32_t(x)), yd - biased(uint32_t(y)), uint32_t(abs(pi.x - x)),
-                                                uint32_t(abs(pi.y - y)), tab, mant, coef), fk, acc);
-                    });
+                    double v;
+                    const bool close = sh <= 6 && __ballot(uint32_t(sx) - uint32_t(near_x) > uint32_t(near_w) ||
+                                                           uint32_t(sy) - uint32_t(near_y) > uint32_t(near_w)) == 0;
+                    if (close && sh <= 5)
+                        v = chunk_sum(cnt, z.S, 4 * z.sl, [&](int from, double acc) -> double {
+                            const int x = __builtin_amdgcn_ds_bpermute(from, sx), y = __builtin_amdgcn_ds_bpermute(from, sy);
+                            const double fk = bperm_d(from, sf);
+                            return fma(tab.near[abs(pi.y - y) * tab.kRow + abs(pi.x - x)], fk, acc);
+                        });
+                    else if (close)
+                        v = chunk_sum(cnt, z.S, 4 * z.sl, [&](int from, double acc) -> double {
+                            const int x = __builtin_amdgcn_ds_bpermute(from, sx), y = __builtin_amdgcn_ds_bpermute(from, sy);
+                            const double fk = bperm_d(from, sf);
+                            const int dx = abs(pi.x - x), dy = abs(pi.y - y), hi = max(dx, dy);
+                            return fma(global(phi_oct_tab)[uint32_t(__mul24(hi, hi + 1)) / 2u + uint32_t(min(dx, dy))], fk, acc);
+                        });
+                    else
+                        v = chunk_sum(cnt, z.S, 4 * z.sl, [&](int from, double acc) -> double {
+                            const int x = __builtin_amdgcn_ds_bpermute(from, sx), y = __builtin_amdgcn_ds_bpermute(from, sy);
+                            const double fk = bperm_d(from, sf);
+                            return fma(phi_fast_any(xd - biased(uint32_t(x)), yd - biased(uint32_t(y)), uint32_t(abs(pi.x - x)),
+                                                    uint32_t(abs(pi.y - y)), tab, mant, coef), fk, acc);
+                        });
                     if (SPLIT) parts.a[0] += v;
                     else parts.add(v);
                 }

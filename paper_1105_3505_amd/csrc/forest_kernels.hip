@@ -917,7 +917,8 @@ __global__ void k_subtrees(int32_t box0, int32_t n, int depth, const int32_t* bo
 }
 
 __global__ void k_ad_records(int32_t nitems, const int32_t* items, AdaptiveLists L, const int32_t* box_pt0,
-                             const int32_t* box_pt1, const int32_t* box_inst, AdLeaf* recs) {
+                             const int32_t* box_pt1, const int32_t* box_inst, const int8_t* box_lev,
+                             const InstInfo* inst, AdLeaf* recs) {
     const int32_t i = int32_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (i >= nitems) return;
     const int32_t g = items[i];
@@ -929,7 +930,7 @@ __global__ void k_ad_records(int32_t nitems, const int32_t* items, AdaptiveLists
     r.w0 = L.off[1][g];
     r.nw = L.off[1][g + 1] - r.w0;
     r.inst = box_inst[g];
-    r.pad = 0;
+    r.shift = inst[r.inst].D - int(box_lev[g]);
     recs[i] = r;
 }
 
@@ -1659,10 +1660,11 @@ void launch_subtrees(int32_t box0, int32_t n, int depth, const int32_t* box_chil
 }
 
 void launch_ad_records(int32_t nitems, const int32_t* items, const AdaptiveLists& lists, const int32_t* box_pt0,
-                       const int32_t* box_pt1, const int32_t* box_inst, AdLeaf* recs, hipStream_t st) {
+                       const int32_t* box_pt1, const int32_t* box_inst, const int8_t* box_lev, const InstInfo* inst,
+                       AdLeaf* recs, hipStream_t st) {
     if (nitems <= 0) return;
     hipLaunchKernelGGL(k_ad_records, dim3(grid_for(nitems)), dim3(kBlock), 0, st, nitems, items, lists, box_pt0, box_pt1,
-                       box_inst, recs);
+                       box_inst, box_lev, inst, recs);
 }
 
 void launch_point_boxes(const int32_t* box_pt0, const int32_t* box_pt1, int32_t nleaf, int32_t* pt_box,

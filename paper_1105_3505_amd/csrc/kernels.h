@@ -359,10 +359,11 @@ struct AdLeaf {
     int32_t t0, t1;        // its points
     int32_t u0, nu;        // its U list in ent[0]
     int32_t w0, nw;        // its W list in ent[1]
-    int32_t inst, pad;
+    int32_t inst, shift;   // its side is 1 << shift
 };
 void launch_ad_records(int32_t nitems, const int32_t* items, const AdaptiveLists& lists, const int32_t* box_pt0,
-                       const int32_t* box_pt1, const int32_t* box_inst, AdLeaf* recs, hipStream_t st);
+                       const int32_t* box_pt1, const int32_t* box_inst, const int8_t* box_lev, const InstInfo* inst,
+                       AdLeaf* recs, hipStream_t st);
 // Adaptive tree passes.  P2L (X lists): u-hat of box tau += phi(skeleton of tau - x_j) f_j over
 // the points of its X leaves, for the nx boxes xitems.  Near field of the adaptive leaves
 // (records): U-list sources, W-list skeletons with their q-hat (M2P), L2P at each point's finest
