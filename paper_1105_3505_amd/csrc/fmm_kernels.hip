@@ -2294,9 +2294,12 @@ constexpr int kWideWaves = 8, kWideChunk = 60, kSplitWaves = 4;
 // 419 / 179 / 219; 254, 5.2e5 - / 762 / 695; 1097; on curves, whose groups hold two leaves: 984 units
 // 22 / 19 / 53; 26, 3.9e3 44 / 26 / 33; 27, 2.5e4 198 / 88 / 72; 87.
 constexpr int64_t kSplitLeaves = 2048, kWaveLeaves = 8192, kWaveLeavesFull = 196608;
-// The same for adaptive leaves (quarter / leaf; gathers): 97 leaves 45 / 320; 88, 2.2e3 134 / 248; 479,
-// 1.4e4 581 / 626; 1022, 7.4e4 2401 / 2030; 2997.
-constexpr int32_t kSplitAdaptive = 16384;
+// The same for adaptive leaves, a quarter or a leaf per wave, by their number and by the sources of one (the mean
+// length of its U and W lists): a list of one or two chunks leaves most of four waves idle.  Measured (quarter / leaf,
+// us): 59 sources, 1,569 leaves 21 / 22, 3,063 27 / 20, 18,295 102 / 50; 94 to 112 sources, 2,742 leaves 41 / 60, 5,393
+// 63 / 83, 10,912 92 / 77, 21,389 120 / 55; 230 sources, 2,329 leaves 65 / 133, 9,677 102 / 113, 29,032 257 / 224; 320 to
+// 360 sources, 3,577 leaves 189 / 335, 10,508 426 / 530, 22,276 401 / 444.
+static int32_t split_adaptive(double sources) { return sources < 90.0 ? 2048 : sources < 150.0 ? 5632 : 16384; }
 
 template <int P, bool SPLIT>
 __global__ __launch_bounds__(64 * (SPLIT ? kSplitWaves : kWideWaves), SPLIT ? 3 : 4) void k_near_wide(
@@ -2966,10 +2969,10 @@ void launch_near_adaptive(int32_t nitems, const AdLeaf* recs, const AdaptiveList
                           const InstInfo* inst, const OpsPtrs* ops, const int32_t* pts,
                           const double* fs, const double* Q, const int32_t* pt_box, const double* U,
                           const int32_t* perm_local, const ExecPtrs* tab, const ExecPtrs& single,
-                          const uint8_t* far_inst, const double* phi_oct, const PhiFast* fast, hipStream_t st) {
+                          const uint8_t* far_inst, const double* phi_oct, const PhiFast* fast, double sources, hipStream_t st) {
     if (nitems <= 0) return;
     const int2* p2 = reinterpret_cast<const int2*>(pts);
-    if (nitems <= kSplitAdaptive) {
+    if (nitems <= split_adaptive(sources)) {
         const unsigned g = persistent_grid(reinterpret_cast<const void*>(&k_near_adaptive<kRankPad, true>),
                                            64 * kSplitWaves, int64_t(nitems) * kSplitWaves);
         hipLaunchKernelGGL((k_near_adaptive<kRankPad, true>), dim3(g), dim3(64 * kSplitWaves), 0, st, nitems, recs,
