@@ -2484,7 +2484,7 @@ __global__ __launch_bounds__(kBlock) void k_p2l(int32_t nx, const int32_t* xitem
 // 1842 -> 960 us (gathers from the 4.2-MB table, and a bisection over the entries for every source,
 // before).  A chunk whose sources are all near to all of a leaf of side up to 64 takes phi from a table
 // instead, in LDS for sides up to 32, the first 67 KB of the octant table for 64 (a third of the
-// instructions; uniform points, N_leaf 64: 300,000 in leaves of side 16 and 32 245 -> 142 us, of side 64
+// instructions; uniform points, N_leaf 64: 300,000 in leaves of side 16 and 32 278 -> 142 us, of side 64
 // 379 -> 239, of which the gathers alone took 239 before).  L2P runs at each point's finest box (its incoming expansion holds those of the adaptive
 // leaf relayed by L2L), then the caller-order write.
 // SPLIT: as in k_near_wide, four waves per leaf.
