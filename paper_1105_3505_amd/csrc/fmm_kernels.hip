@@ -175,16 +175,18 @@ constexpr int kP2mLeaves = 64 / kP2mGroup;     // leaves per wave and step
 // us): side 8, 15 points a leaf, 1,024 leaves 6.6 / 13.2, 4,096 9.6 / 14.7, 16,384 20.0 / 16.1; side 32, 25 points,
 // 1,024 leaves 7.2 / 17.5, 4,096 11.4 / 17.5, 16,384 26.3 / 21.9.
 constexpr int32_t kP2mWaveLeaves = 8192;
-// With more leaves, too, where T_ofs does not fit LDS and the leaves are uneven: the eight leaves of a group take as
-// long as its fullest, and the rows come from L2 either way.  The fullest leaf of a plan holds up to N_leaf points, so
-// that an average below kP2mUneven of it tells clusters (0.03 to 0.10) from uniform points and curves (0.2 to 0.5);
-// leaves of at most kP2mSparsePoints on average are better grouped all the same.  Measured (k_p2m / grouped, us),
-// clusters: side 32, 5.7 points a leaf of N_leaf 64, 123,691 leaves 71 / 46; side 64, 16 of 200, 42,811 leaves 45 / 71;
-// side 128, 51 of 500, 13,673 leaves 56 / 155, 66,168 leaves 169 / 280; uniform points: side 32, 10 of 64, 19,598 leaves
-// 19 / 16; side 64, 14 of 64, 44,100 leaves 36 / 27; 40 of 200, 24,649 leaves 48 / 45; side 128, 162 of 500, 24,649
-// leaves 196 / 167; a curve, side 32, 32 of 64, 14,999 leaves 22.6 / 19.3.  (In LDS the grouped kernel is the faster
-// from 15,625 leaves on at any density: 64 points a leaf 29 / 45, 256 90 / 145.)
+// With more leaves, too, where T_ofs does not fit LDS (the rows then come from L2 either way) and the leaves hold more
+// than kP2mSparsePoints on average, up to kP2mWideLeaves leaves, and with any number if they are uneven: the eight
+// leaves of a group take as long as its fullest.  The fullest leaf of a plan holds up to N_leaf points, so that an
+// average below kP2mUneven of it tells clusters (0.03 to 0.10) from uniform points and curves (0.2 to 0.5).  Measured
+// (k_p2m / grouped, us), clusters: side 32, 5.7 points a leaf of N_leaf 64, 123,691 leaves 71 / 46; side 64, 16 of 200,
+// 42,811 leaves 45 / 71; side 128, 51 of 500, 13,673 leaves 56 / 155, 66,168 leaves 169 / 280; uniform points: side 32, 10
+// of 64, 19,598 leaves 19 / 16; side 64, 14 of 64, 44,100 leaves 36 / 27; 102 of 256, 9,801 leaves 49 / 60; 40 of 200,
+// 24,649 leaves 48 / 45; side 128, 162 of 500, 24,649 leaves 196 / 167; a curve, side 32, 32 of 64, 14,999 leaves
+// 22.6 / 19.3.  (In LDS the grouped kernel is the faster from 15,625 leaves on at any density: 64 points a leaf
+// 29 / 45, 256 90 / 145.)
 constexpr double kP2mUneven = 0.15;
+constexpr int32_t kP2mWideLeaves = 12288;
 constexpr double kP2mSparsePoints = 12.0;
 
 // STAGED false: the same for leaves whose T_ofs is too large for LDS: the operator rows come from global
@@ -2766,8 +2768,9 @@ void launch_p2m(int32_t leaf0, int32_t leaf1, const int32_t* box_pt0, const int3
     const size_t lds = size_t(side * side) * kRankPad * sizeof(double);
     const P2mDevice dv = p2m_device();
     const bool staged = dv.cus > 0 && lds <= size_t(dv.lds);
-    const bool uneven = avg_pts > kP2mSparsePoints && avg_pts < kP2mUneven * double(max_leaf);
-    if (nleaf <= kP2mWaveLeaves || (uneven && !staged)) {
+    const bool full = !staged && avg_pts > kP2mSparsePoints &&
+                        (nleaf <= kP2mWideLeaves || avg_pts < kP2mUneven * double(max_leaf));
+    if (nleaf <= kP2mWaveLeaves || full) {
         hipLaunchKernelGGL(k_p2m<kRankPad>, dim3(grid_for(nleaf, kWaves)), dim3(kBlock), 0, st, leaf0, leaf1, box_pt0,
                            box_pt1, box_key, side, p2, tab, single, perm_local, box_inst, fs, leafT, Q);
         return;
