@@ -103,7 +103,10 @@ typedef enum lfmm_stencil {
 
 /* options.flags: lfmm_execute / lfmm_execute_instances replay a HIP graph of the evaluation
  * passes, recorded at the plan's first execute (one graph launch per execute instead of one
- * launch per pass and height).  Per-phase timing is not available in this mode. */
+ * launch per pass and height).  Per-phase timing is not available in this mode.  Plain executes
+ * of plans of 128 to 16,384 leaves run the near field on a second stream beside the far
+ * field's passes, a graph runs them in turn: on one stream after another execute, the plain
+ * ones can be the faster there (16,000 points 92 against 113 us). */
 #define LFMM_FLAG_GRAPH 1
 /* options.flags: lfmm_execute / lfmm_execute_instances check the loads first (a reduction on
  * the device and a read-back, so the call synchronises the stream): NaN or infinite loads

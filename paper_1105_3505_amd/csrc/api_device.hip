@@ -1475,14 +1475,19 @@ void build_forest(lfmm_plan* pl, int32_t K, const InstanceInput* in, int32_t max
 
 // Whether the plan's near field runs beside its far field on st: from kOverlapLeaves[0] to [1] leaves.  With
 // fewer, the passes are shorter than the fork and the join (some 10 us); with more, they fill the
-// device by themselves and L2P alone costs more than within the near field.  Execute of uniform points, in turn / beside
-// (us): 49 leaves 64 / 64, 169 80 / 71, 652 113 / 92, 2,555 135 / 104, 9,801 176 / 164, 19,600 257 / 262; mixed
-// precision 78 / 65, 96 / 75, 128 / 93, 160 / 117, 243 / 225, 371 / 353; a curve, 100 leaves 64 / 65, 396 88 / 74.
-// The near field has to be worth it as well: a wave takes about 0.9 us for each of its group's ranges of
-// sources (16 where all leaves are there, a quarter of that on curves) and pass of 64 targets, twice that with
-// the quadrant table of side 32 (a curve, side 32, 8: gains as above); below kOverlapRanges of them
-// (16,384 boundary nodes, side 16: 6, the near field 14 us), in turn is faster (a solve of 26
-// iterations 4.09 / 4.25 ms).
+// device by themselves and L2P alone costs more than within the near field.  The near field has to be worth it as
+// well: a wave takes about 0.9 us for each of its group's ranges of sources and pass of 64 targets, twice that with the
+// quadrant table of side 32, and a group has about 16 fill^2 ranges (fill: the share of its four leaves that is there);
+// below kOverlapRanges of them the near field takes some 14 us.  Execute, in turn / beside (us):
+//   uniform points, side 16, 16 ranges: 142 leaves 62 / 61, 323 78 / 62, 625 80 / 65, 1,594 86 / 72, 2,500 90 / 86, 6,283
+//     110 / 107, 15,599 166 / 165, 15,625 175 / 178, 24,674 213 / 212; side 8, 30 ranges: 324 118 / 97, 1,296 121 / 97,
+//     3,136 141 / 115, 7,921 174 / 152; side 32, 50 ranges: 400 105 / 90, 1,600 120 / 101, 9,801 175 / 163; side 4, 16
+//     ranges of few points: 256 60 / 63, 1,293 87 / 71, 5,041 118 / 101, 12,543 153 / 160, 31,329 225 / 263
+//   clusters, side 32, 16 ranges: 548 104 / 99, 1,768 117 / 110, 5,296 138 / 130, 17,652 235 / 214, 35,256 329 / 342
+//   curves, side 32, 8 ranges: 124 leaves 54 / 61, 332 75 / 74, 499 69 / 71, 2,047 86 / 88, 2,478 103 / 97, 4,999 106 / 106,
+//     8,254 157 / 158; side 8, 4 ranges: 499 63 / 70, 1,300 86 / 88, 8,191 111 / 124, 9,676 142 / 150; side 16, 6 ranges
+//     (both ends of the dipoles on 65,532 boundary nodes, a solve of 26 iterations): 4.09 / 4.25 ms
+// so that the line of ranges lies where curves are even: some per cent are lost and won on either side of it.
 // Never in the static workspace: its solve makes no stream and no event.
 constexpr int32_t kOverlapLeaves[2] = {128, 16384};
 constexpr double kOverlapRanges = 7.0;
@@ -1528,8 +1533,9 @@ void enqueue_passes(lfmm_plan* pl, const ExecPtrs* tab, const double* f1, double
     }
     mark(2);
     // The pairs of the near field need the loads alone: for plans that leave the device partly idle they run on a
-    // side stream beside the far field's passes, and L2P follows both (same bits).  Not under capture (the
-    // side stream would belong to the capture until it ends) and not while phases are timed.
+    // side stream beside the far field's passes, and L2P follows both (same bits).  Not while phases are timed, and not
+    // under capture, a graph plan's own included: a fork inside one needs a side stream that nothing else uses until
+    // the capture ends, and lent streams are not kept apart for that.  Graph plans take the times in turn.
     const bool overlap = marks == 0 && beside(pl, st);
     struct Join {
         hipStream_t st;

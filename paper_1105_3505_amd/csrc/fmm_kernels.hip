@@ -1901,8 +1901,8 @@ __global__ __launch_bounds__(kNearBlock, 4) void k_near(
     const uint32_t* pkey, const double* fs, const int32_t* perm_local, const ExecPtrs* tab_ptrs, ExecPtrs single,
     const double* U, const double* leafT, const double* phi_oct_tab, int far_on) {
     constexpr int kNearWaves = kNearBlock / 64;
-    // fixed-size table (largest window: side 32), so that its base is a compile-time constant
-    // and folds into the address of every read
+    // fixed-size table (the quadrant table of side 32, or a window of sides up to 16), so that its base is a
+    // compile-time constant and folds into the address of every read
     __shared__ double tab[kNearTabMax];
     __shared__ double sfar[kNearWaves][64];   // far fields of each wave's targets
     const int tid = threadIdx.x, wave = tid >> 6;

@@ -380,8 +380,10 @@ void launch_near_adaptive(int32_t nitems, const AdLeaf* recs, const AdaptiveList
                           const uint8_t* far_inst, const double* phi_oct, const PhiFast* fast, double sources, hipStream_t st);
 // Radius of the device phi table: the host's quadrature table (radius 128) followed by the
 // far-field expansion for the octant entries up to this radius, filled by
-// launch_phi_extend(oct, 128, radius).  4.2 MB: near-field offsets between the wide leaves of
-// adaptive trees stay table lookups (a gather) instead of logarithms.
+// launch_phi_extend(oct, 128, radius).  4.2 MB, so that P2L (skeleton points of a box and the points of a
+// leaf beside its parent) and the direct sum read most offsets instead of taking a logarithm; the
+// near field of leaves up to side 64 reads at most its first 128 rows (k_near_adaptive), and wider
+// leaves compute phi from radius kNearRadius on.
 constexpr int kPhiDeviceRadius = 1024;
 constexpr size_t kPhiDeviceEntries = size_t(kPhiDeviceRadius + 1) * (kPhiDeviceRadius + 2) / 2;
 void launch_phi_extend(double* oct, int r0, int r1, const PhiFar* far, hipStream_t st);
