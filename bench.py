@@ -65,9 +65,20 @@ WORKLOADS = {
                   "applied by the FMM, GMRES on D q = g"),
 }
 TOLERANCE = {"fp64": 1e-10, "mixed": 1e-7, "mixed-bf16": 1e-7}
-# M2L kernel, its matrix-core peak, and the matrix-core flops it executes per algorithmic flop
-M2L_KERNEL = {"fp64": ("k_m2l", PEAK_FP64_TFLOPS, 1.0), "mixed": ("k_m2l_mixed", PEAK_FP32_TFLOPS, 3.0),
-              "mixed-bf16": ("k_m2l_bf16", PEAK_BF16_TFLOPS, 6.0)}
+# M2L's matrix-core peak, the matrix-core flops it executes per algorithmic flop, its kernel for small
+# plans and the number of 128-box tiles up to which that is taken, and its kernels for others
+M2L_KERNEL = {"fp64": (PEAK_FP64_TFLOPS, 1.0, "k_m2l_fine", 160, "k_m2l<2>"),
+              "mixed": (PEAK_FP32_TFLOPS, 3.0, "k_m2l_mixed_fine", 384, "k_m2l_mixed"),
+              "mixed-bf16": (PEAK_BF16_TFLOPS, 6.0, "k_m2l_bf16_fine", 144, "k_m2l_bf16")}
+
+
+def m2l_kernel(precision: str, info: dict) -> str:
+    """Name of the M2L kernel that a plan of full interaction lists takes."""
+    _, _, small, line, large = M2L_KERNEL[precision]
+    tiles = info["n_boxes"] / 128
+    if precision == "fp64" and line < tiles <= 384:
+        return "k_m2l<1>"
+    return small if tiles <= line else large
 
 
 def measured_traffic(workload: str, kernel: str):
@@ -104,7 +115,8 @@ def _roofline(dom: str, dom_ms: float, info: dict, n: int, precision: str, workl
     if dom == "m2l":
         flops = 2.0 * RANK * RANK * info["m2l_pairs"]
         achieved = flops / sec / 1e12
-        kernel, peak, executed = M2L_KERNEL[precision]
+        kernel = m2l_kernel(precision, info)
+        peak, executed = M2L_KERNEL[precision][:2]
         out = {"kernel": kernel, "bound": "mfma", "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
                "frac": achieved / peak, "traffic": measured_traffic(workload, kernel), "work_per_launch": flops,
                "work_definition": "2 P^2 flops per interaction-list pair, P = 48"}
@@ -117,7 +129,10 @@ def _roofline(dom: str, dom_ms: float, info: dict, n: int, precision: str, workl
         pairs = info["near_pairs"] + info["m2p_terms"]
         flops = 2.0 * pairs + 2.0 * RANK * n
         achieved = flops / sec / 1e12
-        kernel = "k_near_adaptive<48>"
+        # a leaf is split over four waves where there are few, fewer where their lists are short
+        per_leaf = pairs / max(n, 1)
+        split = info["n_leaves"] <= (2048 if per_leaf < 90 else 5632 if per_leaf < 150 else 16384)
+        kernel = "k_near_adaptive<48, %s>" % ("true" if split else "false")
         return {"kernel": kernel, "bound": "alu", "achieved": achieved,
                 "peak": PEAK_FP64_TFLOPS, "unit": "TFLOP/s", "frac": achieved / PEAK_FP64_TFLOPS,
                 "traffic": measured_traffic(workload, kernel), "work_per_launch": flops,
@@ -128,9 +143,10 @@ def _roofline(dom: str, dom_ms: float, info: dict, n: int, precision: str, workl
         flops = 2.0 * info["near_pairs"] + 2.0 * RANK * n
         achieved = flops / sec / 1e12
         side = info["leaf_side"]
-        kernel = "k_near<48, %d>" % (0 if side <= 16 else (1 if side <= 32 else 2))
-        if side >= 64:
-            kernel = "k_near_wide<48>"
+        if side <= 32:
+            kernel = "k_near<48, %d>" % (0 if side <= 16 else 1)
+        else:   # few leaves (units of a quarter of a group, at least as many as leaves) are split over four waves
+            kernel = "k_near_wide<48, %s>" % ("true" if info["n_leaves"] <= 2048 else "false")
         return {"kernel": kernel, "bound": "alu", "achieved": achieved,
                 "peak": PEAK_FP64_TFLOPS, "unit": "TFLOP/s", "frac": achieved / PEAK_FP64_TFLOPS,
                 "traffic": measured_traffic(workload, kernel), "work_per_launch": flops,
