@@ -132,7 +132,8 @@ def _roofline(dom: str, dom_ms: float, info: dict, n: int, precision: str, workl
         # a leaf is split over four waves where there are few, fewer where their lists are short
         per_leaf = pairs / max(n, 1)
         split = info["n_leaves"] <= (2048 if per_leaf < 90 else 5632 if per_leaf < 150 else 16384)
-        kernel = "k_near_adaptive<48, %s>" % ("true" if split else "false")
+        close = info["leaf_side"] <= 64   # phi from tables where sources are near
+        kernel = "k_near_adaptive<48, %s, %s>" % ("true" if split else "false", "true" if close else "false")
         return {"kernel": kernel, "bound": "alu", "achieved": achieved,
                 "peak": PEAK_FP64_TFLOPS, "unit": "TFLOP/s", "frac": achieved / PEAK_FP64_TFLOPS,
                 "traffic": measured_traffic(workload, kernel), "work_per_launch": flops,

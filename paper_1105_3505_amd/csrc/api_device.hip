@@ -1616,9 +1616,11 @@ void enqueue_passes(lfmm_plan* pl, const ExecPtrs* tab, const double* f1, double
     if (pl->adaptive) {
         const double leaves = std::max<int32_t>(pl->n_ad_leaves, 1);
         const double sources = (double(pl->list_len[0]) * double(pl->n) / leaves + double(pl->list_len[1]) * kRankPad) / leaves;
+        int64_t side = pl->ops[0]->dev.leaf_side;
+        for (const CachedOps* o : pl->ops) side = std::min(side, o->dev.leaf_side);
         launch_near_adaptive(pl->n_ad_leaves, pl->ad_recs, lists, pl->box_pt0, pl->box_pt1, pl->box_key, pl->box_lev,
                              pl->d_inst, pl->d_ops, pl->pts, pl->fs, pl->Q, pl->pt_box, pl->U, pl->perm, tab, single,
-                             pl->d_far, pl->ctx->phi_oct, pl->ctx->phi_fast, sources, st);
+                             pl->d_far, pl->ctx->phi_oct, pl->ctx->phi_fast, sources, side, st);
         mark(6);
         return;
     }

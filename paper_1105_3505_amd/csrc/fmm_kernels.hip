@@ -2491,9 +2491,13 @@ __global__ __launch_bounds__(kBlock) void k_p2l(int32_t nx, const int32_t* xitem
 // leaf relayed by L2L), then the caller-order write.
 // SPLIT: as in k_near_wide, four waves per leaf.
 constexpr int kAdWaves = 8, kAdChunk = kWideChunk;
+// CLOSE: with those tables, for plans with leaves of such sides (the smallest side is at most kCloseSide); without,
+// the larger table in LDS and the test cost 1 % of an execute on clusters (35,000 points, leaves of side 128 and more,
+// 250 -> 253 us).
 constexpr int kCloseOffsets = 64, kMidOffsets = 128;   // of either table
+constexpr int kCloseSide = 64;
 
-template <int P, bool SPLIT>
+template <int P, bool SPLIT, bool CLOSE>
 __global__ __launch_bounds__(64 * (SPLIT ? kSplitWaves : kAdWaves), SPLIT ? 3 : 4) void k_near_adaptive(
     int32_t nitems, const AdLeaf* recs, AdaptiveLists L, const int32_t* box_pt0, const int32_t* box_pt1,
     const uint64_t* box_key, const int8_t* box_lev, const InstInfo* inst, const OpsPtrs* ops, const int2* pts,
@@ -2501,7 +2505,7 @@ __global__ __launch_bounds__(64 * (SPLIT ? kSplitWaves : kAdWaves), SPLIT ? 3 : 
     const ExecPtrs* tab_ptrs, ExecPtrs single, const uint8_t* far_inst, const double* phi_oct_tab,
     const PhiFast* fast) {
     constexpr int W = SPLIT ? kSplitWaves : kAdWaves;
-    __shared__ FastTab<kCloseOffsets> tab;
+    __shared__ FastTab<CLOSE ? kCloseOffsets : kNearRadius> tab;
     __shared__ double2_t mant[kFarMantEntries];
     __shared__ double part[SPLIT ? kSplitWaves + 1 : 1][64];
     __shared__ int32_t next;
@@ -2615,7 +2619,7 @@ __global__ __launch_bounds__(64 * (SPLIT ? kSplitWaves : kAdWaves), SPLIT ? 3 : 
                     const int2_t sf = __builtin_bit_cast(int2_t, lane < cnt ? fn : 0.0);   // slots past the last: zero loads
                     if (i + step < chunks) load(i + step);
                     double v;
-                    const bool close = sh <= 6 && __ballot(uint32_t(sx) - uint32_t(near_x) > uint32_t(near_w) ||
+                    const bool close = CLOSE && sh <= 6 && __ballot(uint32_t(sx) - uint32_t(near_x) > uint32_t(near_w) ||
                                                            uint32_t(sy) - uint32_t(near_y) > uint32_t(near_w)) == 0;
                     if (close && sh <= 5)
                         v = chunk_sum(cnt, z.S, 4 * z.sl, [&](int from, double acc) -> double {
@@ -2972,21 +2976,21 @@ void launch_near_adaptive(int32_t nitems, const AdLeaf* recs, const AdaptiveList
                           const InstInfo* inst, const OpsPtrs* ops, const int32_t* pts,
                           const double* fs, const double* Q, const int32_t* pt_box, const double* U,
                           const int32_t* perm_local, const ExecPtrs* tab, const ExecPtrs& single,
-                          const uint8_t* far_inst, const double* phi_oct, const PhiFast* fast, double sources, hipStream_t st) {
+                          const uint8_t* far_inst, const double* phi_oct, const PhiFast* fast, double sources, int64_t side,
+                          hipStream_t st) {
     if (nitems <= 0) return;
     const int2* p2 = reinterpret_cast<const int2*>(pts);
+    auto launch = [&](auto fn, unsigned g, int waves) {
+        hipLaunchKernelGGL(fn, dim3(g), dim3(64 * waves), 0, st, nitems, recs, lists, box_pt0, box_pt1, box_key, box_lev,
+                           inst, ops, p2, fs, Q, pt_box, U, perm_local, tab, single, far_inst, phi_oct, fast);
+    };
     if (nitems <= split_adaptive(sources)) {
-        const unsigned g = persistent_grid(reinterpret_cast<const void*>(&k_near_adaptive<kRankPad, true>),
-                                           64 * kSplitWaves, int64_t(nitems) * kSplitWaves);
-        hipLaunchKernelGGL((k_near_adaptive<kRankPad, true>), dim3(g), dim3(64 * kSplitWaves), 0, st, nitems, recs,
-                           lists, box_pt0, box_pt1, box_key, box_lev, inst, ops, p2, fs, Q, pt_box, U, perm_local, tab,
-                           single, far_inst, phi_oct, fast);
+        auto fn = side <= kCloseSide ? &k_near_adaptive<kRankPad, true, true> : &k_near_adaptive<kRankPad, true, false>;
+        launch(fn, persistent_grid(reinterpret_cast<const void*>(fn), 64 * kSplitWaves, int64_t(nitems) * kSplitWaves), kSplitWaves);
         return;
     }
-    const unsigned g = xcd_grid(reinterpret_cast<const void*>(&k_near_adaptive<kRankPad, false>), 64 * kAdWaves, nitems);
-    hipLaunchKernelGGL((k_near_adaptive<kRankPad, false>), dim3(g), dim3(64 * kAdWaves), 0, st, nitems, recs, lists,
-                       box_pt0, box_pt1, box_key, box_lev, inst, ops, p2, fs, Q, pt_box, U, perm_local, tab, single,
-                       far_inst, phi_oct, fast);
+    auto fn = side <= kCloseSide ? &k_near_adaptive<kRankPad, false, true> : &k_near_adaptive<kRankPad, false, false>;
+    launch(fn, xcd_grid(reinterpret_cast<const void*>(fn), 64 * kAdWaves, nitems), kAdWaves);
 }
 
 void launch_direct(int64_t nt, const int32_t* txy, int64_t ns, const int32_t* sxy, const double* f,

@@ -367,7 +367,8 @@ void launch_ad_records(int32_t nitems, const int32_t* items, const AdaptiveLists
 // Adaptive tree passes.  P2L (X lists): u-hat of box tau += phi(skeleton of tau - x_j) f_j over
 // the points of its X leaves, for the nx boxes xitems.  Near field of the adaptive leaves
 // (records): U-list sources, W-list skeletons with their q-hat (M2P), L2P at each point's finest
-// box, un-permutation; sources, the mean number of a leaf's sources, helps to split the work.
+// box, un-permutation; sources, the mean number of a leaf's sources, helps to split the work, and side, the smallest
+// side of a leaf, to choose where phi comes from.
 void launch_p2l(int32_t nx, const int32_t* xitems, const AdaptiveLists& lists, const int32_t* box_pt0,
                 const int32_t* box_pt1, const uint64_t* box_key, const int8_t* box_lev, const int32_t* box_inst,
                 const InstInfo* inst, const OpsPtrs* ops, const int32_t* pts, const double* fs, double* U,
@@ -377,7 +378,8 @@ void launch_near_adaptive(int32_t nitems, const AdLeaf* recs, const AdaptiveList
                           const InstInfo* inst, const OpsPtrs* ops, const int32_t* pts,
                           const double* fs, const double* Q, const int32_t* pt_box, const double* U,
                           const int32_t* perm_local, const ExecPtrs* tab, const ExecPtrs& single,
-                          const uint8_t* far_inst, const double* phi_oct, const PhiFast* fast, double sources, hipStream_t st);
+                          const uint8_t* far_inst, const double* phi_oct, const PhiFast* fast, double sources, int64_t side,
+                          hipStream_t st);
 // Radius of the device phi table: the host's quadrature table (radius 128) followed by the
 // far-field expansion for the octant entries up to this radius, filled by
 // launch_phi_extend(oct, 128, radius).  4.2 MB, so that P2L (skeleton points of a box and the points of a

@@ -91,3 +91,31 @@ def test_adaptive_chunks_about_the_tables(side, stencil):
             assert np.max(np.abs(u - lf.host_phi(xy - xy[k], stencil=stencil))) <= TOL
         plan.close()
     ctx.close()
+
+
+def test_adaptive_instances_of_wide_and_small_leaves():
+    """An adaptive instance of wide leaves alone (phi computed) gives the same bits beside one of small leaves, whose
+    plan has the tables as well; so does the latter."""
+    import torch
+
+    import paper_1105_3505_amd as lf
+    rng = np.random.default_rng(5)
+    wide = np.unique(np.rint(2000.0 * rng.standard_normal((4000, 2))).astype(np.int32), axis=0)
+    small = np.unique(rng.integers(0, 120, size=(3000, 2)).astype(np.int32), axis=0)
+    ctx = lf.Context(0, adaptive=True, max_leaf=32)
+    sets = [np.ascontiguousarray(p) for p in (wide, small)]
+    dev = [torch.from_numpy(p).cuda() for p in sets]
+    fs = [torch.from_numpy(rng.standard_normal(len(p))).cuda() for p in sets]
+    alone, sides = [], []
+    for x, f in zip(dev, fs):
+        plan = ctx.plan(x)
+        sides.append(plan.info()["leaf_side"])
+        alone.append(plan.execute(f))
+        plan.close()
+    assert sides[0] > 64 >= sides[1]
+    plan = ctx.plan_batch(dev)
+    us = plan.execute_instances(fs)
+    for a, b in zip(alone, us):
+        assert torch.equal(a, b)
+    plan.close()
+    ctx.close()
