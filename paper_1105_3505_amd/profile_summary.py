@@ -109,7 +109,7 @@ def _header(title: str, command: str):
     if title:
         lines += ["# " + title, ""]
     if command:
-        lines += ["Command (GPU box, repo root):", "", "```", command, "```", ""]
+        lines += ["Command (on an MI355X, in the repository):", "", "```", command, "```", ""]
     return lines
 
 
